@@ -3,6 +3,8 @@
 // accumulation) with its backward pass, loss and Adam, and the per-row top-M
 // selection of fine cells.  (The stores, fine and coarse, are written by
 // launch_stack_ingest beside the single-detector ingest.)
+#include <algorithm>
+
 #include "ltgw_proposer.h"
 #include "ddpow.h"
 
@@ -127,11 +129,8 @@ constexpr int kTaps = 5;
 typedef __attribute__((__vector_size__(4 * sizeof(short)))) short bf16x4;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
-__device__ inline short to_bf16(float x) {
-    unsigned u = __float_as_uint(x);
-    if ((u & 0x7f800000u) == 0x7f800000u) return (short)(u >> 16);  // inf/nan kept
-    return (short)((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);
-}
+// round to nearest even (v_cvt_pk_bf16_f32)
+__device__ inline short to_bf16(float x) { return __builtin_bit_cast(short, (__bf16)x); }
 
 struct ConvDims {
     int B, C, L, O, k, p;
@@ -512,6 +511,30 @@ __global__ void cnn_pack_kernel(const float *__restrict__ params, CnnOffsets off
     packed[e] = to_bf16(v);
 }
 
+// A wavefront's weight fragments of one layer, from the packed copy or (TRAIN)
+// straight from the parameter vector W[O][C][KT].
+template <int KT, int KW, int Cp, bool TRAIN>
+__device__ __attribute__((always_inline)) inline void infer_frags(const short *__restrict__ wp,
+                                                                  const float *__restrict__ W, int C, int O,
+                                                                  bf16x4 (&a)[KW / 16]) {
+    const int lane = threadIdx.x & 63, r0 = ((threadIdx.x >> 6) & 1) * 16;
+    const int row = lane & 15, kq = (lane >> 4) * 4;
+#pragma unroll
+    for (int s = 0; s < KW / 16; ++s) {
+        if (!TRAIN) {
+            a[s] = *(const bf16x4 *)&wp[(r0 + row) * KW + s * 16 + kq];
+            continue;
+        }
+        const int t = (s * 16 + kq) / Cp, c = (s * 16 + kq) % Cp;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const bool real = r0 + row < O && t < KT && c + i < C;
+            const float w = W[real ? (unsigned)(((r0 + row) * C + c + i) * KT + t) : 0u];
+            a[s][i] = real ? to_bf16(w) : (short)0;
+        }
+    }
+}
+
 // One layer: 32 output rows (o < O) over the 256 positions from input rows
 // `in` (SXin shorts per row).  Hidden layers write bf16(relu(acc + bias)) to
 // `out` (zero at positions >= L); the last writes acc + bias to gout (when
@@ -522,8 +545,10 @@ __global__ void cnn_pack_kernel(const float *__restrict__ params, CnnOffsets off
 // Inlined with its shapes as constants: a call would pass them at run time
 // (integer divisions for every operand address) and its registers would
 // stay allocated across the whole kernel.
-template <int KT, int KW, int Cp, int SXin>
-__device__ __attribute__((always_inline)) inline void infer_layer(const short *__restrict__ wp,
+// a: this wavefront's weight fragments (infer_frags).  TRAIN: the hidden
+// activations are also written to gout in FP32.
+template <int KT, int KW, int Cp, int SXin, bool TRAIN>
+__device__ __attribute__((always_inline)) inline void infer_layer(const bf16x4 (&a)[KW / 16],
                                                                   const float *__restrict__ bias, int O,
                                                                   const short *in, int L, bool relu, short *out,
                                                                   float *__restrict__ gout,
@@ -533,9 +558,6 @@ __device__ __attribute__((always_inline)) inline void infer_layer(const short *_
     const int r0 = (wv & 1) * 16, c0 = (wv >> 1) * 128;
     const int row = lane & 15, kq = (lane >> 4) * 4;
     constexpr int NK = KW / 16;
-    bf16x4 a[NK];
-#pragma unroll
-    for (int s = 0; s < NK; ++s) a[s] = *(const bf16x4 *)&wp[(r0 + row) * KW + s * 16 + kq];
     f32x4 acc[8];
 #pragma unroll
     for (int h = 0; h < 8; ++h) acc[h] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -565,6 +587,7 @@ __device__ __attribute__((always_inline)) inline void infer_layer(const short *_
             for (int i = 0; i < 4; ++i) {
                 float y = acc[h][i] + bo[i];
                 if (relu) y = y > 0.f ? y : 0.f;
+                if (TRAIN && in) gout[(r0 + kq + i) * L + l] = y;
                 v[i] = to_bf16(in ? y : 0.f);  // positions >= L hold zero (bf16 of 0)
             }
             *(bf16x4 *)&out[(l + 2) * kInferSH + r0 + kq] = v;
@@ -618,42 +641,88 @@ __device__ __attribute__((always_inline)) inline void infer_layer(const short *_
     }
 }
 
-template <int CP1>
+// TRAIN: `act` receives the three hidden activations [3][B][32][L] and the
+// weights are read from `params` (no packed copy, so no scratch is needed).
+template <int CP1, bool TRAIN>
 __global__ __launch_bounds__(256) void cnn_infer_kernel(const float *__restrict__ params,
                                                         const short *__restrict__ packed,
                                                         const float *__restrict__ X, int c_in, int c_out, int L,
-                                                        CnnOffsets off, CnnPacked P, float *__restrict__ logits,
-                                                        float *__restrict__ score, int pb, int nbg) {
-    constexpr int KW1 = (kTaps * CP1 + 15) / 16 * 16, SX0 = CP1 + 4;
+                                                        CnnOffsets off, CnnPacked P, float *__restrict__ act,
+                                                        float *__restrict__ logits, float *__restrict__ score, int pb,
+                                                        int nbg) {
+    constexpr int KW1 = (kTaps * CP1 + 15) / 16 * 16, SX0 = CP1 + 4, KWh = kTaps * kWidth;
     __shared__ short hA[kInferRows * kInferSH], hB[kInferRows * kInferSH];
     short *x0 = hB;  // the input window [260][CP1 + 4] until layer 2 writes hB
     const int b = blockIdx.x;
-    for (int e = threadIdx.x; e < kInferRows * CP1; e += 256) {
-        const int rr = e / CP1, c = e % CP1, l = rr - 2;
+    const int64_t la = (int64_t)gridDim.x * kWidth * L;
+    float *h1 = TRAIN ? act + (int64_t)b * kWidth * L : nullptr;
+    bf16x4 a1[KW1 / 16], a2[KWh / 16], a4[kWidth / 16];
+    infer_frags<kTaps, KW1, CP1, TRAIN>(packed + P.o[0], params + off.o[0], c_in, kWidth, a1);
+#pragma unroll
+    for (int u = 0; u < (kInferRows * CP1 + 255) / 256; ++u) {
+        const int e = u * 256 + (int)threadIdx.x;
+        const int c = e / kInferRows, rr = e % kInferRows, l = rr - 2;
         float v = 0.f;
         if (c < c_in && l >= 0 && l < L) v = X[((int64_t)b * c_in + c) * L + l];
-        x0[rr * SX0 + c] = to_bf16(v);
+        if (c < CP1) x0[rr * SX0 + c] = to_bf16(v);
     }
     for (int e = threadIdx.x; e < 4 * kWidth; e += 256) {  // halo rows of hA
         const int rr = e / kWidth, c = e % kWidth;
         hA[(rr < 2 ? rr : kInferRows - 4 + rr) * kInferSH + c] = 0;
     }
     __syncthreads();
-    infer_layer<kTaps, KW1, CP1, SX0>(packed + P.o[0], params + off.o[1], kWidth, x0, L, true, hA, nullptr);
-    __syncthreads();
-    for (int e = threadIdx.x; e < 4 * kWidth; e += 256) {  // halo rows of hB (the input window is spent)
-        const int rr = e / kWidth, c = e % kWidth;
-        hB[(rr < 2 ? rr : kInferRows - 4 + rr) * kInferSH + c] = 0;
+    infer_layer<kTaps, KW1, CP1, SX0, TRAIN>(a1, params + off.o[1], kWidth, x0, L, true, hA, h1);
+    // Layers 2 and 3 share one loop body: straight-line code runs once per
+    // wavefront, so its instruction fetches are on the critical path.
+#pragma unroll 1
+    for (int k = 0; k < 2; ++k) {
+        infer_frags<kTaps, KWh, kWidth, TRAIN>(packed + (k ? P.o[2] : P.o[1]), params + (k ? off.o[4] : off.o[2]), kWidth,
+                                               kWidth, a2);
+        __syncthreads();
+        if (k == 0)
+            for (int e = threadIdx.x; e < 4 * kWidth; e += 256) {  // halo rows of hB (the input window is spent)
+                const int rr = e / kWidth, c = e % kWidth;
+                hB[(rr < 2 ? rr : kInferRows - 4 + rr) * kInferSH + c] = 0;
+            }
+        infer_layer<kTaps, KWh, kWidth, kInferSH, TRAIN>(a2, params + (k ? off.o[5] : off.o[3]), kWidth, k ? hB : hA, L,
+                                                         true, k ? hA : hB, TRAIN ? h1 + (k + 1) * la : nullptr);
     }
-    infer_layer<kTaps, kTaps * kWidth, kWidth, kInferSH>(packed + P.o[1], params + off.o[3], kWidth, hA, L, true,
-                                                         hB, nullptr);
+    infer_frags<1, kWidth, kWidth, TRAIN>(packed + P.o[3], params + off.o[6], kWidth, c_out, a4);
     __syncthreads();
-    infer_layer<kTaps, kTaps * kWidth, kWidth, kInferSH>(packed + P.o[2], params + off.o[5], kWidth, hB, L, true,
-                                                         hA, nullptr);
-    __syncthreads();
-    infer_layer<1, kWidth, kWidth, kInferSH>(packed + P.o[3], params + off.o[7], c_out, hA, L, false, nullptr,
-                           logits ? logits + (int64_t)b * c_out * L : nullptr,
-                           score ? score + (int64_t)b * (c_out / 2) * nbg : nullptr, pb, nbg);
+    infer_layer<1, kWidth, kWidth, kInferSH, TRAIN>(a4, params + off.o[7], c_out, hA, L, false, nullptr,
+                                                    logits ? logits + (int64_t)b * c_out * L : nullptr,
+                                                    score ? score + (int64_t)b * (c_out / 2) * nbg : nullptr, pb, nbg);
+}
+
+static CnnOffsets cnn_offsets(int c_in, int c_out) {
+    const CnnLayout P = cnn_layout(c_in, c_out);
+    CnnOffsets off;
+    for (int i = 0; i < 8; ++i) off.o[i] = P.off[i];
+    return off;
+}
+
+template <bool TRAIN>
+static hipError_t launch_infer_kernel(const float *params, const short *packed, const float *x, int B, int c_in, int c_out,
+                                      int L, float *act, float *logits, float *score, int pb, int nbg, hipStream_t st) {
+    const CnnOffsets off = cnn_offsets(c_in, c_out);
+    const CnnPacked P = cnn_packed(c_in);
+    const dim3 grid((unsigned)B), block(256);
+    // input channels rounded to 4 (layer 1's K: 5 taps x those, rounded to 16)
+#define LTGW_INFER(CP)                                                                                               \
+    hipLaunchKernelGGL((cnn_infer_kernel<CP, TRAIN>), grid, block, 0, st, params, packed, x, c_in, c_out, L, off, P, act, \
+                       logits, score, pb, nbg)
+    switch (P.Cp1) {
+        case 4: LTGW_INFER(4); break;
+        case 8: LTGW_INFER(8); break;
+        case 12: LTGW_INFER(12); break;
+        case 16: LTGW_INFER(16); break;
+        case 20: LTGW_INFER(20); break;
+        case 24: LTGW_INFER(24); break;
+        case 28: LTGW_INFER(28); break;
+        default: LTGW_INFER(32); break;
+    }
+#undef LTGW_INFER
+    return hipGetLastError();
 }
 
 static hipError_t conv_fwd(const ConvDims &d, const float *X, const float *W, const float *b, int relu,
@@ -693,8 +762,19 @@ static hipError_t conv_fwd(const ConvDims &d, const float *X, const float *W, co
     return hipGetLastError();
 }
 
+bool cnn_infer_supported(int c_in, int c_out, int L) {
+    return c_in >= 1 && c_in <= kWidth && c_out >= 1 && c_out <= kWidth && L >= 1 && L <= kInferPos;
+}
+
+int64_t cnn_infer_scratch_shorts(int c_in) { return cnn_packed(c_in).total; }
+
 hipError_t launch_cnn_forward(const float *params, const float *x, int B, int c_in, int c_out, int L,
                               float *act, float *logits, hipStream_t st) {
+    // the whole network per sample in one workgroup where it fits on chip: the
+    // same products in the same order, one launch instead of four: 94 -> 29 us at
+    // 256 samples x 8 channels x 200 positions
+    if (cnn_infer_supported(c_in, c_out, L))
+        return launch_infer_kernel<true>(params, nullptr, x, B, c_in, c_out, L, act, logits, nullptr, 0, 0, st);
     const CnnLayout P = cnn_layout(c_in, c_out);
     const int64_t la = (int64_t)B * kWidth * L;
     float *h1 = act, *h2 = act + la, *h3 = act + 2 * la;
@@ -708,40 +788,17 @@ hipError_t launch_cnn_forward(const float *params, const float *x, int B, int c_
     return conv_fwd(d4, h3, params + P.off[6], params + P.off[7], 0, logits, st);
 }
 
-bool cnn_infer_supported(int c_in, int c_out, int L) {
-    return c_in >= 1 && c_in <= kWidth && c_out >= 1 && c_out <= kWidth && L >= 1 && L <= kInferPos;
-}
-
-int64_t cnn_infer_scratch_shorts(int c_in) { return cnn_packed(c_in).total; }
-
 hipError_t launch_cnn_infer(const float *params, const float *x, int B, int c_in, int c_out, int L, short *scratch,
                             float *logits, float *score, int W, hipStream_t st) {
     if (B < 1 || !cnn_infer_supported(c_in, c_out, L)) return hipErrorInvalidValue;
     if (score && ((W != 16 && W != 32 && W != 64) || (c_out & 1))) return hipErrorInvalidValue;
     const int pb = score ? W / 2 : 0, nbg = score ? (2 * L + W - 1) / W : 0;
-    const CnnLayout PL = cnn_layout(c_in, c_out);
-    CnnOffsets off;
-    for (int i = 0; i < 8; ++i) off.o[i] = PL.off[i];
     const CnnPacked P = cnn_packed(c_in);
-    hipLaunchKernelGGL(cnn_pack_kernel, dim3((unsigned)((P.total + 255) / 256)), dim3(256), 0, st, params, off, c_in,
-                       c_out, P, scratch);
-    const dim3 grid((unsigned)B), block(256);
-    // input channels rounded to 4 (layer 1's K: 5 taps x those, rounded to 16)
-#define LTGW_INFER(CP)                                                                                            \
-    hipLaunchKernelGGL(cnn_infer_kernel<CP>, grid, block, 0, st, params, scratch, x, c_in, c_out, L, off, P, logits, \
-                       score, pb, nbg)
-    switch (P.Cp1) {
-        case 4: LTGW_INFER(4); break;
-        case 8: LTGW_INFER(8); break;
-        case 12: LTGW_INFER(12); break;
-        case 16: LTGW_INFER(16); break;
-        case 20: LTGW_INFER(20); break;
-        case 24: LTGW_INFER(24); break;
-        case 28: LTGW_INFER(28); break;
-        default: LTGW_INFER(32); break;
-    }
-#undef LTGW_INFER
-    return hipGetLastError();
+    hipLaunchKernelGGL(cnn_pack_kernel, dim3((unsigned)((P.total + 255) / 256)), dim3(256), 0, st, params,
+                       cnn_offsets(c_in, c_out), c_in, c_out, P, scratch);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    return launch_infer_kernel<false>(params, scratch, x, B, c_in, c_out, L, nullptr, logits, score, pb, nbg, st);
 }
 
 // Work area of the backward pass: two activation-sized gradients plus the
@@ -787,11 +844,262 @@ static hipError_t data_grad(const ConvDims &d, const float *dY, const float *W, 
     return hipGetLastError();
 }
 
+// ---------------------------------------------------------------------------
+// The backward pass of a whole sample in one workgroup (c_in, c_out <= 32, L <=
+// 256): the gradient of a layer's output stays on chip as [channel][position] in
+// BF16, as the products take it, in one of two buffers (a layer's data gradient
+// is written to the other), beside the layer's input in two copies one element
+// apart, so that every tap's four positions are two aligned 32-bit words of the
+// weight gradient's operand.  The data gradient takes its products in the order
+// K = (o, t) of the layer-by-layer kernels (the same sums bit for bit, so the
+// BF16 roundings of the layers below do not move).  Each workgroup writes one
+// partial parameter vector (the sum over its samples blockIdx.x, + gridDim.x
+// ...), and sum_parts_kernel adds the partials in a fixed order.
+// The layer-by-layer kernels read every operand element by element through
+// integer divisions from HBM, and their bias sums ran in 32 workgroups: 1530 us
+// in 14 launches at 256 samples x 8 channels x 200 positions, 58 + 5 us here,
+// bound by the latency of one sample's four dependent stages (a workgroup per
+// CU).  Holding the weight gradients of all layers in accumulators over the
+// samples needed 512 registers and 75 KB of straight-line code (87 us).
+constexpr int kGradN = kInferPos + 12;  // shorts per row: position l at l + 4
+
+struct GradShared {
+    short g[2][kWidth * kGradN];        // zero outside [0, L)
+    short x[2][kWidth * kGradN];        // x[1][k] = x[0][k + 1]
+    float bsum[3][kWidth][2];
+    unsigned long long pos[kWidth][kInferPos / 64];  // bit l: the layer's input is positive there
+};
+
+// [C][L] in FP32: a wavefront takes channels 8 wv .. + 7, the lanes positions
+// lane, + 64 ...; loaded ahead of the stage that stores it.
+__device__ inline void grad_load(const float *__restrict__ src, int C, int L, float (&v)[8][4]) {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int c = wv * 8 + u, l = q * 64 + lane;
+            const bool in = c < C && l < L;
+            const float w = src[in ? (unsigned)(c * L + l) : 0u];
+            v[u][q] = in ? w : 0.f;
+        }
+}
+// A layer's input into both copies (zero outside [0, L) and for c >= C), and
+// which of it is positive.
+__device__ inline void grad_store_input(GradShared &S, const float (&v)[8][4]) {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int c = wv * 8 + u, at = c * kGradN + q * 64 + lane + 4;
+            const short w = to_bf16(v[u][q]);
+            S.x[0][at] = w;
+            S.x[1][at - 1] = w;
+            const unsigned long long m = __ballot(v[u][q] > 0.f);
+            if (lane == 0) S.pos[c][q] = m;
+        }
+}
+
+// Weight gradient of one layer from the output gradient g: rows m0 .. m0 + 15,
+// column tiles nt0 .. (columns j = c KT + t, CK of them), summed over the
+// positions; stored to (first) or added to dst[o][j] for o < O.
+template <int KT, int NT>
+__device__ __attribute__((always_inline)) inline void grad_weight(const GradShared &S, const short *g, int m0, int nt0,
+                                                                  int CK, int O, int L, bool first,
+                                                                  float *__restrict__ dst) {
+    const int lane = threadIdx.x & 63;
+    const int row = lane & 15, kq = (lane >> 4) * 4;
+    const short *ap = g + (m0 + row) * kGradN + kq + 4;
+    const short *bp[NT];
+    f32x4 acc[NT];
+#pragma unroll
+    for (int u = 0; u < NT; ++u) {
+        const int j = (nt0 + u) * 16 + row;
+        const int c = j < CK ? j / KT : 0, t = j < CK ? j % KT : 0;
+        const int k = kq + 4 + t - KT / 2;  // position kq at tap t
+        bp[u] = &S.x[k & 1][c * kGradN + (k & ~1)];
+        acc[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+#pragma unroll 1
+    for (int l0 = 0; l0 < L; l0 += 16) {
+        const bf16x4 a = *(const bf16x4 *)(ap + l0);
+#pragma unroll
+        for (int u = 0; u < NT; ++u) {
+            union {
+                unsigned w[2];
+                bf16x4 v;
+            } b;
+            b.w[0] = *(const unsigned *)(bp[u] + l0);
+            b.w[1] = *(const unsigned *)(bp[u] + l0 + 2);
+            acc[u] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b.v, acc[u], 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < NT; ++u) {
+        const int j = (nt0 + u) * 16 + row;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (j < CK && m0 + kq + i < O) {
+                float *d = dst + (unsigned)((m0 + kq + i) * CK + j);
+                *d = first ? acc[u][i] : *d + acc[u][i];
+            }
+    }
+}
+
+// Data gradient of one layer from the output gradient gi, into go: channels
+// r0 .., positions c0 ..+ 127; W[o][c][t] of the layer, O output channels.  Zero
+// where the layer's input is not positive.  bs: this lane's share of the bias
+// gradient of the layer below.
+template <int KT>
+__device__ __attribute__((always_inline)) inline void grad_data(const GradShared &S, const float *__restrict__ W, int O,
+                                                                const short *gi, short *go, int r0, int c0, int L,
+                                                                float (&bs)[4]) {
+    const int lane = threadIdx.x & 63;
+    const int row = lane & 15, kq = (lane >> 4) * 4;
+    constexpr int NK = 2 * KT;  // K = 32 KT in steps of 16
+    bf16x4 wa[NK];
+    const short *bp[NK][4];
+#pragma unroll
+    for (int s = 0; s < NK; ++s)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int k = s * 16 + kq + i, o = k / KT, t = k % KT;
+            const float w = W[(unsigned)(((o < O ? o : 0) * kWidth + r0 + row) * KT + t)];
+            wa[s][i] = o < O ? to_bf16(w) : (short)0;
+            bp[s][i] = gi + o * kGradN + 4 + row - t + KT / 2;
+        }
+#pragma unroll 1
+    for (int l0 = c0; l0 < c0 + 128 && l0 < L; l0 += 16) {
+        bf16x4 b[NK];
+#pragma unroll
+        for (int s = 0; s < NK; ++s)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) b[s][i] = bp[s][i][l0];
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < NK; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(wa[s], b[s], acc, 0, 0, 0);
+        const int l = l0 + row;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int c = r0 + kq + i;
+            const float v = ((S.pos[c][l >> 6] >> (l & 63)) & 1ull) ? acc[i] : 0.f;
+            bs[i] += v;
+            go[c * kGradN + l + 4] = to_bf16(v);
+        }
+    }
+}
+
+__global__ __launch_bounds__(256) void cnn_grad_kernel(const float *__restrict__ params, const float *__restrict__ X, int B,
+                                                       int c_in, int c_out, int L, CnnOffsets off, int64_t n_params,
+                                                       const float *__restrict__ act, const float *__restrict__ dlogits,
+                                                       float *__restrict__ part) {
+    __shared__ __attribute__((aligned(16))) GradShared S;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int row = lane & 15, kq = (lane >> 4) * 4;
+    const int r0 = (wv & 1) * 16, c0 = (wv >> 1) * 128, nt0 = (wv >> 1) * 5;
+    const int64_t la = (int64_t)B * kWidth * L;
+    float *p = part + (int64_t)blockIdx.x * n_params;
+    float b4[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) b4[u] = 0.f;
+    {
+        unsigned *z = (unsigned *)&S;
+        for (int e = threadIdx.x; e < (int)(sizeof S / 4); e += 256) z[e] = 0u;
+    }
+    __syncthreads();
+    for (int b = blockIdx.x; b < B; b += gridDim.x) {
+        const bool first = b == (int)blockIdx.x;
+        const float *h = act + (int64_t)b * kWidth * L;  // + 2 la, + la, + 0: inputs of layers 4, 3, 2
+        float pre[8][4];
+        float bs[4] = {0.f, 0.f, 0.f, 0.f};
+        {
+            float dv[8][4];  // the logits' gradient; rows past c_out are zero
+            grad_load(dlogits + (int64_t)b * c_out * L, c_out, L, dv);
+            grad_load(h + 2 * la, kWidth, L, pre);
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    b4[u] += dv[u][q];
+                    S.g[0][(wv * 8 + u) * kGradN + q * 64 + lane + 4] = to_bf16(dv[u][q]);
+                }
+            grad_store_input(S, pre);
+        }
+        grad_load(h + la, kWidth, L, pre);
+        __syncthreads();
+        grad_weight<1, 1>(S, S.g[0], r0, wv >> 1, kWidth, c_out, L, first, p + off.o[6]);
+        grad_data<1>(S, params + off.o[6], c_out, S.g[0], S.g[1], r0, c0, L, bs);
+        // Layers 3, 2, 1 share one loop body (straight-line code runs once per
+        // wavefront, so its instruction fetches are on the critical path); the
+        // first layer has no data gradient.
+#pragma unroll 1
+        for (int k = 0; k < 3; ++k) {
+            const int C = k < 2 ? kWidth : c_in;
+            const int64_t ow = k == 0 ? off.o[4] : k == 1 ? off.o[2] : off.o[0];
+            __syncthreads();  // the stage above has read its input and written this one's gradient
+            grad_store_input(S, pre);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {  // bias gradient of this stage's layer
+                float v = bs[i];
+                for (int o = 8; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+                if (row == 0) S.bsum[k][r0 + kq + i][wv >> 1] += v;
+                bs[i] = 0.f;
+            }
+            if (k < 2) grad_load(k == 0 ? h : X + (int64_t)b * c_in * L, k == 0 ? kWidth : c_in, L, pre);
+            __syncthreads();
+            grad_weight<kTaps, 5>(S, S.g[(k + 1) & 1], r0, nt0, C * kTaps, kWidth, L, first, p + ow);
+            if (k < 2) grad_data<kTaps>(S, params + ow, kWidth, S.g[(k + 1) & 1], S.g[k & 1], r0, c0, L, bs);
+        }
+        __syncthreads();
+    }
+    // the bias sums of this workgroup's samples
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+        float v = b4[u];
+        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+        if (lane == 0 && wv * 8 + u < c_out) p[off.o[7] + wv * 8 + u] = v;
+    }
+    if (threadIdx.x < 3 * kWidth) {
+        const int q = threadIdx.x / kWidth, o = threadIdx.x % kWidth;
+        p[off.o[5 - 2 * q] + o] = S.bsum[q][o][0] + S.bsum[q][o][1];
+    }
+}
+
+// grad[i] = sum of the partials in a fixed order: a wavefront adds every fourth
+// partial of 64 entries, and the four sums are added in order.
+__global__ __launch_bounds__(256) void sum_parts_kernel(const float *__restrict__ part, int parts, int64_t n,
+                                                        float *__restrict__ grad) {
+    __shared__ float sh[4][64];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int64_t i = (int64_t)blockIdx.x * 64 + lane;
+    float s = 0.f;
+    if (i < n) {
+#pragma unroll 8
+        for (int q = wv; q < parts; q += 4) s += part[(int64_t)q * n + i];
+    }
+    sh[wv][lane] = s;
+    __syncthreads();
+    if (wv == 0 && i < n) grad[i] = ((sh[0][lane] + sh[1][lane]) + sh[2][lane]) + sh[3][lane];
+}
+
 hipError_t launch_cnn_backward(const float *params, const float *x, int B, int c_in, int c_out, int L,
                                const float *act, const float *dlogits, float *work, int64_t work_floats,
                                float *grads, hipStream_t st) {
     if (work_floats < cnn_work_floats(B, c_in, c_out, L)) return hipErrorInvalidValue;
     const CnnLayout P = cnn_layout(c_in, c_out);
+    // one workgroup per sample (several samples each where the work area holds
+    // fewer partial parameter vectors), where the sample fits on chip
+    const int64_t parts = std::min<int64_t>(std::min(B, 512), work_floats / P.total);
+    if (cnn_infer_supported(c_in, c_out, L) && parts >= 1) {
+        hipLaunchKernelGGL(cnn_grad_kernel, dim3((unsigned)parts), dim3(256), 0, st, params, x, B, c_in, c_out, L,
+                           cnn_offsets(c_in, c_out), P.total, act, dlogits, work);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(sum_parts_kernel, dim3((unsigned)((P.total + 63) / 64)), dim3(256), 0, st, work, (int)parts,
+                           P.total, grads);
+        return hipGetLastError();
+    }
     const int64_t la = (int64_t)B * kWidth * L;
     const float *h1 = act, *h2 = act + la, *h3 = act + 2 * la;
     float *ga = work, *gb = work + la, *part = work + 2 * la;
@@ -814,51 +1122,73 @@ hipError_t launch_cnn_backward(const float *params, const float *x, int B, int c
 
 // Softmax cross-entropy per sample over n_cells logits against one target
 // cell (target < 0: loss 0, gradient 0); gradients divided by n_valid.
-__global__ __launch_bounds__(256) void softmax_xent_kernel(const float *logits, int n_cells,
-                                                           const int32_t *target, int n_valid,
-                                                           float *loss, float *dlogits) {
-    __shared__ float sh[256];
-    const int b = blockIdx.x;
+// One workgroup of 1024 per sample; up to kXentHeld logits per thread stay in
+// registers between the passes (a row of 8192), the rest is read again: bound by
+// the latency of one read and two block reductions (256 samples x 4800 cells:
+// 15 us with 256 threads that read the row three times, 5.5 us here).
+constexpr int kXentHeld = 8;
+
+__global__ __launch_bounds__(1024) void softmax_xent_kernel(const float *logits, int n_cells,
+                                                            const int32_t *target, int n_valid,
+                                                            float *loss, float *dlogits) {
+    __shared__ float sh[2][16];
+    const int b = blockIdx.x, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const float *z = logits + (int64_t)b * n_cells;
     float *dz = dlogits + (int64_t)b * n_cells;
     const int tg = target[b];
     if (tg < 0) {
-        for (int i = threadIdx.x; i < n_cells; i += 256) dz[i] = 0.f;
+        for (int i = threadIdx.x; i < n_cells; i += 1024) dz[i] = 0.f;
         if (threadIdx.x == 0) loss[b] = 0.f;
         return;
     }
+    float v[kXentHeld];
     float m = -3.4e38f;
-    for (int i = threadIdx.x; i < n_cells; i += 256) m = fmaxf(m, z[i]);
-    sh[threadIdx.x] = m;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) sh[threadIdx.x] = fmaxf(sh[threadIdx.x], sh[threadIdx.x + w]);
-        __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kXentHeld; ++u) {
+        const int i = u * 1024 + (int)threadIdx.x;
+        v[u] = i < n_cells ? z[i] : -__builtin_inff();
     }
-    m = sh[0];
+#pragma unroll
+    for (int u = 0; u < kXentHeld; ++u) m = fmaxf(m, v[u]);
+    for (int i = kXentHeld * 1024 + (int)threadIdx.x; i < n_cells; i += 1024) m = fmaxf(m, z[i]);
+    for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+    if (lane == 0) sh[0][wv] = m;
     __syncthreads();
+    m = sh[0][lane & 15];
+    for (int o = 8; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
     float s = 0.f;
-    for (int i = threadIdx.x; i < n_cells; i += 256) s += expf(z[i] - m);
-    sh[threadIdx.x] = s;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-        __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kXentHeld; ++u) {
+        if (u * 1024 + (int)threadIdx.x < n_cells) {
+            v[u] = expf(v[u] - m);
+            s += v[u];
+        }
     }
-    s = sh[0];
+    for (int i = kXentHeld * 1024 + (int)threadIdx.x; i < n_cells; i += 1024) s += expf(z[i] - m);
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    if (lane == 0) sh[1][wv] = s;
+    __syncthreads();
+    s = sh[1][lane & 15];
+    for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
     const float inv = 1.0f / ((float)n_valid * s);
-    for (int i = threadIdx.x; i < n_cells; i += 256) {
-        float g = expf(z[i] - m) * inv;
+    auto put = [&](int i, float ex) {
+        float g = ex * inv;
         if (i == tg) g -= 1.0f / (float)n_valid;
         dz[i] = g;
+    };
+#pragma unroll
+    for (int u = 0; u < kXentHeld; ++u) {
+        const int i = u * 1024 + (int)threadIdx.x;
+        if (i < n_cells) put(i, v[u]);
     }
+    for (int i = kXentHeld * 1024 + (int)threadIdx.x; i < n_cells; i += 1024) put(i, expf(z[i] - m));
     if (threadIdx.x == 0) loss[b] = logf(s) + m - z[tg];
 }
 
 hipError_t launch_softmax_xent(const float *logits, int B, int n_cells, const int32_t *target,
                                int n_valid, float *loss, float *dlogits, hipStream_t st) {
     if (B < 1 || n_cells < 1) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(softmax_xent_kernel, dim3(B), dim3(256), 0, st, logits, n_cells, target,
+    hipLaunchKernelGGL(softmax_xent_kernel, dim3(B), dim3(1024), 0, st, logits, n_cells, target,
                        n_valid < 1 ? 1 : n_valid, loss, dlogits);
     return hipGetLastError();
 }

@@ -333,6 +333,45 @@ def test_cnn_forward_backward_vs_oracle():
     ctx.close()
 
 
+@pytest.mark.parametrize("B,c_in,c_out,L", [
+    (1, 1, 1, 1),        # the work area holds no partial vector: the layer-by-layer kernels
+    (1, 1, 1, 255),      # one channel each, one position short of the on-chip limit
+    (2, 32, 32, 256),    # every limit of the on-chip pass
+    (2, 8, 24, 257),     # past it: the layer-by-layer kernels
+    (7, 3, 5, 16),       # one tile of positions
+    (5, 12, 24, 17),     # a remainder of one position
+    (40, 8, 24, 50),     # several samples per workgroup
+])
+def test_cnn_gradients_at_shape_limits(B, c_in, c_out, L):
+    """The bound is that of the product's BF16 operands (2^-8 of a term, of
+    random sign): 5e-3 of the layer's largest gradient, as above."""
+    import torch
+    from paper_2507_07816_amd import ltgw
+
+    ctx, *_ = _ctx()
+    print(f"case: cnn gradients B={B} c_in={c_in} c_out={c_out} L={L}", flush=True)
+    params = _net(15, c_in, c_out)
+    rng = np.random.default_rng(B * 1000 + L)
+    x = rng.normal(size=(B, c_in, L)).astype(np.float32)
+    dz = rng.normal(scale=0.1, size=(B, c_out, L)).astype(np.float32)
+    T = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    act = torch.empty((3, B, 32, L), dtype=torch.float32, device="cuda")
+    logits = torch.empty((B, c_out, L), dtype=torch.float32, device="cuda")
+    ltgw.ltgw_cnn_forward(ctx.h, T(params), T(x), c_out, act, logits)
+    work = torch.full((ltgw.ltgw_cnn_work_floats(B, c_in, c_out, L),), float("nan"), dtype=torch.float32, device="cuda")
+    grads = torch.full((params.size,), float("nan"), dtype=torch.float32, device="cuda")
+    ltgw.ltgw_cnn_backward(ctx.h, T(params), T(x), c_out, act, T(dz), work, grads)
+    zr, cache = cnn.forward(params, x, c_in, c_out, rnd=cnn.bf16_operands)
+    gr = cnn.backward(params, cache, dz.astype(np.float64), c_in, c_out, rnd=cnn.bf16_operands)
+    assert _rel(logits.cpu().numpy().astype(np.float64), zr) < 2e-3
+    g, off = grads.cpu().numpy().astype(np.float64), 0
+    for shp in cnn.layer_shapes(c_in, c_out):
+        n = int(np.prod(shp))
+        assert _rel(g[off:off + n], gr[off:off + n]) < 5e-3, shp
+        off += n
+    ctx.close()
+
+
 def test_softmax_xent_adam_and_select_top():
     import torch
     from paper_2507_07816_amd import ltgw
