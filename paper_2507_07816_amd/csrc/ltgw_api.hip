@@ -219,6 +219,45 @@ static void run_chunks(int nt, const F &f) {
     for (auto &x : th) x.join();
 }
 
+// log2(x) to about 0.09 for finite x >= 1, monotone (the exponent and the mantissa
+// read as one number): enough for an evaluation order.
+static float rough_log2(float x) {
+    uint32_t u;
+    std::memcpy(&u, &x, sizeof u);
+    return (float)((int32_t)u - 0x3f800000) * 0x1p-23f;
+}
+
+// ln(f0 / f) of a template's track about t_span after T0, in base 2 (roughly):
+// templates alike in it and in tau stay near each other over the whole search.
+static float track_drop(const ltgw_template &T, double t_span) {
+    const float r = (float)(1.0 + t_span / T.tau), d = (float)(T.brake - 1.0);
+    return rough_log2(std::min(r, 0x1p100f)) / std::max(d, 0x1p-20f);
+}
+
+// Whether the expansion kernel takes detector D for templates with tau >= tau_min,
+// brake >= brake_min and f0 <= f0_max: its index range, and all but an eighth of
+// the segments within the expansion's reach for the fastest such track (the
+// kernel takes a chunk out of reach segment by segment, at about twice the
+// general kernel's time).
+static bool expansion_suits(const Det &D, double t0, double tau_min, double brake_min, double f0_max) {
+    if (!(f0_max * D.t_sft * (1.0 + D.v_max) < 0x1p19) || D.k_lo >= (1 << 18) || D.n_bins >= (1 << 18)) return false;
+    const double e = 1.0 / (brake_min - 1.0);
+    if (!(e <= kExpandMaxE)) return false;
+    double c7 = 1.0;
+    for (int k = 0; k < 7; ++k) c7 *= (e + k) / (k + 1);
+    // 2 A 1.25 c7 d^7 within half the margin
+    const double reach = std::min(kExpandMaxStep, std::pow(0.5 * kExpandMaxMargin / (2.5 * c7 * f0_max * D.t_sft), 1.0 / 7.0));
+    int64_t out = 0;
+    for (int j0 = 0; j0 < D.n_seg; j0 += kListChunk) {
+        const int nj = std::min(kListChunk, D.n_seg - j0);
+        const double tc = D.h_t[j0 + nj / 2];
+        double dm = 0.0;
+        for (int j = j0; j < j0 + nj; ++j) dm = std::max(dm, std::fabs(D.h_t[j] - tc));
+        if (tc > t0 && dm > reach * (tau_min + (tc - t0))) out += nj;
+    }
+    return 8 * out <= D.n_seg;
+}
+
 extern "C" {
 
 int32_t ltgw_create(int32_t device, void *hip_stream, ltgw_ctx **out) {
@@ -318,7 +357,7 @@ void ltgw_destroy(ltgw_ctx *c) {
         release(d.scale); release(d.v); release(d.g); release(d.H); release(d.wfix); release(d.win);
         release(d.era); release(d.w_sky); release(d.wq_sky);
     }
-    DevBuf *all[] = {&c->staging, &c->counters, &c->cnn_packed, &c->list_d, &c->perm_d, &c->list_dop, &c->list_sky,
+    DevBuf *all[] = {&c->staging, &c->counters, &c->cnn_packed, &c->list_d, &c->perm_d, &c->list_dop, &c->list_sky, &c->list_tab, &c->list_part,
                      &c->tau_d,   &c->brake_d,  &c->sky_d,      &c->res_s, &c->res_c, &c->res_n, &c->res_w1, &c->res_w2, &c->diff,
                      &c->cand_pa, &c->cand_ia, &c->cand_pb, &c->cand_ib, &c->cand_out, &c->n_out};
     for (DevBuf *b : all) release(*b);
@@ -897,17 +936,27 @@ int32_t ltgw_eval_list(ltgw_ctx *c, const ltgw_template *tpl, int64_t n, double 
     // checks, f0 range and whether every template has the first one's sky
     // direction, per chunk; the first invalid template is reported
     const int nt = list_threads(n);
+    double t_span = 0.0;  // the searched time after T0
+    for (int d = 0; d < 32; ++d) {
+        const Det &D = c->det[d];
+        if (!D.loaded || (det_mask && !((det_mask >> d) & 1u))) continue;
+        for (int j : {0, D.n_seg - 1}) t_span = std::max(t_span, D.h_t[(size_t)j] - t0);
+    }
     struct ChunkScan {
         int64_t bad = -1;
-        double f0_lo = 0.0, f0_hi = 0.0;
+        double f0_lo = 0.0, f0_hi = 0.0, tau_lo = 0.0, tau_hi = 0.0, brake_lo = 0.0;
+        float drop_lo = 0.0f, drop_hi = 0.0f;
         bool one_sky = true;
     };
     std::vector<ChunkScan> scan(nt);
     run_chunks(nt, [&](int t) {
         ChunkScan &r = scan[t];
         const int64_t lo = chunk_lo(n, nt, t), hi = chunk_lo(n, nt, t + 1);
-        r.f0_lo = tpl[lo].f0;
-        r.f0_hi = tpl[lo].f0;
+        r.f0_lo = r.f0_hi = tpl[lo].f0;
+        r.tau_lo = r.tau_hi = tpl[lo].tau;
+        r.brake_lo = tpl[lo].brake;
+        r.drop_lo = INFINITY;
+        r.drop_hi = -INFINITY;
         for (int64_t q = lo; q < hi; ++q) {
             const ltgw_template &T = tpl[q];
             if (template_error(T)) {
@@ -916,12 +965,24 @@ int32_t ltgw_eval_list(ltgw_ctx *c, const ltgw_template *tpl, int64_t n, double 
             }
             r.f0_lo = T.f0 < r.f0_lo ? T.f0 : r.f0_lo;
             r.f0_hi = T.f0 > r.f0_hi ? T.f0 : r.f0_hi;
+            r.tau_lo = std::min(r.tau_lo, T.tau);
+            r.tau_hi = std::max(r.tau_hi, T.tau);
+            r.brake_lo = std::min(r.brake_lo, T.brake);
+            const float drop = track_drop(T, t_span);
+            r.drop_lo = std::min(r.drop_lo, drop);
+            r.drop_hi = std::max(r.drop_hi, drop);
             r.one_sky = r.one_sky && std::memcmp(T.sky, tpl[0].sky, sizeof T.sky) == 0;
         }
     });
-    double f0_max = 0.0, f0_lo = 0.0;
+    double f0_max = 0.0, f0_lo = 0.0, tau_lo = tpl[0].tau, tau_hi = tpl[0].tau, brake_lo = tpl[0].brake;
+    float drop_lo = INFINITY, drop_hi = -INFINITY;
     bool one_sky = true;
     for (int t = 0; t < nt; ++t) {
+        tau_lo = std::min(tau_lo, scan[t].tau_lo);
+        tau_hi = std::max(tau_hi, scan[t].tau_hi);
+        brake_lo = std::min(brake_lo, scan[t].brake_lo);
+        drop_lo = std::min(drop_lo, scan[t].drop_lo);
+        drop_hi = std::max(drop_hi, scan[t].drop_hi);
         if (scan[t].bad >= 0)
             return fail(c, LTGW_E_INVALID_ARG, "template %lld: %s", (long long)scan[t].bad,
                         template_error(tpl[scan[t].bad]));
@@ -966,9 +1027,18 @@ int32_t ltgw_eval_list(ltgw_ctx *c, const ltgw_template *tpl, int64_t n, double 
         std::memcpy(V.arms.b, D.arms + 3, sizeof V.arms.b);
         n_seg_total += D.n_seg;
     }
-    // evaluation order: f0 in 2^16 buckets over the list's range (a stable
-    // counting sort), so that neighbouring lanes gather neighbouring columns;
-    // every result goes to its list position, so the order changes none
+    // evaluation order (a stable counting sort into 2^16 buckets): cells of the
+    // track's total drop and of tau, f0 within a cell, so that the templates of a
+    // wavefront follow neighbouring tracks and gather neighbouring columns at all
+    // times; in f0 order alone (tracks that part within the first hours) each
+    // lane reads a line of its own.  The cell counts share log2(wavefronts)
+    // between the drop, tau and f0.  Every result goes to its list position, so
+    // the order changes none.
+    const double waves_log2 = std::log2(std::max(1.0, (double)n / 64.0));
+    const int drop_bits = std::min(5, (int)(0.36 * waves_log2)), tau_bits = std::min(3, (int)(0.22 * waves_log2));
+    const int f0_bits = 16 - drop_bits - tau_bits;
+    auto scale_of = [](double lo, double hi, int bits) { return hi > lo ? ((1 << bits) - 1e-3) / (hi - lo) : 0.0; };
+    const double drop_scale = scale_of(drop_lo, drop_hi, drop_bits), tau_scale = scale_of(tau_lo, tau_hi, tau_bits);
     // the staging is pinned (the uploads run at DMA rate) and reused: wait for
     // the previous call's uploads from it first
     HIP_TRY(c, hipEventSynchronize(c->ev_h2d), "previous upload");
@@ -980,15 +1050,20 @@ int32_t ltgw_eval_list(ltgw_ctx *c, const ltgw_template *tpl, int64_t n, double 
     // staging; a bucket's positions then go to the chunks in list order, so
     // the scatter below gives the serial stable order.
     constexpr int kBuckets = 1 << 16;
-    const double bscale = f0_max > f0_lo ? (kBuckets - 1) / (f0_max - f0_lo) : 0.0;
+    const double f0_scale = scale_of(f0_lo, f0_max, f0_bits);
+    auto cell = [](double v, double lo, double scale, int bits) {
+        return std::max(0, std::min((1 << bits) - 1, (int)((v - lo) * scale)));
+    };
     std::vector<uint16_t> key((size_t)n);
     std::vector<int32_t> pos((size_t)nt * kBuckets, 0);  // [chunk][bucket]
     run_chunks(nt, [&](int t) {
         const int64_t lo = chunk_lo(n, nt, t), hi = chunk_lo(n, nt, t + 1);
         int32_t *cnt = pos.data() + (size_t)t * kBuckets;
         for (int64_t q = lo; q < hi; ++q) {
-            const int b = (int)((tpl[q].f0 - f0_lo) * bscale);
-            key[(size_t)q] = (uint16_t)(b < 0 ? 0 : b > kBuckets - 1 ? kBuckets - 1 : b);
+            const ltgw_template &T = tpl[q];
+            const int u = cell(track_drop(T, t_span), drop_lo, drop_scale, drop_bits);
+            const int v = cell(T.tau, tau_lo, tau_scale, tau_bits);
+            key[(size_t)q] = (uint16_t)((((u << tau_bits) | v) << f0_bits) | cell(T.f0, f0_lo, f0_scale, f0_bits));
             ++cnt[key[(size_t)q]];
         }
         std::memcpy((ltgw_template *)c->h_list.p + lo, tpl + lo, (size_t)(hi - lo) * sizeof(ltgw_template));
@@ -1041,7 +1116,48 @@ int32_t ltgw_eval_list(ltgw_ctx *c, const ltgw_template *tpl, int64_t n, double 
     // same operations in the same order), read per segment by the kernel
     bool any_ant = false;
     for (int q = 0; q < n_slots; ++q) any_ant = any_ant || a.det[q].era != nullptr;
-    if (one_sky && !any_ant) {
+    bool expand = !any_ant;
+    int64_t chunks = 0;
+    for (int q = 0; q < n_slots; ++q) {
+        const Det &D = c->det[slots[q]];
+        expand = expand && expansion_suits(D, t0, tau_lo, brake_lo, f0_max);
+        chunks += (D.n_seg + kListChunk - 1) / kListChunk;
+    }
+    a.slices = 1;
+    if (expand) {
+        // per-segment tables: dt, v/c, Doppler factors and chunks of each detector
+        int64_t tot = 0;
+        for (int q = 0; q < n_slots; ++q) tot += c->det[slots[q]].n_seg;
+        if ((rc = ensure(c, c->list_tab, (size_t)tot * 40 + (size_t)chunks * sizeof(ListChunk), "list tables")) != LTGW_OK)
+            return rc;
+        ListChunk *ch = (ListChunk *)c->list_tab.p;
+        double *tab = (double *)(ch + chunks);
+        for (int q = 0; q < n_slots; ++q) {
+            ListDet &V = a.det[q];
+            double *dt = tab, *vc = dt + V.n_seg, *dop = vc + 3 * (int64_t)V.n_seg;
+            HIP_TRY(c, launch_list_tables(V, one_sky ? tpl[0].sky : nullptr, ch, dt, vc, dop, c->stream),
+                    "list table launch");
+            V.chunk = ch;
+            V.dt = dt;
+            V.vc = vc;
+            V.dop = one_sky ? dop : nullptr;
+            ch += (V.n_seg + kListChunk - 1) / kListChunk;
+            tab += 5 * (int64_t)V.n_seg;
+        }
+        // A list of fewer than four workgroups per CU is split over its chunks into
+        // about eight, where its chunk sums (12 bytes each) fit kPartBytes: 4800
+        // templates x 1024 segments (19 workgroups) took 637 us unsplit.
+        constexpr int64_t kPartBytes = 256 << 20;
+        const int64_t blocks = (n + 255) / 256;
+        const int64_t want = std::min<int64_t>(chunks, ((int64_t)8 * c->cu_count + blocks - 1) / blocks);
+        if (blocks < (int64_t)4 * c->cu_count && want > 1 && n * chunks * 12 <= kPartBytes) {
+            a.slices = (int32_t)want;
+            const size_t part = (size_t)(n * chunks) * 12;
+            if ((rc = ensure(c, c->list_part, part + (size_t)(n * want) * 8, "list chunk sums")) != LTGW_OK) return rc;
+            a.part = (float *)c->list_part.p;
+            a.part_n = (int32_t *)((char *)c->list_part.p + part);
+        }
+    } else if (one_sky && !any_ant) {
         int64_t off = 0, tot = 0;
         for (int q = 0; q < n_slots; ++q) tot += c->det[slots[q]].n_seg;
         if ((rc = ensure(c, c->list_dop, (size_t)tot * 8, "list Doppler tables")) != LTGW_OK) return rc;
@@ -1062,7 +1178,9 @@ int32_t ltgw_eval_list(ltgw_ctx *c, const ltgw_template *tpl, int64_t n, double 
     HIP_TRY(c, hipEventRecord(c->ev_h2d, c->stream), "event record");
     HIP_TRY(c, hipEventRecord(c->ev[0], c->stream), "event record");
     HIP_TRY(c, hipEventRecord(c->ev[1], c->stream), "event record");
-    HIP_TRY(c, launch_template_list(c->det[slots[0]].store, a, c->stream), "template list launch");
+    HIP_TRY(c, expand ? launch_list_expansion(c->det[slots[0]].store, a, c->stream)
+                      : launch_template_list(c->det[slots[0]].store, a, c->stream),
+            "template list launch");
     HIP_TRY(c, hipEventRecord(c->ev[2], c->stream), "event record");
     c->have_eval = true;
     c->results_kept = true;

@@ -158,6 +158,7 @@ struct ltgw_ctx {
     ltgw::DevBuf h_list, h_perm;  // pinned host staging of its templates and of their evaluation order
     ltgw::DevBuf list_d, perm_d;
     ltgw::DevBuf list_dop, list_sky;    // Doppler tables of a one-sky list, and that sky
+    ltgw::DevBuf list_tab, list_part;   // the expansion kernel's per-segment tables and chunk sums
     // data preparation (ltgw_sft_normalise): spectra of a chunk, FFT plans
     struct SftPlan {
         int n_fft, batch;

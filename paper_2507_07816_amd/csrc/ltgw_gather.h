@@ -27,6 +27,8 @@ struct Store;
 template <>
 struct Store<LTGW_STORE_F32> {
     static constexpr int kBytes = 4;
+    // the element as an FP32 value whose sign is the count bit
+    __device__ static float load(__amdgpu_buffer_rsrc_t r, int i, int soff) { return ltgw_sbuf_f32(r, i, 0, soff, 0); }
     // returns |value| and adds the count bit
     __device__ static float get(__amdgpu_buffer_rsrc_t r, int i, int soff, int &cnt) {
         float p = ltgw_sbuf_f32(r, i, 0, soff, 0);
@@ -37,6 +39,9 @@ struct Store<LTGW_STORE_F32> {
 template <>
 struct Store<LTGW_STORE_BF16> {
     static constexpr int kBytes = 2;
+    __device__ static float load(__amdgpu_buffer_rsrc_t r, int i, int soff) {
+        return __uint_as_float((unsigned)ltgw_sbuf_u16(r, i, 0, soff, 0) << 16);
+    }
     __device__ static float get(__amdgpu_buffer_rsrc_t r, int i, int soff, int &cnt) {
         unsigned u = ltgw_sbuf_u16(r, i, 0, soff, 0);
         cnt += (int)(u >> 15);
@@ -46,6 +51,9 @@ struct Store<LTGW_STORE_BF16> {
 template <>
 struct Store<LTGW_STORE_FP8> {
     static constexpr int kBytes = 1;
+    __device__ static float load(__amdgpu_buffer_rsrc_t r, int i, int soff) {
+        return __builtin_amdgcn_cvt_f32_fp8((int)ltgw_sbuf_u8(r, i, 0, soff, 0), 0);
+    }
     __device__ static float get(__amdgpu_buffer_rsrc_t r, int i, int soff, int &cnt) {
         unsigned u = ltgw_sbuf_u8(r, i, 0, soff, 0);
         cnt += (int)(u >> 7);

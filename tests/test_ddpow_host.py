@@ -411,3 +411,94 @@ def test_column_decision_by_enclosure_equals_correct_rounding(tmp_path):
     print(f"fallback: {took[near].mean():.3f} of the near-boundary rows, {took[~near].sum()} of the others")
     assert took[near].mean() > 0.5
     assert took[~near].sum() <= 2
+
+
+EXPAND_DRIVER = r"""
+#include <cstdio>
+#include <cstdlib>
+#include <vector>
+#include "track_expand.h"
+using namespace ltgw;
+int main(int argc, char **argv) {
+    // rows: tau, brake, f0, t0, t_sft, k_lo, tc, t, dtmax, D -> holds, open, column, contract column
+    const long n = atol(argv[3]);
+    std::vector<double> in(10 * n), out(4 * n);
+    FILE *f = fopen(argv[1], "rb");
+    if (fread(in.data(), 8, in.size(), f) != in.size()) return 1;
+    fclose(f);
+    for (long q = 0; q < n; ++q) {
+        const double *a = &in[10 * q];
+        const double tau = a[0], e = 1.0 / (1.0 - a[1]), f0 = a[2], t0 = a[3], T = a[4], k_lo = a[5], D = a[9];
+        const double tau_c = tau + (a[6] - t0), r = 1.0 / tau_c;
+        double G, y, c[7];
+        const bool ok = pow_enclose_value(tau_c * (1.0 / tau), e, &G, &y);
+        expand_series(e, c);
+        const double A = (f0 * T) * G, dm = a[8] * r, m = expand_margin(A, dm, c[6], y, e);
+        double k[7] = {A};
+        for (int i = 0; i < 6; ++i) k[i + 1] = A * c[i];
+        const unsigned mi = ok && expand_holds(dm, m, e) ? expand_margin_units(m) : 0u;
+        unsigned z;
+        const unsigned col = expand_column(expand_x(k, (a[7] - a[6]) * r, D), 0x1p20 + (1.5 - k_lo), mi, &z);
+        int und = 0;
+        const double g = pow_cr(1.0 + (a[7] - t0) / tau, e, &und);
+        const double h = g * D;
+        const double x = f0 * (h * T);
+        out[4 * q] = ok && expand_holds(dm, m, e);
+        out[4 * q + 1] = z < 2u * mi;
+        out[4 * q + 2] = col;
+        out[4 * q + 3] = und ? -1e9 : (double)(long)(x + (1.5 - k_lo));
+    }
+    f = fopen(argv[2], "wb");
+    fwrite(out.data(), 8, out.size(), f);
+    fclose(f);
+    return 0;
+}
+"""
+
+
+def test_column_by_expansion_equals_correct_rounding(tmp_path):
+    """The chunk expansion's column rule (track_expand.h) against the column of
+    the correctly rounded power, over 1.5 million evaluations: braking indices
+    down to 1.25, tau from 300 s, segments of 4 to 1800 s, T0 up to the chunk,
+    k_lo up to 2^18, and a fifth of the tracks placed within 1e-9 bins of a column
+    boundary.  Wherever the series holds and calls a column certain, it is the
+    contract's; what it leaves open stays rare away from boundaries; tracks
+    below the band wrap past any row."""
+    src, exe = tmp_path / "expand.cpp", tmp_path / "expand"
+    src.write_text(EXPAND_DRIVER)
+    subprocess.run(["g++", "-O2", "-std=c++17", "-ffp-contract=off", "-fno-fast-math", "-I", CSRC, str(src), "-o",
+                    str(exe)], check=True)
+    r = np.random.default_rng(67)
+    n = 1_500_000
+    T = r.choice([4.0, 8.0, 60.0, 1800.0], n)
+    tau = np.exp(r.uniform(np.log(300.0), np.log(40000.0), n))
+    brake = r.choice([1.25, 1.5, 2.0, 3.0, 7.0], n) + r.uniform(0.0, 1.0, n)
+    t0 = r.choice([0.0, 1234.5], n)
+    tc = t0 + r.uniform(0.0, 86400.0, n)
+    t = np.maximum(tc + np.round(r.uniform(-16, 15, n)) * T, t0)
+    dtmax = np.maximum(16.0 * T, np.abs(t - tc))
+    D = 1.0 + r.uniform(-1e-4, 1e-4, n)
+    k_lo = r.choice([2.0, 1600.0, 4000.0, 2.0 ** 18 - 1], n)
+    e = 1.0 / (1.0 - brake)
+    g = (1.0 + (t - t0) / tau) ** e
+    x = np.minimum(np.maximum(k_lo, 5.0) * np.exp(r.uniform(-1.0, 1.0, n)), 2.0 ** 18)
+    near = r.uniform(size=n) < 0.2
+    x = np.where(near, np.round(x) + 0.5 + r.uniform(-1e-9, 1e-9, n), x)
+    f0 = x / (g * D * T)
+    ok = f0 * T < 2.0 ** 19
+    rows = np.column_stack([tau, brake, f0, t0, T, k_lo, tc, t, dtmax, D])[ok]
+    near = near[ok]
+    fi, fo = tmp_path / "in.bin", tmp_path / "out.bin"
+    rows.tofile(fi)
+    subprocess.run([str(exe), str(fi), str(fo), str(len(rows))], check=True)
+    holds, open_, col, want = np.fromfile(fo).reshape(-1, 4).T
+    holds, open_ = holds.astype(bool), open_.astype(bool)
+    assert holds.mean() > 0.4 and not holds.all() and not np.any(want == -1e9)
+    sure = holds & ~open_
+    pos = sure & (want >= 1)
+    assert np.array_equal(col[pos], want[pos])
+    assert np.all((col[sure & (want < 1)] == 0) | (col[sure & (want < 1)] >= 2 ** 19))
+    print(f"holds {holds.mean():.3f}, open near boundaries {open_[holds & near].mean():.3f}, "
+          f"elsewhere {open_[holds & ~near].mean():.2e}")
+    assert open_[holds & near].mean() > 0.9
+    assert open_[holds & ~near].mean() < 2.0 ** -12

@@ -222,6 +222,23 @@ def test_list_columns_at_boundaries_take_the_exact_power():
         ctx.close()
 
 
+@pytest.mark.parametrize("n_seg,n_bins,n,k_lo,tau,spacing", [
+    (33, 64, 700, 2 ** 18 - 1, (3500.0, 35000.0), 8.0),      # the last first column of the expansion, a tail of 1
+    (33, 64, 700, 2 ** 18, (3500.0, 35000.0), 8.0),          # past it: the general kernel
+    (64, 300, 2000, 1900, (60.0, 120.0), 1.0),               # chunks that the series holds for and others
+    (40, 300, 2000, 1900, (60.0, 120.0), 37.0),              # a step it does not hold for: the general kernel
+    (5, 200, 262144, 1900, (3500.0, 35000.0), 8.0),          # the shortest list that is not split
+    (64, 200, 262143, 1900, (3500.0, 35000.0), 8.0),         # split, the last workgroup not full
+])
+def test_list_expansion_limits(n_seg, n_bins, n, k_lo, tau, spacing):
+    print(f"case: list expansion n_seg={n_seg} n={n} k_lo={k_lo} tau={tau} spacing={spacing}", flush=True)
+    det = _small(n_seg, n_seg, n_bins, k_lo=k_lo, spacing=spacing, weights=True)
+    params = _bank(n, det, seed=n_seg + n % 97, pad=1.0, tau=tau, brake=(2.0, 6.0))
+    ref = oracle.evaluate_params(det, params)
+    gpu = _list([det], params, k=7)
+    _check(gpu, ref, params, 7)
+
+
 def test_list_two_detectors_and_mask():
     d1 = _small(1, 60, 256, k_lo=1900)
     d2 = _small(2, 45, 200, k_lo=1930, t_sft=4.0)
