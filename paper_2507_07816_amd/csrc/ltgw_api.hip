@@ -289,8 +289,8 @@ int32_t ltgw_create(int32_t device, void *hip_stream, ltgw_ctx **out) {
     }
     c->device = device;
     c->stream = (hipStream_t)hip_stream;
-    int rc = ensure(c, c->counters, kNumCnt * sizeof(unsigned long long), "counters");
-    if (rc == LTGW_OK) rc = zero_counter(c, 0, kNumCnt);
+    int rc = ensure(c, c->counters, kNumCounters * sizeof(unsigned long long), "counters");
+    if (rc == LTGW_OK) rc = zero_counter(c, 0, kNumCounters);
     for (int i = 0; i < 3 && rc == LTGW_OK; ++i) {
         hipError_t ee = hipEventCreate(&c->ev[i]);
         if (ee != hipSuccess) rc = hip_fail(c, ee, "event create");
@@ -359,9 +359,10 @@ void ltgw_destroy(ltgw_ctx *c) {
     }
     DevBuf *all[] = {&c->staging, &c->counters, &c->cnn_packed, &c->list_d, &c->perm_d, &c->list_dop, &c->list_sky, &c->list_tab, &c->list_part,
                      &c->tau_d,   &c->brake_d,  &c->sky_d,      &c->res_s, &c->res_c, &c->res_n, &c->res_w1, &c->res_w2, &c->diff,
-                     &c->cand_pa, &c->cand_ia, &c->cand_pb, &c->cand_ib, &c->cand_out, &c->n_out};
+                     &c->cand};
     for (DevBuf *b : all) release(*b);
     release_pinned(c->h_list);
+    release_pinned(c->h_top);
     release_pinned(c->h_perm);
     delete c;
 }
@@ -1311,34 +1312,38 @@ int32_t ltgw_topk_candidates(ltgw_ctx *c, uint32_t stat, int32_t k, ltgw_candida
     if (!out_host || !n_out) return fail(c, LTGW_E_INVALID_ARG, "output pointers are NULL");
     const int64_t cap = topk_scratch_entries(c->n_templates, k);
     int rc;
-    if ((rc = ensure(c, c->cand_pa, cap * 8, "top-k scratch")) != LTGW_OK) return rc;
-    if ((rc = ensure(c, c->cand_ia, cap * 8, "top-k scratch")) != LTGW_OK) return rc;
-    if ((rc = ensure(c, c->cand_pb, cap * 8, "top-k scratch")) != LTGW_OK) return rc;
-    if ((rc = ensure(c, c->cand_ib, cap * 8, "top-k scratch")) != LTGW_OK) return rc;
-    if ((rc = ensure(c, c->cand_out, (size_t)k * sizeof(ltgw_candidate), "top-k records")) != LTGW_OK) return rc;
-    if ((rc = ensure(c, c->n_out, 8, "top-k count")) != LTGW_OK) return rc;
-    TopkDecode dec;
-    dec.f0_min = c->f0_min;
-    dec.f0_step = c->f0_step;
-    dec.n_f0 = c->n_f0;
-    dec.n_tau = c->n_tau;
-    dec.n_brake = c->n_brake;
-    dec.tau = (const double *)c->tau_d.p;
-    dec.brake = (const double *)c->brake_d.p;
-    dec.list = c->list_mode ? (const ltgw_template *)c->list_d.p : nullptr;
-    const double q = std::exp(-(double)c->rho_th);
-    HIP_TRY(c, launch_topk(stat, c->n_templates, (const double *)c->res_s.p, (const int32_t *)c->res_c.p,
-                           (const int32_t *)c->res_n.p, (const double *)c->res_w1.p,
-                           (const double *)c->res_w2.p, q, k, (double *)c->cand_pa.p,
-                           (int64_t *)c->cand_ia.p, (double *)c->cand_pb.p, (int64_t *)c->cand_ib.p,
-                           cap, dec, (ltgw_candidate *)c->cand_out.p, (int32_t *)c->n_out.p, c->stream),
-            "top-k launch");
-    HIP_TRY(c, hipMemcpyAsync(out_host, c->cand_out.p, (size_t)k * sizeof(ltgw_candidate),
-                              hipMemcpyDeviceToHost, c->stream),
-            "top-k download");
-    HIP_TRY(c, hipMemcpyAsync(n_out, c->n_out.p, sizeof(int32_t), hipMemcpyDeviceToHost, c->stream),
-            "top-k download");
+    if ((rc = ensure(c, c->cand, (size_t)cap * 16, "top-k scratch")) != LTGW_OK) return rc;
+    // the records and their count are written straight to pinned host memory
+    // (every earlier ranking into it has been waited for)
+    constexpr size_t kRecords = LTGW_MAX_TOPK * sizeof(ltgw_candidate);
+    if ((rc = ensure_pinned(c, c->h_top, kRecords + sizeof(int32_t), "top-k records")) != LTGW_OK) return rc;
+    ltgw_candidate *const rec = (ltgw_candidate *)c->h_top.p;
+    int32_t *const n_rec = (int32_t *)((char *)c->h_top.p + kRecords);
+    TopkJob J;
+    J.n = c->n_templates;
+    J.stat = stat;
+    J.s = (const double *)c->res_s.p;
+    J.c = (const int32_t *)c->res_c.p;
+    J.N = (const int32_t *)c->res_n.p;
+    J.w1 = (const double *)c->res_w1.p;
+    J.w2 = (const double *)c->res_w2.p;
+    J.q = std::exp(-(double)c->rho_th);
+    J.cand = c->cand.p;
+    J.done = (unsigned *)((unsigned long long *)c->counters.p + kCntTopk);
+    J.dec.f0_min = c->f0_min;
+    J.dec.f0_step = c->f0_step;
+    J.dec.n_f0 = c->n_f0;
+    J.dec.n_tau = c->n_tau;
+    J.dec.n_brake = c->n_brake;
+    J.dec.tau = (const double *)c->tau_d.p;
+    J.dec.brake = (const double *)c->brake_d.p;
+    J.dec.list = c->list_mode ? (const ltgw_template *)c->list_d.p : nullptr;
+    J.out = rec;
+    J.n_out = n_rec;
+    HIP_TRY(c, launch_topk(1, &J, k, cap, c->stream), "top-k launch");
     HIP_TRY(c, hipStreamSynchronize(c->stream), "top-k");
+    std::memcpy(out_host, rec, (size_t)k * sizeof(ltgw_candidate));
+    *n_out = *n_rec;
     return LTGW_OK;
 }
 

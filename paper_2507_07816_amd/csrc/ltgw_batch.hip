@@ -24,8 +24,8 @@ void free_batch(BatchState &B) {
     if (B.ev1) (void)hipEventDestroy(B.ev1);
     DevBuf *all[] = {&B.searches, &B.tiles, &B.ctr, &B.tiles_done, &B.t_done, &B.t_start,
                      &B.in_band, &B.s, &B.c, &B.n_res, &B.w1, &B.w2, &B.gtab, &B.dtab, &B.win,
-                     &B.tau, &B.brake, &B.sky, &B.cand, &B.n_out, &B.diff, &B.pa, &B.ia,
-                     &B.pb, &B.ib};
+                     &B.tau, &B.brake, &B.sky, &B.cand, &B.n_out, &B.diff, &B.topk,
+                     &B.topk_done};
     for (DevBuf *b : all) release(*b);
     B = BatchState();
 }
@@ -177,17 +177,16 @@ int enqueue(ltgw_ctx *c, BatchState &B, hipStream_t st, int variant, bool with_t
         for (int i = 0; i < B.n; ++i) {
             const int64_t o = B.tpl_off[i];
             const double q = std::exp(-(double)B.plans[i].rho_th);
+            TopkJob J[2];
             for (int st_i = 0; st_i < 2; ++st_i) {
-                const uint32_t stat = st_i == 0 ? LTGW_STAT_POWER : LTGW_STAT_COUNT;
-                HIP_TRY(c, launch_topk(stat, B.plans[i].n_tpl, (const double *)B.s.p + o,
-                                       (const int32_t *)B.c.p + o, (const int32_t *)B.n_res.p + o,
-                                       (const double *)B.w1.p + o, (const double *)B.w2.p + o, q, B.k,
-                                       (double *)B.pa.p, (int64_t *)B.ia.p, (double *)B.pb.p,
-                                       (int64_t *)B.ib.p, B.topk_cap, B.dec[i],
-                                       (ltgw_candidate *)B.cand.p + ((int64_t)i * 2 + st_i) * B.k,
-                                       (int32_t *)B.n_out.p + i * 2 + st_i, st),
-                        "batch top-k launch");
+                J[st_i] = TopkJob{B.plans[i].n_tpl, st_i == 0 ? LTGW_STAT_POWER : LTGW_STAT_COUNT, (const double *)B.s.p + o,
+                                  (const int32_t *)B.c.p + o, (const int32_t *)B.n_res.p + o, (const double *)B.w1.p + o,
+                                  (const double *)B.w2.p + o, q, (char *)B.topk.p + (size_t)st_i * B.topk_cap * 16,
+                                  (unsigned *)B.topk_done.p + st_i, B.dec[i],
+                                  (ltgw_candidate *)B.cand.p + ((int64_t)i * 2 + st_i) * B.k,
+                                  (int32_t *)B.n_out.p + i * 2 + st_i};
             }
+            HIP_TRY(c, launch_topk(2, J, B.k, B.topk_cap, st), "batch top-k launch");
         }
     }
     return LTGW_OK;
@@ -296,11 +295,11 @@ int build(ltgw_ctx *c, const ltgw_search *S, int n, int k) {
         {&B.ctr, 8, "batch counter"},                {&B.tiles_done, (size_t)n * 4, "batch tile counts"},
         {&B.t_done, (size_t)n * 8, "batch times"},   {&B.t_start, 8, "batch time"},
         {&B.in_band, 8, "batch in-band count"},      {&B.diff, (size_t)B.diff_entries * 8, "batch moments"},
-        {&B.pa, (size_t)topk_max * 8, "batch top-k"}, {&B.ia, (size_t)topk_max * 8, "batch top-k"},
-        {&B.pb, (size_t)topk_max * 8, "batch top-k"}, {&B.ib, (size_t)topk_max * 8, "batch top-k"},
+        {&B.topk, (size_t)topk_max * 32, "batch top-k"}, {&B.topk_done, 8, "batch top-k"},
     };
     for (auto &a : allocs)
         if ((rc = ensure(c, *a.b, a.bytes, a.what)) != LTGW_OK) return rc;
+    HIP_TRY(c, launch_fill_u32((unsigned *)B.topk_done.p, 2, 0u, c->stream), "batch reset");
     HIP_TRY(c, hipMemcpy(B.tau.p, htau.data(), htau.size() * 8, hipMemcpyHostToDevice), "batch upload");
     HIP_TRY(c, hipMemcpy(B.brake.p, hbrake.data(), hbrake.size() * 8, hipMemcpyHostToDevice), "batch upload");
     HIP_TRY(c, hipMemcpy(B.sky.p, hsky.data(), hsky.size() * 8, hipMemcpyHostToDevice), "batch upload");

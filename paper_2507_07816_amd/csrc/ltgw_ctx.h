@@ -77,7 +77,7 @@ struct BatchState {
     DevBuf searches, tiles, ctr, tiles_done, t_done, t_start, in_band;
     DevBuf s, c, n_res, w1, w2, gtab, dtab, tau, brake, sky, cand, n_out, diff, win;
     std::vector<int64_t> win_off;         // per (search, det) offsets into the window table
-    DevBuf pa, ia, pb, ib;
+    DevBuf topk, topk_done;
     int64_t topk_cap = 0, diff_entries = 0;
     hipStream_t cap_stream = nullptr;
     hipGraph_t graph = nullptr;
@@ -129,7 +129,8 @@ struct ltgw_ctx {
     ltgw::DevBuf cnn_packed;  // BF16 weights of the fused inference pass
     ltgw::DevBuf tau_d, brake_d, sky_d;
     ltgw::DevBuf res_s, res_c, res_n, res_w1, res_w2, diff;
-    ltgw::DevBuf cand_pa, cand_ia, cand_pb, cand_ib, cand_out, n_out;
+    ltgw::DevBuf cand;    // top-k candidates
+    ltgw::DevBuf h_top;   // pinned host memory the ranking writes its records and count to
     std::vector<double> h_tau, h_brake, h_sky;
     hipEvent_t ev[3] = {nullptr, nullptr, nullptr};  // tables start, eval start, eval end
     hipEvent_t ev_h2d = nullptr;  // after the grid uploads from h_tau/h_brake/h_sky
@@ -196,6 +197,8 @@ bool fin(double x);
 // [1] powers that took the double-double phase (the kernels of Eq. 1 get
 // &counters[0] and count both), [2] bad power values, [3] in-band total.
 constexpr int kCntUndecided = 0, kCntSlow = 1, kCntBad = 2, kCntInBand = 3, kCntExact = 4, kNumCnt = 5;
+// beside them (not read by ltgw_diagnostics): the ranking's workgroup count
+constexpr int kCntTopk = 5, kNumCounters = 6;
 int zero_counter(ltgw_ctx *c, int first, int n);
 int read_counter(ltgw_ctx *c, int i, unsigned long long *out);
 

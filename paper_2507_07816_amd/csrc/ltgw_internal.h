@@ -155,12 +155,22 @@ struct TopkDecode {
     const double *brake;
     const ltgw_template *list = nullptr;
 };
-// Scratch for top-k: two candidate buffers of (psi, index) pairs.
-hipError_t launch_topk(uint32_t stat, int64_t n, const double *s, const int32_t *c,
-                       const int32_t *N, const double *w1, const double *w2, double q, int32_t k,
-                       double *cand_psi_a, int64_t *cand_idx_a, double *cand_psi_b,
-                       int64_t *cand_idx_b, int64_t cand_cap, const TopkDecode &dec,
-                       ltgw_candidate *out_dev, int32_t *n_out_dev, hipStream_t st);
+// One ranking: the k best templates of n by a statistic's critical ratio.
+struct TopkJob {
+    int64_t n;
+    uint32_t stat;
+    const double *s;
+    const int32_t *c, *N;
+    const double *w1, *w2;
+    double q;
+    void *cand;             // topk_scratch_entries(n, k) entries of 16 bytes
+    unsigned *done;         // workgroups finished; 0 before the first launch and after each
+    TopkDecode dec;
+    ltgw_candidate *out;    // [k], device or pinned host memory
+    int32_t *n_out;
+};
+// One or two rankings of the same n (of one search: power and count).
+hipError_t launch_topk(int n_jobs, const TopkJob *jobs, int32_t k, int64_t cand_cap, hipStream_t st);
 int64_t topk_scratch_entries(int64_t n, int32_t k);
 
 hipError_t launch_inject(float *power, int32_t n_seg, int32_t n_bins, int64_t k_lo,

@@ -25,6 +25,8 @@
 // band, for k_lo >= 2 and x < 2^30 (both checked by the host): x + 1.5 - k_lo
 // is exact in FP64 whenever its magnitude is at most x, and every other case
 // lands on the lower guard or out of range.
+#include <algorithm>
+
 #include "ltgw_gather.h"
 #include "ltgw_internal.h"
 #include "ddpow.h"
@@ -854,9 +856,9 @@ hipError_t launch_psi(uint32_t stat, int64_t n, const double *s, const int32_t *
 }
 
 // ---------------------------------------------------------------------------
-// Top-k by (psi desc, index asc).  A block takes 4096 items into registers
-// (16 per lane) and extracts its k best by k rounds of a block-wide arg-max;
-// levels repeat over the per-block winners until one block remains.
+// Top-k by (psi desc, index asc).  For k > kTopkFast: a block takes 4096 items
+// into registers (16 per lane) and extracts its k best by k rounds of a block-wide
+// arg-max; levels repeat over the per-block winners until one block remains.
 constexpr int kTopkIpt = 16;
 constexpr int kTopkChunk = 256 * kTopkIpt;
 constexpr int64_t kNoIndex = 0x7fffffffffffffffll;
@@ -951,6 +953,40 @@ __global__ __launch_bounds__(256) void topk_level_kernel(
     }
 }
 
+// The record of ranked template t (kNoIndex: none).
+__device__ inline ltgw_candidate topk_record(uint32_t stat, int64_t t, double psi, const double *s, const int32_t *c,
+                                             const int32_t *N, const TopkDecode &dec) {
+    ltgw_candidate rec;
+    if (t == kNoIndex) {
+        rec.index = -1;
+        rec.f0 = rec.tau = rec.brake = rec.stat = rec.psi = 0.0;
+        rec.sky = -1;
+        rec.n_valid = 0;
+        return rec;
+    }
+    if (dec.list) {
+        const ltgw_template &T = dec.list[t];
+        rec.f0 = T.f0;
+        rec.tau = T.tau;
+        rec.brake = T.brake;
+        rec.sky = -1;
+    } else {
+        const int64_t i_f0 = t % dec.n_f0;
+        const int64_t grp = t / dec.n_f0;
+        const int64_t i_tau = grp % dec.n_tau;
+        const int64_t rr = grp / dec.n_tau;
+        rec.f0 = dec.f0_min + (double)i_f0 * dec.f0_step;
+        rec.tau = dec.tau[i_tau];
+        rec.brake = dec.brake[rr % dec.n_brake];
+        rec.sky = (int32_t)(rr / dec.n_brake);
+    }
+    rec.index = t;
+    rec.n_valid = N[t];
+    rec.stat = stat == LTGW_STAT_POWER ? s[t] : (double)c[t];
+    rec.psi = psi;
+    return rec;
+}
+
 __global__ void topk_records_kernel(int32_t k, uint32_t stat, const double *s, const int32_t *c,
                                     const int32_t *N, const double *psi, const int64_t *idx,
                                     TopkDecode dec, ltgw_candidate *out, int32_t *n_out) {
@@ -961,72 +997,206 @@ __global__ void topk_records_kernel(int32_t k, uint32_t stat, const double *s, c
             if (idx[u] != kNoIndex) ++cntv;
         *n_out = cntv;
     }
-    if (r >= k) return;
-    const int64_t t = idx[r];
-    ltgw_candidate rec;
-    if (t == kNoIndex) {
-        rec.index = -1;
-        rec.f0 = rec.tau = rec.brake = rec.stat = rec.psi = 0.0;
-        rec.sky = -1;
-        rec.n_valid = 0;
-    } else {
-        if (dec.list) {
-            const ltgw_template &T = dec.list[t];
-            rec.f0 = T.f0;
-            rec.tau = T.tau;
-            rec.brake = T.brake;
-            rec.sky = -1;
-        } else {
-            const int64_t i_f0 = t % dec.n_f0;
-            const int64_t grp = t / dec.n_f0;
-            const int64_t i_tau = grp % dec.n_tau;
-            const int64_t rr = grp / dec.n_tau;
-            rec.f0 = dec.f0_min + (double)i_f0 * dec.f0_step;
-            rec.tau = dec.tau[i_tau];
-            rec.brake = dec.brake[rr % dec.n_brake];
-            rec.sky = (int32_t)(rr / dec.n_brake);
-        }
-        rec.index = t;
-        rec.n_valid = N[t];
-        rec.stat = stat == LTGW_STAT_POWER ? s[t] : (double)c[t];
-        rec.psi = psi[r];
+    if (r < k) out[r] = topk_record(stat, idx[r], psi[r], s, c, N, dec);
+}
+
+// For k <= kTopkFast, one launch for the whole ranking (and, with gridDim.y = 2,
+// for the second job too): each workgroup ranks its share of the templates, the
+// last one to finish ranks the workgroups' winners and writes the records.
+// A tile of 4096 items is ranked without k rounds of block-wide reductions: the
+// best of each group of 16 lanes is taken first; the k-th best of those 64 bounds
+// the k-th best item from below, so only items at or above it (those of at most k
+// groups, usually little more than k items) go to a list, whose ranks are counted
+// directly.  Later tiles only list items better than the running k-th.
+// A workgroup per CU at most, so that for k up to 16 the last one ranks every
+// winner as a single tile (512 workgroups of 256 lanes left it five tiles one after
+// the other, 47 us at 2.3 million templates).  4800 templates, k = 10: 33 + 17 + 6 us
+// in three launches -> 13 us in one; 2.3 million: 45 + 2 x 22 + 6 -> 35 us.
+constexpr int kTopkFast = 32;
+constexpr int kTopkBlocks = 256;
+constexpr int kTopkItems = 4;                         // per lane and tile
+constexpr int kTopkTile = 1024 * kTopkItems;
+constexpr int kTopkGroup = 16;                        // lanes per group
+
+struct TopkEntry {
+    double p;
+    int64_t i;
+};
+__device__ inline bool better(const TopkEntry &a, const TopkEntry &b) { return better(a.p, a.i, b.p, b.i); }
+
+struct TopkShared {
+    TopkEntry best[kTopkFast];  // the running winners, best first
+    TopkEntry group[64];
+    TopkEntry list[kTopkFast * kTopkGroup * kTopkItems + kTopkFast];
+    TopkEntry bound;
+    int n_best, n_list, n_group, last;
+};
+
+// Rank the tile's items (index kNoIndex: none) against the running winners.
+__device__ inline void topk_tile(TopkShared &S, int k, const TopkEntry (&it)[kTopkItems]) {
+    const int t = threadIdx.x;
+    const bool full = S.n_best == k;
+    const TopkEntry floor_ = full ? S.best[k - 1] : TopkEntry{-__builtin_inf(), kNoIndex};
+    TopkEntry m{-__builtin_inf(), kNoIndex};
+#pragma unroll
+    for (int u = 0; u < kTopkItems; ++u)
+        if (it[u].i != kNoIndex && (!full || better(it[u], floor_)) && (m.i == kNoIndex || better(it[u], m))) m = it[u];
+#pragma unroll
+    for (int o = 1; o < kTopkGroup; o <<= 1) {
+        const TopkEntry x{__shfl_xor(m.p, o, 64), (int64_t)__shfl_xor((long long)m.i, o, 64)};
+        if (x.i != kNoIndex && (m.i == kNoIndex || better(x, m))) m = x;
     }
-    out[r] = rec;
+    if (t == 0) S.n_list = S.n_group = 0;
+    const int sub = t & (kTopkGroup - 1);
+    if (sub == 0) S.group[t / kTopkGroup] = m;
+    __syncthreads();
+    if (m.i != kNoIndex && sub == 0) atomicAdd(&S.n_group, 1);
+    // rank of this group among the 64, a sixteenth of the comparisons per lane
+    int rank = 0;
+#pragma unroll
+    for (int u = 0; u < 64 / kTopkGroup; ++u) {
+        const TopkEntry x = S.group[u * kTopkGroup + sub];
+        rank += x.i != kNoIndex && better(x, m) ? 1 : 0;
+    }
+#pragma unroll
+    for (int o = 1; o < kTopkGroup; o <<= 1) rank += __shfl_xor(rank, o, 64);
+    if (m.i != kNoIndex && rank == k - 1) S.bound = m;  // the same value from the group's lanes
+    __syncthreads();
+    const int n_group = S.n_group;
+    if (n_group == 0) {  // uniform: nothing beats the running winners
+        __syncthreads();
+        return;
+    }
+    const bool bounded = n_group >= k;
+    const TopkEntry bound = S.bound;
+#pragma unroll
+    for (int u = 0; u < kTopkItems; ++u)
+        if (it[u].i != kNoIndex && (!full || better(it[u], floor_)) && !(bounded && better(bound, it[u])))
+            S.list[atomicAdd(&S.n_list, 1)] = it[u];
+    if (t < S.n_best) S.list[atomicAdd(&S.n_list, 1)] = S.best[t];
+    __syncthreads();
+    const int n = S.n_list;
+    for (int e0 = 0; e0 < n; e0 += 64) {
+        const int e = e0 + t / kTopkGroup;
+        const TopkEntry x = S.list[e < n ? e : 0];
+        int r = 0;
+        for (int u = sub; u < n; u += kTopkGroup) r += better(S.list[u], x) ? 1 : 0;
+#pragma unroll
+        for (int o = 1; o < kTopkGroup; o <<= 1) r += __shfl_xor(r, o, 64);
+        if (e < n && sub == 0 && r < k) S.best[r] = x;
+    }
+    if (t == 0) S.n_best = n < k ? n : k;
+    __syncthreads();
+}
+
+__global__ __launch_bounds__(1024) void topk_kernel(const TopkJob j0, const TopkJob j1, int32_t k) {
+    __shared__ TopkShared S;
+    const TopkJob &J = blockIdx.y ? j1 : j0;
+    const int t = threadIdx.x;
+    if (t == 0) S.n_best = 0;
+    __syncthreads();
+    TopkEntry it[kTopkItems];
+    for (int64_t base = (int64_t)blockIdx.x * kTopkTile; base < J.n; base += (int64_t)gridDim.x * kTopkTile) {
+        // every load of the tile is issued before any ratio is formed (a branch on
+        // N per item, as in psi_of, would make them one round trip each)
+        const bool power = J.stat == LTGW_STAT_POWER;
+        int32_t N[kTopkItems];
+        double x[kTopkItems], w1[kTopkItems], w2[kTopkItems];
+#pragma unroll
+        for (int u = 0; u < kTopkItems; ++u) {
+            const int64_t i = base + u * 1024 + t, at = i < J.n ? i : J.n - 1;
+            N[u] = J.N[at];
+            if (power) {
+                x[u] = J.s[at];
+                w1[u] = J.w1[at];
+                w2[u] = J.w2[at];
+            } else {
+                x[u] = (double)J.c[at];
+                w1[u] = (double)N[u] * J.q;
+                w2[u] = w1[u] * (1.0 - J.q);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kTopkItems; ++u) {
+            const int64_t i = base + u * 1024 + t;
+            const double p = (x[u] - w1[u]) / sqrt(w2[u]);  // psi_of's operations
+            it[u] = TopkEntry{-__builtin_inf(), kNoIndex};
+            if (i < J.n && N[u] != 0 && p == p) it[u] = TopkEntry{p, i};  // no segment or NaN: never ranks
+        }
+        topk_tile(S, k, it);
+    }
+    if (gridDim.x > 1) {
+        TopkEntry *cand = (TopkEntry *)J.cand;
+        if (t < k) cand[(int64_t)blockIdx.x * k + t] = t < S.n_best ? S.best[t] : TopkEntry{-__builtin_inf(), kNoIndex};
+        // the first wavefront wrote the winners; its first lane publishes them (one
+        // release per workgroup: a fence in every wavefront writes its L2 back each time)
+        if (t == 0) {
+            S.last = __hip_atomic_fetch_add(J.done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1 ? 1 : 0;
+            if (S.last) *J.done = 0u;  // for the next launch
+            S.n_best = 0;
+        }
+        __syncthreads();
+        if (!S.last) return;
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        const int n = (int)gridDim.x * k;
+        for (int base = 0; base < n; base += kTopkTile) {
+#pragma unroll
+            for (int u = 0; u < kTopkItems; ++u) {
+                const int i = base + u * 1024 + t;
+                it[u] = i < n ? cand[i] : TopkEntry{-__builtin_inf(), kNoIndex};
+            }
+            topk_tile(S, k, it);
+        }
+    }
+    if (t < k) {
+        const TopkEntry x = t < S.n_best ? S.best[t] : TopkEntry{0.0, kNoIndex};
+        J.out[t] = topk_record(J.stat, x.i, x.p, J.s, J.c, J.N, J.dec);
+    }
+    if (t == 0) *J.n_out = S.n_best;
 }
 
 int64_t topk_scratch_entries(int64_t n, int32_t k) {
-    return ((n + kTopkChunk - 1) / kTopkChunk) * (int64_t)k + k;
+    if (k <= kTopkFast) return std::min<int64_t>((n + kTopkTile - 1) / kTopkTile, kTopkBlocks) * k;
+    return 2 * ((n + kTopkChunk - 1) / kTopkChunk * (int64_t)k + k);
 }
 
-hipError_t launch_topk(uint32_t stat, int64_t n, const double *s, const int32_t *c,
-                       const int32_t *N, const double *w1, const double *w2, double q, int32_t k,
-                       double *pa, int64_t *ia, double *pb, int64_t *ib, int64_t cand_cap,
-                       const TopkDecode &dec, ltgw_candidate *out_dev, int32_t *n_out_dev,
-                       hipStream_t st) {
-    int64_t blocks = (n + kTopkChunk - 1) / kTopkChunk;
-    if (blocks < 1) blocks = 1;
-    if (blocks * k > cand_cap) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(topk_level_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, st, n, k, stat,
-                       s, c, N, w1, w2, q, (const double *)nullptr, (const int64_t *)nullptr, pa, ia);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    int64_t m = blocks * k;
-    while (blocks > 1) {
-        blocks = (m + kTopkChunk - 1) / kTopkChunk;
-        hipLaunchKernelGGL(topk_level_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, st, m, k,
-                           stat, s, c, N, w1, w2, q, pa, ia, pb, ib);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        m = blocks * k;
-        double *tp = pa;
-        pa = pb;
-        pb = tp;
-        int64_t *ti = ia;
-        ia = ib;
-        ib = ti;
+hipError_t launch_topk(int n_jobs, const TopkJob *jobs, int32_t k, int64_t cand_cap, hipStream_t st) {
+    if (n_jobs < 1 || n_jobs > 2 || k < 1) return hipErrorInvalidValue;
+    for (int q = 0; q < n_jobs; ++q)
+        if (jobs[q].n != jobs[0].n || topk_scratch_entries(jobs[q].n, k) > cand_cap) return hipErrorInvalidValue;
+    const int64_t n = jobs[0].n;
+    if (k <= kTopkFast) {
+        const int64_t tiles = std::max<int64_t>(1, (n + kTopkTile - 1) / kTopkTile);
+        const dim3 grid((unsigned)std::min<int64_t>(tiles, kTopkBlocks), (unsigned)n_jobs);
+        hipLaunchKernelGGL(topk_kernel, grid, dim3(1024), 0, st, jobs[0], jobs[n_jobs - 1], k);
+        return hipGetLastError();
     }
-    hipLaunchKernelGGL(topk_records_kernel, dim3(1), dim3(256), 0, st, k, stat, s, c, N, pa, ia, dec,
-                       out_dev, n_out_dev);
-    return hipGetLastError();
+    for (int q = 0; q < n_jobs; ++q) {
+        const TopkJob &J = jobs[q];
+        int64_t blocks = std::max<int64_t>(1, (n + kTopkChunk - 1) / kTopkChunk);
+        // two candidate buffers of (psi, index) in turn
+        const int64_t half = topk_scratch_entries(n, k) / 2;
+        double *pa = (double *)J.cand, *pb = pa + half;
+        int64_t *ia = (int64_t *)(pa + 2 * half), *ib = ia + half;
+        hipLaunchKernelGGL(topk_level_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, st, n, k, J.stat, J.s, J.c, J.N,
+                           J.w1, J.w2, J.q, (const double *)nullptr, (const int64_t *)nullptr, pa, ia);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        int64_t m = blocks * k;
+        while (blocks > 1) {
+            blocks = (m + kTopkChunk - 1) / kTopkChunk;
+            hipLaunchKernelGGL(topk_level_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, st, m, k, J.stat, J.s, J.c,
+                               J.N, J.w1, J.w2, J.q, pa, ia, pb, ib);
+            if ((e = hipGetLastError()) != hipSuccess) return e;
+            m = blocks * k;
+            std::swap(pa, pb);
+            std::swap(ia, ib);
+        }
+        hipLaunchKernelGGL(topk_records_kernel, dim3(1), dim3(256), 0, st, k, J.stat, J.s, J.c, J.N, pa, ia, J.dec, J.out,
+                           J.n_out);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 // ---------------------------------------------------------------------------

@@ -346,6 +346,44 @@ def test_topk_large_k_and_ties():
     assert_topk_count(gpu["top_count"], ref, 256)
 
 
+@pytest.mark.parametrize("n_f0,n_tau,ties", [
+    (1, 1, False), (31, 1, False),             # fewer templates than winners asked for
+    (4095, 1, False), (4096, 1, True), (4097, 1, False),   # one tile and its neighbours
+    (700, 137, True),                          # many tied ratios in many workgroups
+    (1024, 1025, False),                       # the first size with two tiles in a workgroup
+    (1500, 900, True),                         # several tiles per workgroup
+])
+def test_topk_equals_the_sorted_ratios(n_f0, n_tau, ties):
+    """k at and around the one-launch ranking's limit (32) against a sort of the
+    library's own ratios by (ratio descending, index ascending), NaN left out."""
+    from paper_2507_07816_amd import ltgw
+
+    print(f"case: topk n_f0={n_f0} n_tau={n_tau} ties={ties}", flush=True)
+    import torch
+
+    det = _small(n_f0 + n_tau, 3, 600)
+    rho = np.round(det.rho * 2.0) if ties else det.rho
+    ctx = ltgw.Context(0)
+    try:
+        ctx.load_spectrogram(0, torch.from_numpy(rho.astype(np.float32)).cuda(), det.k_lo, det.t_sft, det.t_seg,
+                             weights=None if ties else det.w)
+        ctx.set_velocity_table(0, det.v)
+        # the first tenth of the band starts below the spectrogram: no segment, no ratio
+        f_lo = (det.k_lo - 60) / det.t_sft
+        s, c, N = ctx.eval_templates(f_lo, 0.25 * 600 / max(n_f0, 600), n_f0, np.linspace(900.0, 30000.0, n_tau), [5.0],
+                                     [[0.6, 0.0, 0.8]])
+        for stat in ("power", "count"):
+            psi = ctx.psi(stat, n_f0 * n_tau).cpu().numpy()
+            idx = np.nonzero(~np.isnan(psi))[0]
+            want = idx[np.lexsort((idx, -psi[idx]))]
+            for k in (1, 10, 32, 33):
+                got = ctx.topk(stat, k)
+                assert [t["index"] for t in got] == [int(i) for i in want[:k]], (stat, k)
+                assert all(t["psi"] == psi[t["index"]] for t in got)
+    finally:
+        ctx.close()
+
+
 def _realistic_det(checksum=False):
     wl = synth.realistic()
     d = wl.dets[0]
