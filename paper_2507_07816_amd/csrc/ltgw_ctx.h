@@ -170,6 +170,11 @@ struct ltgw_ctx {
     // b done, [2..3] its normalisation done (the normalisation runs on `side`)
     hipEvent_t ev_sft[4] = {nullptr, nullptr, nullptr, nullptr};
     std::vector<SftPlan> sft_plans;
+    struct SftTable {
+        int n_fft;
+        ltgw::DevBuf tab;
+    };
+    std::vector<SftTable> sft_tabs;  // tables of the on-chip transform, one per length it has
     int forced_variant = -1;      // ltgw_set_tile_shape; -1 = autotuner
     // device address of this device's static scratch array (the no-allocation
     // entry point), resolved by ltgw_create; NULL when the device has none

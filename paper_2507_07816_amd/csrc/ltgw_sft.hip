@@ -2,16 +2,15 @@
 // -> normalised power rho = P ln 2 / (running median of P over frequency).
 //
 // Segment j is samples [j N, (j + 1) N) of the strain.  Per chunk of segments:
-//   one batched real-to-complex FFT (hipFFT, FP32) of the raw segments;
-//   normalise_kernel: the Hann window applied in frequency: with the periodic
+//   the powers P_k = |X_k|^2 of the band and its median halo, for the lengths that a
+//   workgroup can hold from one kernel that reads the strain and writes them
+//   (ltgw_fft.hip); for the others a batched real-to-complex FFT (hipFFT, FP32) of the
+//   raw segments, and the Hann window applied in frequency: with the periodic
 //   window w_n = 1/2 - 1/2 cos(2 pi n / N) = 1/2 - e^{2 pi i n/N}/4 - e^{-2 pi i n/N}/4
 //   the windowed transform is X_k/2 - (X_{k-1} + X_{k+1})/4 (X_{-1} = conj X_1 and
-//   X_{N/2+1} = conj X_{N/2-1} for real input); P_k = |.|^2 for a 256-bin tile of the band
-//   and its median halo, a bitonic sort of (P, position) in LDS, then each bin's median is the
-//   (h + 1)-th smallest value whose position lies in its window: position
-//   masks of the sorted tile's blocks of 64 entries, counted against the
-//   bin's window, give the block that holds it, and a scan of that block the
-//   entry.  Under Gaussian noise P_k is exponential with
+//   X_{N/2+1} = conj X_{N/2-1} for real input);
+//   normalise_kernel: each bin's median, the (h + 1)-th smallest of its window of
+//   2 h + 1 powers, and the ratio.  Under Gaussian noise P_k is exponential with
 //   mean S_k and median S_k ln 2, hence rho_k = P_k ln 2 / median.
 #include <hip/hip_runtime.h>
 #include <hipfft/hipfft.h>
@@ -21,18 +20,15 @@
 #include <vector>
 
 #include "ltgw_ctx.h"
+#include "ltgw_fft.h"
 
 #pragma clang fp contract(off)
 
 namespace ltgw {
 
-constexpr int kSftTile = 256;      // output bins per workgroup
-constexpr int kSftSort = 512;      // sorted entries: tile + halo, padded to a power of two
-constexpr int kSftMaxWindow = kSftSort - kSftTile + 1;  // 257
+constexpr int kSftMaxWindow = 257;
+constexpr int kMedPer = 8;  // positions per lane of a tile
 
-// One workgroup: segment blockIdx.y, output bins [t0, t0 + 256) of the band;
-// lane t takes bin t0 + t.  (Wider tiles that fill all 512 sorted entries
-// were measured slower: the per-bin scans, not the sort, dominate.)
 __device__ __forceinline__ float2 spec_at(const float2 *row, int64_t k, int64_t half) {
     // X_{-1} = conj X_1, X_{half+1} = conj X_{half-1} (real input)
     if (k < 0) {
@@ -46,112 +42,264 @@ __device__ __forceinline__ float2 spec_at(const float2 *row, int64_t k, int64_t 
     return row[k];
 }
 
-__global__ __launch_bounds__(256) void normalise_kernel(const float2 *__restrict__ spec, int64_t spec_pitch,
-                                                        int64_t k_lo, int n_bins, int h, float *__restrict__ out) {
-    __shared__ float val[kSftSort];
-    __shared__ __attribute__((aligned(16))) short pos[kSftSort];
-    __shared__ float pw[kSftSort];
-    // bit p of bmask[b][p / 64]: position p holds one of sorted entries 64 b .. 64 b + 63
-    constexpr int kBlk = kSftSort / 64;
-    __shared__ unsigned long long bmask[kBlk][kSftSort / 64];
-    const int t = threadIdx.x;
-    const int T = kSftTile;
-    const int t0 = blockIdx.x * T;
-    const int seg = blockIdx.y;
-    const float2 *row = spec + (int64_t)seg * spec_pitch;
-    // tile positions p = 0 .. 255 + 2h hold bin k_lo + t0 - h + p; positions
-    // past the last needed bin (band end + h) are padding that sorts last
-    const int n_pos = T + 2 * h;
-    const int last_needed = n_bins - 1 - t0 + 2 * h;  // last position any output reads
-    for (int p = t; p < kSftSort; p += 256) {
-        float v = __builtin_inff();
-        if (p < n_pos && p <= last_needed) {
-            const int64_t k = k_lo + t0 - h + p;
-            const int64_t half = spec_pitch - 1;
-            const float2 z = row[k], zm = spec_at(row, k - 1, half), zp = spec_at(row, k + 1, half);
-            const float re = 0.5f * z.x - 0.25f * (zm.x + zp.x);
-            const float im = 0.5f * z.y - 0.25f * (zm.y + zp.y);
-            const float a = re * re;
-            const float b = im * im;
-            v = a + b;
+// |windowed transform|^2 of bin k from a row of the raw transform
+__device__ __forceinline__ float hann_power(const float2 *row, int64_t k, int64_t half) {
+    const float2 z = row[k], zm = spec_at(row, k - 1, half), zp = spec_at(row, k + 1, half);
+    const float re = 0.5f * z.x - 0.25f * (zm.x + zp.x);
+    const float im = 0.5f * z.y - 0.25f * (zm.y + zp.y);
+    const float a = re * re;
+    const float b = im * im;
+    return a + b;
+}
+
+// the value of lane ^ X, X = 1, 2, 4 or 8
+template <int X>
+__device__ __forceinline__ unsigned lane_xor(unsigned v) {
+    if constexpr (X == 1) return __builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true);
+    else if constexpr (X == 2) return __builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true);
+    else if constexpr (X == 4)  // lane ^ 7, then ^ 3
+        return __builtin_amdgcn_update_dpp(0, __builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, true), 0x1B, 0xF, 0xF,
+                                           true);
+    else return __builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xF, 0xF, true);
+}
+
+__device__ __forceinline__ void order(unsigned &a, unsigned &b) {
+    const unsigned lo = a < b ? a : b, hi = a < b ? b : a;
+    a = lo;
+    b = hi;
+}
+
+// compare with lane ^ X: the lane without bit X keeps the smaller
+template <int X, int E>
+__device__ __forceinline__ void cross(unsigned (&v)[E], int lane) {
+    if constexpr (X >= 16) {
+        // rows of two registers swapped so that both partners are in one lane, and back
+#pragma unroll
+        for (int r = 0; r < E; r += 2) {
+            const auto s = X == 16 ? __builtin_amdgcn_permlane16_swap(v[r], v[r + 1], false, false)
+                                   : __builtin_amdgcn_permlane32_swap(v[r], v[r + 1], false, false);
+            unsigned a = s[0], b = s[1];
+            order(a, b);
+            const auto q = X == 16 ? __builtin_amdgcn_permlane16_swap(a, b, false, false)
+                                   : __builtin_amdgcn_permlane32_swap(a, b, false, false);
+            v[r] = q[0];
+            v[r + 1] = q[1];
         }
-        val[p] = v;
-        pw[p] = v;
-        pos[p] = (short)p;
+    } else {
+        const unsigned lim = lane & X ? ~0u : 0u;
+#pragma unroll
+        for (int r = 0; r < E; ++r) {
+            const unsigned y = lane_xor<X>(v[r]);
+            const unsigned lo = v[r] < y ? v[r] : y, hi = v[r] < y ? y : v[r];
+            const unsigned m = hi < lim ? hi : lim;  // the middle one of (v, y, lim)
+            v[r] = lo > m ? lo : m;
+        }
     }
-    if (t < kBlk * (kSftSort / 64)) (&bmask[0][0])[t] = 0ull;
+}
+
+// the lane's registers (a bitonic sequence) into ascending order
+template <int E>
+__device__ __forceinline__ void merge_lane(unsigned (&v)[E]) {
+#pragma unroll
+    for (int d = E / 2; d > 0; d >>= 1)
+#pragma unroll
+        for (int r = 0; r < E; ++r)
+            if (!(r & d)) order(v[r], v[r + d]);
+}
+
+// 64 E keys, E per lane, sorted: lane l gets the E l-th .. of them
+template <int E>
+__device__ __forceinline__ void sort_wave(unsigned (&v)[E], int lane) {
+    // A lane whose keys descend (bit k of the lane, runs of 2^k lanes) holds them
+    // complemented, so that every comparison puts the smaller first.
+    unsigned flip = (unsigned)-(lane & 1);
+#pragma unroll
+    for (int r = 0; r < E; ++r) v[r] ^= flip;
+    // in the lane: odd-even merge sort (19 comparisons)
+#pragma unroll
+    for (int p = 1; p < E; p <<= 1)
+#pragma unroll
+        for (int k = p; k >= 1; k >>= 1)
+#pragma unroll
+            for (int j = k % p; j + k < E; j += 2 * k)
+#pragma unroll
+                for (int i = 0; i < k; ++i)
+                    if (j + i + k < E && (i + j) / (2 * p) == (i + j + k) / (2 * p)) order(v[i + j], v[i + j + k]);
+    // runs of 2^(k-1) lanes into runs of 2^k: a loop, not straight-line code, which
+    // a launch of a few waves per CU would spend its time fetching
+#pragma unroll 1
+    for (int k = 1; k <= 6; ++k) {
+        const unsigned next = k < 6 ? (unsigned)-(int)((lane >> k) & 1) : 0u;
+#pragma unroll
+        for (int r = 0; r < E; ++r) v[r] ^= flip ^ next;
+        flip = next;
+        if (k >= 6) cross<32>(v, lane);
+        if (k >= 5) cross<16>(v, lane);
+        if (k >= 4) cross<8>(v, lane);
+        if (k >= 3) cross<4>(v, lane);
+        if (k >= 2) cross<2>(v, lane);
+        cross<1>(v, lane);
+        merge_lane(v);
+    }
+}
+
+// slot of sorted entry i of n in the search tree (children of slot k: 2 k, 2 k + 1)
+template <int N>
+__device__ __forceinline__ int tree_slot(int i) {
+    return i == N - 1 ? 0 : (N + i + 1) >> (__builtin_ctz(i + 1) + 1);
+}
+
+// One wavefront: segment blockIdx.y, a tile of 512 positions = its outputs and
+// their median halo of h on either side.  What bounds it is VALU issue, then LDS,
+// so the work of a position is shared as far as it goes:
+//   the powers (non-negative, so ordered like their bits) are sorted in registers;
+//   each position's rank is found in a search tree of the sorted keys (levels
+//   contiguous: 64 lanes' reads fall on different banks), equal keys taking
+//   successive ranks in any order;
+//   a lane then slides over consecutive outputs with the set of its window's
+//   ranks as bits (512 per lane, interleaved so that every lane has its own
+//   bank): an output removes a rank, adds a rank, and moves the median to the
+//   next member up or down, or not at all.
+// 10800 rows of 8000 outputs, window 101: 0.90 ms (70 % of VALU issue; 3.07 ms for a
+// workgroup sort in LDS with a count of every sorted block per output).  Tiles of 1024
+// positions took 1.53 ms: half the waves fit a CU's LDS, and only windows of 257 gain
+// what they lose.
+// The entry is the (h + 1)-th smallest power of the window, exactly.
+template <bool SPEC>
+__global__ __launch_bounds__(64) void normalise_kernel(const void *__restrict__ rows, int64_t pitch, int64_t k_lo,
+                                                       int n_bins, int h, float *__restrict__ out) {
+    constexpr int E = kMedPer, N = 64 * E, kWords = N / 32;
+    __shared__ __attribute__((aligned(16))) unsigned set[kWords * 64];
+    __shared__ unsigned tree[N];
+    // a rank r as its bit's place: (r / 32) << 8, the word's byte offset among the 64
+    // lanes' words, and r % 32 (ordered like the ranks)
+    __shared__ unsigned short rank[N + 2], med[N];
+    const int lane = threadIdx.x;
+    const int o0 = blockIdx.x * (N - 2 * h);
+    const int n_out = min(N - 2 * h, n_bins - o0);
+    const int n_pos = n_out + 2 * h;  // positions that an output reads; the others sort last
+    auto power = [&](int p) {
+        if constexpr (SPEC)
+            return hann_power((const float2 *)rows + (int64_t)blockIdx.y * pitch, k_lo + o0 - h + p, pitch - 1);
+        else
+            return ((const float *)rows)[(int64_t)blockIdx.y * pitch + o0 + p];
+    };
+    unsigned key[E];
+#pragma unroll
+    for (int i = 0; i < E; ++i) {
+        const int p = 64 * i + lane;
+        key[i] = p < n_pos ? __float_as_uint(power(p)) : ~0u;
+    }
+    {
+        unsigned v[E];
+#pragma unroll
+        for (int i = 0; i < E; ++i) v[i] = key[i];
+        sort_wave(v, lane);
+#pragma unroll
+        for (int r = 0; r < E; ++r) {
+            const int i = lane * E + r;
+            tree[r + 1 < E ? (N + i + 1) >> (__builtin_ctz(r + 1) + 1) : tree_slot<N>(i)] = v[r];
+        }
+    }
+    unsigned *const equal = set;  // ranks given out among equal keys
+#pragma unroll
+    for (int i = 0; i < E; ++i) equal[64 * i + lane] = 0u;
     __syncthreads();
-    // bitonic sort of (val, pos) ascending in val (a workgroup barrier per
-    // stage: ordering the 39 stages that stay inside a wavefront by wavefront
-    // fences instead was measured slower)
-    for (int size = 2; size <= kSftSort; size <<= 1) {
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            const int a = 2 * t - (t & (stride - 1));
-            const int b = a + stride;
-            const bool up = (a & size) == 0;
-            const float va = val[a], vb = val[b];
-            if ((va > vb) == up) {
-                val[a] = vb;
-                val[b] = va;
-                const short pa = pos[a];
-                pos[a] = pos[b];
-                pos[b] = pa;
-            }
-            __syncthreads();
+    {
+        unsigned at[E];
+#pragma unroll
+        for (int i = 0; i < E; ++i) at[i] = 1u;
+#pragma unroll 1
+        for (int s = 1; s < N; s <<= 1)
+#pragma unroll
+            for (int i = 0; i < E; ++i) at[i] = 2 * at[i] + (tree[at[i]] < key[i] ? 1u : 0u);
+#pragma unroll
+        for (int i = 0; i < E; ++i) {
+            unsigned r = at[i] - N;
+            r += atomicAdd(&equal[r], 1u);
+            rank[64 * i + lane] = (unsigned short)((r >> 5 << 8) | (r & 31));
         }
-    }
-    for (int k = t; k < kSftSort; k += 256) {
-        const int p = pos[k];
-        atomicOr(&bmask[k >> 6][p >> 6], 1ull << (p & 63));
     }
     __syncthreads();
-    // output o: window positions [o, o + 2h]; its median is the (h + 1)-th
-    // smallest value among them.  The in-window counts of the sorted blocks,
-    // in order, locate the block of that entry; within the block, four sorted
-    // positions per LDS read, and the group that holds it is resolved entry by
-    // entry.  The entry is the one a scan of the whole sorted tile finds.
-    const short4 *pos4 = reinterpret_cast<const short4 *>(pos);
-    for (int o = t; o < T && t0 + o < n_bins; o += 256) {
-        const int lo = o, hi = o + 2 * h;
-        const int w0 = lo >> 6, w1 = hi >> 6;
-        int cnt = 0, blk = 0;
-        for (; blk < kBlk - 1; ++blk) {
-            int c = 0;
-            for (int w = w0; w <= w1; ++w) {
-                unsigned long long m = bmask[blk][w];
-                if (w == w0) m &= ~0ull << (lo & 63);
-                if (w == w1) m &= ~0ull >> (63 - (hi & 63));
-                c += __popcll(m);
+#pragma unroll
+    for (int w = 0; w < kWords; ++w) set[w * 64 + lane] = 0u;
+    __syncthreads();
+    // the lane's outputs first .. first + mine - 1 (an odd run: rank reads of the
+    // lanes on different banks)
+    const int run = ((n_out + 63) / 64) | 1;
+    // (lanes past the last output do that one again)
+    const int mine = max(min(run, n_out - lane * run), 1);
+    const int first = min(lane * run, n_out - 1);
+    char *const bits = reinterpret_cast<char *>(set + lane);
+    auto word = [&](int m) -> unsigned & { return *reinterpret_cast<unsigned *>(bits + (m & 0xFF00)); };
+    auto toggle = [&](int r) { atomicXor(&word(r), 1u << (r & 31)); };
+#pragma unroll 8
+    for (int i = 0; i <= 2 * h; ++i) toggle(rank[first + i]);
+    int m;  // the median: h members of the set lie below
+    {
+        int below = 0, at = 0, sum = 0;
+#pragma unroll 4
+        for (int w = 0; w < kWords; ++w) {
+            sum += __popc(set[w * 64 + lane]);
+            if (sum <= h) {
+                below = sum;
+                at = w + 1;
             }
-            if (cnt + c > h) break;
-            cnt += c;
         }
-        float med = 0.0f;
-        for (int g = 16 * blk; g < 16 * blk + 16 && cnt <= h; ++g) {
-            const short4 q = pos4[g];
-            const int i0 = (q.x >= lo && q.x <= hi), i1 = (q.y >= lo && q.y <= hi);
-            const int i2 = (q.z >= lo && q.z <= hi), i3 = (q.w >= lo && q.w <= hi);
-            const int c = cnt + ((i0 + i1) + (i2 + i3));
-            if (c > h) {
-                int k = h + 1 - cnt, e = 0;
-                if (i0 && --k == 0) e = 0;
-                else if (i1 && --k == 0) e = 1;
-                else if (i2 && --k == 0) e = 2;
-                else e = 3;
-                med = val[4 * g + e];
+        unsigned y = set[at * 64 + lane];
+        int k = h - below;
+        m = at << 8;
+#pragma unroll
+        for (int s = 16; s > 0; s >>= 1) {
+            const int c = __popc(y & ((1u << s) - 1u));
+            if (k >= c) {
+                k -= c;
+                m += s;
+                y >>= s;
             }
-            cnt = c;
         }
-        const float P = pw[o + h];
+    }
+    // straight-line, with masks for the lanes that stay: the compiler turns branches
+    // here into loops that lanes leave one by one
+    const unsigned short *const leave = rank + first, *const enter = leave + 2 * h + 1;
+    int a = leave[0], b = enter[0];
+    for (int s = 0;; ++s) {
+        med[first + min(s, mine - 1)] = (unsigned short)m;
+        if (s + 1 == run) break;
+        const unsigned on = s + 1 < mine ? 1u : 0u;
+        atomicXor(&word(a), on << (a & 31));
+        atomicXor(&word(b), on << (b & 31));
+        // members below m: h, less a's, plus b's
+        const int more = (b < m) - (a < m), p = m & 31;
+        unsigned x = word(m);
+        const bool stay = on == 0u || (more == 0 && a != m);
+        const int next = min(s + 1, max(mine - 2, 0));
+        a = leave[next];
+        b = enter[next];
+        x &= stay ? 1u << p : more > 0 ? (1u << p) - 1u : ~1u << p;
+        int w = m & 0xFF00;
+        while (x == 0u) {
+            w += more > 0 ? -256 : 256;
+            x = word(w);
+        }
+        m = w + (more > 0 ? 31 - __clz((int)x) : __ffs((int)x) - 1);
+    }
+    __syncthreads();
+#pragma unroll 2
+    for (int o = lane; o < n_out; o += 64) {
+        const int m = med[o];
+        const float f = __uint_as_float(tree[tree_slot<N>((m >> 8 << 5) | (m & 31))]);
         // rho = P ln2 / median; a window whose median is 0 carries no noise-floor estimate: 0
-        const double r = med > 0.0f ? (double)P * 0.69314718055994530942 / (double)med : 0.0;
-        out[(int64_t)seg * n_bins + t0 + o] = (float)r;
+        const double r = f > 0.0f ? (double)power(o + h) * 0.69314718055994530942 / (double)f : 0.0;
+        out[(int64_t)blockIdx.y * n_bins + o0 + o] = (float)r;
     }
 }
 
 void sft_release(ltgw_ctx *c) {
     for (auto &pl : c->sft_plans) (void)hipfftDestroy((hipfftHandle)pl.plan);
     c->sft_plans.clear();
+    for (auto &t : c->sft_tabs) release(t.tab);
+    c->sft_tabs.clear();
     release(c->sft_spec);
     release(c->sft_spec2);
 }
@@ -174,6 +322,52 @@ const char *fft_error(hipfftResult r) {
 }  // namespace
 
 using namespace ltgw;
+
+namespace {
+
+// rows: powers of the outputs and their halo (float), or raw spectra (float2)
+template <bool SPEC>
+hipError_t launch_normalise(const void *rows, int64_t pitch, int64_t k_lo, int n_bins, int h, int n_seg, float *out,
+                            hipStream_t st) {
+    const unsigned tiles = (unsigned)((n_bins - 1) / (64 * kMedPer - 2 * h) + 1);
+    hipLaunchKernelGGL(normalise_kernel<SPEC>, dim3(tiles, (unsigned)n_seg), dim3(64), 0, st, rows, pitch, k_lo, n_bins, h,
+                       out);
+    return hipGetLastError();
+}
+
+// segments with an on-chip transform: powers of a chunk of segments (about 512 MB), then their ratios
+int chip_normalise(ltgw_ctx *c, const float *strain, int n_seg, int n_fft, int64_t k_lo, int n_bins, int h, float *out) {
+    int rc;
+    const float2 *tab = nullptr;
+    for (auto &t : c->sft_tabs)
+        if (t.n_fft == n_fft) tab = (const float2 *)t.tab.p;
+    if (!tab) {
+        DevBuf b;
+        if ((rc = ensure(c, b, chip_fft_table_bytes(n_fft), "transform tables")) != LTGW_OK) return rc;
+        c->sft_tabs.push_back({n_fft, b});
+        tab = (const float2 *)b.p;
+        const hipError_t e = launch_chip_fft_tables(n_fft, (float2 *)b.p, c->stream);
+        if (e != hipSuccess) {
+            release(c->sft_tabs.back().tab);
+            c->sft_tabs.pop_back();
+            return hip_fail(c, e, "transform tables");
+        }
+    }
+    const int row = n_bins + 2 * h;
+    const int batch = (int)std::max<int64_t>(1, std::min<int64_t>(n_seg, ((int64_t)512 << 20) / (4 * (int64_t)row)));
+    if ((rc = ensure(c, c->sft_spec, (size_t)batch * row * 4, "powers")) != LTGW_OK) return rc;
+    for (int j0 = 0; j0 < n_seg; j0 += batch) {
+        const int nb = std::min(batch, n_seg - j0);
+        HIP_TRY(c, launch_chip_fft(n_fft, strain + (int64_t)j0 * n_fft, nb, k_lo - h, row, tab, (float *)c->sft_spec.p,
+                                   c->stream),
+                "transform launch");
+        HIP_TRY(c, launch_normalise<false>(c->sft_spec.p, row, k_lo, n_bins, h, nb, out + (int64_t)j0 * n_bins, c->stream),
+                "normalise launch");
+    }
+    return LTGW_OK;
+}
+
+}  // namespace
 
 // A chunk of strain rows (n_fft reals each) into the transform buffer's rows
 // of n_fft + 2 reals: 8-byte moves (n_fft is even, so every row of both is
@@ -202,6 +396,7 @@ int32_t ltgw_sft_normalise(ltgw_ctx *c, const float *strain, int32_t n_seg, int3
     const int h = window / 2;
     if (n_bins < 1 || k_lo < h || k_lo + n_bins - 1 + h > n_fft / 2)
         return fail(c, LTGW_E_INVALID_ARG, "band [k_lo - window/2, k_lo + n_bins - 1 + window/2] must lie in 0 .. n_fft/2");
+    if (chip_fft_has(n_fft)) return chip_normalise(c, strain, n_seg, n_fft, k_lo, n_bins, h, out);
     int rc;
     // chunks of segments: spectra within about 512 MB
     const int64_t per_seg = (int64_t)(n_fft / 2 + 1) * 8;
@@ -254,10 +449,8 @@ int32_t ltgw_sft_normalise(ltgw_ctx *c, const float *strain, int32_t n_seg, int3
             HIP_TRY(c, hipStreamWaitEvent(c->side, c->ev_sft[b], 0), "normalise order");
             ns = c->side;
         }
-        hipLaunchKernelGGL(normalise_kernel, dim3((unsigned)((n_bins + kSftTile - 1) / kSftTile), (unsigned)nb),
-                           dim3(256), 0, ns, (const float2 *)spec, (int64_t)(n_fft / 2 + 1), k_lo, n_bins, h,
-                           out + (int64_t)j0 * n_bins);
-        HIP_TRY(c, hipGetLastError(), "normalise launch");
+        HIP_TRY(c, launch_normalise<true>(spec, n_fft / 2 + 1, k_lo, n_bins, h, nb, out + (int64_t)j0 * n_bins, ns),
+                "normalise launch");
         if (two) HIP_TRY(c, hipEventRecord(c->ev_sft[2 + b], c->side), "event record");
     }
     if (two)

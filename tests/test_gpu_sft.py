@@ -141,3 +141,26 @@ def test_strain_is_not_written():
         assert np.array_equal(a, b)
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("n_fft,n_seg,k_lo,n_bins,window", [
+    (4096, 5, 0, 2049, 1),          # every bin, DC to Nyquist, of the shortest on-chip transform
+    (8192, 3, 50, 413, 101),        # one output more than a tile of 512 positions holds
+    (16384, 2, 128, 256, 257),      # exactly one tile of the widest window
+    (16384, 2, 12, 1, 25),          # a single output
+    (32768, 3, 1, 16383, 3),        # the longest on-chip transform, DC to Nyquist with the halo
+    (65536, 2, 16000, 975, 51),     # beyond it
+])
+def test_transform_and_tile_limits(n_fft, n_seg, k_lo, n_bins, window):
+    """The bar of this file, on noise, beside a segment of zeros (rho = 0) and a single
+    sample at the middle of a segment: all its powers are 1 within rounding, so every
+    window is one run of near and exact ties and rho = ln 2 (1 + O(eps_32 log2 N))."""
+    print(f"case: sft limits n_fft={n_fft} k_lo={k_lo} n_bins={n_bins} window={window}", flush=True)
+    r = np.random.default_rng(n_bins)
+    x = r.normal(0.0, 2.0, (n_seg + 2, n_fft)).astype(np.float32)
+    x[1] = 0.0
+    x[2] = 0.0
+    x[2, n_fft // 2] = 1.0
+    got, _ = _check(x.reshape(-1), n_fft, k_lo, n_bins, window)
+    assert not got[1].any()
+    assert np.abs(got[2] - np.log(2.0)).max() <= 2e-5
