@@ -72,6 +72,14 @@ struct Store<kStoreCoarse> {
     }
 };
 
+// An element every lane of the wavefront reads at the same address, through
+// the constant address space: for arrays no kernel writes while it runs,
+// this makes the read a scalar load.
+template <typename T>
+__device__ inline T uniform_load(const T *p, int64_t i) {
+    return ((const __attribute__((address_space(4))) T *)p)[i];
+}
+
 // ---------------------------------------------------------------------------
 // Statistic (Sec. 2).  A lane carries TPL templates (f0 256 apart, so each
 // of them is a coalesced wavefront access); segments go in batches of U so
@@ -91,7 +99,7 @@ struct HFromGD {
     const double *D;  // [n_seg] of the group's sky direction
     double t_sft;
     __device__ double operator()(int j) const {
-        const double h = g[j] * D[j];
+        const double h = uniform_load(g, j) * uniform_load(D, j);
         return h * t_sft;
     }
 };
@@ -140,11 +148,11 @@ __device__ __forceinline__ void seg_batch(const DetView &D, __amdgpu_buffer_rsrc
     float wv[U];
     if (MOMENTS) {
 #pragma unroll
-        for (int k = 0; k < U; ++k) wv[k] = D.w[j + k];
+        for (int k = 0; k < U; ++k) wv[k] = uniform_load(D.w, j + k);
     }
 #pragma unroll
     for (int k = 0; k < U; ++k) {
-        const float wq = D.wq[j + k];
+        const float wq = uniform_load(D.wq, j + k);
 #pragma unroll
         for (int t = 0; t < TPL; ++t) {
             sc[t] = __builtin_fmaf(wq, p[t][k], sc[t]);
@@ -274,14 +282,6 @@ __device__ inline void xcd_tile_group(int w, int n_blocks, int n_tiles, int &til
     const int n_groups = (total < 0 ? n_blocks : total) / n_tiles;
     tile = p / n_groups;
     grp = p % n_groups;
-}
-
-// An element every lane of the wavefront reads at the same address, through
-// the constant address space: for arrays no kernel writes while it runs,
-// this makes the read a scalar load.
-template <typename T>
-__device__ inline T uniform_load(const T *p, int64_t i) {
-    return ((const __attribute__((address_space(4))) T *)p)[i];
 }
 
 // A value that is the same in every lane, moved to scalar registers word by
