@@ -6,6 +6,7 @@
 #include <algorithm>
 
 #include "ltgw_proposer.h"
+#include "log_table.h"
 #include "ddpow.h"
 
 #pragma clang fp contract(off)
@@ -40,21 +41,62 @@ __device__ inline void philox4x32_10(uint32_t c[4], uint32_t k0, uint32_t k1) {
 // Exp(1) noise: element e of realisation r takes word e % 4 of
 // Philox(counter = (e/4 low, e/4 high, r, stream), key = seed);
 // u = (word + 1/2) 2^-32 in (0, 1) exactly; value RN_32(-log(u)) (FP64 log).
+//
+// What bounds it is VALU issue (the writes alone take 177 us for 256 realisations of
+// 1024 x 800, which took 654 us with an FP64 library log per element and take 255 now).
+// With v = 2 word + 1 = 2^e m and r, -log(r) of the table for m's top 7 bits,
+// -log(u) = (33 - e) ln 2 + log(r) - log1p(m r - 1); |m r - 1| < 2^-7 is exact, seven
+// terms of the series leave 2^-51.  All rounding together stays below 2^-47, the
+// library's log is within 2^-47 of the logarithm for every word, so where
+// y - 2^-45 and y + 2^-45 round to one FP32 value that is the library's as well; the
+// library decides the rest (one element in 10^5).
 __global__ __launch_bounds__(256) void noise_kernel(uint64_t seed, uint32_t stream, int r0,
-                                                    int64_t n_per, float *__restrict__ out) {
+                                                    int64_t n_per, int wide, float *__restrict__ out) {
+    __shared__ double2 s_log[128];  // r, -log(r)
+    if (threadIdx.x < 128)
+        s_log[threadIdx.x] = make_double2(kLogTab[threadIdx.x][0], kLogTab[threadIdx.x][1] + kLogTab[threadIdx.x][2]);
+    __syncthreads();
     const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int r = blockIdx.y;
     if (q * 4 >= n_per) return;
     uint32_t c[4] = {(uint32_t)q, (uint32_t)((uint64_t)q >> 32), (uint32_t)(r0 + r), stream};
     philox4x32_10(c, (uint32_t)seed, (uint32_t)(seed >> 32));
-    float *o = out + (int64_t)r * n_per;
+    float f[4];
+    bool open[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const int64_t e = q * 4 + i;
-        if (e < n_per) {
-            const double u = ((double)c[i] + 0.5) * 0x1p-32;
-            o[e] = (float)(-log(u));
+        const uint64_t v = __builtin_bit_cast(uint64_t, __builtin_fma((double)c[i], 2.0, 1.0));
+        const int hi = (int)(v >> 32);
+        const double m = __builtin_bit_cast(double, (v & 0x000fffffffffffffull) | 0x3ff0000000000000ull);
+        const double2 t = s_log[(hi >> 13) & 127];
+        const double z = __builtin_fma(m, t.x, -1.0);
+        double p = __builtin_fma(z, -1.0 / 6.0, 0.2);
+        p = __builtin_fma(z, p, -0.25);
+        p = __builtin_fma(z, p, 1.0 / 3.0);
+        p = __builtin_fma(z, p, -0.5);
+        p = __builtin_fma(z * z, p, z);
+        const double y = __builtin_fma((double)(33 + 1023 - (hi >> 20)), 0.69314718055994530942, -t.y) - p;
+        f[i] = (float)(y - 0x1p-45);
+        open[i] = f[i] != (float)(y + 0x1p-45);
+    }
+    if (open[0] || open[1] || open[2] || open[3]) {
+#pragma unroll 1
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t w = i == 0 ? c[0] : i == 1 ? c[1] : i == 2 ? c[2] : c[3];
+            const float g = (float)(-log(((double)w + 0.5) * 0x1p-32));
+            f[0] = i == 0 ? g : f[0];
+            f[1] = i == 1 ? g : f[1];
+            f[2] = i == 2 ? g : f[2];
+            f[3] = i == 3 ? g : f[3];
         }
+    }
+    float *o = out + (int64_t)r * n_per + q * 4;
+    if (wide) {  // every row a multiple of 4 elements from a 16-byte boundary
+        *(float4 *)o = make_float4(f[0], f[1], f[2], f[3]);
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (q * 4 + i < n_per) o[i] = f[i];
     }
 }
 
@@ -63,7 +105,7 @@ hipError_t launch_noise(uint64_t seed, uint32_t stream, int r0, int R, int64_t n
     if (R < 1 || R > 65535 || n_per < 1) return hipErrorInvalidValue;
     const int64_t blocks = ((n_per + 3) / 4 + 255) / 256;
     hipLaunchKernelGGL(noise_kernel, dim3((unsigned)blocks, (unsigned)R), dim3(256), 0, st, seed, stream,
-                       r0, n_per, out);
+                       r0, n_per, (n_per & 3) == 0 && ((uintptr_t)out & 15) == 0, out);
     return hipGetLastError();
 }
 

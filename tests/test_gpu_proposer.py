@@ -110,6 +110,28 @@ def test_noise_matches_oracle():
     ctx.close()
 
 
+@pytest.mark.parametrize("n,offset", [(1 << 20, 0), (1 << 18, 1), (4099, 2), (1, 0)])
+def test_noise_layouts(n, offset):
+    """Whole groups of four on and off a 16-byte boundary, and ragged rows; the bar is
+    test_noise_matches_oracle's (the FP64 logarithms may round one value in 10^4
+    differently), and nothing is written outside the rows."""
+    import torch
+    from paper_2507_07816_amd import ltgw
+
+    ctx, *_ = _ctx()
+    print(f"case: noise layout n {n} offset {offset}", flush=True)
+    buf = torch.full((offset + 2 * n + 4,), -1.0, dtype=torch.float32, device="cuda")
+    ltgw.ltgw_generate_noise(ctx.h, 24680, 1, 2, buf[offset:offset + 2 * n].view(2, n))
+    g = buf.cpu().numpy()
+    ctx.close()
+    assert np.all(g[:offset] == -1.0) and np.all(g[offset + 2 * n:] == -1.0)
+    for i in range(2):
+        ref = oracle.exp_noise(24680, 1, 2 + i, n)
+        diff = np.abs(g[offset + i * n:offset + (i + 1) * n].view(np.int32).astype(np.int64) -
+                      ref.view(np.int32).astype(np.int64))
+        assert diff.max() <= 1 and (diff > 0).sum() <= 1 + n // 10000
+
+
 def test_inject_stack_matches_oracle_bins():
     import torch
     from paper_2507_07816_amd import ltgw
