@@ -16,44 +16,68 @@ namespace ltgw {
 // realisation, so each template's moments W1, W2, N are formed once per
 // lattice (stack_moments_kernel) in the order the in-loop sums would take:
 // FP32 over chunks of 32 segments, carried in FP64.
+//
+// A workgroup of 16 wavefronts takes 64 templates: each wavefront a chunk at a
+// time, its sums left in LDS, which the first wavefront adds in chunk order.
+// There are few templates (thousands), so a lane that walked all segments left
+// most of the chip idle: 4800 templates over 1024 segments took 107 us and take
+// 11 now.
+constexpr int kSplitWaves = 16;
+
 template <int SHIFT>
-__global__ __launch_bounds__(256) void stack_moments_kernel(const EvalArgs a, double *__restrict__ w1,
-                                                            double *__restrict__ w2, int32_t *__restrict__ n) {
-    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (t >= (int64_t)a.n_groups * a.n_f0) return;
-    const int grp = (int)(t / a.n_f0), i = (int)(t % a.n_f0);
+__global__ __launch_bounds__(64 * kSplitWaves) void stack_moments_kernel(const EvalArgs a, double *__restrict__ w1,
+                                                                         double *__restrict__ w2,
+                                                                         int32_t *__restrict__ n) {
+    __shared__ float2 part[2][kSplitWaves][64];
+    __shared__ int count[kSplitWaves][64];
+    const int n_tiles = (a.n_f0 + 63) / 64;
+    const int tile = (int)blockIdx.x % n_tiles, grp = (int)blockIdx.x / n_tiles;
+    const int lane = (int)threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int i = tile * 64 + lane;
     const DetView &D = a.det[0];
     const double f0 = a.f0_min + (double)i * a.f0_step;
-    const double *__restrict__ H = D.H + (int64_t)grp * D.n_seg;
+    const double *H = D.H + (int64_t)grp * D.n_seg;
     const unsigned nb = (unsigned)D.n_bins;
+    const int chunks = (D.n_seg + kChunk - 1) / kChunk;
     double W1 = 0.0, W2 = 0.0;
     int N = 0;
-    for (int j0 = 0; j0 < D.n_seg; j0 += kChunk) {
-        const int je = min(j0 + kChunk, D.n_seg);
+    for (int c0 = 0, b = 0; c0 < chunks; c0 += kSplitWaves, b ^= 1) {
+        const int j0 = (c0 + wv) * kChunk, je = min(j0 + kChunk, D.n_seg);
         float c1 = 0.0f, c2 = 0.0f;
+#pragma unroll 4
         for (int j = j0; j < je; ++j) {
-            const double x = f0 * H[j];
+            const double x = f0 * uniform_load(H, j);
             const double vv = x + D.cshift;
             const unsigned idx = (unsigned)__double2int_rz(vv) >> SHIFT;
             const bool inb = (idx - 1u) < nb;
             N += inb ? 1 : 0;
-            const float wv = D.w[j];
-            const float wj = inb ? wv : 0.0f;
+            const float wj = inb ? uniform_load(D.w, j) : 0.0f;
             c1 += wj;
             c2 = __builtin_fmaf(wj, wj, c2);
         }
-        W1 += (double)c1;
-        W2 += (double)c2;
+        part[b][wv][lane] = make_float2(c1, c2);
+        __syncthreads();  // the other buffer's sums were read before it
+        if (wv == 0)
+            for (int k = 0; k < min(kSplitWaves, chunks - c0); ++k) {
+                const float2 p = part[b][k][lane];
+                W1 += (double)p.x;
+                W2 += (double)p.y;
+            }
     }
+    count[wv][lane] = N;
+    __syncthreads();
+    if (wv != 0 || i >= a.n_f0) return;
+    for (int k = 1; k < kSplitWaves; ++k) N += count[k][lane];
+    const int64_t t = (int64_t)grp * a.n_f0 + i;
     w1[t] = W1;
     w2[t] = W2;
     n[t] = N;
 }
 
 hipError_t launch_stack_moments(int shift, const EvalArgs &a, double *w1, double *w2, int32_t *n, hipStream_t st) {
-    const int64_t t = (int64_t)a.n_groups * a.n_f0;
-    if (t < 1 || t > 0x7fffffffLL) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)((t + 255) / 256)), block(256);
+    const int64_t t = (int64_t)((a.n_f0 + 63) / 64) * a.n_groups;
+    if (t < 1 || (int64_t)a.n_groups * a.n_f0 > 0x7fffffffLL) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)t), block(64 * kSplitWaves);
     if (shift == 0)
         hipLaunchKernelGGL(stack_moments_kernel<0>, grid, block, 0, st, a, w1, w2, n);
     else
@@ -247,15 +271,23 @@ hipError_t launch_coarse_block_scores(const float *x, int R, int nb, int c_in, i
 // idx[r][q] of the grid (any order; each lane reads its own group's track
 // factors).  Writes the power critical ratio (mu = var = 1) or NaN.  Rows
 // rr >= *n_rows are skipped when the device count n_rows is given.
+// 64 templates per workgroup, its 16 wavefronts a chunk of segments each, the
+// chunk sums added in order through LDS: 45 templates on each of 256 realisations
+// of 1024 segments took 106 us with a wavefront per realisation, 42 so.
 template <int STORE>
-__global__ __launch_bounds__(256) void list_eval_kernel(const EvalArgs a, int64_t stack_bytes,
-                                                        int64_t stack_rows, const int32_t *__restrict__ idx,
-                                                        int m, const int32_t *__restrict__ rmap,
-                                                        const int32_t *__restrict__ n_rows, const StackMoments mom,
-                                                        double *__restrict__ out_psi) {
-    const int q = blockIdx.x * 256 + threadIdx.x;
+__global__ __launch_bounds__(64 * kSplitWaves) void list_eval_kernel(const EvalArgs a, int64_t stack_bytes,
+                                                                     int64_t stack_rows,
+                                                                     const int32_t *__restrict__ idx, int m,
+                                                                     const int32_t *__restrict__ rmap,
+                                                                     const int32_t *__restrict__ n_rows,
+                                                                     const StackMoments mom,
+                                                                     double *__restrict__ out_psi) {
+    __shared__ float part[2][kSplitWaves][64];
+    __shared__ int count[kSplitWaves][64];
+    const int lane = (int)threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int q = blockIdx.x * 64 + lane;
     const int rr = blockIdx.y;                  // row of idx and out_psi
-    if (n_rows && rr >= *n_rows) return;
+    if (n_rows && rr >= *n_rows) return;        // the whole workgroup
     const int r = rmap ? rmap[rr] : rr;         // realisation of the stack
     DetView D = a.det[0];
     D.store = (const char *)D.store + (int64_t)r * stack_bytes;
@@ -269,12 +301,13 @@ __global__ __launch_bounds__(256) void list_eval_kernel(const EvalArgs a, int64_
     const double *__restrict__ H = D.H + (int64_t)grp * D.n_seg;
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
         (void *)D.store, Store<STORE>::kBytes, D.n_bins + 2, kBufDword3);
+    const int chunks = (D.n_seg + kChunk - 1) / kChunk;
     double s = 0.0;
     int cnt = 0;
-    for (int j0 = 0; j0 < D.n_seg; j0 += kChunk) {
-        const int je = min(j0 + kChunk, D.n_seg);
+    for (int c0 = 0, b = 0; c0 < chunks; c0 += kSplitWaves, b ^= 1) {
+        const int je = min((c0 + wv + 1) * kChunk, D.n_seg);
         float sc = 0.0f;
-        int j = j0;
+        int j = (c0 + wv) * kChunk;
         // batches of 8 segments: the track factors, then the gathers, then the
         // sums in segment order (the same sums as one segment at a time)
         for (; j + 8 <= je; j += 8) {
@@ -289,17 +322,23 @@ __global__ __launch_bounds__(256) void list_eval_kernel(const EvalArgs a, int64_
 #pragma unroll
             for (int k = 0; k < 8; ++k) p[k] = Store<STORE>::get(rs, (int)ix[k], (j + k) * D.pitch_bytes, cnt);
 #pragma unroll
-            for (int k = 0; k < 8; ++k) sc = __builtin_fmaf(D.wq[j + k], p[k], sc);
+            for (int k = 0; k < 8; ++k) sc = __builtin_fmaf(uniform_load(D.wq, j + k), p[k], sc);
         }
         for (; j < je; ++j) {
             const double x = f0 * H[j];
             const double vv = x + D.cshift;
             const unsigned ix = (unsigned)__double2int_rz(vv);
-            sc = __builtin_fmaf(D.wq[j], Store<STORE>::get(rs, (int)ix, j * D.pitch_bytes, cnt), sc);
+            sc = __builtin_fmaf(uniform_load(D.wq, j), Store<STORE>::get(rs, (int)ix, j * D.pitch_bytes, cnt), sc);
         }
-        s += (double)sc;
+        part[b][wv][lane] = sc;
+        __syncthreads();  // the other buffer's sums were read before it
+        if (wv == 0)
+            for (int k = 0; k < min(kSplitWaves, chunks - c0); ++k) s += (double)part[b][k][lane];
     }
-    if (q >= m) return;
+    count[wv][lane] = cnt;
+    __syncthreads();
+    if (wv != 0 || q >= m) return;
+    for (int k = 1; k < kSplitWaves; ++k) cnt += count[k][lane];
     out_psi[(int64_t)rr * m + q] = bad ? __builtin_nan("") : stack_stat(s, cnt, mom, t, 1.0, 1.0, 0);
 }
 
@@ -307,7 +346,7 @@ hipError_t launch_list_eval(int store, const EvalArgs &a, int R, int64_t stack_b
                             const int32_t *idx, int m, const int32_t *rmap, const int32_t *n_rows, StackMoments mom,
                             double *out_psi, hipStream_t st) {
     if (R > 65535 || R < 1 || m < 1) return hipErrorInvalidValue;
-    dim3 grid((unsigned)((m + 255) / 256), (unsigned)R), block(256);
+    const dim3 grid((unsigned)((m + 63) / 64), (unsigned)R), block(64 * kSplitWaves);
     if (store == LTGW_STORE_F32)
         hipLaunchKernelGGL(list_eval_kernel<LTGW_STORE_F32>, grid, block, 0, st, a, stack_bytes, stack_rows, idx, m, rmap, n_rows, mom, out_psi);
     else if (store == LTGW_STORE_BF16)

@@ -289,6 +289,66 @@ def test_stack_store_against_oracle_odd_shape(ns, nb, store):
     ctx.close()
 
 
+@pytest.mark.parametrize("ns,nb,n_f0,R,store", [
+    (1, 65, 1, 1, "f32"),
+    (31, 190, 65, 3, "bf16"),
+    (33, 189, 63, 2, "fp8"),
+    (512, 190, 64, 5, "f32"),      # 16 chunks of segments
+    (513, 64, 130, 3, "bf16"),     # and one segment more
+    (1057, 131, 257, 9, "f32"),
+])
+def test_stack_sums_over_segments_and_rows(ns, nb, n_f0, R, store):
+    """Both ratios of every template, in full and as a list, at the edges of the
+    chunks of segments, of the 64 f0 of a wavefront and of odd counts of realisations:
+    the oracle's on the values the store holds (counts exact, so that ratio to 1e-12),
+    and the list bit for bit what the whole grid gives."""
+    import torch
+    from paper_2507_07816_amd import ltgw
+
+    print(f"case: stack sums {store} {R} x {ns} x {nb}, {n_f0} f0", flush=True)
+    r = np.random.default_rng(ns)
+    t = np.arange(ns) * (3840.0 / max(ns, 96)) + 2.0
+    v = r.normal(size=(ns, 3))
+    v = v / np.linalg.norm(v, axis=1, keepdims=True) * 3.0e4
+    w = r.uniform(0.5, 2.0, ns).astype(np.float32)
+    ctx = ltgw.Context(0)
+    ctx.load_spectrogram(0, torch.zeros((ns, nb), dtype=torch.float32, device="cuda"), K_LO, T_SFT, t, weights=w)
+    ctx.set_velocity_table(0, v)
+    P = r.exponential(size=(R, ns, nb)).astype(np.float32)
+    ltgw.ltgw_load_stack(ctx.h, 0, torch.from_numpy(P).cuda(), store, coarse=False)
+    d = dict(f0_min=(K_LO - 2) / T_SFT, f0_step=0.25, n_f0=n_f0, tau=[4000.0, 15000.0, 60000.0], brake=[3.0, 5.0],
+             sky=[SKY], t0=0.0)
+    fg, keep = _grid(d)
+    g = _ogrid(d)
+    n = g.n_templates
+    full = torch.empty((R, n), dtype=torch.float64, device="cuda")
+    ltgw.ltgw_stack_psi(ctx.h, fg, 0, full)
+    f = full.cpu().numpy()
+    idx = torch.from_numpy(np.tile(np.arange(n, dtype=np.int32), (R, 1))).cuda()
+    lists = {}
+    for stat in ("power", "count"):
+        out = torch.empty((R, n), dtype=torch.float64, device="cuda")
+        ltgw.ltgw_stack_psi_list(ctx.h, fg, idx, out, stat=stat)
+        lists[stat] = out.cpu().numpy()
+        bi = torch.empty(R, dtype=torch.int32, device="cuda")
+        bp = torch.empty(R, dtype=torch.float64, device="cuda")
+        ltgw.ltgw_stack_best(ctx.h, fg, bi, bp, stat=stat)
+        best = np.where(np.isnan(lists[stat]), -np.inf, lists[stat])
+        assert np.array_equal(bp.cpu().numpy(), best.max(axis=1))
+    assert np.array_equal(lists["power"], f, equal_nan=True)
+    for q in range(R):
+        vals, _ = oracle.dequantised(P[q], store)
+        ref = oracle.evaluate(oracle.Detector(P[q], t, v, K_LO, T_SFT, weights=w, values=vals), g)
+        psi, pc = oracle.psi_power(ref), oracle.psi_count(ref)
+        ok = np.isfinite(psi)
+        assert ok.sum() >= min(n_f0 - 2, 1) and np.array_equal(ok, np.isfinite(f[q]))
+        assert np.all(np.abs(f[q][ok] - psi[ok]) <= psi_tolerance(ref)[ok])
+        okc = np.isfinite(pc)
+        assert np.array_equal(okc, np.isfinite(lists["count"][q]))
+        assert np.all(np.abs(lists["count"][q][okc] - pc[okc]) <= 1e-12 * (1 + np.abs(pc[okc])))
+    ctx.close()
+
+
 def _net(seed, c_in, c_out):
     p = cnn.init_params(c_in, c_out, seed).astype(np.float64)
     p += np.random.default_rng(seed + 1).normal(scale=0.05, size=p.size)
