@@ -499,6 +499,10 @@ int32_t ltgw_stack_features(ltgw_ctx *ctx, const ltgw_grid *g, int32_t counts, f
  * template has N > 0) into device best_index[R], best_psi[R].
  * Asynchronous. */
 int32_t ltgw_stack_best(ltgw_ctx *ctx, const ltgw_grid *g, uint32_t stat, int32_t *best_index, double *best_psi);
+/* ltgw_stack_best_both: ltgw_stack_best for both statistics from one walk over
+ * the stack, the same results. */
+int32_t ltgw_stack_best_both(ltgw_ctx *ctx, const ltgw_grid *g, int32_t *power_index, double *power_psi,
+                             int32_t *count_index, double *count_psi);
 
 /* ltgw_cells_from_templates: fine template t (group g, f0 index i, with fine
  * n_f0 = 2 L) -> network cell (2 g + i % 2) L + i / 2; -1 where t < 0,

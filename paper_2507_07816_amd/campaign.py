@@ -18,7 +18,7 @@ Every statistic comes from the library's kernels through its C ABI:
   templates close to the injection decide, so only they are evaluated, and
   the largest ratio among them is compared with the threshold.
 Over the lattice, realisations go through in stacks (`ltgw_load_stack`, then
-`ltgw_stack_best` for the full searches and `ltgw_stack_psi_list` for the
+`ltgw_stack_best_both` for the full searches and `ltgw_stack_psi_list` for the
 templates near each injection, power and count); over a random bank, whose
 templates share no track tables, one realisation at a time
 (`ltgw_eval_list`, `ltgw_topk_candidates` with k = 1, `ltgw_psi`).
@@ -204,12 +204,10 @@ class Campaign:
         ltgw.ltgw_load_stack(self.ctx.h, self.slot, st, self.store, coarse=0)
         g, keep = ltgw.make_grid(self.grid["f0_min"], self.grid["f0_step"], self.grid["n_f0"], self.grid["tau"],
                                  self.grid["brake"], self.grid["sky"], self.grid.get("t0", 0.0))
-        bi = T.empty(n, dtype=T.int32, device=self.dev)
-        out = []
-        for stat in ("power", "count"):
-            bp = T.empty(n, dtype=T.float64, device=self.dev)
-            ltgw.ltgw_stack_best(self.ctx.h, g, bi, bp, stat=stat)
-            out.append(bp.cpu().numpy())
+        bi = T.empty((2, n), dtype=T.int32, device=self.dev)
+        bp = T.empty((2, n), dtype=T.float64, device=self.dev)
+        ltgw.ltgw_stack_best_both(self.ctx.h, g, bi[0], bp[0], bi[1], bp[1])
+        out = bp.cpu().numpy()
         return out[0], out[1]
 
     def _stack_region(self, st, inj):

@@ -22,7 +22,8 @@ hipError_t launch_stack_moments(int shift, const EvalArgs &a, double *w1, double
 
 hipError_t launch_stack_eval(int store, int shift, const EvalArgs &a, int R, int64_t stack_bytes,
                              int64_t stack_rows, double mu, double var, int nan_to_zero, const int32_t *rmap,
-                             const int32_t *n_rows, StackMoments m, double *out_psi, hipStream_t st);
+                             const int32_t *n_rows, StackMoments m, double *out_power, double *out_count, int cu_count,
+                             hipStream_t st);
 // The network's input from the coarse store (power ratios, and count ratios
 // with counts != 0) in FP32 x[R][channels][n_f0]; psi (optional) the FP64
 // power ratios [R][n_templates], NaN -> 0.

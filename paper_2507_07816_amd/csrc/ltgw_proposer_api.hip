@@ -194,12 +194,12 @@ StackMoments stat_moments(ltgw_ctx *c, int level, uint32_t stat) {
     return m;
 }
 
-int stack_psi_impl(ltgw_ctx *c, const ltgw_grid *g, int level, int nan_to_zero, double *out_psi,
-                   uint32_t stat = LTGW_STAT_POWER) {
+// The power ratios, the count ratios (the fine level), or both from one walk.
+int stack_psi_impl(ltgw_ctx *c, const ltgw_grid *g, int level, int nan_to_zero, double *out_power,
+                   double *out_count = nullptr) {
     int rc = need_stack(c, level);
     if (rc != LTGW_OK) return rc;
     if (level != 0 && level != 1) return fail(c, LTGW_E_INVALID_ARG, "level must be 0 or 1");
-    if ((rc = need_device(c, out_psi, "out_psi")) != LTGW_OK) return rc;
     SearchPlan P;
     if ((rc = stack_tables(c, g, level, P)) != LTGW_OK) return rc;
     int64_t sb = 0, sr = 0;
@@ -208,7 +208,8 @@ int stack_psi_impl(ltgw_ctx *c, const ltgw_grid *g, int level, int nan_to_zero, 
     const int store = level ? kStoreCoarse : c->stack.store;
     const double mu = level ? 2.0 * c->stack.S : 1.0;  // a coarse pixel sums 2 S Exp(1) values
     HIP_TRY(c, launch_stack_eval(store, shift, a, c->stack.R, sb, sr, mu, mu, nan_to_zero, nullptr, nullptr,
-                                 stat_moments(c, level, stat), out_psi, c->stream),
+                                 stat_moments(c, level, out_count ? LTGW_STAT_COUNT : LTGW_STAT_POWER), out_power, out_count,
+                                 c->cu_count, c->stream),
             "stack evaluation launch");
     return LTGW_OK;
 }
@@ -241,6 +242,17 @@ int list_psi_impl(ltgw_ctx *c, const ltgw_grid *g, const int32_t *idx, int rows,
                                 out_psi, c->stream),
             "listed evaluation launch");
     if (plan_out) *plan_out = P;
+    return LTGW_OK;
+}
+
+int stack_best_impl(ltgw_ctx *c, const ltgw_grid *g, int64_t n, uint32_t stat, int32_t *best_index, double *best_psi) {
+    StackState &S = c->stack;
+    int rc = ensure(c, S.psi_all, (size_t)(S.R * n) * 8, "fine ratios");
+    if (rc != LTGW_OK) return rc;
+    double *const psi = (double *)S.psi_all.p;
+    const bool count = stat == LTGW_STAT_COUNT;
+    if ((rc = stack_psi_impl(c, g, 0, 0, count ? nullptr : psi, count ? psi : nullptr)) != LTGW_OK) return rc;
+    HIP_TRY(c, launch_row_best(psi, S.R, n, nullptr, nullptr, best_index, best_psi, c->stream), "reduction launch");
     return LTGW_OK;
 }
 
@@ -416,6 +428,10 @@ int32_t ltgw_load_stack(ltgw_ctx *c, int32_t det, int32_t R, const float *stack,
 int32_t ltgw_stack_psi(ltgw_ctx *c, const ltgw_grid *g, int32_t level, int32_t nan_to_zero, double *out_psi) {
     if (!c) return LTGW_E_INVALID_ARG;
     Enter en(c);
+    int rc = need_stack(c, level);
+    if (rc != LTGW_OK) return rc;
+    if (level != 0 && level != 1) return fail(c, LTGW_E_INVALID_ARG, "level must be 0 or 1");
+    if ((rc = need_device(c, out_psi, "out_psi")) != LTGW_OK) return rc;
     return stack_psi_impl(c, g, level, nan_to_zero, out_psi);
 }
 
@@ -556,14 +572,34 @@ int32_t ltgw_stack_best(ltgw_ctx *c, const ltgw_grid *g, uint32_t stat, int32_t 
     if ((rc = need_device(c, best_index, "best_index")) != LTGW_OK) return rc;
     if ((rc = need_device(c, best_psi, "best_psi")) != LTGW_OK) return rc;
     if (!g) return fail(c, LTGW_E_INVALID_ARG, "grid is NULL");
-    StackState &S = c->stack;
     const int64_t n = (int64_t)g->n_f0 * g->n_tau * g->n_brake * g->n_sky;
     if (n < 1) return fail(c, LTGW_E_INVALID_ARG, "empty grid");
-    if ((rc = ensure(c, S.psi_all, (size_t)(S.R * n) * 8, "fine ratios")) != LTGW_OK) return rc;
-    if ((rc = stack_psi_impl(c, g, 0, 0, (double *)S.psi_all.p, stat)) != LTGW_OK) return rc;
-    HIP_TRY(c, launch_row_best((const double *)S.psi_all.p, S.R, n, nullptr, nullptr, best_index, best_psi,
-                               c->stream),
-            "reduction launch");
+    return stack_best_impl(c, g, n, stat, best_index, best_psi);
+}
+
+int32_t ltgw_stack_best_both(ltgw_ctx *c, const ltgw_grid *g, int32_t *power_index, double *power_psi,
+                             int32_t *count_index, double *count_psi) {
+    if (!c) return LTGW_E_INVALID_ARG;
+    Enter en(c);
+    int rc = need_stack(c, 0);
+    if (rc != LTGW_OK) return rc;
+    const void *ptrs[] = {power_index, power_psi, count_index, count_psi};
+    for (const void *p : ptrs)
+        if ((rc = need_device(c, p, "best index and ratio arrays")) != LTGW_OK) return rc;
+    if (!g) return fail(c, LTGW_E_INVALID_ARG, "grid is NULL");
+    const int64_t n = (int64_t)g->n_f0 * g->n_tau * g->n_brake * g->n_sky;
+    if (n < 1) return fail(c, LTGW_E_INVALID_ARG, "empty grid");
+    StackState &S = c->stack;
+    const size_t all = (size_t)(S.R * n);
+    if (ensure(c, S.psi_all, all * 16, "fine ratios of both statistics") != LTGW_OK) {
+        // room for one at a time
+        if ((rc = stack_best_impl(c, g, n, LTGW_STAT_POWER, power_index, power_psi)) != LTGW_OK) return rc;
+        return stack_best_impl(c, g, n, LTGW_STAT_COUNT, count_index, count_psi);
+    }
+    double *const pp = (double *)S.psi_all.p, *const pc = pp + all;
+    if ((rc = stack_psi_impl(c, g, 0, 0, pp, pc)) != LTGW_OK) return rc;
+    HIP_TRY(c, launch_row_best(pp, S.R, n, nullptr, nullptr, power_index, power_psi, c->stream), "reduction launch");
+    HIP_TRY(c, launch_row_best(pc, S.R, n, nullptr, nullptr, count_index, count_psi, c->stream), "reduction launch");
     return LTGW_OK;
 }
 
@@ -745,7 +781,7 @@ int32_t ltgw_propose(ltgw_ctx *c, const ltgw_grid *fine, const ltgw_grid *coarse
                                 counts + 1, (int32_t *)S.fb.p, c->stream),
             "fallback rows launch");
     HIP_TRY(c, launch_stack_eval(S.store, 0, fa, R, sb, sr, 1.0, 1.0, 0, (const int32_t *)S.rmap.p, counts + 1, fm,
-                                 (double *)S.psi_all.p, c->stream),
+                                 (double *)S.psi_all.p, nullptr, c->cu_count, c->stream),
             "fallback evaluation launch");
     HIP_TRY(c, launch_row_best((const double *)S.psi_all.p, R, n_tpl, nullptr, counts + 1, (int32_t *)S.bi2.p,
                                (double *)S.bp2.p, c->stream),

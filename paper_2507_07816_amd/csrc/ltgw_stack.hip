@@ -5,9 +5,14 @@
 #include "ltgw_gather.h"
 #include "ltgw_proposer.h"
 
+#include <algorithm>
+
 #pragma clang fp contract(off)
 
 namespace ltgw {
+
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 
 // ---------------------------------------------------------------------------
 // Stacks of realisations (the learned proposer's data): R spectrograms of one
@@ -96,12 +101,9 @@ __device__ inline double stack_ratio(double s, const StackMoments &m, int64_t tt
     return num / sqrt(var * m.w2[tt]);
 }
 
-// The ratio a stack kernel writes for a template with power sum s and count
-// c: power (above), or with m.count the count ratio in the operation order of
-// the single-search ratio (the same value bit for bit).
-__device__ inline double stack_stat(double s, int c, const StackMoments &m, int64_t tt, double mu, double var,
-                                    int nan_to_zero) {
-    if (!m.count) return stack_ratio(s, m, tt, mu, var, nan_to_zero);
+// The count ratio of a template with count c, in the operation order of the
+// single-search ratio (the same value bit for bit).
+__device__ inline double stack_count_ratio(int c, const StackMoments &m, int64_t tt, int nan_to_zero) {
     const int nn = m.n[tt];
     if (nn == 0) return nan_to_zero ? 0.0 : __builtin_nan("");
     const double Nq = (double)nn * m.q;
@@ -109,7 +111,14 @@ __device__ inline double stack_stat(double s, int c, const StackMoments &m, int6
     return num / sqrt(Nq * (1.0 - m.q));
 }
 
-// Every template of a grid on every realisation: the power critical ratio.
+// The ratio of the statistic m.count names.
+__device__ inline double stack_stat(double s, int c, const StackMoments &m, int64_t tt, double mu, double var,
+                                    int nan_to_zero) {
+    return m.count ? stack_count_ratio(c, m, tt, nan_to_zero) : stack_ratio(s, m, tt, mu, var, nan_to_zero);
+}
+
+// Every template of a grid on every realisation: the power and the count critical
+// ratio (either output may be NULL; one walk serves both).
 // One workgroup per (256 f0, group, output row) and pass.  The hardware deals
 // workgroups to the XCDs in turn; workgroup w goes to row x + 8 (k / per_row)
 // of XCD x = w % 8 (k = w / 8), so the workgroups of one row run on one XCD
@@ -123,7 +132,7 @@ __global__ __launch_bounds__(256) void stack_eval_kernel(const EvalArgs a, int R
                                                          int64_t stack_rows, double mu, double var,
                                                          int nan_to_zero, const int32_t *__restrict__ rmap,
                                                          const int32_t *__restrict__ n_rows, const StackMoments m,
-                                                         double *__restrict__ out_psi) {
+                                                         double *__restrict__ out_power, double *__restrict__ out_count) {
     const int n_tiles = (a.n_f0 + 255) / 256;
     const int per_row = n_tiles * a.n_groups;
     const int P = (int)gridDim.x / per_row;
@@ -145,15 +154,268 @@ __global__ __launch_bounds__(256) void stack_eval_kernel(const EvalArgs a, int R
         Acc<1> acc;
         acc.zero();
         accumulate_det<STORE, false, 1, 16, HTable, SHIFT>(D, HTable{D.H + (int64_t)grp * D.n_seg}, f0, acc);
-        if (i < a.n_f0)
-            out_psi[(int64_t)rr * ((int64_t)a.n_groups * a.n_f0) + tt] =
-                stack_stat(acc.s[0], acc.cnt[0], m, tt, mu, var, nan_to_zero);
+        if (i >= a.n_f0) continue;
+        const int64_t o = (int64_t)rr * ((int64_t)a.n_groups * a.n_f0) + tt;
+        if (out_power) out_power[o] = stack_ratio(acc.s[0], m, tt, mu, var, nan_to_zero);
+        if (out_count) out_count[o] = stack_count_ratio(acc.cnt[0], m, tt, nan_to_zero);
     }
+}
+
+// The same for two realisations at a time, from LDS.
+// The gather of stack_eval_kernel is bound by its address unit: 64 lanes cost about 14
+// cycles of a CU whatever they read.  Here a workgroup copies whole rows of two
+// realisations, column by column side by side, into LDS (16-byte loads, three batches
+// of 4 segments ahead of the one in use: with one ahead every batch waited for HBM and
+// the launch took as long as the gathers), and its 16 wavefronts take up to 3 slots of
+// 64 f0 of one group each: the column of a (template, segment) is formed once and one
+// LDS read gives both elements.  Track factors and weights come through LDS too: as
+// scalar loads each batch waited for them.  Sums and counts are those of
+// stack_eval_kernel bit for bit (a row past the last segment is zeros: it adds 0 and
+// counts nothing).  256 realisations of 1024 x 800, 4800 templates, FP32: 298 us
+// instead of 460 (VALU issue alone is 230).
+constexpr int kPairSegs = 4, kPairWaves = 16, kPairAhead = 3, kPairSlots = 3 /* per wavefront */;
+template <int STORE>
+constexpr int kPairEls = 16 / Store<STORE>::kBytes;  // columns of a 16-byte piece
+template <int STORE>
+constexpr int kPairCols = kPairWaves * 64 / kPairSegs *kPairEls<STORE>;
+
+// two realisations' pieces -> column pairs
+template <int STORE>
+__device__ __forceinline__ void pair_piece(u32x4 a, u32x4 b, u32x4 &lo, u32x4 &hi) {
+    if constexpr (STORE == LTGW_STORE_F32) {
+        lo = u32x4{a.x, b.x, a.y, b.y};
+        hi = u32x4{a.z, b.z, a.w, b.w};
+    } else {
+        constexpr unsigned kLo = 0x05040100u, kHi = 0x07060302u;  // bytes of (b, a): 16-bit elements
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            lo[2 * k] = __builtin_amdgcn_perm(b[k], a[k], kLo);
+            lo[2 * k + 1] = __builtin_amdgcn_perm(b[k], a[k], kHi);
+            hi[2 * k] = __builtin_amdgcn_perm(b[k + 2], a[k + 2], kLo);
+            hi[2 * k + 1] = __builtin_amdgcn_perm(b[k + 2], a[k + 2], kHi);
+        }
+    }
+}
+
+// both elements of a column, the count bit as the sign
+template <int STORE>
+__device__ __forceinline__ void pair_get(const char *row, unsigned col, float &p0, float &p1) {
+    if constexpr (STORE == LTGW_STORE_F32) {
+        const float2 v = ((const float2 *)row)[col];
+        p0 = v.x;
+        p1 = v.y;
+    } else {
+        const unsigned v = ((const unsigned *)row)[col];
+        p0 = __uint_as_float(v << 16);
+        p1 = __uint_as_float(v & 0xffff0000u);
+    }
+}
+
+template <int STORE>
+__global__ __launch_bounds__(64 * kPairWaves, 4) void stack_pair_kernel(
+    const EvalArgs a, int R, int64_t stack_bytes, int64_t stack_rows, double mu, double var, int nan_to_zero,
+    const StackMoments m, int parts,
+    int cols /* of a row in LDS */, double *__restrict__ out_power, double *__restrict__ out_count) {
+    extern __shared__ __attribute__((aligned(16))) char lds[];  // [2][kPairSegs][cols] pairs
+    constexpr int kEls = kPairEls<STORE>, kPair = 2 * Store<STORE>::kBytes, NS = kPairSlots;
+    const int xcd = (int)blockIdx.x % kXcds, kk = (int)blockIdx.x / kXcds;
+    const int part = kk % parts, pair = xcd + kXcds * (kk / parts);
+    if (2 * pair >= R) return;  // the whole workgroup
+    const int lane = (int)threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int n_tiles = (a.n_f0 + 63) / 64, n_slots = n_tiles * a.n_groups;
+    // an even share of the slots, at most kPairWaves NS, and of those at most NS
+    const int slot0 = part * n_slots / parts, slot1 = (part + 1) * n_slots / parts;
+    const int first = slot0 + wv * (slot1 - slot0) / kPairWaves;
+    const int mine = slot0 + (wv + 1) * (slot1 - slot0) / kPairWaves - first;
+    const DetView &D = a.det[0];
+    const int n_seg = D.n_seg, row_bytes = cols * kPair;
+    const unsigned guard = (unsigned)D.n_bins + 1u;
+    // groups of the workgroup's slots: their track factors of a batch follow the rows in
+    // LDS, and the weights of the batch follow those
+    const int g0 = slot0 / n_tiles, ng = (slot1 - 1) / n_tiles - g0 + 1;
+    const int h_at = kPairSegs * row_bytes, w_at = h_at + kPairWaves * NS * kPairSegs * 8;
+    const int buf_bytes = w_at + 2 * kPairSegs * 4;
+    double f0[NS];
+    int hrow[NS];
+#pragma unroll
+    for (int u = 0; u < NS; ++u) {
+        const int sl = u < mine ? first + u : slot0;
+        f0[u] = a.f0_min + (double)(sl % n_tiles * 64 + lane) * a.f0_step;
+        hrow[u] = h_at + (sl / n_tiles - g0) * kPairSegs * 8;
+    }
+    // this thread's share of a batch: a piece of a row (segment, first column) ...
+    constexpr int kNone = 0x7ffffff0;  // an offset past every resource: reads zeros
+    const int seg = (int)threadIdx.x / (cols / kEls), col = (int)threadIdx.x % (cols / kEls) * kEls;
+    const bool piece = seg < kPairSegs;
+    const int from = piece ? seg * D.pitch_bytes + col * Store<STORE>::kBytes : kNone;
+    const int to = seg * row_bytes + col * kPair;
+    // ... and 8 bytes of the track factors (group g0 + t / 4, segment t % 4) or, in the
+    // last two wavefronts, of the weights of one realisation
+    const bool weights = wv >= kPairWaves - 2;
+    const bool extra = weights ? lane < kPairSegs / 2 : (int)threadIdx.x < ng * kPairSegs;
+    const int efrom = !extra ? kNone
+                      : weights ? lane * 8
+                                : ((int)threadIdx.x / kPairSegs * n_seg + (int)threadIdx.x % kPairSegs) * 8;
+    const int eto = weights ? w_at + (wv - (kPairWaves - 2)) * kPairSegs * 4 + lane * 8 : h_at + (int)threadIdx.x * 8;
+    const int estep = weights ? 4 : 8;
+    const int r0 = 2 * pair, r1 = min(r0 + 1, R - 1);
+    // reads past a realisation's last row, or past its weights, give zeros (past a
+    // group's track factors, the next group's or zeros: they meet rows of zeros)
+    const __amdgpu_buffer_rsrc_t s0 = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)((const char *)D.store + (int64_t)r0 * stack_bytes), 0, (int)stack_bytes, kBufDword3);
+    const __amdgpu_buffer_rsrc_t s1 = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)((const char *)D.store + (int64_t)r1 * stack_bytes), 0, (int)stack_bytes, kBufDword3);
+    const void *const ep = weights ? (const void *)(D.wq + (int64_t)(wv == kPairWaves - 1 ? r1 : r0) * stack_rows)
+                                   : (const void *)(D.H + (int64_t)g0 * n_seg);
+    const __amdgpu_buffer_rsrc_t es =
+        __builtin_amdgcn_make_buffer_rsrc((void *)ep, 0, weights ? n_seg * 4 : ng * n_seg * 8, kBufDword3);
+    // batches on their way
+    u32x4 x0[kPairAhead], x1[kPairAhead];
+    u32x2 xe[kPairAhead];
+    auto issue = [&](int q, int j) {
+        x0[q] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(s0, from, j * D.pitch_bytes, 0));
+        x1[q] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(s1, from, j * D.pitch_bytes, 0));
+        xe[q] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(es, efrom, j * estep, 0));
+    };
+    auto store = [&](int q, int buf) {
+        char *const b = lds + buf * buf_bytes;
+        if (piece) {
+            u32x4 lo, hi;
+            pair_piece<STORE>(x0[q], x1[q], lo, hi);
+            u32x4 *p = (u32x4 *)(b + to);
+            p[0] = lo;
+            p[1] = hi;
+        }
+        if (extra) *(u32x2 *)(b + eto) = xe[q];
+    };
+    double s[NS][2];
+    float sc[NS][2];
+    unsigned bits[NS][2];
+    int cnt[NS][2];
+#pragma unroll
+    for (int u = 0; u < NS; ++u)
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            s[u][e] = 0.0;
+            sc[u][e] = 0.0f;
+            bits[u][e] = 0u;
+            cnt[u][e] = 0;
+        }
+    // the batch from segment j, in LDS buffer buf; set q holds the one after it
+    auto step = [&](int q, int j, int buf) {
+        const char *const base = lds + buf * buf_bytes;
+        const float4 w0 = ((const float4 *)(base + w_at))[0], w1 = ((const float4 *)(base + w_at))[1];
+        const float v0[kPairSegs] = {w0.x, w0.y, w0.z, w0.w}, v1[kPairSegs] = {w1.x, w1.y, w1.z, w1.w};
+#pragma unroll
+        for (int u = 0; u < NS; ++u) {
+            if (u >= mine) break;
+            const double2 ha = ((const double2 *)(base + hrow[u]))[0], hb = ((const double2 *)(base + hrow[u]))[1];
+            const double h[kPairSegs] = {ha.x, ha.y, hb.x, hb.y};
+            float p0[kPairSegs], p1[kPairSegs];
+#pragma unroll
+            for (int k = 0; k < kPairSegs; ++k) {
+                const double x = f0[u] * h[k];
+                const double vv = x + D.cshift;
+                const unsigned idx = (unsigned)__double2int_rz(vv);
+                pair_get<STORE>(base + k * row_bytes, min(idx, guard), p0[k], p1[k]);
+            }
+#pragma unroll
+            for (int k = 0; k < kPairSegs; ++k) {
+                sc[u][0] = __builtin_fmaf(v0[k], __builtin_fabsf(p0[k]), sc[u][0]);
+                sc[u][1] = __builtin_fmaf(v1[k], __builtin_fabsf(p1[k]), sc[u][1]);
+                bits[u][0] = __builtin_amdgcn_alignbit(bits[u][0], __float_as_uint(p0[k]), 31);
+                bits[u][1] = __builtin_amdgcn_alignbit(bits[u][1], __float_as_uint(p1[k]), 31);
+            }
+        }
+        if ((j + kPairSegs) % kChunk == 0 || j + kPairSegs >= n_seg) {
+#pragma unroll
+            for (int u = 0; u < NS; ++u)
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    s[u][e] += (double)sc[u][e];
+                    cnt[u][e] += __popc(bits[u][e]);
+                    sc[u][e] = 0.0f;
+                    bits[u][e] = 0u;
+                }
+        }
+        store(q, buf ^ 1);
+        issue(q, j + (kPairAhead + 1) * kPairSegs);
+        __syncthreads();
+    };
+    issue(0, 0);
+    store(0, 0);
+#pragma unroll
+    for (int q = 0; q < kPairAhead; ++q) issue(q, (q + 1) * kPairSegs);
+    __syncthreads();
+    int buf = 0;
+#pragma unroll 1
+    for (int j = 0; j < n_seg;) {
+#pragma unroll
+        for (int q = 0; q < kPairAhead; ++q)
+            if (j < n_seg) {
+                step(q, j, buf);
+                j += kPairSegs;
+                buf ^= 1;
+            }
+    }
+    const int64_t n_tpl = (int64_t)a.n_groups * a.n_f0;
+#pragma unroll
+    for (int u = 0; u < NS; ++u) {
+        if (u >= mine) break;
+        const int i = (first + u) % n_tiles * 64 + lane;
+        if (i >= a.n_f0) continue;
+        const int64_t tt = (int64_t)((first + u) / n_tiles) * a.n_f0 + i;
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const int64_t o = (int64_t)(e ? r1 : r0) * n_tpl + tt;
+            if (out_power) out_power[o] = stack_ratio(s[u][e], m, tt, mu, var, nan_to_zero);
+            if (out_count) out_count[o] = stack_count_ratio(cnt[u][e], m, tt, nan_to_zero);
+        }
+    }
+}
+
+// Where the pair kernel is faster.  Its workgroups take a time of their own however
+// little each has to do (150 us for 1024 segments), so it needs the chip full: by
+// (f0 / 64) x groups x realisations it draws level at 9000 - 12000 for FP32 and near
+// 18000 for BF16 (84 x 128 FP32: 196 us against 228, 84 x 64: 153 against 98; 84 x 256
+// BF16: 298 against 341, 48 x 256: 200 against 175).
+// The limits on segments and slots keep its 32-bit offsets and shares in range.
+template <int STORE>
+static bool stack_pair_suits(const EvalArgs &a, int R) {
+    const int64_t slots = (int64_t)((a.n_f0 + 63) / 64) * a.n_groups;
+    return a.det[0].n_bins + 2 <= kPairCols<STORE> && a.det[0].n_seg <= (1 << 20) && slots <= (1 << 17) &&
+           slots * R >= (STORE == LTGW_STORE_F32 ? 12000 : 20000);
+}
+
+template <int STORE>
+static hipError_t launch_stack_pair(const EvalArgs &a, int R, int64_t stack_bytes, int64_t stack_rows, double mu,
+                                    double var, int nan_to_zero, StackMoments m, double *out_power, double *out_count,
+                                    int cu_count, hipStream_t st) {
+    // a pair's slots over as many workgroups as fill the chip, or as hold them
+    const int n_slots = (a.n_f0 + 63) / 64 * a.n_groups, pairs = (R + 1) / 2;
+    const int most = kPairWaves * kPairSlots;
+    const int parts = std::max((n_slots + most - 1) / most,
+                               std::min(cu_count / pairs, (n_slots + kPairWaves - 1) / kPairWaves));
+    const int cols = (a.det[0].n_bins + 2 + kPairEls<STORE> - 1) / kPairEls<STORE> * kPairEls<STORE>;
+    const int64_t grid = (int64_t)parts * ((pairs + kXcds - 1) / kXcds * kXcds);
+    if (grid > 0x7fffffff) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(stack_pair_kernel<STORE>, dim3((unsigned)grid), dim3(64 * kPairWaves),
+                       (size_t)2 * kPairSegs * (cols * 2 * Store<STORE>::kBytes + most * 8 + 2 * 4), st, a, R, stack_bytes,
+                       stack_rows, mu, var, nan_to_zero, m, parts, cols, out_power, out_count);
+    return hipGetLastError();
 }
 
 hipError_t launch_stack_eval(int store, int shift, const EvalArgs &a, int R, int64_t stack_bytes,
                              int64_t stack_rows, double mu, double var, int nan_to_zero, const int32_t *rmap,
-                             const int32_t *n_rows, StackMoments m, double *out_psi, hipStream_t st) {
+                             const int32_t *n_rows, StackMoments m, double *out_power, double *out_count, int cu_count,
+                             hipStream_t st) {
+    if (R > 65535 || R < 1) return hipErrorInvalidValue;
+    if (!rmap && !n_rows && store == LTGW_STORE_F32 && stack_pair_suits<LTGW_STORE_F32>(a, R))
+        return launch_stack_pair<LTGW_STORE_F32>(a, R, stack_bytes, stack_rows, mu, var, nan_to_zero, m, out_power,
+                                                 out_count, cu_count, st);
+    if (!rmap && !n_rows && store == LTGW_STORE_BF16 && stack_pair_suits<LTGW_STORE_BF16>(a, R))
+        return launch_stack_pair<LTGW_STORE_BF16>(a, R, stack_bytes, stack_rows, mu, var, nan_to_zero, m, out_power,
+                                                  out_count, cu_count, st);
     // rows per pass: all of them rounded up to a multiple of the XCD count (the
     // extra workgroups return), or at most 256 when a device count may leave
     // most rows idle
@@ -163,7 +425,7 @@ hipError_t launch_stack_eval(int store, int shift, const EvalArgs &a, int R, int
     dim3 grid((unsigned)blocks), block(256);
 #define LTGW_STACK_EVAL(S, SH)                                                                                     \
     hipLaunchKernelGGL((stack_eval_kernel<S, SH>), grid, block, 0, st, a, R, stack_bytes, stack_rows, mu, var, \
-                       nan_to_zero, rmap, n_rows, m, out_psi)
+                       nan_to_zero, rmap, n_rows, m, out_power, out_count)
     if (store == LTGW_STORE_F32 && shift == 0)
         LTGW_STACK_EVAL(LTGW_STORE_F32, 0);
     else if (store == LTGW_STORE_BF16 && shift == 0)

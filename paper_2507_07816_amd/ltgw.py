@@ -49,7 +49,7 @@ EXPORTS = ("ltgw_create", "ltgw_destroy", "ltgw_last_error", "ltgw_load_spectrog
            "ltgw_generate_noise", "ltgw_inject_stack", "ltgw_load_stack", "ltgw_stack_psi",
            "ltgw_stack_psi_list", "ltgw_cnn_param_count", "ltgw_cnn_work_floats", "ltgw_cnn_forward",
            "ltgw_cnn_backward", "ltgw_softmax_xent", "ltgw_adam_step", "ltgw_select_top",
-           "ltgw_propose", "ltgw_stack_features", "ltgw_stack_best", "ltgw_cells_from_templates",
+           "ltgw_propose", "ltgw_stack_features", "ltgw_stack_best", "ltgw_stack_best_both", "ltgw_cells_from_templates",
            "ltgw_eval_list", "ltgw_eval_templates_noalloc", "ltgw_proposer_save", "ltgw_proposer_load")
 
 
@@ -160,6 +160,7 @@ def library():
             "ltgw_select_top": (i32, [P, P, i32, i32, i32, P]),
             "ltgw_stack_features": (i32, [P, C.POINTER(ltgw_grid), i32, P]),
             "ltgw_stack_best": (i32, [P, C.POINTER(ltgw_grid), u32, P, P]),
+            "ltgw_stack_best_both": (i32, [P, C.POINTER(ltgw_grid), P, P, P, P]),
             "ltgw_cells_from_templates": (i32, [P, P, i32, i32, P, P, d, P]),
             "ltgw_propose": (i32, [P, C.POINTER(ltgw_grid), C.POINTER(ltgw_grid), C.POINTER(ltgw_proposer),
                                    P, P, P]),
@@ -479,6 +480,13 @@ def ltgw_stack_best(ctx, grid, best_index, best_psi, stat="power"):
     import torch
     _check(ctx, library().ltgw_stack_best(ctx, C.byref(grid), STATS.get(stat, stat), _dev(best_index, torch.int32),
                                           _dev(best_psi, torch.float64)))
+
+
+def ltgw_stack_best_both(ctx, grid, power_index, power_psi, count_index, count_psi):
+    import torch
+    _check(ctx, library().ltgw_stack_best_both(ctx, C.byref(grid), _dev(power_index, torch.int32),
+                                               _dev(power_psi, torch.float64), _dev(count_index, torch.int32),
+                                               _dev(count_psi, torch.float64)))
 
 
 def ltgw_cells_from_templates(ctx, tpl, L, cells, mask=None, psi=None, min_psi=0.0):

@@ -296,6 +296,8 @@ def test_stack_store_against_oracle_odd_shape(ns, nb, store):
     (512, 190, 64, 5, "f32"),      # 16 chunks of segments
     (513, 64, 130, 3, "bf16"),     # and one segment more
     (1057, 131, 257, 9, "f32"),
+    (37, 1022, 1000, 126, "f32"),  # two realisations per workgroup: the widest row it holds
+    (66, 61, 1000, 211, "bf16"),   # an odd count of them
 ])
 def test_stack_sums_over_segments_and_rows(ns, nb, n_f0, R, store):
     """Both ratios of every template, in full and as a list, at the edges of the
@@ -335,8 +337,15 @@ def test_stack_sums_over_segments_and_rows(ns, nb, n_f0, R, store):
         ltgw.ltgw_stack_best(ctx.h, fg, bi, bp, stat=stat)
         best = np.where(np.isnan(lists[stat]), -np.inf, lists[stat])
         assert np.array_equal(bp.cpu().numpy(), best.max(axis=1))
+        lists[stat + " best"] = bi.cpu().numpy(), bp.cpu().numpy()
+    bi = torch.empty((2, R), dtype=torch.int32, device="cuda")
+    bp = torch.empty((2, R), dtype=torch.float64, device="cuda")
+    ltgw.ltgw_stack_best_both(ctx.h, fg, bi[0], bp[0], bi[1], bp[1])
+    for k, stat in enumerate(("power", "count")):
+        assert np.array_equal(bi[k].cpu().numpy(), lists[stat + " best"][0])
+        assert np.array_equal(bp[k].cpu().numpy(), lists[stat + " best"][1])
     assert np.array_equal(lists["power"], f, equal_nan=True)
-    for q in range(R):
+    for q in range(R) if R < 16 else (0, R - 1):
         vals, _ = oracle.dequantised(P[q], store)
         ref = oracle.evaluate(oracle.Detector(P[q], t, v, K_LO, T_SFT, weights=w, values=vals), g)
         psi, pc = oracle.psi_power(ref), oracle.psi_count(ref)
