@@ -428,7 +428,7 @@ int32_t ltgw_load_spectrogram(ltgw_ctx *c, int32_t det, const ltgw_spec_desc *d,
     c->have_ingest = false;
     HIP_TRY(c, hipEventRecord(c->ev_ing[0], c->stream), "event record");
     HIP_TRY(c, launch_ingest(d->store, src, d->n_seg, d->n_bins, pitch, D.store_buf.p,
-                             (float *)D.scale.p, (const float *)D.w.p, (float *)D.wq.p, d->rho_th,
+                             (float *)D.scale.p, (const float *)D.w.p, d->n_seg, (float *)D.wq.p, d->rho_th,
                              (unsigned long long *)c->counters.p + kCntBad, c->stream),
             "ingest launch");
     HIP_TRY(c, hipEventRecord(c->ev_ing[1], c->stream), "event record");

@@ -61,13 +61,15 @@ struct EvalArgs {
 };
 
 // Kernel launchers (all asynchronous on `st`; return the launch status).
+// (row j has weight w[j % w_rows]: a stack's realisations share theirs)
 hipError_t launch_ingest(int store, const float *power, int32_t n_seg, int32_t n_bins,
-                         int64_t pitch, void *out, float *scale, const float *w, float *wq,
+                         int64_t pitch, void *out, float *scale, const float *w, int32_t w_rows, float *wq,
                          float rho_th, unsigned long long *bad, hipStream_t st);
 // The learned proposer's stacks: realisations [R][n_seg][n_bins] into the fine
 // store (as launch_ingest per row) and, in the same pass, the coarse store of
 // S x 2 blocks: [R][n_seg / S][pitch2] words (bfloat16 sum << 16 | count);
 // crs NULL: the fine store alone, S rows per workgroup (n_bins even).
+// w: [n_seg], the weights of every realisation; wq: [R][n_seg].
 hipError_t launch_stack_ingest(int store, const float *power, int R, int32_t n_seg, int32_t n_bins, int S,
                                int64_t pitch, void *out, float *scale, const float *w, float *wq, float rho_th,
                                int64_t pitch2, unsigned *crs, unsigned long long *bad, hipStream_t st);

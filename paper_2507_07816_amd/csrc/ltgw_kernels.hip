@@ -64,7 +64,7 @@ template <int STORE>
 __global__ __launch_bounds__(256) void ingest_kernel(const float *__restrict__ in, int n_bins,
                                                      int64_t pitch, void *__restrict__ out,
                                                      float *__restrict__ scale,
-                                                     const float *__restrict__ w,
+                                                     const float *__restrict__ w, int w_rows,
                                                      float *__restrict__ wq, float th,
                                                      unsigned long long *bad) {
     __shared__ float sh[4];
@@ -102,23 +102,23 @@ __global__ __launch_bounds__(256) void ingest_kernel(const float *__restrict__ i
     if (nbad) atomicAdd(bad, (unsigned long long)nbad);
     if (threadIdx.x == 0) {
         scale[j] = sc;
-        wq[j] = w[j] * sc;
+        wq[j] = w[j % w_rows] * sc;
     }
 }
 
 hipError_t launch_ingest(int store, const float *power, int32_t n_seg, int32_t n_bins,
-                         int64_t pitch, void *out, float *scale, const float *w, float *wq,
+                         int64_t pitch, void *out, float *scale, const float *w, int32_t w_rows, float *wq,
                          float rho_th, unsigned long long *bad, hipStream_t st) {
     dim3 grid(n_seg), block(256);
     if (store == LTGW_STORE_F32)
         hipLaunchKernelGGL(ingest_kernel<LTGW_STORE_F32>, grid, block, 0, st, power, n_bins, pitch,
-                           out, scale, w, wq, rho_th, bad);
+                           out, scale, w, w_rows, wq, rho_th, bad);
     else if (store == LTGW_STORE_BF16)
         hipLaunchKernelGGL(ingest_kernel<LTGW_STORE_BF16>, grid, block, 0, st, power, n_bins, pitch,
-                           out, scale, w, wq, rho_th, bad);
+                           out, scale, w, w_rows, wq, rho_th, bad);
     else
         hipLaunchKernelGGL(ingest_kernel<LTGW_STORE_FP8>, grid, block, 0, st, power, n_bins, pitch,
-                           out, scale, w, wq, rho_th, bad);
+                           out, scale, w, w_rows, wq, rho_th, bad);
     return hipGetLastError();
 }
 
@@ -158,7 +158,7 @@ __global__ __launch_bounds__(256) void stack_ingest_kernel(const float *__restri
         if (threadIdx.x == 0) {
             ssc[k] = sc;
             scale[row0 + k] = sc;
-            wq[row0 + k] = w[row0 + k] * sc;
+            wq[row0 + k] = w[S * j2 + k] * sc;  // one realisation's weights serve all
         }
     }
     __syncthreads();

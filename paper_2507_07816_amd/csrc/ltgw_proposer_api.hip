@@ -166,7 +166,7 @@ EvalArgs stack_args(const StackState &S, int level, const ltgw_grid *g, const Se
         V.n_seg = S.n_seg / S.S;
         V.n_bins = S.n_bins / 2;
         stack_bytes = (int64_t)(S.n_seg / S.S) * S.pitch2 * 4;
-        stack_rows = S.n_seg / S.S;
+        stack_rows = 0;  // one row of weights for every realisation
     }
     V.H = (const double *)L.H.p;
     V.g = (const double *)L.g.p;
@@ -343,14 +343,13 @@ int32_t ltgw_load_stack(ltgw_ctx *c, int32_t det, int32_t R, const float *stack,
     HIP_TRY(c, hipEventSynchronize(S.ev_h2d), "previous upload");
     const int64_t rows = (int64_t)R * ns;
     if ((rc = ensure(c, S.fine, (size_t)(rows * pitch * esize(store)), "stack store")) != LTGW_OK) return rc;
-    if ((rc = ensure(c, S.w, (size_t)rows * 4, "stack weights")) != LTGW_OK) return rc;
+    if ((rc = ensure(c, S.w, (size_t)ns * 4, "stack weights")) != LTGW_OK) return rc;
     if ((rc = ensure(c, S.wq, (size_t)rows * 4, "stack scaled weights")) != LTGW_OK) return rc;
     if ((rc = ensure(c, S.scale, (size_t)rows * 4, "stack scales")) != LTGW_OK) return rc;
     if ((rc = ensure(c, S.t, (size_t)ns * 8, "stack segment times")) != LTGW_OK) return rc;
     if ((rc = ensure(c, S.v, (size_t)ns * 24, "stack velocities")) != LTGW_OK) return rc;
-    std::vector<float> hw((size_t)rows);
-    for (int64_t r = 0; r < R; ++r) std::memcpy(&hw[(size_t)(r * ns)], D.h_w.data(), (size_t)ns * 4);
-    if ((rc = h2d(c, S.w.p, hw.data(), hw.size() * 4, "stack weights upload")) != LTGW_OK) return rc;
+    // one row of weights for every realisation
+    if ((rc = h2d(c, S.w.p, D.h_w.data(), (size_t)ns * 4, "stack weights upload")) != LTGW_OK) return rc;
     if ((rc = h2d(c, S.t.p, D.h_t.data(), (size_t)ns * 8, "segment times upload")) != LTGW_OK) return rc;
     if ((rc = h2d(c, S.v.p, D.h_v.data(), (size_t)ns * 24, "velocity upload")) != LTGW_OK) return rc;
     std::vector<float> hw2;
@@ -362,17 +361,16 @@ int32_t ltgw_load_stack(ltgw_ctx *c, int32_t det, int32_t R, const float *stack,
         if (ns2 * pitch2 * 4 >= ((int64_t)1 << 31))
             return fail(c, LTGW_E_UNSUPPORTED, "one realisation's coarse store exceeds 2^31 bytes");
         if ((rc = ensure(c, S.crs, (size_t)(R * ns2 * pitch2 * 4), "coarse store")) != LTGW_OK) return rc;
-        if ((rc = ensure(c, S.w2, (size_t)(R * ns2) * 4, "coarse weights")) != LTGW_OK) return rc;
+        if ((rc = ensure(c, S.w2, (size_t)ns2 * 4, "coarse weights")) != LTGW_OK) return rc;
         if ((rc = ensure(c, S.t2, (size_t)ns2 * 8, "coarse segment times")) != LTGW_OK) return rc;
         if ((rc = ensure(c, S.v2, (size_t)ns2 * 24, "coarse velocities")) != LTGW_OK) return rc;
         // a group's weight: its S weights summed in order, times 1/S (FP32)
-        hw2.resize((size_t)(R * ns2));
+        hw2.resize((size_t)ns2);
         for (int64_t j = 0; j < ns2; ++j) {
             float acc = D.h_w[(size_t)(Sg * j)];
             for (int k = 1; k < Sg; ++k) acc = acc + D.h_w[(size_t)(Sg * j + k)];
             hw2[(size_t)j] = acc * (1.0f / (float)Sg);
         }
-        for (int64_t r = 1; r < R; ++r) std::memcpy(&hw2[(size_t)(r * ns2)], hw2.data(), (size_t)ns2 * 4);
         ht2.resize((size_t)ns2);
         hv2.resize((size_t)ns2 * 3);
         for (int64_t j = 0; j < ns2; ++j) {
@@ -401,7 +399,7 @@ int32_t ltgw_load_stack(ltgw_ctx *c, int32_t det, int32_t R, const float *stack,
                 "stack ingest launch");
     else
         HIP_TRY(c, launch_ingest(store, stack, (int32_t)rows, (int32_t)nb, pitch, S.fine.p, (float *)S.scale.p,
-                                 (const float *)S.w.p, (float *)S.wq.p, D.rho_th,
+                                 (const float *)S.w.p, (int32_t)ns, (float *)S.wq.p, D.rho_th,
                                  (unsigned long long *)c->counters.p + kCntBad, c->stream),
                 "stack ingest launch");
     HIP_TRY(c, hipEventRecord(c->ev_ing[1], c->stream), "event record");

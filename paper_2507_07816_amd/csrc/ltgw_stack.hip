@@ -17,7 +17,7 @@ typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 // ---------------------------------------------------------------------------
 // Stacks of realisations (the learned proposer's data): R spectrograms of one
 // geometry, realisation r at byte offset r * stack_bytes of the store and
-// r * stack_rows of the per-row weights.  The weights are the same for every
+// r * stack_rows of the scaled weights (wq).  The weights are the same for every
 // realisation, so each template's moments W1, W2, N are formed once per
 // lattice (stack_moments_kernel) in the order the in-loop sums would take:
 // FP32 over chunks of 32 segments, carried in FP64.
@@ -150,7 +150,6 @@ __global__ __launch_bounds__(256) void stack_eval_kernel(const EvalArgs a, int R
         DetView D = a.det[0];
         D.store = (const char *)D.store + (int64_t)r * stack_bytes;
         D.wq += (int64_t)r * stack_rows;
-        D.w += (int64_t)r * stack_rows;
         Acc<1> acc;
         acc.zero();
         accumulate_det<STORE, false, 1, 16, HTable, SHIFT>(D, HTable{D.H + (int64_t)grp * D.n_seg}, f0, acc);
@@ -469,7 +468,6 @@ __global__ __launch_bounds__(256) void stack_features_kernel(const EvalArgs a, i
         DetView D = a.det[0];
         D.store = (const char *)D.store + (int64_t)r * stack_bytes;
         D.wq += (int64_t)r * stack_rows;
-        D.w += (int64_t)r * stack_rows;
         Acc<1> acc;
         acc.zero();
         accumulate_det<kStoreCoarse, false, 1, 16, HTable, 1>(D, HTable{D.H + (int64_t)grp * D.n_seg}, f0, acc);
