@@ -358,7 +358,7 @@ void ltgw_destroy(ltgw_ctx *c) {
         release(d.era); release(d.w_sky); release(d.wq_sky);
     }
     DevBuf *all[] = {&c->staging, &c->counters, &c->cnn_packed, &c->list_d, &c->perm_d, &c->list_dop, &c->list_sky, &c->list_tab, &c->list_part,
-                     &c->tau_d,   &c->brake_d,  &c->sky_d,      &c->res_s, &c->res_c, &c->res_n, &c->res_w1, &c->res_w2, &c->diff,
+                     &c->tau_d,   &c->brake_d,  &c->sky_d,      &c->res_s, &c->res_c, &c->res_n, &c->res_w1, &c->res_w2,
                      &c->cand};
     for (DevBuf *b : all) release(*b);
     release_pinned(c->h_list);
@@ -687,8 +687,10 @@ struct EvalMem {
     }
 };
 
-// Bytes of scratch the evaluation of plan P takes (every table, window,
-// moment array and per-template result), each slice rounded up to 256.
+// Bytes of scratch the evaluation of plan P is accounted (every table, window,
+// moment array and per-template result, and 8 bytes per in-band sum of a template,
+// which the moments once kept there: the entry point's limit stays where it was),
+// each slice rounded up to 256.
 size_t eval_bytes(const ltgw_ctx *c, const SearchPlan &P, const Moments &M, const ltgw_grid *g) {
     auto r = [](size_t b) { return ((b ? b : 16) + 255) & ~(size_t)255; };
     size_t t = r((size_t)g->n_tau * 8) + r((size_t)g->n_brake * 8) + r((size_t)g->n_sky * 24);
@@ -863,12 +865,9 @@ int eval_single(ltgw_ctx *c, const ltgw_grid *g, uint32_t stats, float *out_s, i
         }
     } join{c};
     if (!moments_in_loop) {
-        const size_t n_diff = (size_t)(M.mode ? 4 : 1) * (size_t)P.n_groups * (size_t)(g->n_f0 + 1);
-        void *diff_p;
-        if ((rc = mem.get(c->diff, n_diff * 8, "moment difference arrays", &diff_p)) != LTGW_OK) return rc;
         HIP_TRY(c, hipEventRecord(c->ev_fork, c->stream), "event record");
         HIP_TRY(c, hipStreamWaitEvent(c->side, c->ev_fork, 0), "stream wait");
-        const hipError_t me = launch_moments(a, M.mode, M.e0, (int64_t *)diff_p, c->side);
+        const hipError_t me = launch_moments(a, M.mode, M.e0, c->side);
         const hipError_t je = hipEventRecord(c->ev_join, c->side);
         join.on = je == hipSuccess;
         HIP_TRY(c, me, "moments launch");

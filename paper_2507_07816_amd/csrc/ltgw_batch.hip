@@ -24,7 +24,7 @@ void free_batch(BatchState &B) {
     if (B.ev1) (void)hipEventDestroy(B.ev1);
     DevBuf *all[] = {&B.searches, &B.tiles, &B.ctr, &B.tiles_done, &B.t_done, &B.t_start,
                      &B.in_band, &B.s, &B.c, &B.n_res, &B.w1, &B.w2, &B.gtab, &B.dtab, &B.win,
-                     &B.tau, &B.brake, &B.sky, &B.cand, &B.n_out, &B.diff, &B.topk,
+                     &B.tau, &B.brake, &B.sky, &B.cand, &B.n_out, &B.topk,
                      &B.topk_done};
     for (DevBuf *b : all) release(*b);
     B = BatchState();
@@ -140,27 +140,38 @@ int enqueue(ltgw_ctx *c, BatchState &B, hipStream_t st, int variant, bool with_t
     HIP_TRY(c, launch_fill_u64((unsigned long long *)B.t_start.p, 1, ~0ull, st), "batch reset");
     HIP_TRY(c, launch_fill_u64((unsigned long long *)B.in_band.p, 1, 0ull, st), "batch reset");
     HIP_TRY(c, launch_fill_u64((unsigned long long *)B.t_done.p, B.n, 0ull, st), "batch reset");
+    // The tables of the searches in turn on two streams, then the moments on the side
+    // stream while the statistic runs: the launches before it are small, and the
+    // statistic reads nothing that the moments write (the ranking waits for both).
+    auto to = [&](hipStream_t from, hipStream_t by, hipEvent_t ev) {
+        const hipError_t e = hipEventRecord(ev, from);
+        return e == hipSuccess ? hipStreamWaitEvent(by, ev, 0) : e;
+    };
+    HIP_TRY(c, to(st, c->side, c->ev_fork), "batch fork");
     for (int i = 0; i < B.n; ++i) {
         const SearchPlan &P = B.plans[i];
+        const hipStream_t ts = i & 1 ? c->side : st;
         for (int q = 0; q < P.n_sel; ++q) {
             const Det &D = c->det[P.sel[q]];
             const DetView &V = B.hsearch[i].det[q];
             HIP_TRY(c, launch_spin_factor((const double *)D.t_seg.p, D.n_seg, B.t0[i],
                                           (const double *)B.tau.p + B.tau_off[i], P.n_tau,
                                           (const double *)B.brake.p + B.brake_off[i], P.n_brake,
-                                          (double *)V.g, (unsigned long long *)c->counters.p + kCntUndecided, st),
+                                          (double *)V.g, (unsigned long long *)c->counters.p + kCntUndecided, ts),
                     "batch spin-factor launch");
             HIP_TRY(c, launch_doppler((const double *)D.v.p, D.n_seg, (const double *)B.sky.p + B.sky_off[i],
-                                      P.n_sky, (double *)V.D, st),
+                                      P.n_sky, (double *)V.D, ts),
                     "batch Doppler launch");
             HIP_TRY(c, launch_windows(V, (int)P.n_groups, P.n_tn, B.hsearch[i].f0_min, B.hsearch[i].f0_step, P.n_f0,
-                                      (int2 *)V.win, st),
+                                      (int2 *)V.win, ts),
                     "batch window launch");
         }
     }
+    HIP_TRY(c, to(c->side, st, c->ev_join), "batch tables");
+    HIP_TRY(c, to(st, c->side, c->ev_fork), "batch tables");
     if (!B.moments_in_loop)
         for (int i = 0; i < B.n; ++i)
-            HIP_TRY(c, launch_moments(B.args[i], B.mom[i].mode, B.e0, (int64_t *)B.diff.p, st),
+            HIP_TRY(c, launch_moments(B.args[i], B.mom[i].mode, B.e0, c->side),
                     "batch moments launch");
     BatchArgs ba;
     ba.searches = (const BatchSearch *)B.searches.p;
@@ -173,6 +184,7 @@ int enqueue(ltgw_ctx *c, BatchState &B, hipStream_t st, int variant, bool with_t
     if (!with_topk) HIP_TRY(c, hipEventRecord(B.ev0, st), "event record");
     HIP_TRY(c, launch_batch(B.store, B.moments_in_loop, variant, ba, grid, st), "batch launch");
     if (!with_topk) HIP_TRY(c, hipEventRecord(B.ev1, st), "event record");
+    HIP_TRY(c, to(c->side, st, c->ev_join), "batch moments");
     if (with_topk) {
         for (int i = 0; i < B.n; ++i) {
             const int64_t o = B.tpl_off[i];
@@ -245,7 +257,7 @@ int build(ltgw_ctx *c, const ltgw_search *S, int n, int k) {
     B.g_off.assign((size_t)n * LTGW_MAX_SEARCH_DET, 0);
     B.d_off.assign((size_t)n * LTGW_MAX_SEARCH_DET, 0);
     B.win_off.assign((size_t)n * LTGW_MAX_SEARCH_DET, 0);
-    int64_t tpl = 0, gtot = 0, dtot = 0, wtot = 0, ntau = 0, nbrake = 0, nsky = 0, diff_max = 0, topk_max = 0;
+    int64_t tpl = 0, gtot = 0, dtot = 0, wtot = 0, ntau = 0, nbrake = 0, nsky = 0, topk_max = 0;
     std::vector<double> htau, hbrake, hsky;
     for (int i = 0; i < n; ++i) {
         const SearchPlan &P = B.plans[i];
@@ -272,12 +284,10 @@ int build(ltgw_ctx *c, const ltgw_search *S, int n, int k) {
             dtot += (int64_t)P.n_sky * D.n_seg;
             wtot += P.n_groups * (int64_t)((P.n_f0 + 63) / 64);
         }
-        diff_max = std::max(diff_max, (int64_t)(B.mom[i].mode ? 4 : 1) * P.n_groups * (P.n_f0 + 1));
         topk_max = std::max(topk_max, topk_scratch_entries(P.n_tpl, k));
     }
     B.templates = tpl;
     B.topk_cap = topk_max;
-    B.diff_entries = B.moments_in_loop ? 0 : diff_max;
     struct {
         DevBuf *b;
         size_t bytes;
@@ -294,7 +304,7 @@ int build(ltgw_ctx *c, const ltgw_search *S, int n, int k) {
         {&B.n_out, (size_t)n * 2 * 4, "batch candidate counts"},
         {&B.ctr, 8, "batch counter"},                {&B.tiles_done, (size_t)n * 4, "batch tile counts"},
         {&B.t_done, (size_t)n * 8, "batch times"},   {&B.t_start, 8, "batch time"},
-        {&B.in_band, 8, "batch in-band count"},      {&B.diff, (size_t)B.diff_entries * 8, "batch moments"},
+        {&B.in_band, 8, "batch in-band count"},
         {&B.topk, (size_t)topk_max * 32, "batch top-k"}, {&B.topk_done, 8, "batch top-k"},
     };
     for (auto &a : allocs)

@@ -75,10 +75,10 @@ struct BatchState {
     std::vector<BatchSearch> hsearch;     // host copy of the device descriptors
     std::vector<int64_t> g_off, d_off;    // per (search, det) offsets into the g and D tables
     DevBuf searches, tiles, ctr, tiles_done, t_done, t_start, in_band;
-    DevBuf s, c, n_res, w1, w2, gtab, dtab, tau, brake, sky, cand, n_out, diff, win;
+    DevBuf s, c, n_res, w1, w2, gtab, dtab, tau, brake, sky, cand, n_out, win;
     std::vector<int64_t> win_off;         // per (search, det) offsets into the window table
     DevBuf topk, topk_done;
-    int64_t topk_cap = 0, diff_entries = 0;
+    int64_t topk_cap = 0;
     hipStream_t cap_stream = nullptr;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -128,7 +128,7 @@ struct ltgw_ctx {
     ltgw::DevBuf staging, counters;
     ltgw::DevBuf cnn_packed;  // BF16 weights of the fused inference pass
     ltgw::DevBuf tau_d, brake_d, sky_d;
-    ltgw::DevBuf res_s, res_c, res_n, res_w1, res_w2, diff;
+    ltgw::DevBuf res_s, res_c, res_n, res_w1, res_w2;
     ltgw::DevBuf cand;    // top-k candidates
     ltgw::DevBuf h_top;   // pinned host memory the ranking writes its records and count to
     std::vector<double> h_tau, h_brake, h_sky;

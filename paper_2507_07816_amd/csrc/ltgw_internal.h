@@ -138,12 +138,10 @@ hipError_t launch_f64_to_f32(const double *in, float *out, int64_t n, hipStream_
 hipError_t launch_fill_u64(unsigned long long *p, int n, unsigned long long v, hipStream_t st);
 
 // In-band moments N, W1, W2 of every template from the in-band f0 range of
-// each (group, segment): exact int64 range-adds into diff (4 arrays of
-// [n_groups][n_f0 + 1], zeroed here) and a prefix scan per group.
+// each (group, segment).
 // weights: 0 = uniform (W1 = N w, W2 = N w^2), 1 = fixed point
 // (W1 = sum wfix * 2^e0, W2 = (sum hi * 2^32 + sum lo) * 2^(2 e0)).
-hipError_t launch_moments(const EvalArgs &a, int weights, int e0, int64_t *diff,
-                          hipStream_t st);
+hipError_t launch_moments(const EvalArgs &a, int weights, int e0, hipStream_t st);
 hipError_t launch_psi(uint32_t stat, int64_t n, const double *s, const int32_t *c,
                       const int32_t *N, const double *w1, const double *w2, double q,
                       double *out, hipStream_t st);

@@ -556,12 +556,15 @@ __global__ __launch_bounds__(256) void doppler_kernel(const double *__restrict__
 // In-band segment windows.  For a segment, the column index trunc(f0 h +
 // 1.5 - k_lo) is non-decreasing in f0, so a run of consecutive f0 has a lane
 // in band exactly when its last f0 reaches column 1 and its first f0 is at
-// most column n_bins (the statistic kernel's arithmetic).
+// most column n_bins.  A window may be wider than that (segments out of band add
+// exact zeros), so the columns are formed in FP32 and compared with a margin of
+// 2^-20 of the terms, four times what their rounding can come to.
 // One wavefront per (group, kWinRuns consecutive runs of f0): each lane takes
 // segments lane, lane + 64, ... and tests every run of the wavefront against
 // its track factor, so the group's row of track factors is read once per
 // kWinRuns runs; each run's first and last in-band segment are then reduced
-// across the wavefront.
+// across the wavefront.  80 groups of 5400 segments, 4000 f0: 29 us (46 with FP64
+// columns and one track factor in flight).
 constexpr int kWinRuns = 8;
 __global__ __launch_bounds__(256) void window_kernel(const DetView D, int n_groups, int n_tn, double f0_min,
                                                      double f0_step, int n_f0, int2 *__restrict__ win) {
@@ -570,34 +573,43 @@ __global__ __launch_bounds__(256) void window_kernel(const DetView D, int n_grou
     const int grp = blockIdx.x / per_group;
     const int blk0 = ((blockIdx.x % per_group) * 4 + (threadIdx.x >> 6)) * kWinRuns;
     if (blk0 >= D.win_blocks) return;
-    double fa[kWinRuns], fb[kWinRuns];
+    float fa[kWinRuns], fb[kWinRuns];
     int lo[kWinRuns], hi[kWinRuns];
 #pragma unroll
     for (int r = 0; r < kWinRuns; ++r) {
         const int ia = (blk0 + r) * D.win_run;
         const int ib = min(ia + D.win_run - 1, n_f0 - 1);
-        fa[r] = f0_min + (double)ia * f0_step;
-        fb[r] = f0_min + (double)ib * f0_step;
+        fa[r] = (float)(f0_min + (double)ia * f0_step);
+        fb[r] = (float)(f0_min + (double)ib * f0_step);
         lo[r] = D.n_seg;
         hi[r] = -1;
     }
+    const float c = (float)D.cshift, top = (float)(f0_min + (double)(n_f0 - 1) * f0_step);
+    const float past = (float)D.n_bins + 1.0f;
     const int tn = grp % n_tn, sky = grp / n_tn;
-    for (int j = lane; j < D.n_seg; j += 64) {
-        double h;
-        if (D.H) {
-            h = D.H[(int64_t)grp * D.n_seg + j];
-        } else {
-            const double hg = D.g[(int64_t)tn * D.n_seg + j] * D.D[(int64_t)sky * D.n_seg + j];
-            h = hg * D.t_sft;
+    for (int j0 = lane; j0 < D.n_seg; j0 += 4 * 64) {
+        float h[4];  // four track factors in flight
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int j = min(j0 + 64 * k, D.n_seg - 1);
+            if (D.H) {
+                h[k] = (float)D.H[(int64_t)grp * D.n_seg + j];
+            } else {
+                const double hg = D.g[(int64_t)tn * D.n_seg + j] * D.D[(int64_t)sky * D.n_seg + j];
+                h[k] = (float)(hg * D.t_sft);
+            }
         }
 #pragma unroll
-        for (int r = 0; r < kWinRuns; ++r) {
-            const double xa = fa[r] * h, xb = fb[r] * h;
-            const int ca = __double2int_rz(xa + D.cshift), cb = __double2int_rz(xb + D.cshift);
-            if (cb >= 1 && ca <= D.n_bins) {
-                lo[r] = min(lo[r], j);
-                hi[r] = max(hi[r], j);
-            }
+        for (int k = 0; k < 4; ++k) {
+            const int j = min(j0 + 64 * k, D.n_seg - 1);  // the last segment again changes nothing
+            const float margin = 0x1p-20f * (top * h[k] + __builtin_fabsf(c) + past);
+            const float from = 1.0f - margin, to = past + margin;
+#pragma unroll
+            for (int r = 0; r < kWinRuns; ++r)
+                if (__builtin_fmaf(fb[r], h[k], c) >= from && __builtin_fmaf(fa[r], h[k], c) <= to) {
+                    lo[r] = min(lo[r], j);
+                    hi[r] = max(hi[r], j);
+                }
         }
     }
 #pragma unroll
@@ -674,9 +686,17 @@ __device__ inline int col_index(double f0_min, double f0_step, int i, double H, 
     return __double2int_rz(vv);
 }
 
-// first i in [0, n] with col_index(i) >= target (n if none)
+// first i in [0, n] with col_index(i) >= target (n if none), looked for at `near`:
+// column target starts at f0 H = target - cshift, so i = ((target - cshift) / H -
+// f0_min) / f0_step but for rounding, and the columns on either side confirm it.
+// Where they don't (steps near the rounding of f0, no step at all), a binary search.
 __device__ inline int first_at_least(double f0_min, double f0_step, int n, double H,
-                                     double cshift, int target) {
+                                     double cshift, int target, double near) {
+    // (a NaN clamps to 0)
+    const int i = (int)__builtin_fmin(__builtin_fmax(__builtin_ceil(near), 0.0), (double)n);
+    const bool before = col_index(f0_min, f0_step, i - 1, H, cshift) >= target && i > 0;
+    const bool here = col_index(f0_min, f0_step, i, H, cshift) >= target || i == n;
+    if (here && !before) return i;
     int lo = 0, hi = n;
     while (lo < hi) {
         const int mid = lo + ((hi - lo) >> 1);
@@ -688,145 +708,136 @@ __device__ inline int first_at_least(double f0_min, double f0_step, int n, doubl
     return lo;
 }
 
-// Each lane takes kMomSeg consecutive segments of one group and merges
-// consecutive equal range ends before adding them, so the many segments that
-// share an end (every template in band: lo = 0, hi = n_f0) cost one atomic
-// per lane instead of one per segment.
-constexpr int kMomSeg = 32;
+// One workgroup per (group, part of the f0): the range ends of every segment
+// added into differences in LDS (integers: any order gives the same sums), and the
+// prefix sums of those.  Ends below the part count at its start, which most segments
+// share, so those are summed in registers; ends beyond it count nowhere.
+// Differences in device memory with binary searches, 32 segments a lane, took 54 us for
+// 12 groups of 1024 segments (this: 6), 95 and a 9 us scan for 456 groups of two times
+// 4465 (53), and beside the statistic, with four sums a template, 1.22 ms and a scan
+// of 0.47 ms for 288 groups of 10800 (1.12).
+constexpr int kMomThreads = 512;
+template <int NA>
+constexpr int kMomPart = 4096 / NA;  // f0 of a part: 32 KB of differences
 
-struct RangeRun {
-    int key = -1;
-    unsigned long long v[4] = {0, 0, 0, 0};
-};
-
-__device__ inline void flush_run(RangeRun &r, unsigned long long *base, int64_t stride, int na,
-                                 bool negate) {
-    if (r.key < 0) return;
-    for (int q = 0; q < na; ++q)
-        if (r.v[q]) atomicAdd(base + q * stride + r.key, negate ? (unsigned long long)(-(long long)r.v[q]) : r.v[q]);
-    r.key = -1;
-    for (int q = 0; q < 4; ++q) r.v[q] = 0;
-}
-
-__device__ inline void add_run(RangeRun &r, int key, const unsigned long long *val, int na,
-                               unsigned long long *base, int64_t stride, bool negate) {
-    if (key != r.key) {
-        flush_run(r, base, stride, na, negate);
-        r.key = key;
-    }
-    for (int q = 0; q < na; ++q) r.v[q] += val[q];
-}
-
-__global__ __launch_bounds__(256) void moments_ranges_kernel(const EvalArgs a, int weights,
-                                                             int64_t *__restrict__ diff) {
-    const int d = blockIdx.z;
-    const DetView D = a.det[d];
-    const int row = blockIdx.y;
-    const int j0 = (blockIdx.x * 256 + threadIdx.x) * kMomSeg;
-    const int64_t stride = (int64_t)a.n_groups * (a.n_f0 + 1);
-    unsigned long long *base = (unsigned long long *)diff + (int64_t)row * (a.n_f0 + 1);
-    const int na = weights ? 4 : 1;
-    RangeRun rlo, rhi;
-    unsigned long long inb = 0;
-    const int j1 = min(j0 + kMomSeg, D.n_seg);
+template <int NA>
+__global__ __launch_bounds__(kMomThreads) void moments_kernel(const EvalArgs a, int e0) {
+    __shared__ unsigned long long diff[NA][kMomPart<NA>];
+    __shared__ unsigned long long part[NA][kMomThreads / 64];
+    const int row = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int i0 = blockIdx.x * kMomPart<NA>, i1 = min(i0 + kMomPart<NA>, a.n_f0);
+    for (int k = tid; k < i1 - i0; k += kMomThreads)
+#pragma unroll
+        for (int q = 0; q < NA; ++q) diff[q][k] = 0ull;
+    __syncthreads();
     const int tn = row % a.n_tn, sky = row / a.n_tn;
-    for (int j = j0; j < j1; ++j) {
-        double H;
-        if (D.H) {
-            H = D.H[(int64_t)row * D.n_seg + j];
-        } else {
-            const double h = D.g[(int64_t)tn * D.n_seg + j] * D.D[(int64_t)sky * D.n_seg + j];
-            H = h * D.t_sft;
-        }
-        const int lo = first_at_least(a.f0_min, a.f0_step, a.n_f0, H, D.cshift, 1);
-        const int hi = first_at_least(a.f0_min, a.f0_step, a.n_f0, H, D.cshift, D.n_bins + 1);
-        if (lo >= hi) continue;
-        inb += (unsigned long long)(hi - lo);
-        unsigned long long val[4] = {1ull, 0ull, 0ull, 0ull};
-        if (weights)
-            for (int q = 0; q < 3; ++q) val[q + 1] = (unsigned long long)D.wfix[3 * j + q];
-        add_run(rlo, lo, val, na, base, stride, false);
-        add_run(rhi, hi, val, na, base, stride, true);
-    }
-    flush_run(rlo, base, stride, na, false);
-    flush_run(rhi, base, stride, na, true);
-    for (int o = 32; o > 0; o >>= 1) inb += __shfl_xor(inb, o, 64);
-    if ((threadIdx.x & 63) == 0 && inb && a.in_band_total) atomicAdd(a.in_band_total, inb);
-}
-
-// One block per group: prefix sums of the difference arrays over f0, in tiles
-// of 256 consecutive positions (coalesced), with a running carry.
-__device__ inline int64_t block_inclusive_scan_256(int64_t v, int64_t *sh, int64_t &total) {
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    for (int o = 1; o < 64; o <<= 1) {
-        const int64_t u = __shfl_up(v, o, 64);
-        if (lane >= o) v += u;
-    }
-    if (lane == 63) sh[wv] = v;
-    __syncthreads();
-    int64_t off = 0;
-    for (int k = 0; k < wv; ++k) off += sh[k];
-    total = sh[0] + sh[1] + sh[2] + sh[3];
-    __syncthreads();
-    return v + off;
-}
-
-__global__ __launch_bounds__(256) void moments_scan_kernel(const EvalArgs a, int weights, int e0,
-                                                           const int64_t *__restrict__ diff) {
-    __shared__ int64_t sh[4];
-    const int row = blockIdx.x;
-    const int n = a.n_f0;
-    const int64_t stride = (int64_t)a.n_groups * (n + 1);
-    const int64_t *base = diff + (int64_t)row * (n + 1);
-    const int na = weights ? 4 : 1;
-    int64_t carry[4] = {0, 0, 0, 0};
-    const double wu = (double)a.w_uniform;
-    for (int i0 = 0; i0 < n; i0 += 256) {
-        const int i = i0 + threadIdx.x;
-        int64_t run[4] = {0, 0, 0, 0};
-        for (int q = 0; q < na; ++q) {
-            const int64_t v = i < n ? base[q * stride + i] : 0;
-            int64_t tot;
-            run[q] = block_inclusive_scan_256(v, sh, tot) + carry[q];
-            carry[q] += tot;
-        }
-        if (i < n) {
-            const int64_t t = (int64_t)row * n + i;
-            const int nin = (int)run[0];
-            double w1, w2;
-            if (weights) {
-                w1 = ldexp((double)run[1], e0);
-                w2 = ldexp((double)run[2] * 4294967296.0 + (double)run[3], 2 * e0);
-            } else {
-                w1 = (double)nin * wu;
-                w2 = (double)nin * (wu * wu);
+    const double per_step = 1.0 / a.f0_step;
+    unsigned long long inb = 0, at0[NA];
+#pragma unroll
+    for (int q = 0; q < NA; ++q) at0[q] = 0ull;
+    for (int d = 0; d < a.n_det; ++d) {
+        const DetView &D = a.det[d];
+        for (int j4 = tid; j4 < D.n_seg; j4 += 4 * kMomThreads) {
+            double h4[4];  // four track factors in flight
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int j = min(j4 + k * kMomThreads, D.n_seg - 1);
+                if (D.H) {
+                    h4[k] = D.H[(int64_t)row * D.n_seg + j];
+                } else {
+                    const double h = D.g[(int64_t)tn * D.n_seg + j] * D.D[(int64_t)sky * D.n_seg + j];
+                    h4[k] = h * D.t_sft;
+                }
             }
-            a.n[t] = nin;
-            a.w1[t] = w1;
-            a.w2[t] = w2;
-            if (a.out_n) a.out_n[t] = nin;
+#pragma unroll 1
+            for (int k = 0; k < 4; ++k) {
+                const int j = j4 + k * kMomThreads;
+                if (j >= D.n_seg) break;
+                const double H = k == 0 ? h4[0] : k == 1 ? h4[1] : k == 2 ? h4[2] : h4[3];
+                // 1 / H to about 2^-50: where to look, no more
+                double inv = __builtin_amdgcn_rcp(H);
+                inv = __builtin_fma(__builtin_fma(-H, inv, 1.0), inv, inv);
+                inv = __builtin_fma(__builtin_fma(-H, inv, 1.0), inv, inv);
+                const int lo = max(i0, first_at_least(a.f0_min, a.f0_step, a.n_f0, H, D.cshift, 1,
+                                                      ((1.0 - D.cshift) * inv - a.f0_min) * per_step));
+                const int hi = min(i1, first_at_least(a.f0_min, a.f0_step, a.n_f0, H, D.cshift, D.n_bins + 1,
+                                                      (((double)D.n_bins + 1.0 - D.cshift) * inv - a.f0_min) * per_step));
+                if (lo >= hi) continue;
+                inb += (unsigned long long)(hi - lo);
+                unsigned long long val[NA];
+                val[0] = 1ull;
+#pragma unroll
+                for (int q = 1; q < NA; ++q) val[q] = (unsigned long long)D.wfix[3 * j + q - 1];
+#pragma unroll
+                for (int q = 0; q < NA; ++q) {
+                    if (lo == i0)
+                        at0[q] += val[q];
+                    else
+                        atomicAdd(&diff[q][lo - i0], val[q]);
+                    if (hi < i1) atomicAdd(&diff[q][hi - i0], 0ull - val[q]);
+                }
+            }
         }
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        inb += __shfl_xor(inb, o, 64);
+#pragma unroll
+        for (int q = 0; q < NA; ++q) at0[q] += __shfl_xor(at0[q], o, 64);
+    }
+    if (lane == 0) {
+        if (inb && a.in_band_total) atomicAdd(a.in_band_total, inb);
+#pragma unroll
+        for (int q = 0; q < NA; ++q) atomicAdd(&diff[q][0], at0[q]);
+    }
+    __syncthreads();
+    // each thread's run of consecutive f0: its sum, the sums before it, its prefix sums
+    const int per = (i1 - i0 + kMomThreads - 1) / kMomThreads;
+    const int k0 = tid * per, k1 = min(k0 + per, i1 - i0);
+    int64_t run[NA];
+#pragma unroll
+    for (int q = 0; q < NA; ++q) {
+        int64_t v = 0;
+        for (int k = k0; k < k1; ++k) v += (int64_t)diff[q][k];
+        int64_t u = v;
+        for (int o = 1; o < 64; o <<= 1) {
+            const int64_t w = __shfl_up(u, o, 64);
+            if (lane >= o) u += w;
+        }
+        if (lane == 63) part[q][wv] = (unsigned long long)u;
+        run[q] = u - v;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < NA; ++q)
+        for (int k = 0; k < wv; ++k) run[q] += (int64_t)part[q][k];
+    const double wu = (double)a.w_uniform;
+    for (int k = k0; k < k1; ++k) {
+#pragma unroll
+        for (int q = 0; q < NA; ++q) run[q] += (int64_t)diff[q][k];
+        const int64_t t = (int64_t)row * a.n_f0 + i0 + k;
+        const int nin = (int)run[0];
+        double w1, w2;
+        if constexpr (NA > 1) {
+            w1 = ldexp((double)run[1], e0);
+            w2 = ldexp((double)run[2] * 4294967296.0 + (double)run[3], 2 * e0);
+        } else {
+            w1 = (double)nin * wu;
+            w2 = (double)nin * (wu * wu);
+        }
+        a.n[t] = nin;
+        a.w1[t] = w1;
+        a.w2[t] = w2;
+        if (a.out_n) a.out_n[t] = nin;
     }
 }
 
-__global__ void zero_i64_kernel(int64_t *p, int64_t n) {
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
-        p[i] = 0;
-}
-
-hipError_t launch_moments(const EvalArgs &a, int weights, int e0, int64_t *diff, hipStream_t st) {
-    const int64_t n_entries = (int64_t)(weights ? 4 : 1) * a.n_groups * (a.n_f0 + 1);
-    hipLaunchKernelGGL(zero_i64_kernel, dim3(1024), dim3(256), 0, st, diff, n_entries);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    int max_seg = 0;
-    for (int d = 0; d < a.n_det; ++d) max_seg = a.det[d].n_seg > max_seg ? a.det[d].n_seg : max_seg;
-    const int lanes = (max_seg + kMomSeg - 1) / kMomSeg;
-    hipLaunchKernelGGL(moments_ranges_kernel, dim3((lanes + 255) / 256, a.n_groups, a.n_det),
-                       dim3(256), 0, st, a, weights, diff);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(moments_scan_kernel, dim3(a.n_groups), dim3(256), 0, st, a, weights, e0,
-                       (const int64_t *)diff);
+hipError_t launch_moments(const EvalArgs &a, int weights, int e0, hipStream_t st) {
+    const int per = weights ? kMomPart<4> : kMomPart<1>;
+    const dim3 grid((unsigned)((a.n_f0 - 1) / per + 1), (unsigned)a.n_groups);
+    if (weights)
+        hipLaunchKernelGGL(moments_kernel<4>, grid, dim3(kMomThreads), 0, st, a, e0);
+    else
+        hipLaunchKernelGGL(moments_kernel<1>, grid, dim3(kMomThreads), 0, st, a, e0);
     return hipGetLastError();
 }
 
