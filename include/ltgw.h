@@ -415,7 +415,11 @@ int32_t ltgw_batch_latency(ltgw_ctx *ctx, double *out_ms);
  * (the workgroups of a generation walk the segments together and share the
  * spectrogram rows in L2) and bit 8 = one search detector's segments walked
  * in slabs of 1024, one launch per slab (results bit-identical to one pass).
- * Variants 0..15.  A batch uses shape (value & 3): its persistent launch is
+ * Variants 0..15.  A lattice whose templates are few for the device, or span few
+ * columns, goes to a kernel of its own instead (workgroups that share the
+ * segments, the same bits) unless ltgw_set_tile_shape asks for a shape; the
+ * diagnostics then name the shape it would have had.
+ * A batch uses shape (value & 3): its persistent launch is
  * one generation already.
  * Keys describe the work (single search or batch, store, moment mode and
  * size classes); values are the fastest variant measured on this device.

@@ -874,6 +874,8 @@ int eval_single(ltgw_ctx *c, const ltgw_grid *g, uint32_t stats, float *out_s, i
         HIP_TRY(c, je, "event record");
     }
     if (variant < 0) variant = c->forced_variant;
+    // a shape asked for is the shape used; else the split kernel goes before a tuned one
+    const int split = variant < 0 ? eval_split_waves(P.store, moments_in_loop, a, c->cu_count) : 0;
     if (variant < 0) {
         char key[160];
         tune_key_eval(P, moments_in_loop, key);
@@ -883,7 +885,12 @@ int eval_single(ltgw_ctx *c, const ltgw_grid *g, uint32_t stats, float *out_s, i
     HIP_TRY(c, hipEventRecord(c->ev_h2d, c->stream), "event record");
     HIP_TRY(c, hipEventRecord(c->ev[1], c->stream), "event record");
     int launches = 0;
-    HIP_TRY(c, launch_eval(P.store, moments_in_loop, variant, a, c->cu_count, c->stream, &launches), "eval launch");
+    if (split) {
+        HIP_TRY(c, launch_eval_split(P.store, moments_in_loop, split, a, c->stream), "eval launch");
+        launches = 1;
+    } else {
+        HIP_TRY(c, launch_eval(P.store, moments_in_loop, variant, a, c->cu_count, c->stream, &launches), "eval launch");
+    }
     c->last_launches = launches;
     HIP_TRY(c, hipEventRecord(c->ev[2], c->stream), "event record");
     c->have_eval = true;

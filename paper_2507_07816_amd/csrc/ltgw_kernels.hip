@@ -350,6 +350,116 @@ __global__ __launch_bounds__(256) void eval_kernel(const EvalArgs a, int first, 
                                 last ? a.in_band_total : nullptr);
 }
 
+// The same with the segments shared: 64 templates per workgroup, its wavefronts a chunk
+// of segments each, and the first wavefront adds the chunk sums in their order, so the
+// bits are the same.  A lane of eval_kernel walks all its segments alone: with few
+// templates most of the chip is idle, with more the longest walks are what a launch
+// waits for (12 x 400 templates over 1024 segments: 58 us there, 10 here).
+template <int STORE, bool MOMENTS, int kSplitWaves>
+__global__ __launch_bounds__(64 * kSplitWaves) void eval_split_kernel(const EvalArgs a) {
+    constexpr int kSums = MOMENTS ? 3 : 1, kCounts = MOMENTS ? 2 : 1;
+    __shared__ float part[2][kSums][kSplitWaves][64];
+    __shared__ int count[kCounts][kSplitWaves][64];
+    const int n_tiles = (a.n_f0 + 63) / 64;
+    const int tile = (int)blockIdx.x % n_tiles, grp = (int)blockIdx.x / n_tiles;
+    const int lane = (int)threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int i[1] = {tile * 64 + lane};
+    const double f0[1] = {a.f0_min + (double)i[0] * a.f0_step};
+    Acc<1> acc;  // counts of this wavefront's chunks; sums of all (first wavefront)
+    acc.zero();
+    int b = 0;
+    for (int d = 0; d < a.n_det; ++d) {
+        DetView D = a.det[d];
+        if (D.w_sky_stride) {  // antenna-pattern weights: the row of this group's sky point
+            const int64_t off = (int64_t)(grp / a.n_tn) * D.w_sky_stride;
+            D.wq += off;
+            D.w += off;
+        }
+        const HTable hs{D.H + (int64_t)grp * D.n_seg};
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+            (void *)D.store, Store<STORE>::kBytes, D.n_bins + 2, kBufDword3);
+        int jb, jn;
+        const int run = D.win ? tile * 64 / D.win_run : 0;
+        seg_window(D, grp, run, run + 1, jb, jn);
+        const int chunks = (jn + kChunk - 1) / kChunk;
+        for (int c0 = jb / kChunk; c0 < chunks; c0 += kSplitWaves, b ^= 1) {
+            int j = (c0 + wv) * kChunk;
+            const int je = min(j + kChunk, jn);
+            float sc[1] = {0.0f}, w1c[1] = {0.0f}, w2c[1] = {0.0f};
+#pragma unroll 1
+            for (; j + 16 <= je; j += 16)
+                seg_batch<STORE, MOMENTS, 1, 16>(D, rs, hs, j, f0, sc, w1c, w2c, acc);
+#pragma unroll 1
+            for (; j < je; ++j) seg_batch<STORE, MOMENTS, 1, 1>(D, rs, hs, j, f0, sc, w1c, w2c, acc);
+            part[b][0][wv][lane] = sc[0];
+            if constexpr (MOMENTS) {
+                part[b][1][wv][lane] = w1c[0];
+                part[b][2][wv][lane] = w2c[0];
+            }
+            __syncthreads();  // the other buffer's sums were read before it
+            if (wv == 0)
+                for (int k = 0; k < min(kSplitWaves, chunks - c0); ++k) {
+                    acc.s[0] += (double)part[b][0][k][lane];
+                    if constexpr (MOMENTS) {
+                        acc.w1[0] += (double)part[b][1][k][lane];
+                        acc.w2[0] += (double)part[b][2][k][lane];
+                    }
+                }
+        }
+    }
+    count[0][wv][lane] = acc.cnt[0];
+    if constexpr (MOMENTS) count[1][wv][lane] = acc.nin[0];
+    __syncthreads();
+    if (wv != 0) return;
+    for (int k = 1; k < kSplitWaves; ++k) {
+        acc.cnt[0] += count[0][k][lane];
+        if constexpr (MOMENTS) acc.nin[0] += count[1][k][lane];
+    }
+    store_results<MOMENTS, 1>(acc, i, grp, a.n_f0, a.s, a.c, a.n, a.w1, a.w2, a.out_s, a.out_c, a.out_n,
+                              a.in_band_total);
+}
+
+// How many wavefronts share 64 templates, 0 for eval_kernel.  By n = (f0 / 64) x groups:
+// with n below two workgroups a CU 16 (n = 300 of 10000 FP32 segments: 70 us, 101 with
+// 8, 171 with 4, 529 in eval_kernel), then 8 (n = 756 of 3000 BF16: 50 us, 67 with 16,
+// 61 with 4, 160), then 4 (n = 5304 of 2 x 2699 BF16: 307 us; 603).  The workgroups in
+// flight walk different rows, so the more columns they cover the less their caches
+// serve: eval_kernel, whose order keeps an XCD on few columns, is level at n x bytes of
+// the lattice's columns in a row of 40 - 60 MB (8000 FP32 columns: 258 us against 264
+// at n = 1500, 818 against 499 at 4500; 4000 BF16: 305 against 355 at 5040, 593 against
+// 549 at 9072).  With moments in the loop the line is n x columns = 8 - 10 million
+// (4000 columns: 270 us against 277 at n = 2268, 470 against 385 at 5040).
+int eval_split_waves(int store, bool moments, const EvalArgs &a, int cu_count) {
+    const int64_t n = (int64_t)((a.n_f0 + 63) / 64) * a.n_groups;
+    const int bytes = store == LTGW_STORE_F32 ? 4 : store == LTGW_STORE_BF16 ? 2 : 1;
+    if (moments ? n * a.n_f0 > 8000000 : n * a.n_f0 * bytes > 40000000) return 0;
+    return n <= 2 * cu_count ? 16 : n <= 5 * cu_count ? 8 : 4;
+}
+
+template <int STORE, bool MOMENTS>
+static hipError_t launch_eval_split_m(int waves, const EvalArgs &a, hipStream_t st) {
+    const int64_t n = (int64_t)((a.n_f0 + 63) / 64) * a.n_groups;
+    if (n < 1 || n > 0x7fffffff) return hipErrorInvalidValue;
+    if (waves == 16)
+        hipLaunchKernelGGL((eval_split_kernel<STORE, MOMENTS, 16>), dim3((unsigned)n), dim3(64 * 16), 0, st, a);
+    else if (waves == 8)
+        hipLaunchKernelGGL((eval_split_kernel<STORE, MOMENTS, 8>), dim3((unsigned)n), dim3(64 * 8), 0, st, a);
+    else
+        hipLaunchKernelGGL((eval_split_kernel<STORE, MOMENTS, 4>), dim3((unsigned)n), dim3(64 * 4), 0, st, a);
+    return hipGetLastError();
+}
+
+template <int STORE>
+static hipError_t launch_eval_split_s(bool moments, int waves, const EvalArgs &a, hipStream_t st) {
+    return moments ? launch_eval_split_m<STORE, true>(waves, a, st) : launch_eval_split_m<STORE, false>(waves, a, st);
+}
+
+hipError_t launch_eval_split(int store, bool moments, int waves, const EvalArgs &a, hipStream_t st) {
+    if (store == LTGW_STORE_F32) return launch_eval_split_s<LTGW_STORE_F32>(moments, waves, a, st);
+    if (store == LTGW_STORE_BF16) return launch_eval_split_s<LTGW_STORE_BF16>(moments, waves, a, st);
+    return launch_eval_split_s<LTGW_STORE_FP8>(moments, waves, a, st);
+}
+
 // Tile shapes: (templates per lane, segments per gather batch).
 constexpr int kVariantTpl[kNumShapes] = {1, 1, 2, 2};
 

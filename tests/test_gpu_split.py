@@ -1,0 +1,54 @@
+"""The statistic with a workgroup's wavefronts sharing the segments: bit for bit what the
+forced tile shapes give, at the edges of its chunks (32 segments), of the 64 f0 of a
+workgroup, and for each number of wavefronts (16, 8, 4 by the size of the lattice), with
+and without antenna weights (moments in the loop), for one and two detectors."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+SKY = np.array([0.6, 0.0, 0.8])
+
+
+@pytest.mark.parametrize("ns,n_f0,n_tau,dets,store,antenna", [
+    (1, 1, 1, 1, "f32", False),
+    (31, 65, 2, 2, "bf16", False),
+    (33, 64, 2, 1, "fp8", True),
+    (513, 130, 3, 1, "f32", False),      # 16 wavefronts and one segment more than their chunks
+    (1100, 63, 2, 2, "f32", True),
+    (300, 180, 200, 1, "bf16", False),   # 600 workgroups: 8 wavefronts
+    (70, 180, 300, 1, "fp8", True),
+    (90, 130, 700, 2, "f32", False),     # 2100: 4 wavefronts
+    (90, 130, 700, 1, "bf16", True),
+])
+def test_split_equals_tile_shapes(ns, n_f0, n_tau, dets, store, antenna):
+    import torch
+    from paper_2507_07816_amd import ltgw
+
+    print(f"case: split {store} {dets} x {ns}, {n_f0} f0 x {n_tau}, antenna {antenna}", flush=True)
+    nb, k_lo, t_sft = 150, 1880, 4.0
+    r = np.random.default_rng(ns + n_f0)
+    ctx = ltgw.Context(0)
+    for d in range(dets):
+        t = np.arange(ns) * (3600.0 / max(ns, 60)) + 2.0 + d
+        v = r.normal(size=(ns, 3))
+        v = v / np.linalg.norm(v, axis=1, keepdims=True) * 3.0e4
+        ctx.load_spectrogram(d, torch.from_numpy(r.exponential(size=(ns, nb)).astype(np.float32)).cuda(), k_lo, t_sft, t,
+                             weights=r.uniform(0.5, 2.0, ns).astype(np.float32), store=store)
+        ctx.set_velocity_table(d, v)
+        if antenna:
+            a = np.array([[0.36, 0.48, 0.8], [-0.8, 0.6, 0.0]])
+            ctx.set_antenna(d, a, np.linspace(0.1, 2.0, ns))
+    g = dict(f0_min=(k_lo - 3) / t_sft, f0_step=0.25, n_f0=n_f0, tau=np.geomspace(3000.0, 60000.0, n_tau), brake=[5.0],
+             sky=[SKY], t0=0.0, det_mask=(1 << dets) - 1)
+    n = n_f0 * n_tau
+    out = []
+    for shape in (-1, 0, 3):
+        ctx.set_tile_shape(shape)
+        out.append([x.cpu().numpy() for x in ctx.eval_templates(**g)] +
+                   [ctx.psi(s, n).cpu().numpy() for s in ("power", "count")] + [ctx.diagnostics()["in_band"]])
+    ctx.close()
+    assert out[0][5] > 0 or n == 1  # the single template starts below the band
+    for o in out[1:]:
+        for x, y in zip(out[0], o):
+            assert np.array_equal(x, y, equal_nan=True)
