@@ -875,7 +875,7 @@ int eval_single(ltgw_ctx *c, const ltgw_grid *g, uint32_t stats, float *out_s, i
     }
     if (variant < 0) variant = c->forced_variant;
     // a shape asked for is the shape used; else the split kernel goes before a tuned one
-    const int split = variant < 0 ? eval_split_waves(P.store, moments_in_loop, a, c->cu_count) : 0;
+    const int split = variant < 0 ? eval_split_waves(P.store, a, c->cu_count) : 0;
     if (variant < 0) {
         char key[160];
         tune_key_eval(P, moments_in_loop, key);

@@ -382,10 +382,17 @@ __global__ __launch_bounds__(64 * kSplitWaves) void eval_split_kernel(const Eval
         const int run = D.win ? tile * 64 / D.win_run : 0;
         seg_window(D, grp, run, run + 1, jb, jn);
         const int chunks = (jn + kChunk - 1) / kChunk;
+        ChunkWeights cw;
         for (int c0 = jb / kChunk; c0 < chunks; c0 += kSplitWaves, b ^= 1) {
             int j = (c0 + wv) * kChunk;
             const int je = min(j + kChunk, jn);
             float sc[1] = {0.0f}, w1c[1] = {0.0f}, w2c[1] = {0.0f};
+            if (MOMENTS && je - j == kChunk && chunk_in_band<1>(D, hs, j, f0)) {
+                cw.get(D.w, c0 + wv, kSplitWaves, D.n_seg / kChunk, w1c[0], w2c[0]);
+                acc.nin[0] += kChunk;
+#pragma unroll 1
+                for (; j < je; j += 16) seg_batch<STORE, false, 1, 16>(D, rs, hs, j, f0, sc, w1c, w2c, acc);
+            }
 #pragma unroll 1
             for (; j + 16 <= je; j += 16)
                 seg_batch<STORE, MOMENTS, 1, 16>(D, rs, hs, j, f0, sc, w1c, w2c, acc);
@@ -427,12 +434,11 @@ __global__ __launch_bounds__(64 * kSplitWaves) void eval_split_kernel(const Eval
 // serve: eval_kernel, whose order keeps an XCD on few columns, is level at n x bytes of
 // the lattice's columns in a row of 40 - 60 MB (8000 FP32 columns: 258 us against 264
 // at n = 1500, 818 against 499 at 4500; 4000 BF16: 305 against 355 at 5040, 593 against
-// 549 at 9072).  With moments in the loop the line is n x columns = 8 - 10 million
-// (4000 columns: 270 us against 277 at n = 2268, 470 against 385 at 5040).
-int eval_split_waves(int store, bool moments, const EvalArgs &a, int cu_count) {
+// 549 at 9072; with moments in the loop 4000 FP8: 471 against 488 at 9072).
+int eval_split_waves(int store, const EvalArgs &a, int cu_count) {
     const int64_t n = (int64_t)((a.n_f0 + 63) / 64) * a.n_groups;
     const int bytes = store == LTGW_STORE_F32 ? 4 : store == LTGW_STORE_BF16 ? 2 : 1;
-    if (moments ? n * a.n_f0 > 8000000 : n * a.n_f0 * bytes > 40000000) return 0;
+    if (n * a.n_f0 * bytes > 40000000) return 0;
     return n <= 2 * cu_count ? 16 : n <= 5 * cu_count ? 8 : 4;
 }
 
