@@ -95,7 +95,7 @@ int tpl_of(int variant) { return variant_templates_per_block(variant) / 256; }
 
 // Tile list for a tile shape: searches largest first (segments per template);
 // within a search, f0 tile by f0 tile, and for each the (tau, n) groups with
-// their sky points innermost; a tile is one wavefront's 64 x TPL f0 of one
+// their sky points innermost; a tile is one workgroup's 64 x TPL f0 of one
 // (tau, n, sky) group.  The tracks of one f0 tile and (tau, n) differ across
 // the sky points only by their Doppler shifts (a bin or two), and start at
 // the same bins for every (tau, n): in this order the tiles in flight at any
@@ -127,7 +127,7 @@ int upload_tiles(ltgw_ctx *c, BatchState &B, int variant) {
     HIP_TRY(c, hipMemcpy(B.searches.p, B.hsearch.data(), B.hsearch.size() * sizeof(BatchSearch),
                          hipMemcpyHostToDevice),
             "search upload");
-    B.grid = (int)std::min<int64_t>((total + 3) / 4, (int64_t)c->cu_count *
+    B.grid = (int)std::min<int64_t>(total, (int64_t)c->cu_count *
                                                batch_blocks_per_cu(B.store, B.moments_in_loop, variant));
     if (B.grid < 1) B.grid = 1;
     return LTGW_OK;
@@ -180,7 +180,7 @@ int enqueue(ltgw_ctx *c, BatchState &B, hipStream_t st, int variant, bool with_t
     ba.counter = (unsigned *)B.ctr.p;
     ba.t_start = (unsigned long long *)B.t_start.p;
     ba.in_band_total = (unsigned long long *)B.in_band.p;
-    const int grid = std::min(B.grid, std::max((ba.n_tiles + 3) / 4, 1));  // 4 waves per workgroup
+    const int grid = std::min(B.grid, std::max(ba.n_tiles, 1));
     if (!with_topk) HIP_TRY(c, hipEventRecord(B.ev0, st), "event record");
     HIP_TRY(c, launch_batch(B.store, B.moments_in_loop, variant, ba, grid, st), "batch launch");
     if (!with_topk) HIP_TRY(c, hipEventRecord(B.ev1, st), "event record");

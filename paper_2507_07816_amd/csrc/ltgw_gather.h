@@ -309,6 +309,79 @@ __device__ __forceinline__ void accumulate_det(const DetView &D, const HS &hs,
     }
 }
 
+// Segments [jb, je) (whole chunks, but for the detector's last) shared by the W
+// wavefronts of a workgroup, a chunk each in turn: its counts stay with its wavefront,
+// its sums go to LDS and the first wavefront adds them in chunk order, so the sums are
+// those of accumulate_det bit for bit.  b: the LDS buffer to use next.
+template <bool MOMENTS, int TPL, int W>
+struct SharedSums {
+    float s[2][MOMENTS ? 3 : 1][TPL][W][64];
+};
+
+template <int STORE, bool MOMENTS, int TPL, int U, int W, class HS>
+__device__ __forceinline__ void accumulate_shared(const DetView &D, const HS &hs, const double (&f0)[TPL], Acc<TPL> &acc,
+                                                  int jb, int je, int wv, SharedSums<MOMENTS, TPL, W> &part, int &b) {
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)D.store, Store<STORE>::kBytes, D.n_bins + 2, kBufDword3);
+    const int lane = (int)threadIdx.x & 63, chunks = (je + kChunk - 1) / kChunk;
+    ChunkWeights cw;
+    for (int c0 = jb / kChunk; c0 < chunks; c0 += W, b ^= 1) {
+        int j = (c0 + wv) * kChunk;
+        const int jc = min(j + kChunk, je);
+        float sc[TPL], w1c[TPL], w2c[TPL];
+        for (int t = 0; t < TPL; ++t) sc[t] = w1c[t] = w2c[t] = 0.0f;
+        if (MOMENTS && jc - j == kChunk && chunk_in_band<TPL>(D, hs, j, f0)) {
+            float u1, u2;
+            cw.get(D.w, c0 + wv, W, D.n_seg / kChunk, u1, u2);
+            for (int t = 0; t < TPL; ++t) {
+                w1c[t] = u1;
+                w2c[t] = u2;
+                acc.nin[t] += kChunk;
+            }
+#pragma unroll 1
+            for (; j < jc; j += U) seg_batch<STORE, false, TPL, U>(D, rs, hs, j, f0, sc, w1c, w2c, acc);
+        }
+#pragma unroll 1
+        for (; j + U <= jc; j += U) seg_batch<STORE, MOMENTS, TPL, U>(D, rs, hs, j, f0, sc, w1c, w2c, acc);
+#pragma unroll 1
+        for (; j < jc; ++j) seg_batch<STORE, MOMENTS, TPL, 1>(D, rs, hs, j, f0, sc, w1c, w2c, acc);
+        for (int t = 0; t < TPL; ++t) {
+            part.s[b][0][t][wv][lane] = sc[t];
+            if constexpr (MOMENTS) {
+                part.s[b][1][t][wv][lane] = w1c[t];
+                part.s[b][2][t][wv][lane] = w2c[t];
+            }
+        }
+        __syncthreads();  // the other buffer's sums were read before it
+        if (wv == 0)
+            for (int k = 0; k < min(W, chunks - c0); ++k)
+                for (int t = 0; t < TPL; ++t) {
+                    acc.s[t] += (double)part.s[b][0][t][k][lane];
+                    if constexpr (MOMENTS) {
+                        acc.w1[t] += (double)part.s[b][1][t][k][lane];
+                        acc.w2[t] += (double)part.s[b][2][t][k][lane];
+                    }
+                }
+    }
+}
+
+// The wavefronts' counts added up in the first one.
+template <bool MOMENTS, int TPL, int W>
+__device__ __forceinline__ void add_counts(Acc<TPL> &acc, int wv, int (&count)[MOMENTS ? 2 : 1][TPL][W][64]) {
+    const int lane = (int)threadIdx.x & 63;
+    for (int t = 0; t < TPL; ++t) {
+        count[0][t][wv][lane] = acc.cnt[t];
+        if constexpr (MOMENTS) count[1][t][wv][lane] = acc.nin[t];
+    }
+    __syncthreads();
+    if (wv == 0)
+        for (int k = 1; k < W; ++k)
+            for (int t = 0; t < TPL; ++t) {
+                acc.cnt[t] += count[0][t][k][lane];
+                if constexpr (MOMENTS) acc.nin[t] += count[1][t][k][lane];
+            }
+}
+
 // Results of a lane's templates; template index grp*n_f0 + i.
 template <bool MOMENTS, int TPL>
 __device__ __forceinline__ void store_results(const Acc<TPL> &acc, const int (&i)[TPL], int grp,

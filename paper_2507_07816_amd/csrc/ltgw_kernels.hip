@@ -357,15 +357,14 @@ __global__ __launch_bounds__(256) void eval_kernel(const EvalArgs a, int first, 
 // waits for (12 x 400 templates over 1024 segments: 58 us there, 10 here).
 template <int STORE, bool MOMENTS, int kSplitWaves>
 __global__ __launch_bounds__(64 * kSplitWaves) void eval_split_kernel(const EvalArgs a) {
-    constexpr int kSums = MOMENTS ? 3 : 1, kCounts = MOMENTS ? 2 : 1;
-    __shared__ float part[2][kSums][kSplitWaves][64];
-    __shared__ int count[kCounts][kSplitWaves][64];
+    __shared__ SharedSums<MOMENTS, 1, kSplitWaves> part;
+    __shared__ int count[MOMENTS ? 2 : 1][1][kSplitWaves][64];
     const int n_tiles = (a.n_f0 + 63) / 64;
     const int tile = (int)blockIdx.x % n_tiles, grp = (int)blockIdx.x / n_tiles;
-    const int lane = (int)threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int i[1] = {tile * 64 + lane};
+    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int i[1] = {tile * 64 + ((int)threadIdx.x & 63)};
     const double f0[1] = {a.f0_min + (double)i[0] * a.f0_step};
-    Acc<1> acc;  // counts of this wavefront's chunks; sums of all (first wavefront)
+    Acc<1> acc;
     acc.zero();
     int b = 0;
     for (int d = 0; d < a.n_det; ++d) {
@@ -375,53 +374,14 @@ __global__ __launch_bounds__(64 * kSplitWaves) void eval_split_kernel(const Eval
             D.wq += off;
             D.w += off;
         }
-        const HTable hs{D.H + (int64_t)grp * D.n_seg};
-        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-            (void *)D.store, Store<STORE>::kBytes, D.n_bins + 2, kBufDword3);
-        int jb, jn;
+        int jb, je;
         const int run = D.win ? tile * 64 / D.win_run : 0;
-        seg_window(D, grp, run, run + 1, jb, jn);
-        const int chunks = (jn + kChunk - 1) / kChunk;
-        ChunkWeights cw;
-        for (int c0 = jb / kChunk; c0 < chunks; c0 += kSplitWaves, b ^= 1) {
-            int j = (c0 + wv) * kChunk;
-            const int je = min(j + kChunk, jn);
-            float sc[1] = {0.0f}, w1c[1] = {0.0f}, w2c[1] = {0.0f};
-            if (MOMENTS && je - j == kChunk && chunk_in_band<1>(D, hs, j, f0)) {
-                cw.get(D.w, c0 + wv, kSplitWaves, D.n_seg / kChunk, w1c[0], w2c[0]);
-                acc.nin[0] += kChunk;
-#pragma unroll 1
-                for (; j < je; j += 16) seg_batch<STORE, false, 1, 16>(D, rs, hs, j, f0, sc, w1c, w2c, acc);
-            }
-#pragma unroll 1
-            for (; j + 16 <= je; j += 16)
-                seg_batch<STORE, MOMENTS, 1, 16>(D, rs, hs, j, f0, sc, w1c, w2c, acc);
-#pragma unroll 1
-            for (; j < je; ++j) seg_batch<STORE, MOMENTS, 1, 1>(D, rs, hs, j, f0, sc, w1c, w2c, acc);
-            part[b][0][wv][lane] = sc[0];
-            if constexpr (MOMENTS) {
-                part[b][1][wv][lane] = w1c[0];
-                part[b][2][wv][lane] = w2c[0];
-            }
-            __syncthreads();  // the other buffer's sums were read before it
-            if (wv == 0)
-                for (int k = 0; k < min(kSplitWaves, chunks - c0); ++k) {
-                    acc.s[0] += (double)part[b][0][k][lane];
-                    if constexpr (MOMENTS) {
-                        acc.w1[0] += (double)part[b][1][k][lane];
-                        acc.w2[0] += (double)part[b][2][k][lane];
-                    }
-                }
-        }
+        seg_window(D, grp, run, run + 1, jb, je);
+        accumulate_shared<STORE, MOMENTS, 1, 16, kSplitWaves>(D, HTable{D.H + (int64_t)grp * D.n_seg}, f0, acc, jb, je, wv,
+                                                              part, b);
     }
-    count[0][wv][lane] = acc.cnt[0];
-    if constexpr (MOMENTS) count[1][wv][lane] = acc.nin[0];
-    __syncthreads();
+    add_counts<MOMENTS, 1, kSplitWaves>(acc, wv, count);
     if (wv != 0) return;
-    for (int k = 1; k < kSplitWaves; ++k) {
-        acc.cnt[0] += count[0][k][lane];
-        if constexpr (MOMENTS) acc.nin[0] += count[1][k][lane];
-    }
     store_results<MOMENTS, 1>(acc, i, grp, a.n_f0, a.s, a.c, a.n, a.w1, a.w2, a.out_s, a.out_c, a.out_n,
                               a.in_band_total);
 }
@@ -537,23 +497,28 @@ hipError_t launch_eval(int store, bool moments, int variant, const EvalArgs &a, 
 
 // ---------------------------------------------------------------------------
 // Many searches in one persistent launch.  Tiles (search, group, 64 x TPL
-// consecutive f0) are listed largest search first; every resident wavefront
+// consecutive f0) are listed largest search first; every resident workgroup
 // takes the next tile from an atomic counter until the list is exhausted (the
-// loop ends for every wave once the counter passes the tile count).  The wave
-// that finishes a search's last tile stamps the search's completion time.
+// loop ends for every workgroup once the counter passes the tile count), its
+// wavefronts sharing the tile's segments.  The workgroup that finishes a search's
+// last tile stamps the search's completion time.
+// 41000 tiles of 64 f0, 2.2e9 in-band evaluations: 1.02 ms with a tile per workgroup, 1.29
+// with one per wavefront (the last ones walked alone).  Counting the tiles through a
+// generic pointer, 64 flat atomics each on one address, had made it 17.0 ms.
 template <int STORE, bool MOMENTS, int TPL, int U>
 __global__ __launch_bounds__(256) void batch_kernel(const BatchArgs a) {
-    // Work is pulled per wavefront.  The loop body has no lane-divergent
-    // branch around the tile hand-out: every lane issues the atomic (lane 0
-    // adds 1, the others 0) and the wave takes lane 0's ticket as a scalar, so
-    // the compiler keeps one wave-uniform loop (a lane-0-only branch there let
-    // it split the loop, parking lane 0 while the other lanes re-read a stale
-    // ticket forever).  No barrier is used.
-    const int lane = threadIdx.x & 63;
+    constexpr int kWaves = 4;
+    __shared__ SharedSums<MOMENTS, TPL, kWaves> part;
+    __shared__ int count[MOMENTS ? 2 : 1][TPL][kWaves][64];
+    __shared__ int ticket;
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     if (threadIdx.x == 0 && a.t_start) atomicMin(a.t_start, (unsigned long long)wall_clock64());
+    int b = 0;
     for (;;) {
-        const unsigned ticket = atomicAdd(a.counter, lane == 0 ? 1u : 0u);
-        const int tt = __builtin_amdgcn_readfirstlane((int)ticket);
+        __syncthreads();  // the last tile's reads of LDS
+        if (threadIdx.x == 0) ticket = (int)atomicAdd(a.counter, 1u);
+        __syncthreads();
+        const int tt = __builtin_amdgcn_readfirstlane(ticket);
         if (tt >= a.n_tiles) break;
         // descriptors are read into scalar registers (uniform loop bounds, buffer
         // resources and table pointers)
@@ -576,25 +541,20 @@ __global__ __launch_bounds__(256) void batch_kernel(const BatchArgs a) {
             int jb, je;
             const int runs = D.win ? 64 * TPL / D.win_run : 1;  // the batch's windows are per 64 f0
             seg_window(D, T.grp, T.tile * runs, (T.tile + 1) * runs, jb, je);
-            accumulate_det<STORE, MOMENTS, TPL, U>(D, hs, f0, acc, jb, je);
+            accumulate_shared<STORE, MOMENTS, TPL, U, kWaves>(D, hs, f0, acc, jb, je, wv, part, b);
         }
+        add_counts<MOMENTS, TPL, kWaves>(acc, wv, count);
+        if (wv != 0) continue;
         store_results<MOMENTS, TPL>(acc, i, T.grp, n_f0, uniform(Sp->s), uniform(Sp->c), uniform(Sp->n),
                                     uniform(Sp->w1), uniform(Sp->w2), nullptr, nullptr, nullptr,
                                     a.in_band_total);
         // the tile's stores have left the wave before it counts as done; later kernels
         // of the stream read them, so no cache is written back here
         __builtin_amdgcn_s_waitcnt(0);
-        // through a global pointer: the wave's 64 additions become one.  Through a
-        // generic one every lane's is an atomic of its own, and 64 per tile on one
-        // address, one after the other, were the kernel's whole time: 17.0 ms for
-        // 20500 tiles of 128 f0 (2.2e9 in-band evaluations), now 1.29 ms.
-        typedef __attribute__((address_space(1))) unsigned GlobalCount;
-        GlobalCount *const tiles_done = (GlobalCount *)(uintptr_t)uniform(Sp->tiles_done);
-        unsigned long long *const t_done = uniform(Sp->t_done);
-        const unsigned done = (unsigned)__builtin_amdgcn_readfirstlane(
-                                  (int)__hip_atomic_fetch_add(tiles_done, lane == 0 ? 1u : 0u, __ATOMIC_RELAXED,
-                                                              __HIP_MEMORY_SCOPE_AGENT)) + 1u;
-        if (done == (unsigned)uniform(Sp->n_tiles) && t_done) *t_done = wall_clock64();  // same value, every lane
+        if (lane == 0) {
+            unsigned long long *const t_done = Sp->t_done;
+            if (atomicAdd(Sp->tiles_done, 1u) + 1u == (unsigned)Sp->n_tiles && t_done) *t_done = wall_clock64();
+        }
     }
 }
 
