@@ -1034,7 +1034,7 @@ int32_t ltgw_eval_list(ltgw_ctx *c, const ltgw_template *tpl, int64_t n, double 
         std::memcpy(V.arms.b, D.arms + 3, sizeof V.arms.b);
         n_seg_total += D.n_seg;
     }
-    // evaluation order (a stable counting sort into 2^16 buckets): cells of the
+    // evaluation order (a stable counting sort into up to 2^16 buckets): cells of the
     // track's total drop and of tau, f0 within a cell, so that the templates of a
     // wavefront follow neighbouring tracks and gather neighbouring columns at all
     // times; in f0 order alone (tracks that part within the first hours) each
@@ -1043,7 +1043,10 @@ int32_t ltgw_eval_list(ltgw_ctx *c, const ltgw_template *tpl, int64_t n, double 
     // the order changes none.
     const double waves_log2 = std::log2(std::max(1.0, (double)n / 64.0));
     const int drop_bits = std::min(5, (int)(0.36 * waves_log2)), tau_bits = std::min(3, (int)(0.22 * waves_log2));
-    const int f0_bits = 16 - drop_bits - tau_bits;
+    // as many buckets as templates or two times as many, 2^16 at most: 2^16 for a list
+    // of 4800 were most of the call's host time
+    const int bits = std::max(8, std::min(16, 1 + (int)std::log2((double)n)));
+    const int f0_bits = bits - drop_bits - tau_bits;
     auto scale_of = [](double lo, double hi, int bits) { return hi > lo ? ((1 << bits) - 1e-3) / (hi - lo) : 0.0; };
     const double drop_scale = scale_of(drop_lo, drop_hi, drop_bits), tau_scale = scale_of(tau_lo, tau_hi, tau_bits);
     // the staging is pinned (the uploads run at DMA rate) and reused: wait for
@@ -1056,7 +1059,7 @@ int32_t ltgw_eval_list(ltgw_ctx *c, const ltgw_template *tpl, int64_t n, double 
     // Each chunk counts its keys per bucket and copies itself into the
     // staging; a bucket's positions then go to the chunks in list order, so
     // the scatter below gives the serial stable order.
-    constexpr int kBuckets = 1 << 16;
+    const int kBuckets = 1 << bits;
     const double f0_scale = scale_of(f0_lo, f0_max, f0_bits);
     auto cell = [](double v, double lo, double scale, int bits) {
         return std::max(0, std::min((1 << bits) - 1, (int)((v - lo) * scale)));
@@ -1081,14 +1084,32 @@ int32_t ltgw_eval_list(ltgw_ctx *c, const ltgw_template *tpl, int64_t n, double 
     if ((rc = ensure(c, c->perm_d, (size_t)n * 4, "template order")) != LTGW_OK) return rc;
     if ((rc = h2d(c, c->list_d.p, c->h_list.p, (size_t)n * sizeof(ltgw_template), "template upload")) != LTGW_OK)
         return rc;
-    int32_t next = 0;
-    for (int b = 0; b < kBuckets; ++b)
-        for (int t = 0; t < nt; ++t) {
-            int32_t &p = pos[(size_t)t * kBuckets + b];
-            const int32_t m = p;
-            p = next;
-            next += m;
-        }
+    // positions: the totals of nt ranges of buckets, then each range's running sums (by
+    // one thread the counts of 16 chunks, 256 KB apart, took as long as all the rest)
+    std::vector<int32_t> before(nt, 0);
+    run_chunks(nt, [&](int r) {
+        const int lo = (int)chunk_lo(kBuckets, nt, r), hi = (int)chunk_lo(kBuckets, nt, r + 1);
+        int32_t sum = 0;
+        for (int t = 0; t < nt; ++t)
+            for (int b = lo; b < hi; ++b) sum += pos[(size_t)t * kBuckets + b];
+        before[r] = sum;
+    });
+    for (int r = 0, next = 0; r < nt; ++r) {
+        const int32_t m = before[r];
+        before[r] = next;
+        next += m;
+    }
+    run_chunks(nt, [&](int r) {
+        const int lo = (int)chunk_lo(kBuckets, nt, r), hi = (int)chunk_lo(kBuckets, nt, r + 1);
+        int32_t next = before[r];
+        for (int b = lo; b < hi; ++b)
+            for (int t = 0; t < nt; ++t) {
+                int32_t &p = pos[(size_t)t * kBuckets + b];
+                const int32_t m = p;
+                p = next;
+                next += m;
+            }
+    });
     int32_t *perm = (int32_t *)c->h_perm.p;
     run_chunks(nt, [&](int t) {
         int32_t *at = pos.data() + (size_t)t * kBuckets;
