@@ -48,7 +48,7 @@ KERNEL_SOURCES = ("paper_2507_07816_amd/csrc/ltgw_kernels.hip", "paper_2507_0781
 # the explicit-template kernel's code (its committed FP64 instruction count)
 LIST_SOURCES = ("paper_2507_07816_amd/csrc/ltgw_list.hip", "paper_2507_07816_amd/csrc/ltgw_list.h",
                 "paper_2507_07816_amd/csrc/ddpow.h", "paper_2507_07816_amd/csrc/pow_enclose.h",
-                "paper_2507_07816_amd/csrc/ltgw_gather.h",
+                "paper_2507_07816_amd/csrc/track_expand.h", "paper_2507_07816_amd/csrc/ltgw_gather.h",
                 "paper_2507_07816_amd/csrc/ltgw_antenna.h", "paper_2507_07816_amd/csrc/exp2_table.h",
                 "paper_2507_07816_amd/csrc/log_table.h")
 
