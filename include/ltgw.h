@@ -419,7 +419,8 @@ int32_t ltgw_batch_latency(ltgw_ctx *ctx, double *out_ms);
  * Variants 0..15.  A lattice whose templates are few for the device, or span few
  * columns, goes to a kernel of its own instead (workgroups that share the
  * segments, the same bits) unless ltgw_set_tile_shape asks for a shape; the
- * diagnostics then name the shape it would have had.
+ * diagnostics then name the shape it would have had.  Untuned, a lattice has shape 1,
+ * or 9 where it is long and large.
  * A batch uses shape (value & 3): its persistent launch is
  * one generation already.
  * Keys describe the work (single search or batch, store, moment mode and

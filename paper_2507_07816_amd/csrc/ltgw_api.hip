@@ -708,6 +708,18 @@ size_t eval_bytes(const ltgw_ctx *c, const SearchPlan &P, const Moments &M, cons
     return t;
 }
 
+// The shape of an untuned lattice: one template per lane and 16 segments per batch, for
+// a long search of one detector in slabs of segments, whose rows the caches hold for
+// all of a slab's workgroups: 8000 FP32 columns of 5000 segments, 36000 x 64 templates,
+// 2.94 ms against 4.53; 6000 of 10000, 27072 x 64, 4.13 against 5.99; BF16 2.71 against
+// 2.80.  Below about 20 workgroups of 64 templates a CU, or with few slabs, the launches
+// cost what they give (4536 x 64: 484 us against 472; 1500 segments, 9000 x 64: 311 against
+// 285).
+int default_shape(const EvalArgs &a, int split, int cu_count) {
+    const int64_t n = (int64_t)((a.n_f0 + 63) / 64) * a.n_groups;
+    return !split && a.n_det == 1 && a.det[0].n_seg >= 4096 && n >= (int64_t)20 * cu_count ? 9 : 1;
+}
+
 // The single-search evaluation; variant < 0 takes the tuned (or default)
 // shape.  scratch != NULL: every buffer is a slice of it (no allocation) and
 // the results are not kept for ltgw_psi / ltgw_topk_candidates.
@@ -880,7 +892,7 @@ int eval_single(ltgw_ctx *c, const ltgw_grid *g, uint32_t stats, float *out_s, i
         char key[160];
         tune_key_eval(P, moments_in_loop, key);
         const auto it = c->tune.find(key);
-        variant = it == c->tune.end() ? 1 : it->second;
+        variant = it == c->tune.end() ? default_shape(a, split, c->cu_count) : it->second;
     }
     HIP_TRY(c, hipEventRecord(c->ev_h2d, c->stream), "event record");
     HIP_TRY(c, hipEventRecord(c->ev[1], c->stream), "event record");

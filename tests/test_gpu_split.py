@@ -52,3 +52,31 @@ def test_split_equals_tile_shapes(ns, n_f0, n_tau, dets, store, antenna):
     for o in out[1:]:
         for x, y in zip(out[0], o):
             assert np.array_equal(x, y, equal_nan=True)
+
+
+def test_untuned_large_lattice_in_slabs():
+    """2000 f0 x 160 tau over 4100 segments, where an untuned lattice is walked in slabs
+    (four and a remainder): bit for bit the one-pass shape, which a forced 1 is."""
+    import torch
+    from paper_2507_07816_amd import ltgw
+
+    print("case: untuned 2000 x 160 over 4100 segments", flush=True)
+    ns, nb, k_lo, t_sft = 4100, 2100, 4000, 8.0
+    r = np.random.default_rng(9)
+    t = np.arange(ns) * 8.0 + 4.0
+    v = r.normal(size=(ns, 3))
+    v = v / np.linalg.norm(v, axis=1, keepdims=True) * 3.0e4
+    ctx = ltgw.Context(0)
+    ctx.load_spectrogram(0, torch.from_numpy(r.exponential(size=(ns, nb)).astype(np.float32)).cuda(), k_lo, t_sft, t)
+    ctx.set_velocity_table(0, v)
+    g = dict(f0_min=k_lo / t_sft, f0_step=1.0 / t_sft, n_f0=2000, tau=np.geomspace(20000.0, 90000.0, 160), brake=[5.0],
+             sky=[SKY], t0=0.0)
+    out = []
+    for shape in (-1, 1):
+        ctx.set_tile_shape(shape)
+        out.append([x.cpu().numpy() for x in ctx.eval_templates(**g)])
+        d = ctx.diagnostics()
+        assert (d["tile_shape"], d["eval_launches"]) == ((9, 5) if shape < 0 else (1, 1))
+    ctx.close()
+    for x, y in zip(*out):
+        assert np.array_equal(x, y)
