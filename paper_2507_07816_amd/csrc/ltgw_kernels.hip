@@ -502,7 +502,7 @@ hipError_t launch_eval(int store, bool moments, int variant, const EvalArgs &a, 
 // loop ends for every workgroup once the counter passes the tile count), its
 // wavefronts sharing the tile's segments.  The workgroup that finishes a search's
 // last tile stamps the search's completion time.
-// 41000 tiles of 64 f0, 2.2e9 in-band evaluations: 1.02 ms with a tile per workgroup, 1.29
+// 41000 tiles of 64 f0, 2.2e9 in-band evaluations: 1.07 ms with a tile per workgroup, 1.29
 // with one per wavefront (the last ones walked alone).  Counting the tiles through a
 // generic pointer, 64 flat atomics each on one address, had made it 17.0 ms.
 template <int STORE, bool MOMENTS, int TPL, int U>
@@ -514,9 +514,17 @@ __global__ __launch_bounds__(256) void batch_kernel(const BatchArgs a) {
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     if (threadIdx.x == 0 && a.t_start) atomicMin(a.t_start, (unsigned long long)wall_clock64());
     int b = 0;
+    // No lane-divergent branch stands around the hand-out or at the loop's end: the
+    // first wavefront's lanes all issue the atomic (lane 0 adds 1, the others 0; through
+    // a global pointer that is one atomic) and all write the ticket.  With a lane-0-only
+    // branch there the compiler once split the loop, parking lane 0 while the other
+    // lanes went round with a stale ticket.
     for (;;) {
         __syncthreads();  // the last tile's reads of LDS
-        if (threadIdx.x == 0) ticket = (int)atomicAdd(a.counter, 1u);
+        if (wv == 0) {
+            const unsigned t = atomicAdd(a.counter, lane == 0 ? 1u : 0u);
+            ticket = __builtin_amdgcn_readfirstlane((int)t);
+        }
         __syncthreads();
         const int tt = __builtin_amdgcn_readfirstlane(ticket);
         if (tt >= a.n_tiles) break;
@@ -551,10 +559,13 @@ __global__ __launch_bounds__(256) void batch_kernel(const BatchArgs a) {
         // the tile's stores have left the wave before it counts as done; later kernels
         // of the stream read them, so no cache is written back here
         __builtin_amdgcn_s_waitcnt(0);
-        if (lane == 0) {
-            unsigned long long *const t_done = Sp->t_done;
-            if (atomicAdd(Sp->tiles_done, 1u) + 1u == (unsigned)Sp->n_tiles && t_done) *t_done = wall_clock64();
-        }
+        typedef __attribute__((address_space(1))) unsigned GlobalCount;
+        GlobalCount *const tiles_done = (GlobalCount *)(uintptr_t)uniform(Sp->tiles_done);
+        unsigned long long *const t_done = uniform(Sp->t_done);
+        const unsigned done = (unsigned)__builtin_amdgcn_readfirstlane(
+                                  (int)__hip_atomic_fetch_add(tiles_done, lane == 0 ? 1u : 0u, __ATOMIC_RELAXED,
+                                                              __HIP_MEMORY_SCOPE_AGENT)) + 1u;
+        if (done == (unsigned)uniform(Sp->n_tiles) && t_done) *t_done = wall_clock64();  // same value, every lane
     }
 }
 
