@@ -21,6 +21,7 @@
 
 #include "ltgw_ctx.h"
 #include "ltgw_fft.h"
+#include "median_slide.h"
 
 #pragma clang fp contract(off)
 
@@ -173,7 +174,7 @@ __global__ __launch_bounds__(64) void normalise_kernel(const void *__restrict__ 
     __shared__ unsigned tree[N];
     // a rank r as its bit's place: (r / 32) << 8, the word's byte offset among the 64
     // lanes' words, and r % 32 (ordered like the ranks)
-    __shared__ unsigned short rank[N + 2], med[N];
+    __shared__ unsigned short rank[N], med[N];
     const int lane = threadIdx.x;
     const int o0 = blockIdx.x * (N - 2 * h);
     const int n_out = min(N - 2 * h, n_bins - o0);
@@ -224,12 +225,10 @@ __global__ __launch_bounds__(64) void normalise_kernel(const void *__restrict__ 
 #pragma unroll
     for (int w = 0; w < kWords; ++w) set[w * 64 + lane] = 0u;
     __syncthreads();
-    // the lane's outputs first .. first + mine - 1 (an odd run: rank reads of the
-    // lanes on different banks)
-    const int run = ((n_out + 63) / 64) | 1;
-    // (lanes past the last output do that one again)
-    const int mine = max(min(run, n_out - lane * run), 1);
-    const int first = min(lane * run, n_out - 1);
+    // the lane's outputs first .. first + mine - 1
+    const int run = slide_length(n_out);
+    const SlideRun own = slide_run(lane, n_out, h);
+    const int first = own.first, mine = own.mine;
     char *const bits = reinterpret_cast<char *>(set + lane);
     auto word = [&](int m) -> unsigned & { return *reinterpret_cast<unsigned *>(bits + (m & 0xFF00)); };
     auto toggle = [&](int r) { atomicXor(&word(r), 1u << (r & 31)); };
@@ -261,7 +260,7 @@ __global__ __launch_bounds__(64) void normalise_kernel(const void *__restrict__ 
     }
     // straight-line, with masks for the lanes that stay: the compiler turns branches
     // here into loops that lanes leave one by one
-    const unsigned short *const leave = rank + first, *const enter = leave + 2 * h + 1;
+    const unsigned short *const leave = rank + first, *const enter = rank + own.enter;
     int a = leave[0], b = enter[0];
     for (int s = 0;; ++s) {
         med[first + min(s, mine - 1)] = (unsigned short)m;
@@ -273,7 +272,7 @@ __global__ __launch_bounds__(64) void normalise_kernel(const void *__restrict__ 
         const int more = (b < m) - (a < m), p = m & 31;
         unsigned x = word(m);
         const bool stay = on == 0u || (more == 0 && a != m);
-        const int next = min(s + 1, max(mine - 2, 0));
+        const int next = slide_next(s, mine);
         a = leave[next];
         b = enter[next];
         x &= stay ? 1u << p : more > 0 ? (1u << p) - 1u : ~1u << p;
