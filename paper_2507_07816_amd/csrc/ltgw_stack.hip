@@ -4,6 +4,7 @@
 // rule.  They use the statistic's gather and accumulation (ltgw_gather.h).
 #include "ltgw_gather.h"
 #include "ltgw_proposer.h"
+#include "pair_fetch.h"
 
 #include <algorithm>
 
@@ -172,7 +173,7 @@ __global__ __launch_bounds__(256) void stack_eval_kernel(const EvalArgs a, int R
 // stack_eval_kernel bit for bit (a row past the last segment is zeros: it adds 0 and
 // counts nothing).  256 realisations of 1024 x 800, 4800 templates, FP32: 298 us
 // instead of 460 (VALU issue alone is 230).
-constexpr int kPairSegs = 4, kPairWaves = 16, kPairAhead = 3, kPairSlots = 3 /* per wavefront */;
+constexpr int kPairWaves = 16, kPairSlots = 3 /* per wavefront */;
 template <int STORE>
 constexpr int kPairEls = 16 / Store<STORE>::kBytes;  // columns of a 16-byte piece
 template <int STORE>
@@ -258,8 +259,9 @@ __global__ __launch_bounds__(64 * kPairWaves, 4) void stack_pair_kernel(
     const int eto = weights ? w_at + (wv - (kPairWaves - 2)) * kPairSegs * 4 + lane * 8 : h_at + (int)threadIdx.x * 8;
     const int estep = weights ? 4 : 8;
     const int r0 = 2 * pair, r1 = min(r0 + 1, R - 1);
-    // reads past a realisation's last row, or past its weights, give zeros (past a
-    // group's track factors, the next group's or zeros: they meet rows of zeros)
+    // the last batch's reads past a realisation's last row, or past its weights, give
+    // zeros (past a group's track factors, the next group's or zeros: they meet rows of
+    // zeros)
     const __amdgpu_buffer_rsrc_t s0 = __builtin_amdgcn_make_buffer_rsrc(
         (void *)((const char *)D.store + (int64_t)r0 * stack_bytes), 0, (int)stack_bytes, kBufDword3);
     const __amdgpu_buffer_rsrc_t s1 = __builtin_amdgcn_make_buffer_rsrc(
@@ -271,7 +273,8 @@ __global__ __launch_bounds__(64 * kPairWaves, 4) void stack_pair_kernel(
     // batches on their way
     u32x4 x0[kPairAhead], x1[kPairAhead];
     u32x2 xe[kPairAhead];
-    auto issue = [&](int q, int j) {
+    auto issue = [&](int q, int j_want) {
+        const int j = pair_fetch_segment(j_want, n_seg);
         x0[q] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(s0, from, j * D.pitch_bytes, 0));
         x1[q] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(s1, from, j * D.pitch_bytes, 0));
         xe[q] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(es, efrom, j * estep, 0));
