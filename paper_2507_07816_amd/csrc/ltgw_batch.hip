@@ -25,7 +25,7 @@ void free_batch(BatchState &B) {
     DevBuf *all[] = {&B.searches, &B.tiles, &B.ctr, &B.tiles_done, &B.t_done, &B.t_start,
                      &B.in_band, &B.s, &B.c, &B.n_res, &B.w1, &B.w2, &B.gtab, &B.dtab, &B.win,
                      &B.tau, &B.brake, &B.sky, &B.cand, &B.n_out, &B.topk,
-                     &B.topk_done};
+                     &B.topk_done, &B.wfix};
     for (DevBuf *b : all) release(*b);
     B = BatchState();
 }
@@ -313,13 +313,21 @@ int build(ltgw_ctx *c, const ltgw_search *S, int n, int k) {
     HIP_TRY(c, hipMemcpy(B.tau.p, htau.data(), htau.size() * 8, hipMemcpyHostToDevice), "batch upload");
     HIP_TRY(c, hipMemcpy(B.brake.p, hbrake.data(), hbrake.size() * 8, hipMemcpyHostToDevice), "batch upload");
     HIP_TRY(c, hipMemcpy(B.sky.p, hsky.data(), hsky.size() * 8, hipMemcpyHostToDevice), "batch upload");
-    if (Mg.mode == 1)
+    // fixed-point weights in the batch's exponent: a copy of its own (Det::wfix has the
+    // exponent of the last single search)
+    std::vector<int64_t> wfix_off(LTGW_MAX_DET, 0);
+    if (Mg.mode == 1) {
+        int64_t tot = 0;
         for (int d : all_slots) {
-            Det &D = c->det[d];
-            if ((rc = ensure(c, D.wfix, D.h_wfix.size() * 8, "fixed-point weights")) != LTGW_OK) return rc;
-            HIP_TRY(c, hipMemcpy(D.wfix.p, D.h_wfix.data(), D.h_wfix.size() * 8, hipMemcpyHostToDevice),
-                    "weights upload");
+            wfix_off[d] = tot;
+            tot += (int64_t)c->det[d].h_wfix.size();
         }
+        if ((rc = ensure(c, B.wfix, (size_t)tot * 8, "fixed-point weights")) != LTGW_OK) return rc;
+        for (int d : all_slots)
+            HIP_TRY(c, hipMemcpy((int64_t *)B.wfix.p + wfix_off[d], c->det[d].h_wfix.data(), c->det[d].h_wfix.size() * 8,
+                                 hipMemcpyHostToDevice),
+                    "weights upload");
+    }
     // descriptors
     B.hsearch.assign(n, BatchSearch());
     B.args.assign(n, EvalArgs());
@@ -343,7 +351,7 @@ int build(ltgw_ctx *c, const ltgw_search *S, int n, int k) {
             V.t_sft = D.t_sft;
             V.wq = (const float *)D.wq.p;
             V.w = (const float *)D.w.p;
-            V.wfix = Mg.mode == 1 ? (const int64_t *)D.wfix.p : nullptr;
+            V.wfix = Mg.mode == 1 ? (const int64_t *)B.wfix.p + wfix_off[P.sel[q]] : nullptr;
             V.cshift = 1.5 - (double)D.k_lo;
             V.n_seg = D.n_seg;
             V.n_bins = D.n_bins;

@@ -78,6 +78,7 @@ struct BatchState {
     DevBuf s, c, n_res, w1, w2, gtab, dtab, tau, brake, sky, cand, n_out, win;
     std::vector<int64_t> win_off;         // per (search, det) offsets into the window table
     DevBuf topk, topk_done;
+    DevBuf wfix;                          // fixed-point weights of the batch's slots
     int64_t topk_cap = 0;
     hipStream_t cap_stream = nullptr;
     hipGraph_t graph = nullptr;

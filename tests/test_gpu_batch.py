@@ -315,3 +315,28 @@ def test_batch_long_ragged_searches_equal_single_and_oracle():
     lat = ctx.batch_latency(len(searches))
     assert np.all(lat > 0) and lat.max() <= st["kernel_ms"] + 1e-6
     ctx.close()
+
+
+def test_replay_after_a_single_search_of_other_weights():
+    """The exact moments scale the weights by the smallest of the searched detectors.  A
+    single search of one detector between two runs of a batch that also holds a
+    detector of much smaller weights leaves the batch's moments as they were."""
+    import torch
+    from paper_2507_07816_amd import ltgw
+
+    print("case: batch, single search of one slot, replayed batch", flush=True)
+    ctx = ltgw.Context(0)
+    dets = [_det(11, 130, 256, 1900, "rand"), _det(12, 90, 256, 1900, 0.0625)]
+    for d, det in enumerate(dets):
+        ctx.load_spectrogram(d, torch.from_numpy(det.rho).cuda(), det.k_lo, det.t_sft, det.t_seg, weights=det.w)
+        ctx.set_velocity_table(d, det.v)
+    g = dict(f0_min=480.0, f0_step=0.25, n_f0=200, tau=[9000.0], brake=[5.0], sky=SKY[:1], t0=0.0)
+    searches = [dict(g, dets=[0, 1]), dict(g, dets=[0])]
+    want = [_single(ctx, s) for s in searches]
+    for rep in range(3):
+        _, _, st = ctx.eval_batch(searches, k=5)
+        assert st["graph_replayed"] == (rep > 0)
+        for i, s in enumerate(searches):
+            _same(_batch(ctx, i, s), want[i])
+        _single(ctx, searches[1])
+    ctx.close()
