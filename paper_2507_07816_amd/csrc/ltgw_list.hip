@@ -350,6 +350,11 @@ __global__ __launch_bounds__(256) void list_expansion_kernel(const ListArgs a, i
 #pragma unroll
                     for (int b = 0; b < kListBatch; ++b)
                         p[b] = Store<STORE>::load(rs, (int)idx[b], (j0 + min(jb + b, nj - 1)) * D.pitch_bytes);
+                    // a power that BF16 rounded to infinity is not to meet the weight 0 of a
+                    // segment past the last (the other stores hold finite values)
+                    if (STORE == LTGW_STORE_BF16 && jb + kListBatch > nj)
+#pragma unroll
+                        for (int b = 0; b < kListBatch; ++b) p[b] = jb + b < nj ? p[b] : 0.0f;
 #pragma unroll
                     for (int b = 0; b < kListBatch; ++b) {
                         // a segment past the last has weight 0 and its count bit is shifted out below

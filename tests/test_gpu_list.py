@@ -402,3 +402,30 @@ def test_list_realistic_full_size_equals_lattice():
         assert np.array_equal(lst[key], lat[key][idx]), key
     assert lst["diag"]["pow_undecided"] == 0
     assert math.isfinite(lst["diag"]["eval_kernel_ms"])
+
+
+@pytest.mark.parametrize("n_seg,n", [(33, 700), (39, 700), (64, 700), (37, 262144)])
+def test_list_overflowed_power_in_the_last_segment(n_seg, n):
+    """A power that BF16 rounds to infinity in the last segment, which the chunk's
+    batches of 8 read again up to 7 times where they go past it: the listed templates'
+    sums are the lattice's (infinite where the track ends in band), split and unsplit."""
+    from paper_2507_07816_amd import ltgw
+
+    print(f"case: list overflowed power, {n_seg} segments, {n} templates", flush=True)
+    det = _small(n_seg, n_seg, 128, k_lo=1920, spacing=8.0)
+    rho = det.rho.copy()
+    rho[-1, :] = 3.4e38
+    det = oracle.Detector(rho, det.t_seg, det.v, det.k_lo, det.t_sft, weights=det.w)
+    grid = oracle.Grid(479.0, 0.125, 350, [9000.0, 30000.0], [5.0], [SKY], 0.0)
+    params = np.tile(_lattice_params(grid), (-(-n // grid.n_templates), 1))[:n]
+    ctx = ltgw.Context(0)
+    try:
+        _load(ctx, [det], "bf16")
+        want = [x.cpu().numpy() for x in ctx.eval_templates(grid.f0_min, grid.f0_step, grid.n_f0, grid.tau, grid.brake,
+                                                            grid.sky, 0.0)]
+        got = [x.cpu().numpy() for x in ctx.eval_list(params)]
+    finally:
+        ctx.close()
+    assert np.isinf(want[0]).sum() > 200 and np.isfinite(want[0]).sum() > 20
+    for g, w in zip(got, want):
+        assert np.array_equal(g, np.tile(w, -(-n // grid.n_templates))[:n])
