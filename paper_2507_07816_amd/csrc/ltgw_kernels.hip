@@ -26,6 +26,7 @@
 // is exact in FP64 whenever its magnitude is at most x, and every other case
 // lands on the lower guard or out of range.
 #include <algorithm>
+#include <cmath>
 
 #include "ltgw_gather.h"
 #include "ltgw_internal.h"
@@ -645,7 +646,10 @@ __global__ __launch_bounds__(256) void doppler_kernel(const double *__restrict__
 // in band exactly when its last f0 reaches column 1 and its first f0 is at
 // most column n_bins.  A window may be wider than that (segments out of band add
 // exact zeros), so the columns are formed in FP32 and compared with a margin of
-// 2^-20 of the terms, four times what their rounding can come to.
+// 2^-20 of the terms, four times what their rounding can come to.  f0 goes in times
+// the power of two that brings the largest below 1 and the track factors divided by it,
+// so that neither leaves FP32's range, whatever the unit of time: columns stay below
+// 2^30, and a term that underflows is far below the first column.
 // One wavefront per (group, kWinRuns consecutive runs of f0): each lane takes
 // segments lane, lane + 64, ... and tests every run of the wavefront against
 // its track factor, so the group's row of track factors is read once per
@@ -654,7 +658,8 @@ __global__ __launch_bounds__(256) void doppler_kernel(const double *__restrict__
 // columns and one track factor in flight).
 constexpr int kWinRuns = 8;
 __global__ __launch_bounds__(256) void window_kernel(const DetView D, int n_groups, int n_tn, double f0_min,
-                                                     double f0_step, int n_f0, int2 *__restrict__ win) {
+                                                     double f0_step, int n_f0, double h_scale,
+                                                     int2 *__restrict__ win) {
     const int lane = threadIdx.x & 63;
     const int per_group = (D.win_blocks + 4 * kWinRuns - 1) / (4 * kWinRuns);
     const int grp = blockIdx.x / per_group;
@@ -680,10 +685,10 @@ __global__ __launch_bounds__(256) void window_kernel(const DetView D, int n_grou
         for (int k = 0; k < 4; ++k) {
             const int j = min(j0 + 64 * k, D.n_seg - 1);
             if (D.H) {
-                h[k] = (float)D.H[(int64_t)grp * D.n_seg + j];
+                h[k] = (float)(D.H[(int64_t)grp * D.n_seg + j] * h_scale);
             } else {
                 const double hg = D.g[(int64_t)tn * D.n_seg + j] * D.D[(int64_t)sky * D.n_seg + j];
-                h[k] = (float)(hg * D.t_sft);
+                h[k] = (float)(hg * D.t_sft * h_scale);
             }
         }
 #pragma unroll
@@ -714,8 +719,12 @@ hipError_t launch_windows(const DetView &D, int n_groups, int n_tn, double f0_mi
                           int2 *win, hipStream_t st) {
     const int64_t blocks = (int64_t)((D.win_blocks + 4 * kWinRuns - 1) / (4 * kWinRuns)) * n_groups;
     if (n_groups < 1 || D.win_blocks < 1 || blocks > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(window_kernel, dim3((unsigned)blocks), dim3(256), 0, st, D, n_groups, n_tn, f0_min, f0_step,
-                       n_f0, win);
+    int ex = 0;  // (both powers of two are doubles of full precision)
+    (void)std::frexp(f0_min + (double)(n_f0 - 1) * f0_step, &ex);
+    ex = std::min(std::max(ex, -1000), 1000);
+    const double down = std::ldexp(1.0, -ex);
+    hipLaunchKernelGGL(window_kernel, dim3((unsigned)blocks), dim3(256), 0, st, D, n_groups, n_tn, f0_min * down,
+                       f0_step * down, n_f0, std::ldexp(1.0, ex), win);
     return hipGetLastError();
 }
 
