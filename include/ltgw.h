@@ -319,7 +319,8 @@ typedef struct {
                                (Eq. 1 powers, Eq. 2 factors, in-band windows);
                                the in-band moments run beside the statistic
                                kernel on a second stream of the context    */
-    int32_t tile_shape;     /* tile shape of the last eval's statistic kernel */
+    int32_t tile_shape;     /* tile shape of the last eval's statistic kernel, or
+                               the one it would have had (ltgw_shared_wavefronts) */
     int32_t eval_launches;  /* dispatches of the statistic kernel in the last
                                eval (segment slabs, generations of workgroups) */
     double ingest_ms;       /* duration of the store kernels of the last
@@ -337,6 +338,11 @@ typedef struct {
 
 /* ltgw_diagnostics: synchronous; reads the device counters of the last eval. */
 int32_t ltgw_diagnostics(ltgw_ctx *ctx, ltgw_diag *out);
+
+/* ltgw_shared_wavefronts: how many wavefronts shared the segments of each 64
+ * templates in the last eval's statistic kernel; 0 where the kernel of the tile
+ * shape ran.  Errors: INVALID_ARG (NULL). */
+int32_t ltgw_shared_wavefronts(ltgw_ctx *ctx, int32_t *out);
 
 /* ltgw_inject_track: add amp * w_j to the FP32 spectrogram `power`
  * ([n_seg][n_bins] device buffer of detector det's shape) at the bin of
@@ -416,17 +422,19 @@ int32_t ltgw_batch_latency(ltgw_ctx *ctx, double *out_ms);
  * (the workgroups of a generation walk the segments together and share the
  * spectrogram rows in L2) and bit 8 = one search detector's segments walked
  * in slabs of 1024, one launch per slab (results bit-identical to one pass).
- * Variants 0..15.  A lattice whose templates are few for the device, or span few
- * columns, goes to a kernel of its own instead (workgroups that share the
- * segments, the same bits) unless ltgw_set_tile_shape asks for a shape; the
- * diagnostics then name the shape it would have had.  Untuned, a lattice has shape 1,
- * or 9 where it is long and large.
+ * Variants 0..15.  An untuned lattice whose templates are few for the device, or span
+ * few columns, goes to a kernel of its own instead (workgroups whose wavefronts share
+ * the segments, the same bits); another untuned one has shape 1, or 9 where it is long
+ * and large.  A tuned lattice runs whichever of its shape and that kernel was faster
+ * when it was tuned, and ltgw_set_tile_shape's shape is always the one that runs.
+ * ltgw_shared_wavefronts says which it was; ltgw_diag.tile_shape is the lattice's shape.
  * A batch uses shape (value & 3): its persistent launch is
  * one generation already.
  * Keys describe the work (single search or batch, store, moment mode and
  * size classes); values are the fastest variant measured on this device.
  * ltgw_autotune times every variant on the given grid (single search) and
- * records the winner; ltgw_eval_batch tunes a new batch key by itself.
+ * records the winner (*best_variant), and beside it (key "shared/..", 1 or 0) whether
+ * the kernel of shared segments, where it suits the grid, was faster still; ltgw_eval_batch tunes a new batch key by itself.
  * ltgw_tune_save / ltgw_tune_load write and read the cache as JSON text
  * ({"ltgw_tune": {"<key>": <variant>, ...}}). */
 int32_t ltgw_autotune(ltgw_ctx *ctx, const ltgw_grid *g, int32_t *best_variant);

@@ -640,8 +640,8 @@ static int ilog2(int64_t v) {
     return r;
 }
 
-void tune_key_eval(const SearchPlan &P, bool moments_in_loop, char (&buf)[160]) {
-    snprintf(buf, sizeof buf, "eval/store%d/mom%d/seg%d/bins%d/tpl%d", P.store, moments_in_loop ? 1 : 0,
+void tune_key_eval(const SearchPlan &P, bool moments_in_loop, char (&buf)[160], const char *head) {
+    snprintf(buf, sizeof buf, "%s/store%d/mom%d/seg%d/bins%d/tpl%d", head, P.store, moments_in_loop ? 1 : 0,
              ilog2(P.n_seg_total), ilog2(P.max_bins), ilog2(P.n_tpl));
 }
 
@@ -719,6 +719,10 @@ int default_shape(const EvalArgs &a, int split, int cu_count) {
     const int64_t n = (int64_t)((a.n_f0 + 63) / 64) * a.n_groups;
     return !split && a.n_det == 1 && a.det[0].n_seg >= 4096 && n >= (int64_t)20 * cu_count ? 9 : 1;
 }
+
+// The kernel whose workgroups share the segments, as eval_single's variant (where it
+// suits the lattice; else shape 1).
+constexpr int kVariantShared = kNumVariants;
 
 // The single-search evaluation; variant < 0 takes the tuned (or default)
 // shape.  scratch != NULL: every buffer is a slice of it (no allocation) and
@@ -886,13 +890,23 @@ int eval_single(ltgw_ctx *c, const ltgw_grid *g, uint32_t stats, float *out_s, i
         HIP_TRY(c, je, "event record");
     }
     if (variant < 0) variant = c->forced_variant;
-    // a shape asked for is the shape used; else the split kernel goes before a tuned one
-    const int split = variant < 0 ? eval_split_waves(P.store, a, c->cu_count) : 0;
+    // a shape asked for is the shape used; a tuned lattice runs what tuning found faster,
+    // its shape or the shared segments; an untuned one those where they suit it
+    int split = variant < 0 || variant == kVariantShared ? eval_split_waves(P.store, g->n_f0, P.n_groups, c->cu_count) : 0;
     if (variant < 0) {
         char key[160];
         tune_key_eval(P, moments_in_loop, key);
         const auto it = c->tune.find(key);
-        variant = it == c->tune.end() ? default_shape(a, split, c->cu_count) : it->second;
+        if (it == c->tune.end()) {
+            variant = default_shape(a, split, c->cu_count);
+        } else {
+            variant = it->second;
+            tune_key_eval(P, moments_in_loop, key, "shared");
+            const auto sh = c->tune.find(key);
+            if (sh == c->tune.end() || !sh->second) split = 0;
+        }
+    } else if (variant == kVariantShared) {
+        variant = 1;
     }
     HIP_TRY(c, hipEventRecord(c->ev_h2d, c->stream), "event record");
     HIP_TRY(c, hipEventRecord(c->ev[1], c->stream), "event record");
@@ -909,6 +923,7 @@ int eval_single(ltgw_ctx *c, const ltgw_grid *g, uint32_t stats, float *out_s, i
     c->results_kept = scratch == nullptr;
     c->list_mode = false;
     c->last_variant = variant;
+    c->last_split = split;
     c->n_templates = n_tpl;
     c->n_evals = P.n_evals;
     c->f0_min = g->f0_min;
@@ -1226,6 +1241,7 @@ int32_t ltgw_eval_list(ltgw_ctx *c, const ltgw_template *tpl, int64_t n, double 
     c->results_kept = true;
     c->list_mode = true;
     c->last_variant = -1;
+    c->last_split = 0;
     c->last_launches = 1;
     c->n_templates = n;
     c->n_evals = n * n_seg_total;
@@ -1236,15 +1252,17 @@ int32_t ltgw_eval_list(ltgw_ctx *c, const ltgw_template *tpl, int64_t n, double 
 int32_t ltgw_autotune(ltgw_ctx *c, const ltgw_grid *g, int32_t *best_variant) {
     if (!c) return LTGW_E_INVALID_ARG;
     Enter en(c);
-    float best_ms = 0.0f;
-    int best = -1;
-    std::string key;
-    for (int v = 0; v < kNumVariants; ++v) {
-        int rc = eval_single(c, g, LTGW_STAT_POWER | LTGW_STAT_COUNT, nullptr, nullptr, nullptr, v);
+    auto timed = [&](int v, float *ms) {
+        const int rc = eval_single(c, g, LTGW_STAT_POWER | LTGW_STAT_COUNT, nullptr, nullptr, nullptr, v);
         if (rc != LTGW_OK) return rc;
         HIP_TRY(c, hipEventSynchronize(c->ev[2]), "autotune");
-        float ms = 0.0f;
-        HIP_TRY(c, hipEventElapsedTime(&ms, c->ev[1], c->ev[2]), "autotune timing");
+        HIP_TRY(c, hipEventElapsedTime(ms, c->ev[1], c->ev[2]), "autotune timing");
+        return (int)LTGW_OK;
+    };
+    float best_ms = 0.0f, ms = 0.0f;
+    int best = -1, rc;
+    for (int v = 0; v < kNumVariants; ++v) {
+        if ((rc = timed(v, &ms)) != LTGW_OK) return rc;
         if (best < 0 || ms < best_ms) {
             best = v;
             best_ms = ms;
@@ -1255,10 +1273,23 @@ int32_t ltgw_autotune(ltgw_ctx *c, const ltgw_grid *g, int32_t *best_variant) {
         for (int d = 0; d < 32 && n_slots < LTGW_MAX_SEARCH_DET; ++d)
             if (g->det_mask ? ((g->det_mask >> d) & 1u) : c->det[d].loaded) slots[n_slots++] = d;
         SearchPlan P;
-        int rc = plan_search(c, g, slots, n_slots, P);
-        if (rc != LTGW_OK) return rc;
+        if ((rc = plan_search(c, g, slots, n_slots, P)) != LTGW_OK) return rc;
         const Moments M = plan_moments(c, P.sel, P.n_sel);
         c->tune[tune_key_eval(P, M.mode == 2)] = best;
+        char key[160];
+        tune_key_eval(P, M.mode == 2, key, "shared");
+        c->tune.erase(key);
+        if (eval_split_waves(P.store, g->n_f0, P.n_groups, c->cu_count)) {
+            // each the better of two runs (a kernel's first one looks it up)
+            float shared_ms = 0.0f;
+            for (int rep = 0; rep < 2; ++rep) {
+                if ((rc = timed(kVariantShared, &ms)) != LTGW_OK) return rc;
+                shared_ms = rep == 0 || ms < shared_ms ? ms : shared_ms;
+                if ((rc = timed(best, &ms)) != LTGW_OK) return rc;
+                best_ms = ms < best_ms ? ms : best_ms;
+            }
+            c->tune[key] = shared_ms < best_ms ? 1 : 0;
+        }
     }
     if (best_variant) *best_variant = best;
     c->have_eval = false;  // the last tuning run left results of a forced shape; evaluate again
@@ -1323,6 +1354,9 @@ int32_t ltgw_tune_load(ltgw_ctx *c, const char *path) {
         pos = txt.find_first_of(",}", (size_t)(end - txt.c_str()));
         if (pos == std::string::npos || txt[pos] == '}') break;
     }
+    // a lattice's entries go together: one that the file lacks is not left from before
+    for (const auto &kv : got)
+        if (kv.first.compare(0, 5, "eval/") == 0) c->tune.erase("shared/" + kv.first.substr(5));
     for (const auto &kv : got) c->tune[kv.first] = kv.second;
     return LTGW_OK;
 }
@@ -1415,6 +1449,14 @@ int32_t ltgw_diagnostics(ltgw_ctx *c, ltgw_diag *out) {
         if (hipEventElapsedTime(&b, c->ev[0], c->ev[1]) == hipSuccess) out->tables_ms = b;
         (void)hipGetLastError();
     }
+    return LTGW_OK;
+}
+
+int32_t ltgw_shared_wavefronts(ltgw_ctx *c, int32_t *out) {
+    if (!c) return LTGW_E_INVALID_ARG;
+    Enter en(c);
+    if (!out) return fail(c, LTGW_E_INVALID_ARG, "out is NULL");
+    *out = c->have_eval ? c->last_split : 0;
     return LTGW_OK;
 }
 

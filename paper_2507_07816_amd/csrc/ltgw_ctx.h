@@ -155,6 +155,7 @@ struct ltgw_ctx {
     int32_t n_f0 = 0, n_tau = 0, n_brake = 0, n_sky = 0;
     float rho_th = 1.6f;
     int last_variant = 1;
+    int last_split = 0;  // wavefronts that shared the segments in the last eval (0: last_variant's kernel)
     int last_launches = 0;  // statistic-kernel dispatches of the last eval
     bool list_mode = false;      // the last eval was an explicit template list
     ltgw::DevBuf h_list, h_perm;  // pinned host staging of its templates and of their evaluation order
@@ -224,7 +225,7 @@ int plan_search(ltgw_ctx *c, const ltgw_grid *g, const int *slots, int n_slots, 
 Moments plan_moments(ltgw_ctx *c, const int *slots, int n_slots);
 // Autotuner keys.
 std::string tune_key_eval(const SearchPlan &P, bool moments_in_loop);
-void tune_key_eval(const SearchPlan &P, bool moments_in_loop, char (&buf)[160]);
+void tune_key_eval(const SearchPlan &P, bool moments_in_loop, char (&buf)[160], const char *head = "eval");
 std::string tune_key_batch(int store, bool moments_in_loop, int n_searches, int64_t evals);
 void free_batch(BatchState &B);
 void free_stack(StackState &S);

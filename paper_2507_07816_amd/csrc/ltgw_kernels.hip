@@ -396,10 +396,10 @@ __global__ __launch_bounds__(64 * kSplitWaves) void eval_split_kernel(const Eval
 // the lattice's columns in a row of 40 - 60 MB (8000 FP32 columns: 258 us against 264
 // at n = 1500, 818 against 499 at 4500; 4000 BF16: 305 against 355 at 5040, 593 against
 // 549 at 9072; with moments in the loop 4000 FP8: 471 against 488 at 9072).
-int eval_split_waves(int store, const EvalArgs &a, int cu_count) {
-    const int64_t n = (int64_t)((a.n_f0 + 63) / 64) * a.n_groups;
+int eval_split_waves(int store, int n_f0, int64_t n_groups, int cu_count) {
+    const int64_t n = (int64_t)((n_f0 + 63) / 64) * n_groups;
     const int bytes = store == LTGW_STORE_F32 ? 4 : store == LTGW_STORE_BF16 ? 2 : 1;
-    if (n * a.n_f0 * bytes > 40000000) return 0;
+    if (n * n_f0 * bytes > 40000000) return 0;
     return n <= 2 * cu_count ? 16 : n <= 5 * cu_count ? 8 : 4;
 }
 

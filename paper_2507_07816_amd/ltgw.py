@@ -43,7 +43,7 @@ TILE_SHAPES = {0: (1, 8), 1: (1, 16), 2: (2, 8), 3: (2, 16)}  # (templates per l
 # every symbol include/ltgw.h declares
 EXPORTS = ("ltgw_create", "ltgw_destroy", "ltgw_last_error", "ltgw_load_spectrogram",
            "ltgw_set_velocity_table", "ltgw_set_antenna", "ltgw_sft_normalise", "ltgw_eval_templates", "ltgw_psi",
-           "ltgw_topk_candidates", "ltgw_diagnostics", "ltgw_inject_track", "ltgw_read_store", "ltgw_read_tables",
+           "ltgw_topk_candidates", "ltgw_diagnostics", "ltgw_shared_wavefronts", "ltgw_inject_track", "ltgw_read_store", "ltgw_read_tables",
            "ltgw_eval_batch", "ltgw_batch_results", "ltgw_batch_latency", "ltgw_autotune",
            "ltgw_set_tile_shape", "ltgw_tune_save", "ltgw_tune_load",
            "ltgw_generate_noise", "ltgw_inject_stack", "ltgw_load_stack", "ltgw_stack_psi",
@@ -136,6 +136,7 @@ def library():
             "ltgw_psi": (i32, [P, u32, P]),
             "ltgw_topk_candidates": (i32, [P, u32, i32, C.POINTER(ltgw_candidate), C.POINTER(i32)]),
             "ltgw_diagnostics": (i32, [P, C.POINTER(ltgw_diag)]),
+            "ltgw_shared_wavefronts": (i32, [P, C.POINTER(i32)]),
             "ltgw_inject_track": (i32, [P, i32, P, d, d, d, P, d, f]),
             "ltgw_read_store": (i32, [P, i32, P, P]),
             "ltgw_read_tables": (i32, [P, i32, P, P, P]),
@@ -335,6 +336,12 @@ def ltgw_diagnostics(ctx):
     d = ltgw_diag()
     _check(ctx, library().ltgw_diagnostics(ctx, C.byref(d)))
     return {f: getattr(d, f) for f, _ in ltgw_diag._fields_}
+
+
+def ltgw_shared_wavefronts(ctx):
+    n = C.c_int32()
+    _check(ctx, library().ltgw_shared_wavefronts(ctx, C.byref(n)))
+    return n.value
 
 
 def ltgw_inject_track(ctx, det, power, f0, tau, brake, sky, t0, amp):
@@ -656,6 +663,9 @@ class Context:
 
     def diagnostics(self):
         return ltgw_diagnostics(self.h)
+
+    def shared_wavefronts(self):
+        return ltgw_shared_wavefronts(self.h)
 
     def inject_track(self, det, power, f0, tau, brake, sky, t0, amp):
         ltgw_inject_track(self.h, det, power, f0, tau, brake, sky, t0, amp)

@@ -80,3 +80,71 @@ def test_untuned_large_lattice_in_slabs():
     ctx.close()
     for x, y in zip(*out):
         assert np.array_equal(x, y)
+
+
+def _lattice(ns, nb, k_lo, t_sft, n_f0, n_tau, store="f32"):
+    import torch
+    from paper_2507_07816_amd import ltgw
+
+    r = np.random.default_rng(ns + n_f0)
+    v = r.normal(size=(ns, 3))
+    v = v / np.linalg.norm(v, axis=1, keepdims=True) * 3.0e4
+    ctx = ltgw.Context(0)
+    ctx.load_spectrogram(0, torch.from_numpy(r.exponential(size=(ns, nb)).astype(np.float32)).cuda(), k_lo, t_sft,
+                         np.arange(ns) * 40.0 + 2.0, store=store)
+    ctx.set_velocity_table(0, v)
+    return ctx, dict(f0_min=(k_lo - 3) / t_sft, f0_step=1.0 / t_sft, n_f0=n_f0, tau=np.geomspace(3000.0, 60000.0, n_tau),
+                     brake=[5.0], sky=[SKY], t0=0.0)
+
+
+@pytest.mark.parametrize("n_f0,n_tau,waves", [
+    (1, 1, 16),
+    (64, 512, 16), (64, 513, 8),        # two workgroups a CU of 256
+    (64, 1280, 8), (64, 1281, 4),       # five
+    (2500, 100, 4), (2500, 101, 0),     # 40 MB of the lattice's columns
+])
+def test_which_kernel_an_untuned_lattice_runs(n_f0, n_tau, waves):
+    import torch
+
+    print(f"case: untuned {n_f0} f0 x {n_tau} tau", flush=True)
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the sizes are those of 256 CUs")
+    ctx, g = _lattice(40, 150, 1880, 4.0, n_f0, n_tau)
+    ctx.eval_templates(**g)
+    assert ctx.shared_wavefronts() == waves and ctx.diagnostics()["tile_shape"] == 1
+    ctx.set_tile_shape(2)  # a shape asked for is the one that runs
+    ctx.eval_templates(**g)
+    assert ctx.shared_wavefronts() == 0 and ctx.diagnostics()["tile_shape"] == 2
+    ctx.close()
+
+
+def test_a_tuned_shape_runs(tmp_path):
+    """A tuned lattice runs what the tuning found faster: its shape where the file says so
+    (one that knows the shapes alone, or 0 for the shared segments), those where it says 1,
+    and what ltgw_autotune measured after it."""
+    import json
+
+    from paper_2507_07816_amd import ltgw
+
+    print("case: tuned lattice", flush=True)
+    ctx, g = _lattice(1024, 300, 1880, 4.0, 130, 3)
+    ref = [x.cpu().numpy() for x in ctx.eval_templates(**g)]
+    assert ctx.shared_wavefronts() == 16
+    best = ctx.autotune(**g)
+    path = tmp_path / "tune.json"
+    ctx.tune_save(str(path))
+    saved = json.loads(path.read_text())["ltgw_tune"]
+    (key,) = [k for k in saved if k.startswith("eval/")]
+    shared = "shared/" + key[5:]
+    assert saved[key] == best and saved[shared] in (0, 1)
+    # a lane walking 1024 segments alone against 16 wavefronts sharing them: a factor of five
+    assert saved[shared] == 1
+    for entries, want in (({key: 3}, (3, 0)), ({key: 2, shared: 0}, (2, 0)), ({key: 0, shared: 1}, (0, 16)),
+                          ({key: 3}, (3, 0)), (saved, (best, 16))):
+        path.write_text(json.dumps({"ltgw_tune": entries}))
+        ctx.tune_load(str(path))
+        out = [x.cpu().numpy() for x in ctx.eval_templates(**g)]
+        assert (ctx.diagnostics()["tile_shape"], ctx.shared_wavefronts()) == want
+        for x, y in zip(out, ref):
+            assert np.array_equal(x, y)
+    ctx.close()
