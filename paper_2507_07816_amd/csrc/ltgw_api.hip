@@ -93,6 +93,14 @@ int ensure(ltgw_ctx *c, DevBuf &b, size_t bytes, const char *what) {
     return LTGW_OK;
 }
 
+int ensure_if_room(ltgw_ctx *c, DevBuf &b, size_t bytes, bool *got) {
+    const int rc = ensure(c, b, bytes, "a buffer that the call can do without");
+    *got = rc == LTGW_OK;
+    if (rc != LTGW_E_NOMEM) return rc;
+    c->err.clear();
+    return LTGW_OK;
+}
+
 void release(DevBuf &b) {
     if (b.p) (void)hipFree(b.p);
     b.p = nullptr;
@@ -1179,12 +1187,12 @@ int32_t ltgw_eval_list(ltgw_ctx *c, const ltgw_template *tpl, int64_t n, double 
         chunks += (D.n_seg + kListChunk - 1) / kListChunk;
     }
     a.slices = 1;
+    // per-segment tables: dt, v/c, Doppler factors and chunks of each detector (where there
+    // is no room for them the general kernel, which needs none)
+    if (expand && (rc = ensure_if_room(c, c->list_tab, (size_t)n_seg_total * 40 + (size_t)chunks * sizeof(ListChunk),
+                                       &expand)) != LTGW_OK)
+        return rc;
     if (expand) {
-        // per-segment tables: dt, v/c, Doppler factors and chunks of each detector
-        int64_t tot = 0;
-        for (int q = 0; q < n_slots; ++q) tot += c->det[slots[q]].n_seg;
-        if ((rc = ensure(c, c->list_tab, (size_t)tot * 40 + (size_t)chunks * sizeof(ListChunk), "list tables")) != LTGW_OK)
-            return rc;
         ListChunk *ch = (ListChunk *)c->list_tab.p;
         double *tab = (double *)(ch + chunks);
         for (int q = 0; q < n_slots; ++q) {
@@ -1200,15 +1208,16 @@ int32_t ltgw_eval_list(ltgw_ctx *c, const ltgw_template *tpl, int64_t n, double 
             tab += 5 * (int64_t)V.n_seg;
         }
         // A list of fewer than four workgroups per CU is split over its chunks into
-        // about eight, where its chunk sums (12 bytes each) fit kPartBytes: 4800
-        // templates x 1024 segments (19 workgroups) took 637 us unsplit.
+        // about eight, where its chunk sums (12 bytes each) fit kPartBytes and the
+        // device: 4800 templates x 1024 segments (19 workgroups) took 637 us unsplit.
         constexpr int64_t kPartBytes = 256 << 20;
         const int64_t blocks = (n + 255) / 256;
         const int64_t want = std::min<int64_t>(chunks, ((int64_t)8 * c->cu_count + blocks - 1) / blocks);
-        if (blocks < (int64_t)4 * c->cu_count && want > 1 && n * chunks * 12 <= kPartBytes) {
+        const size_t part = (size_t)(n * chunks) * 12;
+        bool split = blocks < (int64_t)4 * c->cu_count && want > 1 && n * chunks * 12 <= kPartBytes;
+        if (split && (rc = ensure_if_room(c, c->list_part, part + (size_t)(n * want) * 8, &split)) != LTGW_OK) return rc;
+        if (split) {
             a.slices = (int32_t)want;
-            const size_t part = (size_t)(n * chunks) * 12;
-            if ((rc = ensure(c, c->list_part, part + (size_t)(n * want) * 8, "list chunk sums")) != LTGW_OK) return rc;
             a.part = (float *)c->list_part.p;
             a.part_n = (int32_t *)((char *)c->list_part.p + part);
         }

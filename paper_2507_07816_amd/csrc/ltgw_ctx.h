@@ -190,6 +190,8 @@ namespace ltgw {
 int fail(ltgw_ctx *c, int code, const char *fmt, ...);
 int hip_fail(ltgw_ctx *c, hipError_t e, const char *what);
 int ensure(ltgw_ctx *c, DevBuf &b, size_t bytes, const char *what);
+// the same for a buffer that a call can do without: no room is no error, and *got false
+int ensure_if_room(ltgw_ctx *c, DevBuf &b, size_t bytes, bool *got);
 void release(DevBuf &b);
 // pinned host staging, grown like ensure()
 int ensure_pinned(ltgw_ctx *c, DevBuf &b, size_t bytes, const char *what);

@@ -589,8 +589,9 @@ int32_t ltgw_stack_best_both(ltgw_ctx *c, const ltgw_grid *g, int32_t *power_ind
     if (n < 1) return fail(c, LTGW_E_INVALID_ARG, "empty grid");
     StackState &S = c->stack;
     const size_t all = (size_t)(S.R * n);
-    if (ensure(c, S.psi_all, all * 16, "fine ratios of both statistics") != LTGW_OK) {
-        // room for one at a time
+    bool both = false;
+    if ((rc = ensure_if_room(c, S.psi_all, all * 16, &both)) != LTGW_OK) return rc;
+    if (!both) {  // room for one at a time
         if ((rc = stack_best_impl(c, g, n, LTGW_STAT_POWER, power_index, power_psi)) != LTGW_OK) return rc;
         return stack_best_impl(c, g, n, LTGW_STAT_COUNT, count_index, count_psi);
     }
