@@ -7,10 +7,16 @@
 //     A = f0 T_sft U^e, c_k = C(e, k).
 // Against the contract's chain of correctly rounded operations x is off by less than
 //     m = 2 A (1.25 |C(e, 7)| dmax^7 + (1 + |y| + |e|) 2^-44),  y = e log U,
-// for |d| <= dmax <= 1/8, -4 <= e < 0 and D < 1.001: the truncation, whose terms
-// shrink by at most (7 + |e|)/8 dmax <= 11/64 each; the enclosure value's
-// 2^-50 (1 + |y| + |e|) in A; the chain's own (3 |e| + 6) 2^-53; and at most
-// 60 2^-53 for d, the coefficients, the polynomial and the products.
+// for |d| <= dmax <= 1/8, -4 <= e < 0 and any 0 < D < 2 (|v| < c):
+//   the truncation, whose terms shrink by at most (7 + |e|)/8 dmax <= 11/64 each: below
+//   1.25 |C(e, 7)| dmax^7 A D, the first term of m;
+//   relative to x, which (1 + d)^e <= (7/8)^-4 < 1.71 keeps below 1.71 A D < 3.42 A: the
+//   enclosure value's 2^-50 (1 + |y| + |e|) in A and 3 |e| 2^-53 for its U; the chain's
+//   own (3 |e| + 6) 2^-53; and at most 60 2^-53 for d, the coefficients, the polynomial
+//   (sum |c_k d^k| < 1.71 as well) and the products, together below
+//   2^-46.6 (1 + |y| + |e|) and so below 2^-44.8 A (1 + |y| + |e|), of a second term
+//   twice as large and more;
+//   2^-51 in D itself where it is formed by FMAs, below 2^-50.2 A.
 // The column trunc(x + 1.5 - k_lo) is then certain unless x + 1.5 - k_lo lies within
 // m of an integer.  It is taken on top of 2^20, where the sum's low word is its
 // fraction in units of 2^-32 and the low 20 bits of its high word its integer part:
