@@ -376,34 +376,60 @@ __global__ __launch_bounds__(64 * kPairWaves, 4) void stack_pair_kernel(
     }
 }
 
-// Where the pair kernel is faster.  Its workgroups take a time of their own however
-// little each has to do (150 us for 1024 segments), so it needs the chip full: by
-// (f0 / 64) x groups x realisations it draws level at 9000 - 12000 for FP32 and near
-// 18000 for BF16 (84 x 128 FP32: 196 us against 228, 84 x 64: 153 against 98; 84 x 256
-// BF16: 298 against 341, 48 x 256: 200 against 175).
+// A pair's slots go over as many workgroups as fill the chip, or as hold them.
+struct PairShape {
+    int n_slots, pairs, parts;
+};
+static PairShape pair_shape(const EvalArgs &a, int R, int cu_count) {
+    PairShape s;
+    s.n_slots = (a.n_f0 + 63) / 64 * a.n_groups;
+    s.pairs = (R + 1) / 2;
+    const int most = kPairWaves * kPairSlots;
+    s.parts = std::max((s.n_slots + most - 1) / most,
+                       std::min(cu_count / s.pairs, (s.n_slots + kPairWaves - 1) / kPairWaves));
+    return s;
+}
+
+// Where the pair kernel is faster: where its time, a workgroup per CU for as many
+// rounds as the fullest XCD takes, is below the gathers'.  A batch costs it a part of its
+// own (the barrier, the copy of a row) and a part per slot of a wavefront, busy or not;
+// the gathers cost 15 ns per slot and 1000 segments where 64 lanes read neighbouring
+// columns, up to twice that where f0 steps by two, and more where the chip isn't full.
+// Over 707 shapes (40 - 1024 segments of 100 - 2000 columns, f0 steps of half a bin to
+// two, 1 - 40 groups, 3000 - 30000 slots x realisations) this took the pair kernel for
+// 82, none of them slower, 1.0 to 2.6 times as fast; of the others it would have been
+// faster by more than a tenth for 11.  The number of slots x realisations alone (12000
+// for FP32, 20000 for BF16, the earlier rule) took it where one slot kept 15 of 16
+// wavefronts idle: 12000 realisations of 32 segments, 160 us against 20.
 // The limits on segments and slots keep its 32-bit offsets and shares in range.
 template <int STORE>
-static bool stack_pair_suits(const EvalArgs &a, int R) {
+static bool stack_pair_suits(const EvalArgs &a, int R, int cu_count) {
+    const DetView &D = a.det[0];
     const int64_t slots = (int64_t)((a.n_f0 + 63) / 64) * a.n_groups;
-    return a.det[0].n_bins + 2 <= kPairCols<STORE> && a.det[0].n_seg <= (1 << 20) && slots <= (1 << 17) &&
-           slots * R >= (STORE == LTGW_STORE_F32 ? 12000 : 20000);
+    if (D.n_bins + 2 > kPairCols<STORE> || D.n_seg > (1 << 20) || slots > (1 << 17)) return false;
+    constexpr bool kF32 = STORE == LTGW_STORE_F32;
+    const PairShape s = pair_shape(a, R, cu_count);
+    const int per_xcd = std::max(1, cu_count / kXcds), blocks = (s.pairs + kXcds - 1) / kXcds * s.parts;
+    const int rounds = (blocks + per_xcd - 1) / per_xcd;
+    const int per_wave = ((s.n_slots + s.parts - 1) / s.parts + kPairWaves - 1) / kPairWaves;
+    const double batch_us = kF32 ? 0.21 + 0.256 * per_wave + 2.6e-4 * D.n_bins : 0.152 + 0.327 * per_wave + 1.4e-4 * D.n_bins;
+    const double pair_us = rounds * (5.0 + batch_us * ((D.n_seg + kPairSegs - 1) / kPairSegs));
+    const double step = std::min(std::max(a.f0_step * D.t_sft, 1.0), 2.0);
+    const double gather_us = 1.5e-5 * step * (double)slots * R * D.n_seg * 256.0 / cu_count;
+    return pair_us < gather_us;
 }
 
 template <int STORE>
 static hipError_t launch_stack_pair(const EvalArgs &a, int R, int64_t stack_bytes, int64_t stack_rows, double mu,
                                     double var, int nan_to_zero, StackMoments m, double *out_power, double *out_count,
                                     int cu_count, hipStream_t st) {
-    // a pair's slots over as many workgroups as fill the chip, or as hold them
-    const int n_slots = (a.n_f0 + 63) / 64 * a.n_groups, pairs = (R + 1) / 2;
-    const int most = kPairWaves * kPairSlots;
-    const int parts = std::max((n_slots + most - 1) / most,
-                               std::min(cu_count / pairs, (n_slots + kPairWaves - 1) / kPairWaves));
+    const PairShape s = pair_shape(a, R, cu_count);
     const int cols = (a.det[0].n_bins + 2 + kPairEls<STORE> - 1) / kPairEls<STORE> * kPairEls<STORE>;
-    const int64_t grid = (int64_t)parts * ((pairs + kXcds - 1) / kXcds * kXcds);
+    const int64_t grid = (int64_t)s.parts * ((s.pairs + kXcds - 1) / kXcds * kXcds);
     if (grid > 0x7fffffff) return hipErrorInvalidValue;
     hipLaunchKernelGGL(stack_pair_kernel<STORE>, dim3((unsigned)grid), dim3(64 * kPairWaves),
-                       (size_t)2 * kPairSegs * (cols * 2 * Store<STORE>::kBytes + most * 8 + 2 * 4), st, a, R, stack_bytes,
-                       stack_rows, mu, var, nan_to_zero, m, parts, cols, out_power, out_count);
+                       (size_t)2 * kPairSegs * (cols * 2 * Store<STORE>::kBytes + kPairWaves * kPairSlots * 8 + 2 * 4), st, a,
+                       R, stack_bytes, stack_rows, mu, var, nan_to_zero, m, s.parts, cols, out_power, out_count);
     return hipGetLastError();
 }
 
@@ -412,10 +438,10 @@ hipError_t launch_stack_eval(int store, int shift, const EvalArgs &a, int R, int
                              const int32_t *n_rows, StackMoments m, double *out_power, double *out_count, int cu_count,
                              hipStream_t st) {
     if (R > 65535 || R < 1) return hipErrorInvalidValue;
-    if (!rmap && !n_rows && store == LTGW_STORE_F32 && stack_pair_suits<LTGW_STORE_F32>(a, R))
+    if (!rmap && !n_rows && store == LTGW_STORE_F32 && stack_pair_suits<LTGW_STORE_F32>(a, R, cu_count))
         return launch_stack_pair<LTGW_STORE_F32>(a, R, stack_bytes, stack_rows, mu, var, nan_to_zero, m, out_power,
                                                  out_count, cu_count, st);
-    if (!rmap && !n_rows && store == LTGW_STORE_BF16 && stack_pair_suits<LTGW_STORE_BF16>(a, R))
+    if (!rmap && !n_rows && store == LTGW_STORE_BF16 && stack_pair_suits<LTGW_STORE_BF16>(a, R, cu_count))
         return launch_stack_pair<LTGW_STORE_BF16>(a, R, stack_bytes, stack_rows, mu, var, nan_to_zero, m, out_power,
                                                   out_count, cu_count, st);
     // rows per pass: all of them rounded up to a multiple of the XCD count (the

@@ -896,3 +896,15 @@ def test_trained_network_beats_coarse_ranking_at_equal_budget():
     assert ev["detectable"] > 200
     assert ev["fallback_frac"] == 0.0 and ev["coarse_only"]["fallback_frac"] == 0.0
     assert ev["recall_no_fallback"] >= ev["coarse_only"]["recall_no_fallback"] + 0.1
+
+
+@pytest.mark.parametrize("ns,nb,n_f0,R,store,t_sft", [
+    (133, 1022, 1000, 256, "f32", 4.0),   # the widest row; a last batch of one segment
+    (99, 61, 1000, 255, "bf16", 4.0),     # of three, and an odd count of realisations
+    (41, 2046, 1000, 255, "bf16", 8.0),   # the widest row, f0 in steps of two bins
+    (38, 1021, 1000, 255, "f32", 8.0),
+])
+def test_stack_sums_two_realisations_at_a_time(ns, nb, n_f0, R, store, t_sft, monkeypatch):
+    """The same at sizes that the kernel for two realisations takes."""
+    monkeypatch.setitem(globals(), "T_SFT", t_sft)
+    test_stack_sums_over_segments_and_rows(ns, nb, n_f0, R, store)
