@@ -1164,22 +1164,25 @@ hipError_t launch_cnn_backward(const float *params, const float *x, int B, int c
 
 // Softmax cross-entropy per sample over n_cells logits against one target
 // cell (target < 0: loss 0, gradient 0); gradients divided by n_valid.
-// One workgroup of 1024 per sample; up to kXentHeld logits per thread stay in
-// registers between the passes (a row of 8192), the rest is read again: bound by
-// the latency of one read and two block reductions (256 samples x 4800 cells:
-// 15 us with 256 threads that read the row three times, 5.5 us here).
+// One workgroup of T per sample; up to kXentHeld logits per thread stay in
+// registers between the passes (with 1024 a row of 8192), the rest is read again: bound
+// by the latency of one read and two reductions (256 samples x 4800 cells: 15 us with
+// 256 threads that read the row three times, 5.5 us here).  A short row takes a
+// wavefront, whose reductions need no barrier, or four.
 constexpr int kXentHeld = 8;
 
-__global__ __launch_bounds__(1024) void softmax_xent_kernel(const float *logits, int n_cells,
+template <int T>
+__global__ __launch_bounds__(T) void softmax_xent_kernel(const float *logits, int n_cells,
                                                             const int32_t *target, int n_valid,
                                                             float *loss, float *dlogits) {
-    __shared__ float sh[2][16];
+    constexpr int W = T / 64;
+    __shared__ float sh[2][W];
     const int b = blockIdx.x, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const float *z = logits + (int64_t)b * n_cells;
     float *dz = dlogits + (int64_t)b * n_cells;
     const int tg = target[b];
     if (tg < 0) {
-        for (int i = threadIdx.x; i < n_cells; i += 1024) dz[i] = 0.f;
+        for (int i = threadIdx.x; i < n_cells; i += T) dz[i] = 0.f;
         if (threadIdx.x == 0) loss[b] = 0.f;
         return;
     }
@@ -1187,31 +1190,35 @@ __global__ __launch_bounds__(1024) void softmax_xent_kernel(const float *logits,
     float m = -3.4e38f;
 #pragma unroll
     for (int u = 0; u < kXentHeld; ++u) {
-        const int i = u * 1024 + (int)threadIdx.x;
+        const int i = u * T + (int)threadIdx.x;
         v[u] = i < n_cells ? z[i] : -__builtin_inff();
     }
 #pragma unroll
     for (int u = 0; u < kXentHeld; ++u) m = fmaxf(m, v[u]);
-    for (int i = kXentHeld * 1024 + (int)threadIdx.x; i < n_cells; i += 1024) m = fmaxf(m, z[i]);
+    for (int i = kXentHeld * T + (int)threadIdx.x; i < n_cells; i += T) m = fmaxf(m, z[i]);
     for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
-    if (lane == 0) sh[0][wv] = m;
-    __syncthreads();
-    m = sh[0][lane & 15];
-    for (int o = 8; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+    if constexpr (W > 1) {
+        if (lane == 0) sh[0][wv] = m;
+        __syncthreads();
+        m = sh[0][lane & (W - 1)];
+        for (int o = W / 2; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+    }
     float s = 0.f;
 #pragma unroll
     for (int u = 0; u < kXentHeld; ++u) {
-        if (u * 1024 + (int)threadIdx.x < n_cells) {
+        if (u * T + (int)threadIdx.x < n_cells) {
             v[u] = expf(v[u] - m);
             s += v[u];
         }
     }
-    for (int i = kXentHeld * 1024 + (int)threadIdx.x; i < n_cells; i += 1024) s += expf(z[i] - m);
+    for (int i = kXentHeld * T + (int)threadIdx.x; i < n_cells; i += T) s += expf(z[i] - m);
     for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-    if (lane == 0) sh[1][wv] = s;
-    __syncthreads();
-    s = sh[1][lane & 15];
-    for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    if constexpr (W > 1) {
+        if (lane == 0) sh[1][wv] = s;
+        __syncthreads();
+        s = sh[1][lane & (W - 1)];
+        for (int o = W / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    }
     const float inv = 1.0f / ((float)n_valid * s);
     auto put = [&](int i, float ex) {
         float g = ex * inv;
@@ -1220,19 +1227,30 @@ __global__ __launch_bounds__(1024) void softmax_xent_kernel(const float *logits,
     };
 #pragma unroll
     for (int u = 0; u < kXentHeld; ++u) {
-        const int i = u * 1024 + (int)threadIdx.x;
+        const int i = u * T + (int)threadIdx.x;
         if (i < n_cells) put(i, v[u]);
     }
-    for (int i = kXentHeld * 1024 + (int)threadIdx.x; i < n_cells; i += 1024) put(i, expf(z[i] - m));
+    for (int i = kXentHeld * T + (int)threadIdx.x; i < n_cells; i += T) put(i, expf(z[i] - m));
     if (threadIdx.x == 0) loss[b] = logf(s) + m - z[tg];
+}
+
+template <int T>
+static hipError_t launch_xent(const float *logits, int B, int n_cells, const int32_t *target, int n_valid, float *loss,
+                              float *dlogits, hipStream_t st) {
+    hipLaunchKernelGGL(softmax_xent_kernel<T>, dim3(B), dim3(T), 0, st, logits, n_cells, target,
+                       n_valid < 1 ? 1 : n_valid, loss, dlogits);
+    return hipGetLastError();
 }
 
 hipError_t launch_softmax_xent(const float *logits, int B, int n_cells, const int32_t *target,
                                int n_valid, float *loss, float *dlogits, hipStream_t st) {
     if (B < 1 || n_cells < 1) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(softmax_xent_kernel, dim3(B), dim3(1024), 0, st, logits, n_cells, target,
-                       n_valid < 1 ? 1 : n_valid, loss, dlogits);
-    return hipGetLastError();
+    // rows that stay in a wavefront's registers, or about in four's (16384 rows of 64: 8.7 us
+    // with 64 threads, 24 with 256, 110 with 1024; of 512: 13, 27 and 111; of 1000: 32, 29
+    // and 112; of 3000: 137, 100 and 126; of 4800: 245, 207 and 137)
+    if (n_cells <= kXentHeld * 64) return launch_xent<64>(logits, B, n_cells, target, n_valid, loss, dlogits, st);
+    if (n_cells <= 3072) return launch_xent<256>(logits, B, n_cells, target, n_valid, loss, dlogits, st);
+    return launch_xent<1024>(logits, B, n_cells, target, n_valid, loss, dlogits, st);
 }
 
 // Adam (Kingma and Ba) on FP32 master weights.

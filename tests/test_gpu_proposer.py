@@ -908,3 +908,30 @@ def test_stack_sums_two_realisations_at_a_time(ns, nb, n_f0, R, store, t_sft, mo
     """The same at sizes that the kernel for two realisations takes."""
     monkeypatch.setitem(globals(), "T_SFT", t_sft)
     test_stack_sums_over_segments_and_rows(ns, nb, n_f0, R, store)
+
+
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 511, 512, 513, 2049, 3072, 3073, 8192, 8193, 20000])
+def test_softmax_xent_row_lengths(n):
+    """Rows at and around the lengths that a wavefront, four of them and sixteen take and
+    hold in registers, some logits masked to -inf; the bars of the test above (an FP32
+    sum of n terms in a tree and 20 in line)."""
+    import torch
+    from paper_2507_07816_amd import ltgw
+
+    ctx, *_ = _ctx()
+    print(f"case: softmax of {n}", flush=True)
+    rng = np.random.default_rng(n)
+    B = 7
+    z = rng.normal(scale=3.0, size=(B, n)).astype(np.float32)
+    z[1, : n // 2] = -np.inf
+    tg = np.array([0, n - 1, n // 2, -1, n - 1, n // 3, 0], np.int32)
+    T = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    loss = torch.empty(B, dtype=torch.float32, device="cuda")
+    dz = torch.full((B, n), float("nan"), dtype=torch.float32, device="cuda")
+    ltgw.ltgw_softmax_xent(ctx.h, T(z), T(tg), 6, loss, dz)
+    l_g, d_g = loss.cpu().numpy(), dz.cpu().numpy()
+    ctx.close()
+    for b in range(B):
+        lr_, dr = cnn.softmax_xent(z[b:b + 1].astype(np.float64), tg[b:b + 1])
+        assert abs(l_g[b] - lr_) <= 1e-5 * max(1.0, abs(lr_))
+        assert np.allclose(d_g[b] * 6, dr[0], atol=1e-6)
