@@ -812,17 +812,16 @@ __device__ inline int first_at_least(double f0_min, double f0_step, int n, doubl
 // 12 groups of 1024 segments (this: 6), 95 and a 9 us scan for 456 groups of two times
 // 4465 (53), and beside the statistic, with four sums a template, 1.22 ms and a scan
 // of 0.47 ms for 288 groups of 10800 (1.12).
-constexpr int kMomThreads = 512;
-template <int NA>
-constexpr int kMomPart = 4096 / NA;  // f0 of a part: 32 KB of differences
+template <int NA, int T>
+constexpr int kMomPart = 8 * T / NA;  // f0 of a part: with 512 threads 32 KB of differences
 
-template <int NA>
-__global__ __launch_bounds__(kMomThreads) void moments_kernel(const EvalArgs a, int e0) {
-    __shared__ unsigned long long diff[NA][kMomPart<NA>];
-    __shared__ unsigned long long part[NA][kMomThreads / 64];
+template <int NA, int T>
+__global__ __launch_bounds__(T) void moments_kernel(const EvalArgs a, int e0) {
+    __shared__ unsigned long long diff[NA][kMomPart<NA, T>];
+    __shared__ unsigned long long part[NA][T / 64];
     const int row = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int i0 = blockIdx.x * kMomPart<NA>, i1 = min(i0 + kMomPart<NA>, a.n_f0);
-    for (int k = tid; k < i1 - i0; k += kMomThreads)
+    const int i0 = blockIdx.x * kMomPart<NA, T>, i1 = min(i0 + kMomPart<NA, T>, a.n_f0);
+    for (int k = tid; k < i1 - i0; k += T)
 #pragma unroll
         for (int q = 0; q < NA; ++q) diff[q][k] = 0ull;
     __syncthreads();
@@ -833,11 +832,11 @@ __global__ __launch_bounds__(kMomThreads) void moments_kernel(const EvalArgs a, 
     for (int q = 0; q < NA; ++q) at0[q] = 0ull;
     for (int d = 0; d < a.n_det; ++d) {
         const DetView &D = a.det[d];
-        for (int j4 = tid; j4 < D.n_seg; j4 += 4 * kMomThreads) {
+        for (int j4 = tid; j4 < D.n_seg; j4 += 4 * T) {
             double h4[4];  // four track factors in flight
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                const int j = min(j4 + k * kMomThreads, D.n_seg - 1);
+                const int j = min(j4 + k * T, D.n_seg - 1);
                 if (D.H) {
                     h4[k] = D.H[(int64_t)row * D.n_seg + j];
                 } else {
@@ -847,7 +846,7 @@ __global__ __launch_bounds__(kMomThreads) void moments_kernel(const EvalArgs a, 
             }
 #pragma unroll 1
             for (int k = 0; k < 4; ++k) {
-                const int j = j4 + k * kMomThreads;
+                const int j = j4 + k * T;
                 if (j >= D.n_seg) break;
                 const double H = k == 0 ? h4[0] : k == 1 ? h4[1] : k == 2 ? h4[2] : h4[3];
                 // 1 / H to about 2^-50: where to look, no more
@@ -887,7 +886,7 @@ __global__ __launch_bounds__(kMomThreads) void moments_kernel(const EvalArgs a, 
     }
     __syncthreads();
     // each thread's run of consecutive f0: its sum, the sums before it, its prefix sums
-    const int per = (i1 - i0 + kMomThreads - 1) / kMomThreads;
+    const int per = (i1 - i0 + T - 1) / T;
     const int k0 = tid * per, k1 = min(k0 + per, i1 - i0);
     int64_t run[NA];
 #pragma unroll
@@ -927,14 +926,30 @@ __global__ __launch_bounds__(kMomThreads) void moments_kernel(const EvalArgs a, 
     }
 }
 
-hipError_t launch_moments(const EvalArgs &a, int weights, int e0, hipStream_t st) {
-    const int per = weights ? kMomPart<4> : kMomPart<1>;
+template <int T>
+static hipError_t launch_moments_t(const EvalArgs &a, int weights, int e0, hipStream_t st) {
+    const int per = weights ? kMomPart<4, T> : kMomPart<1, T>;
     const dim3 grid((unsigned)((a.n_f0 - 1) / per + 1), (unsigned)a.n_groups);
     if (weights)
-        hipLaunchKernelGGL(moments_kernel<4>, grid, dim3(kMomThreads), 0, st, a, e0);
+        hipLaunchKernelGGL((moments_kernel<4, T>), grid, dim3(T), 0, st, a, e0);
     else
-        hipLaunchKernelGGL(moments_kernel<1>, grid, dim3(kMomThreads), 0, st, a, e0);
+        hipLaunchKernelGGL((moments_kernel<1, T>), grid, dim3(T), 0, st, a, e0);
     return hipGetLastError();
+}
+
+// 64 threads where the groups fill the chip and one part of them holds the f0: with 512 most
+// of a workgroup waits for its segments, and its LDS keeps others out (4 f0 x 60000
+// groups of 200 segments: the evaluation 1154 us with 64, 2070 with 512; 300 x 3000 of
+// 1000: 197 and 259), while for fewer groups the segments are the work to share (300 groups
+// of 5000: 128 us with 64, 104 with 512).  256 for few segments and many f0, whose longer
+// prefix sums are most of it (5000 f0 x 3000 groups of 64 segments: 448 us, 531 with 512).
+hipError_t launch_moments(const EvalArgs &a, int weights, int e0, hipStream_t st) {
+    int max_seg = 0;
+    for (int d = 0; d < a.n_det; ++d) max_seg = std::max(max_seg, a.det[d].n_seg);
+    if (a.n_groups >= 2048 && a.n_f0 <= (weights ? kMomPart<4, 64> : kMomPart<1, 64>))
+        return launch_moments_t<64>(a, weights, e0, st);
+    if (!weights && max_seg <= 256 && a.n_f0 > kMomPart<1, 256>) return launch_moments_t<256>(a, weights, e0, st);
+    return launch_moments_t<512>(a, weights, e0, st);
 }
 
 // ---------------------------------------------------------------------------

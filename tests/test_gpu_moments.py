@@ -56,3 +56,41 @@ def test_moments_at_part_edges(n_f0, step, weighted, dets):
     assert np.all(np.abs(pp[ok] - po[ok]) <= psi_tolerance(ref).reshape(-1)[ok])
     okc = np.isfinite(co)
     assert np.all(np.abs(pc[okc] - co[okc]) <= 1e-12 * (1 + np.abs(co[okc])))
+
+
+@pytest.mark.parametrize("n_f0,weighted,dets,ns", [
+    (1, False, 1, 41), (512, False, 2, 41), (513, False, 1, 300),   # parts of 512 f0 for many groups
+    (128, True, 1, 300), (129, True, 2, 41),                        # of 128 with weights
+])
+def test_moments_of_many_groups(n_f0, weighted, dets, ns):
+    """2048 groups, from which on a wavefront takes a group."""
+    import torch
+    from paper_2507_07816_amd import ltgw
+
+    print(f"case: moments of 2048 groups, n_f0 {n_f0} weighted {weighted} dets {dets} segments {ns}", flush=True)
+    nb, k_lo, t_sft = 60, 1880, 4.0
+    r = np.random.default_rng(n_f0)
+    ctx = ltgw.Context(0)
+    od = []
+    for d in range(dets):
+        t = np.arange(ns) * (3600.0 / ns) + 2.0 + d
+        v = r.normal(size=(ns, 3))
+        v = v / np.linalg.norm(v, axis=1, keepdims=True) * 3.0e4
+        w = r.uniform(0.5, 2.0, ns).astype(np.float32) if weighted else None
+        P = r.exponential(size=(ns, nb)).astype(np.float32)
+        ctx.load_spectrogram(d, torch.from_numpy(P).cuda(), k_lo, t_sft, t, weights=w)
+        ctx.set_velocity_table(d, v)
+        od.append(oracle.Detector(P, t, v, k_lo, t_sft, weights=w))
+    g = dict(f0_min=(k_lo + 20) / t_sft, f0_step=20.0 / n_f0, n_f0=n_f0, tau=np.geomspace(2000.0, 60000.0, 1024),
+             brake=[3.0, 5.0], sky=[SKY], t0=0.0)
+    s, c, N = ctx.eval_templates(**g, det_mask=(1 << dets) - 1)
+    pp = ctx.psi("power", n_f0 * 2048).cpu().numpy()
+    got, total = N.cpu().numpy().reshape(-1), ctx.diagnostics()["in_band"]
+    ctx.close()
+    ref = oracle.evaluate(od if dets > 1 else od[0], oracle.Grid(*[g[k] for k in ("f0_min", "f0_step", "n_f0", "tau",
+                                                                                "brake", "sky", "t0")]))
+    assert np.array_equal(got, ref["N"].reshape(-1)) and total == int(ref["N"].sum())
+    po = oracle.psi_power(ref).reshape(-1)
+    ok = np.isfinite(po)
+    assert np.array_equal(ok, np.isfinite(pp))
+    assert np.all(np.abs(pp[ok] - po[ok]) <= psi_tolerance(ref).reshape(-1)[ok])
