@@ -35,7 +35,7 @@ hipError_t launch_coarse_block_scores(const float *x, int R, int nb, int c_in, i
                                       const int32_t *map, float *score, hipStream_t st);
 hipError_t launch_list_eval(int store, const EvalArgs &a, int R, int64_t stack_bytes, int64_t stack_rows,
                             const int32_t *idx, int m, const int32_t *rmap, const int32_t *n_rows, StackMoments mom,
-                            double *out_psi, hipStream_t st);
+                            double *out_psi, int cu_count, hipStream_t st);
 // Whether launch_block_eval takes blocks of W templates.
 bool block_eval_supported(int W);
 hipError_t launch_block_eval(int store, int W, const EvalArgs &a, int R, int64_t stack_bytes, int64_t stack_rows,

@@ -239,7 +239,7 @@ int list_psi_impl(ltgw_ctx *c, const ltgw_grid *g, const int32_t *idx, int rows,
     int64_t sb = 0, sr = 0;
     const EvalArgs a = stack_args(c->stack, 0, g, P, sb, sr);
     HIP_TRY(c, launch_list_eval(c->stack.store, a, rows, sb, sr, idx, m, rmap, n_rows, stat_moments(c, 0, stat),
-                                out_psi, c->stream),
+                                out_psi, c->cu_count, c->stream),
             "listed evaluation launch");
     if (plan_out) *plan_out = P;
     return LTGW_OK;
@@ -718,7 +718,7 @@ int32_t ltgw_propose(ltgw_ctx *c, const ltgw_grid *fine, const ltgw_grid *coarse
         }
         HIP_TRY(c, launch_expand_blocks(blk, K, W, 2 * L, nbg, rmap, n_rows, R, tpl, c->stream),
                 "block expansion launch");
-        HIP_TRY(c, launch_list_eval(S.store, fa, R, sb, sr, tpl, K * W, rmap, n_rows, fm, psi, c->stream),
+        HIP_TRY(c, launch_list_eval(S.store, fa, R, sb, sr, tpl, K * W, rmap, n_rows, fm, psi, c->cu_count, c->stream),
                 "listed evaluation launch");
         return LTGW_OK;
     };

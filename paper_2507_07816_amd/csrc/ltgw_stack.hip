@@ -560,23 +560,27 @@ hipError_t launch_coarse_block_scores(const float *x, int R, int nb, int c_in, i
 // idx[r][q] of the grid (any order; each lane reads its own group's track
 // factors).  Writes the power critical ratio (mu = var = 1) or NaN.  Rows
 // rr >= *n_rows are skipped when the device count n_rows is given.
-// 64 templates per workgroup, its 16 wavefronts a chunk of segments each, the
-// chunk sums added in order through LDS: 45 templates on each of 256 realisations
-// of 1024 segments took 106 us with a wavefront per realisation, 42 so.
-template <int STORE>
-__global__ __launch_bounds__(64 * kSplitWaves) void list_eval_kernel(const EvalArgs a, int64_t stack_bytes,
+// 64 templates per workgroup, its W wavefronts a chunk of segments each, the chunk
+// sums added in order through LDS: 45 templates on each of 256 realisations of 1024
+// segments took 106 us with a wavefront per realisation, 42 with 16.  by_xcd: the
+// workgroups of a row run on one XCD (as in stack_eval_kernel), so that its L2 alone
+// holds the row; else they are spread over all.
+template <int STORE, int W>
+__global__ __launch_bounds__(64 * W) void list_eval_kernel(const EvalArgs a, int64_t stack_bytes,
                                                                      int64_t stack_rows,
                                                                      const int32_t *__restrict__ idx, int m,
                                                                      const int32_t *__restrict__ rmap,
                                                                      const int32_t *__restrict__ n_rows,
-                                                                     const StackMoments mom,
+                                                                     const StackMoments mom, int R, int by_xcd,
                                                                      double *__restrict__ out_psi) {
-    __shared__ float part[2][kSplitWaves][64];
-    __shared__ int count[kSplitWaves][64];
+    __shared__ float part[2][W][64];
+    __shared__ int count[W][64];
     const int lane = (int)threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int q = blockIdx.x * 64 + lane;
-    const int rr = blockIdx.y;                  // row of idx and out_psi
-    if (n_rows && rr >= *n_rows) return;        // the whole workgroup
+    const int tiles = (m + 63) / 64;
+    const int at = by_xcd ? (int)blockIdx.x / kXcds : (int)blockIdx.x;
+    const int q = at % tiles * 64 + lane;
+    const int rr = by_xcd ? (int)blockIdx.x % kXcds + kXcds * (at / tiles) : at / tiles;  // row of idx and out_psi
+    if (rr >= R || (n_rows && rr >= *n_rows)) return;  // the whole workgroup
     const int r = rmap ? rmap[rr] : rr;         // realisation of the stack
     DetView D = a.det[0];
     D.store = (const char *)D.store + (int64_t)r * stack_bytes;
@@ -593,7 +597,7 @@ __global__ __launch_bounds__(64 * kSplitWaves) void list_eval_kernel(const EvalA
     const int chunks = (D.n_seg + kChunk - 1) / kChunk;
     double s = 0.0;
     int cnt = 0;
-    for (int c0 = 0, b = 0; c0 < chunks; c0 += kSplitWaves, b ^= 1) {
+    for (int c0 = 0, b = 0; c0 < chunks; c0 += W, b ^= 1) {
         const int je = min((c0 + wv + 1) * kChunk, D.n_seg);
         float sc = 0.0f;
         int j = (c0 + wv) * kChunk;
@@ -619,30 +623,67 @@ __global__ __launch_bounds__(64 * kSplitWaves) void list_eval_kernel(const EvalA
             const unsigned ix = (unsigned)__double2int_rz(vv);
             sc = __builtin_fmaf(uniform_load(D.wq, j), Store<STORE>::get(rs, (int)ix, j * D.pitch_bytes, cnt), sc);
         }
-        part[b][wv][lane] = sc;
-        __syncthreads();  // the other buffer's sums were read before it
-        if (wv == 0)
-            for (int k = 0; k < min(kSplitWaves, chunks - c0); ++k) s += (double)part[b][k][lane];
+        if constexpr (W == 1) {
+            s += (double)sc;
+        } else {
+            part[b][wv][lane] = sc;
+            __syncthreads();  // the other buffer's sums were read before it
+            if (wv == 0)
+                for (int k = 0; k < min(W, chunks - c0); ++k) s += (double)part[b][k][lane];
+        }
     }
-    count[wv][lane] = cnt;
-    __syncthreads();
-    if (wv != 0 || q >= m) return;
-    for (int k = 1; k < kSplitWaves; ++k) cnt += count[k][lane];
+    if constexpr (W > 1) {
+        count[wv][lane] = cnt;
+        __syncthreads();
+        if (wv != 0) return;
+        for (int k = 1; k < W; ++k) cnt += count[k][lane];
+    }
+    if (q >= m) return;
     out_psi[(int64_t)rr * m + q] = bad ? __builtin_nan("") : stack_stat(s, cnt, mom, t, 1.0, 1.0, 0);
+}
+
+// How many wavefronts share 64 listed templates: as many as keep the chip full and have a
+// chunk of segments each.
+static int list_waves(const EvalArgs &a, int R, int m, int cu_count) {
+    const int chunks = (a.det[0].n_seg + kChunk - 1) / kChunk;
+    const int64_t n = (int64_t)((m + 63) / 64) * R;
+    return chunks >= 8 && n <= 3 * cu_count ? 16 : chunks >= 4 ? 4 : 1;
+}
+
+template <int STORE>
+static hipError_t launch_list_store(const EvalArgs &a, int R, int64_t stack_bytes, int64_t stack_rows, const int32_t *idx,
+                                    int m, const int32_t *rmap, const int32_t *n_rows, StackMoments mom, double *out_psi,
+                                    int cu_count, hipStream_t st) {
+    // rows to XCDs in turn once each has eight or more
+    const int by_xcd = R >= 8 * kXcds;
+    const int64_t blocks = (int64_t)((m + 63) / 64) * (by_xcd ? (R + kXcds - 1) / kXcds * kXcds : R);
+    if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+    const int waves = list_waves(a, R, m, cu_count);
+    const dim3 grid((unsigned)blocks), block(64 * (unsigned)waves);
+#define LTGW_LIST_EVAL(W)                                                                                          \
+    hipLaunchKernelGGL((list_eval_kernel<STORE, W>), grid, block, 0, st, a, stack_bytes, stack_rows, idx, m, rmap, \
+                       n_rows, mom, R, by_xcd, out_psi)
+    if (waves == 16)
+        LTGW_LIST_EVAL(16);
+    else if (waves == 4)
+        LTGW_LIST_EVAL(4);
+    else
+        LTGW_LIST_EVAL(1);
+#undef LTGW_LIST_EVAL
+    return hipGetLastError();
 }
 
 hipError_t launch_list_eval(int store, const EvalArgs &a, int R, int64_t stack_bytes, int64_t stack_rows,
                             const int32_t *idx, int m, const int32_t *rmap, const int32_t *n_rows, StackMoments mom,
-                            double *out_psi, hipStream_t st) {
+                            double *out_psi, int cu_count, hipStream_t st) {
     if (R > 65535 || R < 1 || m < 1) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)((m + 63) / 64), (unsigned)R), block(64 * kSplitWaves);
     if (store == LTGW_STORE_F32)
-        hipLaunchKernelGGL(list_eval_kernel<LTGW_STORE_F32>, grid, block, 0, st, a, stack_bytes, stack_rows, idx, m, rmap, n_rows, mom, out_psi);
-    else if (store == LTGW_STORE_BF16)
-        hipLaunchKernelGGL(list_eval_kernel<LTGW_STORE_BF16>, grid, block, 0, st, a, stack_bytes, stack_rows, idx, m, rmap, n_rows, mom, out_psi);
-    else
-        hipLaunchKernelGGL(list_eval_kernel<LTGW_STORE_FP8>, grid, block, 0, st, a, stack_bytes, stack_rows, idx, m, rmap, n_rows, mom, out_psi);
-    return hipGetLastError();
+        return launch_list_store<LTGW_STORE_F32>(a, R, stack_bytes, stack_rows, idx, m, rmap, n_rows, mom, out_psi, cu_count,
+                                                 st);
+    if (store == LTGW_STORE_BF16)
+        return launch_list_store<LTGW_STORE_BF16>(a, R, stack_bytes, stack_rows, idx, m, rmap, n_rows, mom, out_psi,
+                                                  cu_count, st);
+    return launch_list_store<LTGW_STORE_FP8>(a, R, stack_bytes, stack_rows, idx, m, rmap, n_rows, mom, out_psi, cu_count, st);
 }
 
 // Proposal blocks evaluated in place: workgroup (x, rr) of TPB threads takes

@@ -935,3 +935,44 @@ def test_softmax_xent_row_lengths(n):
         lr_, dr = cnn.softmax_xent(z[b:b + 1].astype(np.float64), tg[b:b + 1])
         assert abs(l_g[b] - lr_) <= 1e-5 * max(1.0, abs(lr_))
         assert np.allclose(d_g[b] * 6, dr[0], atol=1e-6)
+
+
+@pytest.mark.parametrize("ns,R,m,store", [
+    (33, 70, 65, "f32"),       # a wavefront per 64 templates, the rows dealt to XCDs, the last deal not full
+    (96, 63, 64, "bf16"),      # not dealt
+    (97, 64, 63, "fp8"),       # four share them, with a last chunk of one segment
+    (300, 70, 700, "f32"),     # 770 workgroups: four
+    (300, 64, 768, "bf16"),    # 768: sixteen
+    (225, 1, 1, "f32"),        # sixteen with eight chunks
+])
+def test_stack_list_shapes(ns, R, m, store):
+    """Listed templates, some outside the grid, at the edges of how many wavefronts share
+    them and of how rows go to workgroups: the whole grid's ratios bit for bit."""
+    import torch
+    from paper_2507_07816_amd import ltgw
+
+    print(f"case: stack list {store} {R} x {ns}, {m} templates", flush=True)
+    nb, n_f0 = 70, 90
+    r = np.random.default_rng(ns + m)
+    t = np.arange(ns) * (3840.0 / ns) + 2.0
+    v = r.normal(size=(ns, 3))
+    v = v / np.linalg.norm(v, axis=1, keepdims=True) * 3.0e4
+    ctx = ltgw.Context(0)
+    ctx.load_spectrogram(0, torch.zeros((ns, nb), dtype=torch.float32, device="cuda"), K_LO, T_SFT, t,
+                         weights=r.uniform(0.5, 2.0, ns).astype(np.float32))
+    ctx.set_velocity_table(0, v)
+    P = torch.from_numpy(r.exponential(size=(R, ns, nb)).astype(np.float32)).cuda()
+    ltgw.ltgw_load_stack(ctx.h, 0, P, store, coarse=False)
+    fg, keep = _grid(dict(f0_min=(K_LO - 2) / T_SFT, f0_step=0.25, n_f0=n_f0, tau=[4000.0, 15000.0, 60000.0],
+                          brake=[3.0, 5.0], sky=[SKY], t0=0.0))
+    n = n_f0 * 6
+    full = torch.empty((R, n), dtype=torch.float64, device="cuda")
+    ltgw.ltgw_stack_psi(ctx.h, fg, 0, full)
+    idx = r.integers(-1, n + 1, (R, m)).astype(np.int32)
+    out = torch.empty((R, m), dtype=torch.float64, device="cuda")
+    ltgw.ltgw_stack_psi_list(ctx.h, fg, torch.from_numpy(idx).cuda(), out)
+    f, o = full.cpu().numpy(), out.cpu().numpy()
+    ctx.close()
+    inside = (idx >= 0) & (idx < n)
+    want = np.where(inside, np.take_along_axis(f, np.clip(idx, 0, n - 1), axis=1), np.nan)
+    assert np.array_equal(o, want, equal_nan=True) and (m == 1 or np.isfinite(o).any())
