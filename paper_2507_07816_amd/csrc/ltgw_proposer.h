@@ -18,7 +18,8 @@ struct StackMoments {
     double q = 0.0;
 };
 
-hipError_t launch_stack_moments(int shift, const EvalArgs &a, double *w1, double *w2, int32_t *n, hipStream_t st);
+hipError_t launch_stack_moments(int shift, const EvalArgs &a, double *w1, double *w2, int32_t *n, int cu_count,
+                                hipStream_t st);
 
 hipError_t launch_stack_eval(int store, int shift, const EvalArgs &a, int R, int64_t stack_bytes,
                              int64_t stack_rows, double mu, double var, int nan_to_zero, const int32_t *rmap,

@@ -75,7 +75,7 @@ int stack_moments(ltgw_ctx *c, const ltgw_grid *g, int level, const SearchPlan &
     if ((rc = ensure(c, L.mn, (size_t)n * 4, "moments")) != LTGW_OK) return rc;
     int64_t sb = 0, sr = 0;
     const EvalArgs a = stack_args(S, level, g, P, sb, sr);
-    HIP_TRY(c, launch_stack_moments(level, a, (double *)L.mw1.p, (double *)L.mw2.p, (int32_t *)L.mn.p, c->stream),
+    HIP_TRY(c, launch_stack_moments(level, a, (double *)L.mw1.p, (double *)L.mw2.p, (int32_t *)L.mn.p, c->cu_count, c->stream),
             "moments launch");
     L.m_f0_min = g->f0_min;
     L.m_f0_step = g->f0_step;

@@ -23,19 +23,24 @@ typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 // lattice (stack_moments_kernel) in the order the in-loop sums would take:
 // FP32 over chunks of 32 segments, carried in FP64.
 //
-// A workgroup of 16 wavefronts takes 64 templates: each wavefront a chunk at a
+// A workgroup of W wavefronts takes 64 templates: each wavefront a chunk at a
 // time, its sums left in LDS, which the first wavefront adds in chunk order.
 // There are few templates (thousands), so a lane that walked all segments left
 // most of the chip idle: 4800 templates over 1024 segments took 107 us and take
-// 11 now.
-constexpr int kSplitWaves = 16;
+// 11 with 16 wavefronts.
 
-template <int SHIFT>
-__global__ __launch_bounds__(64 * kSplitWaves) void stack_moments_kernel(const EvalArgs a, double *__restrict__ w1,
-                                                                         double *__restrict__ w2,
-                                                                         int32_t *__restrict__ n) {
-    __shared__ float2 part[2][kSplitWaves][64];
-    __shared__ int count[kSplitWaves][64];
+// How many wavefronts share 64 templates, of n such workgroups: as many as keep the chip
+// full and have a chunk of segments each.
+static int shared_waves(int n_seg, int64_t n, int cu_count) {
+    const int chunks = (n_seg + kChunk - 1) / kChunk;
+    return chunks >= 8 && n <= 3 * cu_count ? 16 : chunks >= 4 ? 4 : 1;
+}
+
+template <int SHIFT, int W>
+__global__ __launch_bounds__(64 * W) void stack_moments_kernel(const EvalArgs a, double *__restrict__ w1,
+                                                               double *__restrict__ w2, int32_t *__restrict__ n) {
+    __shared__ float2 part[2][W][64];
+    __shared__ int count[W][64];
     const int n_tiles = (a.n_f0 + 63) / 64;
     const int tile = (int)blockIdx.x % n_tiles, grp = (int)blockIdx.x / n_tiles;
     const int lane = (int)threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -47,7 +52,7 @@ __global__ __launch_bounds__(64 * kSplitWaves) void stack_moments_kernel(const E
     const int chunks = (D.n_seg + kChunk - 1) / kChunk;
     double W1 = 0.0, W2 = 0.0;
     int N = 0;
-    for (int c0 = 0, b = 0; c0 < chunks; c0 += kSplitWaves, b ^= 1) {
+    for (int c0 = 0, b = 0; c0 < chunks; c0 += W, b ^= 1) {
         const int j0 = (c0 + wv) * kChunk, je = min(j0 + kChunk, D.n_seg);
         float c1 = 0.0f, c2 = 0.0f;
 #pragma unroll 4
@@ -64,7 +69,7 @@ __global__ __launch_bounds__(64 * kSplitWaves) void stack_moments_kernel(const E
         part[b][wv][lane] = make_float2(c1, c2);
         __syncthreads();  // the other buffer's sums were read before it
         if (wv == 0)
-            for (int k = 0; k < min(kSplitWaves, chunks - c0); ++k) {
+            for (int k = 0; k < min(W, chunks - c0); ++k) {
                 const float2 p = part[b][k][lane];
                 W1 += (double)p.x;
                 W2 += (double)p.y;
@@ -73,22 +78,31 @@ __global__ __launch_bounds__(64 * kSplitWaves) void stack_moments_kernel(const E
     count[wv][lane] = N;
     __syncthreads();
     if (wv != 0 || i >= a.n_f0) return;
-    for (int k = 1; k < kSplitWaves; ++k) N += count[k][lane];
+    for (int k = 1; k < W; ++k) N += count[k][lane];
     const int64_t t = (int64_t)grp * a.n_f0 + i;
     w1[t] = W1;
     w2[t] = W2;
     n[t] = N;
 }
 
-hipError_t launch_stack_moments(int shift, const EvalArgs &a, double *w1, double *w2, int32_t *n, hipStream_t st) {
+template <int W>
+static hipError_t launch_stack_moments_w(int shift, const EvalArgs &a, unsigned n_blocks, double *w1, double *w2, int32_t *n,
+                                         hipStream_t st) {
+    if (shift == 0)
+        hipLaunchKernelGGL((stack_moments_kernel<0, W>), dim3(n_blocks), dim3(64 * W), 0, st, a, w1, w2, n);
+    else
+        hipLaunchKernelGGL((stack_moments_kernel<1, W>), dim3(n_blocks), dim3(64 * W), 0, st, a, w1, w2, n);
+    return hipGetLastError();
+}
+
+hipError_t launch_stack_moments(int shift, const EvalArgs &a, double *w1, double *w2, int32_t *n, int cu_count,
+                                hipStream_t st) {
     const int64_t t = (int64_t)((a.n_f0 + 63) / 64) * a.n_groups;
     if (t < 1 || (int64_t)a.n_groups * a.n_f0 > 0x7fffffffLL) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)t), block(64 * kSplitWaves);
-    if (shift == 0)
-        hipLaunchKernelGGL(stack_moments_kernel<0>, grid, block, 0, st, a, w1, w2, n);
-    else
-        hipLaunchKernelGGL(stack_moments_kernel<1>, grid, block, 0, st, a, w1, w2, n);
-    return hipGetLastError();
+    const int waves = shared_waves(a.det[0].n_seg, t, cu_count);
+    if (waves == 16) return launch_stack_moments_w<16>(shift, a, (unsigned)t, w1, w2, n, st);
+    if (waves == 4) return launch_stack_moments_w<4>(shift, a, (unsigned)t, w1, w2, n, st);
+    return launch_stack_moments_w<1>(shift, a, (unsigned)t, w1, w2, n, st);
 }
 
 // The critical ratio of template tt from its power sum s and the moments:
@@ -642,23 +656,15 @@ __global__ __launch_bounds__(64 * W) void list_eval_kernel(const EvalArgs a, int
     out_psi[(int64_t)rr * m + q] = bad ? __builtin_nan("") : stack_stat(s, cnt, mom, t, 1.0, 1.0, 0);
 }
 
-// How many wavefronts share 64 listed templates: as many as keep the chip full and have a
-// chunk of segments each.
-static int list_waves(const EvalArgs &a, int R, int m, int cu_count) {
-    const int chunks = (a.det[0].n_seg + kChunk - 1) / kChunk;
-    const int64_t n = (int64_t)((m + 63) / 64) * R;
-    return chunks >= 8 && n <= 3 * cu_count ? 16 : chunks >= 4 ? 4 : 1;
-}
-
 template <int STORE>
 static hipError_t launch_list_store(const EvalArgs &a, int R, int64_t stack_bytes, int64_t stack_rows, const int32_t *idx,
                                     int m, const int32_t *rmap, const int32_t *n_rows, StackMoments mom, double *out_psi,
                                     int cu_count, hipStream_t st) {
     // rows to XCDs in turn once each has eight or more
     const int by_xcd = R >= 8 * kXcds;
-    const int64_t blocks = (int64_t)((m + 63) / 64) * (by_xcd ? (R + kXcds - 1) / kXcds * kXcds : R);
+    const int64_t tiles = (m + 63) / 64, blocks = tiles * (by_xcd ? (R + kXcds - 1) / kXcds * kXcds : R);
     if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-    const int waves = list_waves(a, R, m, cu_count);
+    const int waves = shared_waves(a.det[0].n_seg, tiles * R, cu_count);
     const dim3 grid((unsigned)blocks), block(64 * (unsigned)waves);
 #define LTGW_LIST_EVAL(W)                                                                                          \
     hipLaunchKernelGGL((list_eval_kernel<STORE, W>), grid, block, 0, st, a, stack_bytes, stack_rows, idx, m, rmap, \
