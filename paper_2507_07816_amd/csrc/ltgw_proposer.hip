@@ -173,6 +173,14 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
 // round to nearest even (v_cvt_pk_bf16_f32)
 __device__ inline short to_bf16(float x) { return __builtin_bit_cast(short, (__bf16)x); }
+// The same values by integer operations (inf and NaN kept), for the layer-by-layer
+// kernels: with the conversion their loads of operands lose what overlap they have (weight
+// gradients of a layer at 256 x 32 x 300: 285 us so, 380 with it; data gradients 34 and 38).
+__device__ inline short round_bf16(float x) {
+    const unsigned u = __float_as_uint(x);
+    if ((u & 0x7f800000u) == 0x7f800000u) return (short)(u >> 16);
+    return (short)((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);
+}
 
 struct ConvDims {
     int B, C, L, O, k, p;
@@ -211,8 +219,8 @@ __global__ __launch_bounds__(256) void conv_fwd_kernel(ConvDims d, const float *
                 const int li = nl + t - (KT / 2);
                 if (n < N && li >= 0 && li < d.L) bv = X[((int64_t)nb * d.C + c) * d.L + li];
             }
-            a[i] = to_bf16(av);
-            b[i] = to_bf16(bv);
+            a[i] = round_bf16(av);
+            b[i] = round_bf16(bv);
         }
         acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc, 0, 0, 0);
     }
@@ -253,7 +261,7 @@ __global__ __launch_bounds__(256) void conv_fwd_lds_kernel(ConvDims d, const flo
         const int o = o0 + r;
         float v = 0.f;
         if (o < d.O && k < K) v = W[(int64_t)o * K + k];
-        wt[r * S + k] = to_bf16(v);
+        wt[r * S + k] = round_bf16(v);
     }
     for (int e = threadIdx.x; e < Kpad * 64; e += 256) {
         const int k = e / 64, col = e % 64;
@@ -263,7 +271,7 @@ __global__ __launch_bounds__(256) void conv_fwd_lds_kernel(ConvDims d, const flo
             const int l = l0 + col + t - KT / 2;
             if (l0 + col < d.L && l >= 0 && l < d.L) v = X[((int64_t)b * d.C + c) * d.L + l];
         }
-        xt[col * S + k] = to_bf16(v);
+        xt[col * S + k] = round_bf16(v);
     }
     __syncthreads();
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -319,14 +327,14 @@ __global__ __launch_bounds__(256) void conv_fwd_win_kernel(ConvDims d, const flo
         const int t = k / Cp, c = k % Cp, o = o0 + r;
         float v = 0.f;
         if (o < d.O && t < KT && c < d.C) v = W[((int64_t)o * d.C + c) * KT + t];
-        wt[r * SW + k] = to_bf16(v);
+        wt[r * SW + k] = round_bf16(v);
     }
     for (int e = threadIdx.x; e < Cp * P; e += 256) {
         const int c = e / P, pos = e % P;
         const int l = l0 + pos - KT / 2;
         float v = 0.f;
         if (c < d.C && l >= 0 && l < d.L) v = X[((int64_t)b * d.C + c) * d.L + l];
-        xw[pos * SX + c] = to_bf16(v);
+        xw[pos * SX + c] = round_bf16(v);
     }
     __syncthreads();
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -390,8 +398,8 @@ __global__ __launch_bounds__(256) void conv_bwd_data_kernel(ConvDims d, const fl
                 const int li = nl - t + (KT / 2);
                 if (n < N && li >= 0 && li < d.L) bv = dY[((int64_t)nb * d.O + o) * d.L + li];
             }
-            a[i] = to_bf16(av);
-            b[i] = to_bf16(bv);
+            a[i] = round_bf16(av);
+            b[i] = round_bf16(bv);
         }
         acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc, 0, 0, 0);
     }
@@ -440,8 +448,8 @@ __global__ __launch_bounds__(256) void conv_bwd_weight_kernel(ConvDims d, const 
                 const int li = nl + bt - (KT / 2);
                 if (jcol < CK && li >= 0 && li < d.L) bv = X[((int64_t)nb * d.C + bc) * d.L + li];
             }
-            a[i] = to_bf16(av);
-            b[i] = to_bf16(bv);
+            a[i] = round_bf16(av);
+            b[i] = round_bf16(bv);
         }
         acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc, 0, 0, 0);
     }
