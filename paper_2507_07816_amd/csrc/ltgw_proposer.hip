@@ -1138,10 +1138,18 @@ hipError_t launch_cnn_backward(const float *params, const float *x, int B, int c
                                float *grads, hipStream_t st) {
     if (work_floats < cnn_work_floats(B, c_in, c_out, L)) return hipErrorInvalidValue;
     const CnnLayout P = cnn_layout(c_in, c_out);
-    // one workgroup per sample (several samples each where the work area holds
-    // fewer partial parameter vectors), where the sample fits on chip
+    // One workgroup per sample where the sample fits on chip, several samples each, one
+    // after the other, where the work area holds fewer partial parameter vectors: for
+    // short samples it holds few, and then the layers' kernels may be faster.  A sample on
+    // chip takes 24 us and 0.11 a position; the 14 launches 47 us and 0.28 a column up to a
+    // chunk of them.  128 samples of one position: 80 us by layers, 2750 by one workgroup;
+    // 40 of 16: 223 and 337 (three); 128 of 16: 613 and 322 (ten); 4 of 50: 100 and 123
+    // (one); 8 of 50: 150 and 122 (two).
     const int64_t parts = std::min<int64_t>(std::min(B, 512), work_floats / P.total);
-    if (cnn_infer_supported(c_in, c_out, L) && parts >= 1) {
+    const int64_t in_turn = parts ? (B + parts - 1) / parts : 0;
+    const double chip_us = 5.0 + (double)in_turn * (24.0 + 0.11 * L);
+    const double layers_us = 47.0 + 0.28 * (double)std::min<int64_t>((int64_t)B * L, kWgradChunk);
+    if (cnn_infer_supported(c_in, c_out, L) && parts >= 1 && chip_us < layers_us) {
         hipLaunchKernelGGL(cnn_grad_kernel, dim3((unsigned)parts), dim3(256), 0, st, params, x, B, c_in, c_out, L,
                            cnn_offsets(c_in, c_out), P.total, act, dlogits, work);
         hipError_t e = hipGetLastError();

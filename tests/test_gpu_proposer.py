@@ -976,3 +976,13 @@ def test_stack_list_shapes(ns, R, m, store):
     inside = (idx >= 0) & (idx < n)
     want = np.where(inside, np.take_along_axis(f, np.clip(idx, 0, n - 1), axis=1), np.nan)
     assert np.array_equal(o, want, equal_nan=True) and (m == 1 or np.isfinite(o).any())
+
+
+@pytest.mark.parametrize("B,c_in,c_out,L", [
+    (4, 8, 24, 50), (8, 8, 24, 50),       # by layers, and two workgroups of four samples
+    (40, 8, 24, 16), (128, 8, 24, 16),    # by layers, and ten of thirteen
+    (1000, 1, 2, 7),                      # 43 of 24
+])
+def test_cnn_gradients_of_short_samples(B, c_in, c_out, L):
+    """Samples so short that the work area holds few partial parameter vectors."""
+    test_cnn_gradients_at_shape_limits(B, c_in, c_out, L)
