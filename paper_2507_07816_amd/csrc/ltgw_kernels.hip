@@ -819,11 +819,13 @@ template <int NA, int T>
 __global__ __launch_bounds__(T) void moments_kernel(const EvalArgs a, int e0) {
     __shared__ unsigned long long diff[NA][kMomPart<NA, T>];
     __shared__ unsigned long long part[NA][T / 64];
+    __shared__ unsigned long long in_band;
     const int row = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int i0 = blockIdx.x * kMomPart<NA, T>, i1 = min(i0 + kMomPart<NA, T>, a.n_f0);
     for (int k = tid; k < i1 - i0; k += T)
 #pragma unroll
         for (int q = 0; q < NA; ++q) diff[q][k] = 0ull;
+    if (tid == 0) in_band = 0ull;
     __syncthreads();
     const int tn = row % a.n_tn, sky = row / a.n_tn;
     const double per_step = 1.0 / a.f0_step;
@@ -880,11 +882,14 @@ __global__ __launch_bounds__(T) void moments_kernel(const EvalArgs a, int e0) {
         for (int q = 0; q < NA; ++q) at0[q] += __shfl_xor(at0[q], o, 64);
     }
     if (lane == 0) {
-        if (inb && a.in_band_total) atomicAdd(a.in_band_total, inb);
+        if (inb) atomicAdd(&in_band, inb);
 #pragma unroll
         for (int q = 0; q < NA; ++q) atomicAdd(&diff[q][0], at0[q]);
     }
     __syncthreads();
+    // one addition per workgroup to the search's total: they queue at its address, 12 ns
+    // each (25,000 from the wavefronts of 3150 workgroups were all of a launch's 311 us)
+    if (tid == 0 && in_band && a.in_band_total) atomicAdd(a.in_band_total, in_band);
     // each thread's run of consecutive f0: its sum, the sums before it, its prefix sums
     const int per = (i1 - i0 + T - 1) / T;
     const int k0 = tid * per, k1 = min(k0 + per, i1 - i0);
