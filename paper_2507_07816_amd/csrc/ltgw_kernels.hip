@@ -942,17 +942,16 @@ static hipError_t launch_moments_t(const EvalArgs &a, int weights, int e0, hipSt
     return hipGetLastError();
 }
 
-// 64 threads where the groups fill the chip and one part of them holds the f0: with 512 most
-// of a workgroup waits for its segments, and its LDS keeps others out (4 f0 x 60000
-// groups of 200 segments: the evaluation 1154 us with 64, 2070 with 512; 300 x 3000 of
-// 1000: 197 and 259), while for fewer groups the segments are the work to share (300 groups
-// of 5000: 128 us with 64, 104 with 512).  256 for few segments and many f0, whose longer
-// prefix sums are most of it (5000 f0 x 3000 groups of 64 segments: 448 us, 531 with 512).
+// 64 threads where weighted groups fill the chip and one part of them holds the f0: with
+// 512 most of a workgroup waits for its segments, and the LDS of four sums a template
+// keeps others out (1 f0 x 60000 groups of 64 segments: the evaluation 817 us with 64, 992
+// with 512; 4 f0 of 200 segments 1166 and 1198; with one sum 512 are as fast or faster).
+// 256 for few segments and many f0, whose longer prefix sums are most of it (5000 f0 x
+// 3000 groups of 64 segments: 447 us, 527 with 512; of 200: 727 and 797).
 hipError_t launch_moments(const EvalArgs &a, int weights, int e0, hipStream_t st) {
     int max_seg = 0;
     for (int d = 0; d < a.n_det; ++d) max_seg = std::max(max_seg, a.det[d].n_seg);
-    if (a.n_groups >= 2048 && a.n_f0 <= (weights ? kMomPart<4, 64> : kMomPart<1, 64>))
-        return launch_moments_t<64>(a, weights, e0, st);
+    if (weights && a.n_groups >= 2048 && a.n_f0 <= kMomPart<4, 64>) return launch_moments_t<64>(a, weights, e0, st);
     if (!weights && max_seg <= 256 && a.n_f0 > kMomPart<1, 256>) return launch_moments_t<256>(a, weights, e0, st);
     return launch_moments_t<512>(a, weights, e0, st);
 }
