@@ -7,6 +7,8 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <limits>
+#include <memory>
 #include <mutex>
 #include <string>
 #include <thread>
@@ -190,13 +192,13 @@ int read_counter(ltgw_ctx *c, int i, unsigned long long *out) {
 
 
 // What is wrong with a listed template, or NULL.
-static const char *template_error(const ltgw_template &T) {
-    if (!fin(T.f0) || !(T.f0 > 0.0)) return "f0 must be > 0";
-    if (!fin(T.tau) || !(T.tau > 0.0)) return "tau must be > 0";
-    if (!fin(T.brake) || !(T.brake > 1.0)) return "the braking index must be > 1";
+static const char *template_error(const ltgw_template &T, bool check_sky) {
+    constexpr double kMax = std::numeric_limits<double>::max();  // (comparisons that a NaN fails)
+    if (!(T.f0 > 0.0 && T.f0 <= kMax)) return "f0 must be > 0";
+    if (!(T.tau > 0.0 && T.tau <= kMax)) return "tau must be > 0";
+    if (!(T.brake > 1.0 && T.brake <= kMax)) return "the braking index must be > 1";
     const double *k = T.sky;
-    if (!fin(k[0]) || !fin(k[1]) || !fin(k[2]) ||
-        std::fabs(std::sqrt(k[0] * k[0] + k[1] * k[1] + k[2] * k[2]) - 1.0) > 1e-12)
+    if (check_sky && !(std::fabs(std::sqrt(k[0] * k[0] + k[1] * k[1] + k[2] * k[2]) - 1.0) <= 1e-12))
         return "sky is not a unit vector";
     return nullptr;
 }
@@ -241,6 +243,15 @@ static float track_drop(const ltgw_template &T, double t_span) {
     const float r = (float)(1.0 + t_span / T.tau), d = (float)(T.brake - 1.0);
     return rough_log2(std::min(r, 0x1p100f)) / std::max(d, 0x1p-20f);
 }
+
+// From how many bytes of the selected rows on (segments x the store's bytes) the
+// expansion's lists are ordered by cells of their tracks and not by f0 alone.  A cell costs
+// the host about 10 ns a template on one thread, 2 where the list is long enough for
+// several, and saves the kernel 2.5 ps a template, segment and 4 bytes of a column
+// (FP32, 1000 - 10800 segments; a quarter for FP8): 60000 templates of 1024 segments 1054
+// us in cells, 387 in f0 order; of 10800 1044 and 2446; a million of 1024 4.2 ms and 3.5, of
+// 2700 4.5 and 12.5.
+constexpr double kCellBytes = 16000.0, kCellBytesThreads = 5000.0;
 
 // Whether the expansion kernel takes detector D for templates with tau >= tau_min,
 // brake >= brake_min and f0 <= f0_max: its index range, and all but an eighth of
@@ -979,11 +990,16 @@ int32_t ltgw_eval_list(ltgw_ctx *c, const ltgw_template *tpl, int64_t n, double 
     // direction, per chunk; the first invalid template is reported
     const int nt = list_threads(n);
     double t_span = 0.0;  // the searched time after T0
+    double seg_bytes = 0.0;
+    bool antenna = false;
     for (int d = 0; d < 32; ++d) {
         const Det &D = c->det[d];
         if (!D.loaded || (det_mask && !((det_mask >> d) & 1u))) continue;
         for (int j : {0, D.n_seg - 1}) t_span = std::max(t_span, D.h_t[(size_t)j] - t0);
+        seg_bytes += (double)D.n_seg * (D.store == LTGW_STORE_F32 ? 4 : D.store == LTGW_STORE_BF16 ? 2 : 1);
+        antenna = antenna || D.has_antenna;
     }
+    const bool cells = !antenna && seg_bytes >= (nt > 1 ? kCellBytesThreads : kCellBytes);
     struct ChunkScan {
         int64_t bad = -1;
         double f0_lo = 0.0, f0_hi = 0.0, tau_lo = 0.0, tau_hi = 0.0, brake_lo = 0.0;
@@ -991,8 +1007,9 @@ int32_t ltgw_eval_list(ltgw_ctx *c, const ltgw_template *tpl, int64_t n, double 
         bool one_sky = true;
     };
     std::vector<ChunkScan> scan(nt);
+    const std::unique_ptr<float[]> drops(cells ? new float[(size_t)n] : nullptr);  // filled below, thread by thread
     run_chunks(nt, [&](int t) {
-        ChunkScan &r = scan[t];
+        ChunkScan r;  // (in registers: its home may alias the list)
         const int64_t lo = chunk_lo(n, nt, t), hi = chunk_lo(n, nt, t + 1);
         r.f0_lo = r.f0_hi = tpl[lo].f0;
         r.tau_lo = r.tau_hi = tpl[lo].tau;
@@ -1001,20 +1018,25 @@ int32_t ltgw_eval_list(ltgw_ctx *c, const ltgw_template *tpl, int64_t n, double 
         r.drop_hi = -INFINITY;
         for (int64_t q = lo; q < hi; ++q) {
             const ltgw_template &T = tpl[q];
-            if (template_error(T)) {
+            // (a direction that all so far have has been checked)
+            r.one_sky = r.one_sky && std::memcmp(T.sky, tpl[0].sky, sizeof T.sky) == 0;
+            if (template_error(T, !r.one_sky || q == lo)) {
                 r.bad = q;
-                return;
+                break;
             }
             r.f0_lo = T.f0 < r.f0_lo ? T.f0 : r.f0_lo;
             r.f0_hi = T.f0 > r.f0_hi ? T.f0 : r.f0_hi;
             r.tau_lo = std::min(r.tau_lo, T.tau);
-            r.tau_hi = std::max(r.tau_hi, T.tau);
             r.brake_lo = std::min(r.brake_lo, T.brake);
-            const float drop = track_drop(T, t_span);
-            r.drop_lo = std::min(r.drop_lo, drop);
-            r.drop_hi = std::max(r.drop_hi, drop);
-            r.one_sky = r.one_sky && std::memcmp(T.sky, tpl[0].sky, sizeof T.sky) == 0;
+            if (cells) {
+                r.tau_hi = std::max(r.tau_hi, T.tau);
+                const float drop = track_drop(T, t_span);
+                drops[(size_t)q] = drop;
+                r.drop_lo = std::min(r.drop_lo, drop);
+                r.drop_hi = std::max(r.drop_hi, drop);
+            }
         }
+        scan[t] = r;
     });
     double f0_max = 0.0, f0_lo = 0.0, tau_lo = tpl[0].tau, tau_hi = tpl[0].tau, brake_lo = tpl[0].brake;
     float drop_lo = INFINITY, drop_hi = -INFINITY;
@@ -1027,7 +1049,7 @@ int32_t ltgw_eval_list(ltgw_ctx *c, const ltgw_template *tpl, int64_t n, double 
         drop_hi = std::max(drop_hi, scan[t].drop_hi);
         if (scan[t].bad >= 0)
             return fail(c, LTGW_E_INVALID_ARG, "template %lld: %s", (long long)scan[t].bad,
-                        template_error(tpl[scan[t].bad]));
+                        template_error(tpl[scan[t].bad], true));
         f0_max = t == 0 || scan[t].f0_hi > f0_max ? scan[t].f0_hi : f0_max;
         f0_lo = t == 0 || scan[t].f0_lo < f0_lo ? scan[t].f0_lo : f0_lo;
         one_sky = one_sky && scan[t].one_sky;
@@ -1089,8 +1111,9 @@ int32_t ltgw_eval_list(ltgw_ctx *c, const ltgw_template *tpl, int64_t n, double 
     // antenna weights over 500 of 1000 Hz 4111, 3998 in cells).  Every result goes to its
     // list position, so the order changes none.
     const double waves_log2 = std::log2(std::max(1.0, (double)n / 64.0));
-    const int drop_bits = expand ? std::min(5, (int)(0.36 * waves_log2)) : 0;
-    const int tau_bits = expand ? std::min(3, (int)(0.22 * waves_log2)) : 0;
+    const bool by_track = cells && expand;
+    const int drop_bits = by_track ? std::min(5, (int)(0.36 * waves_log2)) : 0;
+    const int tau_bits = by_track ? std::min(3, (int)(0.22 * waves_log2)) : 0;
     // as many buckets as templates or two times as many, 2^16 at most: 2^16 for a list
     // of 4800 were most of the call's host time
     const int bits = std::max(8, std::min(16, 1 + (int)std::log2((double)n)));
@@ -1119,9 +1142,12 @@ int32_t ltgw_eval_list(ltgw_ctx *c, const ltgw_template *tpl, int64_t n, double 
         int32_t *cnt = pos.data() + (size_t)t * kBuckets;
         for (int64_t q = lo; q < hi; ++q) {
             const ltgw_template &T = tpl[q];
-            const int u = cell(track_drop(T, t_span), drop_lo, drop_scale, drop_bits);
-            const int v = cell(T.tau, tau_lo, tau_scale, tau_bits);
-            key[(size_t)q] = (uint16_t)((((u << tau_bits) | v) << f0_bits) | cell(T.f0, f0_lo, f0_scale, f0_bits));
+            int k = cell(T.f0, f0_lo, f0_scale, f0_bits);
+            if (by_track) {
+                const int u = cell(drops[(size_t)q], drop_lo, drop_scale, drop_bits);
+                k |= ((u << tau_bits) | cell(T.tau, tau_lo, tau_scale, tau_bits)) << f0_bits;
+            }
+            key[(size_t)q] = (uint16_t)k;
             ++cnt[key[(size_t)q]];
         }
         std::memcpy((ltgw_template *)c->h_list.p + lo, tpl + lo, (size_t)(hi - lo) * sizeof(ltgw_template));
@@ -1135,7 +1161,7 @@ int32_t ltgw_eval_list(ltgw_ctx *c, const ltgw_template *tpl, int64_t n, double 
     // positions: the totals of nt ranges of buckets, then each range's running sums (by
     // one thread the counts of 16 chunks, 256 KB apart, took as long as all the rest)
     std::vector<int32_t> before(nt, 0);
-    run_chunks(nt, [&](int r) {
+    if (nt > 1) run_chunks(nt, [&](int r) {
         const int lo = (int)chunk_lo(kBuckets, nt, r), hi = (int)chunk_lo(kBuckets, nt, r + 1);
         int32_t sum = 0;
         for (int t = 0; t < nt; ++t)

@@ -429,3 +429,29 @@ def test_list_overflowed_power_in_the_last_segment(n_seg, n):
     assert np.isinf(want[0]).sum() > 200 and np.isfinite(want[0]).sum() > 20
     for g, w in zip(got, want):
         assert np.array_equal(g, np.tile(w, -(-n // grid.n_templates))[:n])
+
+
+@pytest.mark.parametrize("n", [3, 140000])
+def test_list_directions_are_checked(n):
+    """Equal directions are checked once: one that is no unit vector is found wherever it
+    stands, in short lists and in those that several threads look over."""
+    from paper_2507_07816_amd import ltgw
+
+    print(f"case: list directions, {n} templates", flush=True)
+    det = _small(4, 5, 64, k_lo=1920)
+    params = _bank(n, det, seed=1)
+    ctx = ltgw.Context(0)
+    try:
+        _load(ctx, [det])
+        ctx.eval_list(params)
+        for at in (0, 1, n // 2, n - 1, slice(None)):
+            for val in (0.5, np.nan, np.inf, -1e200):
+                p = params.copy()
+                p[at, 4] = val
+                with pytest.raises(ltgw.LtgwError) as ei:
+                    ctx.eval_list(p)
+                assert ei.value.code == ltgw.LTGW_E_INVALID_ARG
+                first = 0 if isinstance(at, slice) else at
+                assert f"template {first}: sky is not a unit vector" in str(ei.value)
+    finally:
+        ctx.close()
