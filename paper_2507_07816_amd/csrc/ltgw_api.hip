@@ -597,6 +597,7 @@ int plan_search(ltgw_ctx *c, const ltgw_grid *g, const int *slots, int n_slots, 
         P.n_evals += (int64_t)D.n_seg * P.n_tpl;
         P.n_seg_total += D.n_seg;
         P.max_bins = D.n_bins > P.max_bins ? D.n_bins : P.max_bins;
+        P.max_seg = D.n_seg > P.max_seg ? D.n_seg : P.max_seg;
     }
     P.n_sel = n_slots;
     P.store = c->det[slots[0]].store;
@@ -911,7 +912,7 @@ int eval_single(ltgw_ctx *c, const ltgw_grid *g, uint32_t stats, float *out_s, i
     if (variant < 0) variant = c->forced_variant;
     // a shape asked for is the shape used; a tuned lattice runs what tuning found faster,
     // its shape or the shared segments; an untuned one those where they suit it
-    int split = variant < 0 || variant == kVariantShared ? eval_split_waves(P.store, g->n_f0, P.n_groups, c->cu_count) : 0;
+    int split = variant < 0 || variant == kVariantShared ? eval_split_waves(P.store, P.max_seg, g->n_f0, P.n_groups, c->cu_count) : 0;
     if (variant < 0) {
         char key[160];
         tune_key_eval(P, moments_in_loop, key);
@@ -1318,7 +1319,7 @@ int32_t ltgw_autotune(ltgw_ctx *c, const ltgw_grid *g, int32_t *best_variant) {
         char key[160];
         tune_key_eval(P, M.mode == 2, key, "shared");
         c->tune.erase(key);
-        if (eval_split_waves(P.store, g->n_f0, P.n_groups, c->cu_count)) {
+        if (eval_split_waves(P.store, P.max_seg, g->n_f0, P.n_groups, c->cu_count)) {
             // each the better of two runs (a kernel's first one looks it up)
             float shared_ms = 0.0f;
             for (int rep = 0; rep < 2; ++rep) {

@@ -53,7 +53,7 @@ struct SearchPlan {
     float rho_th = 1.6f;
     int32_t n_f0 = 0, n_tau = 0, n_brake = 0, n_sky = 0, n_tn = 0;
     int64_t n_groups = 0, n_tpl = 0, n_evals = 0, n_seg_total = 0;
-    int32_t max_bins = 0;
+    int32_t max_bins = 0, max_seg = 0;
 };
 
 struct BatchState {

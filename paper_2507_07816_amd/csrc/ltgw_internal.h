@@ -98,7 +98,7 @@ hipError_t launch_eval(int store, bool moments_in_loop, int variant, const EvalA
                        hipStream_t st, int *launches);
 // The same with the chunks of segments shared by the wavefronts of a workgroup: how many
 // suit this lattice (0: none), and the launch.
-int eval_split_waves(int store, int n_f0, int64_t n_groups, int cu_count);
+int eval_split_waves(int store, int n_seg, int n_f0, int64_t n_groups, int cu_count);
 hipError_t launch_eval_split(int store, bool moments, int waves, const EvalArgs &a, hipStream_t st);
 
 // Batched searches (device-resident descriptors).

@@ -395,8 +395,11 @@ __global__ __launch_bounds__(64 * kSplitWaves) void eval_split_kernel(const Eval
 // serve: eval_kernel, whose order keeps an XCD on few columns, is level at n x bytes of
 // the lattice's columns in a row of 40 - 60 MB (8000 FP32 columns: 258 us against 264
 // at n = 1500, 818 against 499 at 4500; 4000 BF16: 305 against 355 at 5040, 593 against
-// 549 at 9072; with moments in the loop 4000 FP8: 471 against 488 at 9072).
-int eval_split_waves(int store, int n_f0, int64_t n_groups, int cu_count) {
+// 549 at 9072; with moments in the loop 4000 FP8: 471 against 488 at 9072).  One or two chunks of segments
+// are nothing to share: eval_kernel's larger workgroups start sooner (500 f0 x 600 groups
+// of 32 segments: 14.5 us against 17.7, 1990 x 140 of 64 11.6 against 15.6).
+int eval_split_waves(int store, int n_seg, int n_f0, int64_t n_groups, int cu_count) {
+    if (n_seg <= 2 * kChunk) return 0;
     const int64_t n = (int64_t)((n_f0 + 63) / 64) * n_groups;
     const int bytes = store == LTGW_STORE_F32 ? 4 : store == LTGW_STORE_BF16 ? 2 : 1;
     if (n * n_f0 * bytes > 40000000) return 0;

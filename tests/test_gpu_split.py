@@ -97,19 +97,19 @@ def _lattice(ns, nb, k_lo, t_sft, n_f0, n_tau, store="f32"):
                      brake=[5.0], sky=[SKY], t0=0.0)
 
 
-@pytest.mark.parametrize("n_f0,n_tau,waves", [
-    (1, 1, 16),
-    (64, 512, 16), (64, 513, 8),        # two workgroups a CU of 256
-    (64, 1280, 8), (64, 1281, 4),       # five
-    (2500, 100, 4), (2500, 101, 0),     # 40 MB of the lattice's columns
+@pytest.mark.parametrize("ns,n_f0,n_tau,waves", [
+    (65, 1, 1, 16), (64, 1, 1, 0),              # three chunks of segments, and two
+    (70, 64, 512, 16), (70, 64, 513, 8),        # two workgroups a CU of 256
+    (70, 64, 1280, 8), (70, 64, 1281, 4),       # five
+    (70, 2500, 100, 4), (70, 2500, 101, 0),     # 40 MB of the lattice's columns
 ])
-def test_which_kernel_an_untuned_lattice_runs(n_f0, n_tau, waves):
+def test_which_kernel_an_untuned_lattice_runs(ns, n_f0, n_tau, waves):
     import torch
 
-    print(f"case: untuned {n_f0} f0 x {n_tau} tau", flush=True)
+    print(f"case: untuned {n_f0} f0 x {n_tau} tau, {ns} segments", flush=True)
     if torch.cuda.get_device_properties(0).multi_processor_count != 256:
         pytest.skip("the sizes are those of 256 CUs")
-    ctx, g = _lattice(40, 150, 1880, 4.0, n_f0, n_tau)
+    ctx, g = _lattice(ns, 150, 1880, 4.0, n_f0, n_tau)
     ctx.eval_templates(**g)
     assert ctx.shared_wavefronts() == waves and ctx.diagnostics()["tile_shape"] == 1
     ctx.set_tile_shape(2)  # a shape asked for is the one that runs
