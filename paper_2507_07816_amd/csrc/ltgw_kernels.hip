@@ -914,23 +914,45 @@ __global__ __launch_bounds__(T) void moments_kernel(const EvalArgs a, int e0) {
     for (int q = 0; q < NA; ++q)
         for (int k = 0; k < wv; ++k) run[q] += (int64_t)part[q][k];
     const double wu = (double)a.w_uniform;
-    for (int k = k0; k < k1; ++k) {
-#pragma unroll
-        for (int q = 0; q < NA; ++q) run[q] += (int64_t)diff[q][k];
-        const int64_t t = (int64_t)row * a.n_f0 + i0 + k;
-        const int nin = (int)run[0];
+    const int64_t t0 = (int64_t)row * a.n_f0 + i0;
+    auto put = [&](int k, const int64_t (&r)[NA]) {
+        const int nin = (int)r[0];
         double w1, w2;
         if constexpr (NA > 1) {
-            w1 = ldexp((double)run[1], e0);
-            w2 = ldexp((double)run[2] * 4294967296.0 + (double)run[3], 2 * e0);
+            w1 = ldexp((double)r[1], e0);
+            w2 = ldexp((double)r[2] * 4294967296.0 + (double)r[3], 2 * e0);
         } else {
             w1 = (double)nin * wu;
             w2 = (double)nin * (wu * wu);
         }
-        a.n[t] = nin;
-        a.w1[t] = w1;
-        a.w2[t] = w2;
-        if (a.out_n) a.out_n[t] = nin;
+        a.n[t0 + k] = nin;
+        a.w1[t0 + k] = w1;
+        a.w2[t0 + k] = w2;
+        if (a.out_n) a.out_n[t0 + k] = nin;
+    };
+    if (per == 1) {
+        if (k0 < k1) {
+#pragma unroll
+            for (int q = 0; q < NA; ++q) run[q] += (int64_t)diff[q][k0];
+            put(k0, run);
+        }
+        return;
+    }
+    // runs: the sums back to their places, from where neighbouring lanes write neighbouring
+    // templates (a thread's run of 8 written by itself, 64 bytes from the next one's, took a
+    // search of 17 million templates of 3 segments 594 us, so 317)
+    for (int k = k0; k < k1; ++k)
+#pragma unroll
+        for (int q = 0; q < NA; ++q) {
+            run[q] += (int64_t)diff[q][k];
+            diff[q][k] = (unsigned long long)run[q];
+        }
+    __syncthreads();
+    for (int k = tid; k < i1 - i0; k += T) {
+        int64_t r[NA];
+#pragma unroll
+        for (int q = 0; q < NA; ++q) r[q] = (int64_t)diff[q][k];
+        put(k, r);
     }
 }
 
