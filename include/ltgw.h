@@ -425,7 +425,7 @@ int32_t ltgw_batch_latency(ltgw_ctx *ctx, double *out_ms);
  * Variants 0..15.  An untuned lattice whose templates are few for the device, or span
  * few columns, goes to a kernel of its own instead (workgroups whose wavefronts share
  * the segments, the same bits); another untuned one has shape 1, or 9 where it is long
- * and large.  A tuned lattice runs whichever of its shape and that kernel was faster
+ * and large in FP32 rows of 2000 columns or more.  A tuned lattice runs whichever of its shape and that kernel was faster
  * when it was tuned, and ltgw_set_tile_shape's shape is always the one that runs.
  * ltgw_shared_wavefronts says which it was; ltgw_diag.tile_shape is the lattice's shape.
  * A batch uses shape (value & 3): its persistent launch is

@@ -729,15 +729,19 @@ size_t eval_bytes(const ltgw_ctx *c, const SearchPlan &P, const Moments &M, cons
 }
 
 // The shape of an untuned lattice: one template per lane and 16 segments per batch, for
-// a long search of one detector in slabs of segments, whose rows the caches hold for
-// all of a slab's workgroups: 8000 FP32 columns of 5000 segments, 36000 x 64 templates,
-// 2.94 ms against 4.53; 6000 of 10000, 27072 x 64, 4.13 against 5.99; BF16 2.71 against
-// 2.80.  Below about 20 workgroups of 64 templates a CU, or with few slabs, the launches
-// cost what they give (4536 x 64: 484 us against 472; 1500 segments, 9000 x 64: 311 against
-// 285).
-int default_shape(const EvalArgs &a, int split, int cu_count) {
+// a long FP32 search of one detector in slabs of segments, whose rows the caches hold for
+// all of a slab's workgroups: 8000 columns of 5000 segments, 36000 x 64 templates,
+// 2.94 ms against 4.53; 6000 of 10000, 27072 x 64, 4.13 against 5.99.  Rows that the
+// caches hold without slabs give up the faster shape for nothing: 2000 columns between
+// 0.98 and 1.10 of shape 1's rate, 1000 between 0.72 and 0.94, and in BF16 and FP8 0.93 to
+// 1.10 with 4000 columns and 0.71 to 0.93 with 1000.  Below about 20 workgroups of 64
+// templates a CU, or with few slabs, the launches cost what they give (4536 x 64: 484 us
+// against 472; 1500 segments, 9000 x 64: 311 against 285).
+int default_shape(const SearchPlan &P, const EvalArgs &a, int split, int cu_count) {
     const int64_t n = (int64_t)((a.n_f0 + 63) / 64) * a.n_groups;
-    return !split && a.n_det == 1 && a.det[0].n_seg >= 4096 && n >= (int64_t)20 * cu_count ? 9 : 1;
+    const bool in_slabs = !split && P.store == LTGW_STORE_F32 && a.n_det == 1 && a.det[0].n_seg >= 4096 &&
+                          a.det[0].n_bins >= 2000 && n >= (int64_t)20 * cu_count;
+    return in_slabs ? 9 : 1;
 }
 
 // The kernel whose workgroups share the segments, as eval_single's variant (where it
@@ -918,7 +922,7 @@ int eval_single(ltgw_ctx *c, const ltgw_grid *g, uint32_t stats, float *out_s, i
         tune_key_eval(P, moments_in_loop, key);
         const auto it = c->tune.find(key);
         if (it == c->tune.end()) {
-            variant = default_shape(a, split, c->cu_count);
+            variant = default_shape(P, a, split, c->cu_count);
         } else {
             variant = it->second;
             tune_key_eval(P, moments_in_loop, key, "shared");

@@ -118,6 +118,21 @@ def test_which_kernel_an_untuned_lattice_runs(ns, n_f0, n_tau, waves):
     ctx.close()
 
 
+@pytest.mark.parametrize("store,nb,shape", [("f32", 2000, 9), ("f32", 1999, 1), ("bf16", 2100, 1), ("fp8", 2100, 1)])
+def test_slabs_are_for_rows_the_caches_do_not_hold(store, nb, shape):
+    import torch
+
+    n_tau = {"f32": 160, "bf16": 330, "fp8": 650}[store]  # 40 MB of columns and more
+    print(f"case: {nb} {store} columns of 4100 segments, 2000 x {n_tau} templates", flush=True)
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the sizes are those of 256 CUs")
+    ctx, g = _lattice(4100, nb, 8000, 8.0, 2000, n_tau, store)
+    ctx.eval_templates(**g)
+    d = ctx.diagnostics()
+    assert (d["tile_shape"], d["eval_launches"], ctx.shared_wavefronts()) == (shape, 5 if shape == 9 else 1, 0)
+    ctx.close()
+
+
 def test_a_tuned_shape_runs(tmp_path):
     """A tuned lattice runs what the tuning found faster: its shape where the file says so
     (one that knows the shapes alone, or 0 for the shared segments), those where it says 1,
