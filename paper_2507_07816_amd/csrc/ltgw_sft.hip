@@ -28,7 +28,6 @@
 namespace ltgw {
 
 constexpr int kSftMaxWindow = 257;
-constexpr int kMedPer = 8;  // positions per lane of a tile
 
 __device__ __forceinline__ float2 spec_at(const float2 *row, int64_t k, int64_t half) {
     // X_{-1} = conj X_1, X_{half+1} = conj X_{half-1} (real input)
@@ -150,32 +149,34 @@ __device__ __forceinline__ int tree_slot(int i) {
     return i == N - 1 ? 0 : (N + i + 1) >> (__builtin_ctz(i + 1) + 1);
 }
 
-// One wavefront: segment blockIdx.y, a tile of 512 positions = its outputs and
-// their median halo of h on either side.  What bounds it is VALU issue, then LDS,
+// One workgroup of W wavefronts: segment blockIdx.y, a tile of 64 E positions = its outputs
+// and their median halo of h on either side.  What bounds it is VALU issue, then LDS,
 // so the work of a position is shared as far as it goes:
-//   the powers (non-negative, so ordered like their bits) are sorted in registers;
+//   the powers (non-negative, so ordered like their bits) are sorted in registers, by
+//   the first wavefront;
 //   each position's rank is found in a search tree of the sorted keys (levels
 //   contiguous: 64 lanes' reads fall on different banks), equal keys taking
 //   successive ranks in any order;
 //   a lane then slides over consecutive outputs with the set of its window's
-//   ranks as bits (512 per lane, interleaved so that every lane has its own
+//   ranks as bits (64 E per lane, interleaved so that every lane has its own
 //   bank): an output removes a rank, adds a rank, and moves the median to the
 //   next member up or down, or not at all.
+// The W wavefronts share the ranks, the first windows and the outputs; the first one slides.
 // 10800 rows of 8000 outputs, window 101: 0.90 ms (70 % of VALU issue; 3.07 ms for a
 // workgroup sort in LDS with a count of every sorted block per output).  Tiles of 1024
 // positions took 1.53 ms: half the waves fit a CU's LDS, and only windows of 257 gain
 // what they lose.
 // The entry is the (h + 1)-th smallest power of the window, exactly.
-template <bool SPEC>
-__global__ __launch_bounds__(64) void normalise_kernel(const void *__restrict__ rows, int64_t pitch, int64_t k_lo,
-                                                       int n_bins, int h, float *__restrict__ out) {
-    constexpr int E = kMedPer, N = 64 * E, kWords = N / 32;
+template <bool SPEC, int E, int W>
+__global__ __launch_bounds__(64 * W) void normalise_kernel(const void *__restrict__ rows, int64_t pitch, int64_t k_lo,
+                                                           int n_bins, int h, float *__restrict__ out) {
+    constexpr int N = 64 * E, kWords = N / 32, kMine = E > W ? E / W : 1;
     __shared__ __attribute__((aligned(16))) unsigned set[kWords * 64];
     __shared__ unsigned tree[N];
     // a rank r as its bit's place: (r / 32) << 8, the word's byte offset among the 64
     // lanes' words, and r % 32 (ordered like the ranks)
     __shared__ unsigned short rank[N], med[N];
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & 63, wv = W > 1 ? threadIdx.x >> 6 : 0;
     const int o0 = blockIdx.x * (N - 2 * h);
     const int n_out = min(N - 2 * h, n_bins - o0);
     const int n_pos = n_out + 2 * h;  // positions that an output reads; the others sort last
@@ -185,16 +186,15 @@ __global__ __launch_bounds__(64) void normalise_kernel(const void *__restrict__ 
         else
             return ((const float *)rows)[(int64_t)blockIdx.y * pitch + o0 + p];
     };
-    unsigned key[E];
+    auto load = [&](int p) { return p < n_pos ? __float_as_uint(power(p)) : ~0u; };
+    const bool ranks = kMine * wv < E;  // a wavefront beyond E has none to find
+    unsigned key[kMine];
 #pragma unroll
-    for (int i = 0; i < E; ++i) {
-        const int p = 64 * i + lane;
-        key[i] = p < n_pos ? __float_as_uint(power(p)) : ~0u;
-    }
-    {
+    for (int i = 0; i < kMine; ++i) key[i] = ranks ? load(64 * (kMine * wv + i) + lane) : ~0u;
+    if (wv == 0) {
         unsigned v[E];
 #pragma unroll
-        for (int i = 0; i < E; ++i) v[i] = key[i];
+        for (int i = 0; i < E; ++i) v[i] = i < kMine ? key[i] : load(64 * i + lane);
         sort_wave(v, lane);
 #pragma unroll
         for (int r = 0; r < E; ++r) {
@@ -204,26 +204,26 @@ __global__ __launch_bounds__(64) void normalise_kernel(const void *__restrict__ 
     }
     unsigned *const equal = set;  // ranks given out among equal keys
 #pragma unroll
-    for (int i = 0; i < E; ++i) equal[64 * i + lane] = 0u;
+    for (int i = wv; i < E; i += W) equal[64 * i + lane] = 0u;
     __syncthreads();
-    {
-        unsigned at[E];
+    if (ranks) {
+        unsigned at[kMine];
 #pragma unroll
-        for (int i = 0; i < E; ++i) at[i] = 1u;
+        for (int i = 0; i < kMine; ++i) at[i] = 1u;
 #pragma unroll 1
         for (int s = 1; s < N; s <<= 1)
 #pragma unroll
-            for (int i = 0; i < E; ++i) at[i] = 2 * at[i] + (tree[at[i]] < key[i] ? 1u : 0u);
+            for (int i = 0; i < kMine; ++i) at[i] = 2 * at[i] + (tree[at[i]] < key[i] ? 1u : 0u);
 #pragma unroll
-        for (int i = 0; i < E; ++i) {
+        for (int i = 0; i < kMine; ++i) {
             unsigned r = at[i] - N;
             r += atomicAdd(&equal[r], 1u);
-            rank[64 * i + lane] = (unsigned short)((r >> 5 << 8) | (r & 31));
+            rank[64 * (kMine * wv + i) + lane] = (unsigned short)((r >> 5 << 8) | (r & 31));
         }
     }
     __syncthreads();
 #pragma unroll
-    for (int w = 0; w < kWords; ++w) set[w * 64 + lane] = 0u;
+    for (int w = wv; w < kWords; w += W) set[w * 64 + lane] = 0u;
     __syncthreads();
     // the lane's outputs first .. first + mine - 1
     const int run = slide_length(n_out);
@@ -232,60 +232,63 @@ __global__ __launch_bounds__(64) void normalise_kernel(const void *__restrict__ 
     char *const bits = reinterpret_cast<char *>(set + lane);
     auto word = [&](int m) -> unsigned & { return *reinterpret_cast<unsigned *>(bits + (m & 0xFF00)); };
     auto toggle = [&](int r) { atomicXor(&word(r), 1u << (r & 31)); };
-#pragma unroll 8
-    for (int i = 0; i <= 2 * h; ++i) toggle(rank[first + i]);
-    int m;  // the median: h members of the set lie below
-    {
-        int below = 0, at = 0, sum = 0;
+#pragma unroll 16
+    for (int i = wv; i <= 2 * h; i += W) toggle(rank[first + i]);
+    if (W > 1) __syncthreads();
+    if (wv == 0) {
+        int m;  // the median: h members of the set lie below
+        {
+            int below = 0, at = 0, sum = 0;
 #pragma unroll 4
-        for (int w = 0; w < kWords; ++w) {
-            sum += __popc(set[w * 64 + lane]);
-            if (sum <= h) {
-                below = sum;
-                at = w + 1;
+            for (int w = 0; w < kWords; ++w) {
+                sum += __popc(set[w * 64 + lane]);
+                if (sum <= h) {
+                    below = sum;
+                    at = w + 1;
+                }
             }
-        }
-        unsigned y = set[at * 64 + lane];
-        int k = h - below;
-        m = at << 8;
+            unsigned y = set[at * 64 + lane];
+            int k = h - below;
+            m = at << 8;
 #pragma unroll
-        for (int s = 16; s > 0; s >>= 1) {
-            const int c = __popc(y & ((1u << s) - 1u));
-            if (k >= c) {
-                k -= c;
-                m += s;
-                y >>= s;
+            for (int s = 16; s > 0; s >>= 1) {
+                const int c = __popc(y & ((1u << s) - 1u));
+                if (k >= c) {
+                    k -= c;
+                    m += s;
+                    y >>= s;
+                }
             }
         }
-    }
-    // straight-line, with masks for the lanes that stay: the compiler turns branches
-    // here into loops that lanes leave one by one
-    const unsigned short *const leave = rank + first, *const enter = rank + own.enter;
-    int a = leave[0], b = enter[0];
-    for (int s = 0;; ++s) {
-        med[first + min(s, mine - 1)] = (unsigned short)m;
-        if (s + 1 == run) break;
-        const unsigned on = s + 1 < mine ? 1u : 0u;
-        atomicXor(&word(a), on << (a & 31));
-        atomicXor(&word(b), on << (b & 31));
-        // members below m: h, less a's, plus b's
-        const int more = (b < m) - (a < m), p = m & 31;
-        unsigned x = word(m);
-        const bool stay = on == 0u || (more == 0 && a != m);
-        const int next = slide_next(s, mine);
-        a = leave[next];
-        b = enter[next];
-        x &= stay ? 1u << p : more > 0 ? (1u << p) - 1u : ~1u << p;
-        int w = m & 0xFF00;
-        while (x == 0u) {
-            w += more > 0 ? -256 : 256;
-            x = word(w);
+        // straight-line, with masks for the lanes that stay: the compiler turns branches
+        // here into loops that lanes leave one by one
+        const unsigned short *const leave = rank + first, *const enter = rank + own.enter;
+        int a = leave[0], b = enter[0];
+        for (int s = 0;; ++s) {
+            med[first + min(s, mine - 1)] = (unsigned short)m;
+            if (s + 1 == run) break;
+            const unsigned on = s + 1 < mine ? 1u : 0u;
+            atomicXor(&word(a), on << (a & 31));
+            atomicXor(&word(b), on << (b & 31));
+            // members below m: h, less a's, plus b's
+            const int more = (b < m) - (a < m), p = m & 31;
+            unsigned x = word(m);
+            const bool stay = on == 0u || (more == 0 && a != m);
+            const int next = slide_next(s, mine);
+            a = leave[next];
+            b = enter[next];
+            x &= stay ? 1u << p : more > 0 ? (1u << p) - 1u : ~1u << p;
+            int w = m & 0xFF00;
+            while (x == 0u) {
+                w += more > 0 ? -256 : 256;
+                x = word(w);
+            }
+            m = w + (more > 0 ? 31 - __clz((int)x) : __ffs((int)x) - 1);
         }
-        m = w + (more > 0 ? 31 - __clz((int)x) : __ffs((int)x) - 1);
     }
     __syncthreads();
 #pragma unroll 2
-    for (int o = lane; o < n_out; o += 64) {
+    for (int o = threadIdx.x; o < n_out; o += 64 * W) {
         const int m = med[o];
         const float f = __uint_as_float(tree[tree_slot<N>((m >> 8 << 5) | (m & 31))]);
         // rho = P ln2 / median; a window whose median is 0 carries no noise-floor estimate: 0
@@ -324,14 +327,42 @@ using namespace ltgw;
 
 namespace {
 
-// rows: powers of the outputs and their halo (float), or raw spectra (float2)
-template <bool SPEC>
-hipError_t launch_normalise(const void *rows, int64_t pitch, int64_t k_lo, int n_bins, int h, int n_seg, float *out,
-                            hipStream_t st) {
-    const unsigned tiles = (unsigned)((n_bins - 1) / (64 * kMedPer - 2 * h) + 1);
-    hipLaunchKernelGGL(normalise_kernel<SPEC>, dim3(tiles, (unsigned)n_seg), dim3(64), 0, st, rows, pitch, k_lo, n_bins, h,
-                       out);
+template <bool SPEC, int E, int W>
+hipError_t launch_normalise_e(const void *rows, int64_t pitch, int64_t k_lo, int n_bins, int h, int n_seg, float *out,
+                              hipStream_t st) {
+    const int span = 64 * E - 2 * h;
+    const unsigned tiles = (unsigned)((n_bins - 1) / span + 1);
+    hipLaunchKernelGGL((normalise_kernel<SPEC, E, W>), dim3(tiles, (unsigned)n_seg), dim3(64 * W), 0, st, rows, pitch,
+                       k_lo, n_bins, h, out);
     return hipGetLastError();
+}
+
+// rows: powers of the outputs and their halo (float), or raw spectra (float2).  Few tiles
+// are a chain of waits, so they are short and their work is shared; many are issue and
+// LDS, so the halo counts.  Whole calls, in us, on 256 CUs, with 64 E positions by W
+// wavefronts:
+//   up to 16 tiles of 128 a CU, where the halo leaves half of one, or one tile a row
+//     (64 segments of 700 bins, window 1: 16.2 by <2, 1>, 18.9 by <4, 1>, 27.0 by <8, 1>;
+//     4000 of 60, 52.4, 55.1 and 61.2); then 256 (1024 of 7000, window 51: 85.5; <2, 1>
+//     139.7, <8, 1> 87.7; window 65: 93.1 and 83.6);
+//   up to 6 tiles of 256 a CU, four wavefronts (256 of 700, window 101: 21.6; <4, 1> 23.4,
+//     <8, 4> 23.9, <8, 1> 26.4; with 16 a CU 51.0, 48.3, 40.6 and 37.4);
+//   up to 3 tiles of 512 a CU, eight (one of 60, window 257: 14.3; <8, 4> 15.5, <8, 1>
+//     17.9; 256 of 700, 24.2, 24.4 and 28.0; with 7 a CU 30.1, 26.6 and 31.3);
+//   up to 8, four (1000 of 700, window 257: 49.8; <8, 1> 54.2; with 10
+//     a CU and window 101 84.6 and 81.9).
+template <bool SPEC>
+hipError_t launch_normalise(const void *rows, int64_t pitch, int64_t k_lo, int n_bins, int h, int n_seg, int cu_count,
+                            float *out, hipStream_t st) {
+    auto tiles = [&](int positions) { return ((int64_t)(n_bins - 1) / (positions - 2 * h) + 1) * n_seg; };
+    if (2 * h <= 64 && (n_bins <= 128 - 2 * h || tiles(128) <= 16 * cu_count))
+        return launch_normalise_e<SPEC, 2, 1>(rows, pitch, k_lo, n_bins, h, n_seg, out, st);
+    if (2 * h <= 50) return launch_normalise_e<SPEC, 4, 1>(rows, pitch, k_lo, n_bins, h, n_seg, out, st);
+    if (2 * h <= 192 && tiles(256) <= 6 * cu_count)
+        return launch_normalise_e<SPEC, 4, 4>(rows, pitch, k_lo, n_bins, h, n_seg, out, st);
+    if (tiles(512) <= 3 * cu_count) return launch_normalise_e<SPEC, 8, 8>(rows, pitch, k_lo, n_bins, h, n_seg, out, st);
+    if (tiles(512) <= 8 * cu_count) return launch_normalise_e<SPEC, 8, 4>(rows, pitch, k_lo, n_bins, h, n_seg, out, st);
+    return launch_normalise_e<SPEC, 8, 1>(rows, pitch, k_lo, n_bins, h, n_seg, out, st);
 }
 
 // segments with an on-chip transform: powers of a chunk of segments (about 512 MB), then their ratios
@@ -360,7 +391,8 @@ int chip_normalise(ltgw_ctx *c, const float *strain, int n_seg, int n_fft, int64
         HIP_TRY(c, launch_chip_fft(n_fft, strain + (int64_t)j0 * n_fft, nb, k_lo - h, row, tab, (float *)c->sft_spec.p,
                                    c->stream),
                 "transform launch");
-        HIP_TRY(c, launch_normalise<false>(c->sft_spec.p, row, k_lo, n_bins, h, nb, out + (int64_t)j0 * n_bins, c->stream),
+        HIP_TRY(c, launch_normalise<false>(c->sft_spec.p, row, k_lo, n_bins, h, nb, c->cu_count,
+                                          out + (int64_t)j0 * n_bins, c->stream),
                 "normalise launch");
     }
     return LTGW_OK;
@@ -448,7 +480,8 @@ int32_t ltgw_sft_normalise(ltgw_ctx *c, const float *strain, int32_t n_seg, int3
             HIP_TRY(c, hipStreamWaitEvent(c->side, c->ev_sft[b], 0), "normalise order");
             ns = c->side;
         }
-        HIP_TRY(c, launch_normalise<true>(spec, n_fft / 2 + 1, k_lo, n_bins, h, nb, out + (int64_t)j0 * n_bins, ns),
+        HIP_TRY(c, launch_normalise<true>(spec, n_fft / 2 + 1, k_lo, n_bins, h, nb, c->cu_count,
+                                         out + (int64_t)j0 * n_bins, ns),
                 "normalise launch");
         if (two) HIP_TRY(c, hipEventRecord(c->ev_sft[2 + b], c->side), "event record");
     }

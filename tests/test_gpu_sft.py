@@ -164,3 +164,35 @@ def test_transform_and_tile_limits(n_fft, n_seg, k_lo, n_bins, window):
     got, _ = _check(x.reshape(-1), n_fft, k_lo, n_bins, window)
     assert not got[1].any()
     assert np.abs(got[2] - np.log(2.0)).max() <= 2e-5
+
+
+@pytest.mark.parametrize("n_fft", [1024, 4096])  # the library's transform and the on-chip one
+@pytest.mark.parametrize("n_seg,n_bins,window", [
+    (5, 64, 65),        # one tile of 128 positions, full
+    (2048, 65, 65),     # two, 16 a CU of 256
+    (2049, 65, 65),     # more, and more than 6 of 256 a CU, and of 512 than 8
+    (2049, 79, 51),     # tiles of 256, by one wavefront
+    (3, 130, 193),      # two full tiles of 256 and a ragged one, by four
+    (1536, 156, 101),   # 6 of them a CU
+    (1537, 156, 101),   # more: tiles of 512
+    (3, 319, 195),      # the first window whose halo leaves too little of 256: one of 512, by eight
+    (768, 256, 257),    # 3 of those a CU
+    (769, 256, 257),    # more: by four
+    (2048, 256, 257),   # 8 a CU
+    (2049, 256, 257),   # more: one wavefront
+])
+def test_tiles_of_a_call(n_fft, n_seg, n_bins, window):
+    """Every size of the running median's tiles, on both sides of the lines between them:
+    five different segments (one of zeros, one of ties) over and over, the bar of this file."""
+    print(f"case: sft tiles n_fft={n_fft} n_seg={n_seg} n_bins={n_bins} window={window}", flush=True)
+    r = np.random.default_rng(n_bins + window)
+    x = r.normal(0.0, 2.0, (5, n_fft)).astype(np.float32)
+    x[1] = 0.0
+    x[2] = 0.0
+    x[2, n_fft // 2] = 1.0
+    k_lo = window // 2
+    got = _run(np.tile(x, ((n_seg + 4) // 5, 1))[:n_seg].reshape(-1), n_fft, k_lo, n_bins, window)
+    want = sft.normalised_power(x.reshape(-1), n_fft, k_lo, n_bins, window)
+    m = min(n_seg, 5)
+    assert (np.abs(got[:m] - want[:m]) / (1.0 + want[:m])).max() <= 2e-5
+    assert all(np.array_equal(got[j], got[j % 5]) for j in range(n_seg))

@@ -14,9 +14,9 @@ DRIVER = r"""
 #include "median_slide.h"
 using namespace ltgw;
 int main() {
-    const int N = 512;
     long tiles = 0;
-    for (int h = 0; h <= 128; ++h)
+    for (const int N : {128, 256, 512})
+    for (int h = 0; h <= 128 && 2 * h <= N - 64; ++h)
         for (int n_out = 1; n_out <= N - 2 * h; n_out += n_out < 4 || n_out + 70 > N - 2 * h ? 1 : 7) {
             const int n_pos = n_out + 2 * h, run = slide_length(n_out);
             std::vector<int> got(n_out, 0);
