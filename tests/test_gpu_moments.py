@@ -58,16 +58,19 @@ def test_moments_at_part_edges(n_f0, step, weighted, dets):
     assert np.all(np.abs(pc[okc] - co[okc]) <= 1e-12 * (1 + np.abs(co[okc])))
 
 
-@pytest.mark.parametrize("n_f0,weighted,dets,ns", [
-    (1, False, 1, 41), (512, False, 2, 41), (513, False, 1, 300),   # parts of 512 f0 for many groups
-    (128, True, 1, 300), (129, True, 2, 41),                        # of 128 with weights
+@pytest.mark.parametrize("n_f0,weighted,dets,ns,groups", [
+    (1, False, 1, 41, 2048), (512, False, 2, 41, 2048), (513, False, 1, 300, 2048),  # parts of 512 f0
+    (128, True, 1, 300, 2048), (129, True, 2, 41, 2048),                             # of 128 with weights
+    (3, False, 1, 65, 4097), (2, True, 2, 41, 9000),        # workgroups of two groups and one, of three
+    (4097, False, 1, 5, 2049), (1025, True, 1, 5, 2049),    # and in two parts, of 4096 and 1024
 ])
-def test_moments_of_many_groups(n_f0, weighted, dets, ns):
-    """2048 groups, from which on a wavefront takes a group."""
+def test_moments_of_many_groups(n_f0, weighted, dets, ns, groups):
+    """2048 groups, from which on a wavefront takes a group, and more than 4096 workgroups,
+    from which on each takes several."""
     import torch
     from paper_2507_07816_amd import ltgw
 
-    print(f"case: moments of 2048 groups, n_f0 {n_f0} weighted {weighted} dets {dets} segments {ns}", flush=True)
+    print(f"case: moments of {groups} groups, n_f0 {n_f0} weighted {weighted} dets {dets} segments {ns}", flush=True)
     nb, k_lo, t_sft = 60, 1880, 4.0
     r = np.random.default_rng(n_f0)
     ctx = ltgw.Context(0)
@@ -81,10 +84,10 @@ def test_moments_of_many_groups(n_f0, weighted, dets, ns):
         ctx.load_spectrogram(d, torch.from_numpy(P).cuda(), k_lo, t_sft, t, weights=w)
         ctx.set_velocity_table(d, v)
         od.append(oracle.Detector(P, t, v, k_lo, t_sft, weights=w))
-    g = dict(f0_min=(k_lo + 20) / t_sft, f0_step=20.0 / n_f0, n_f0=n_f0, tau=np.geomspace(2000.0, 60000.0, 1024),
-             brake=[3.0, 5.0], sky=[SKY], t0=0.0)
+    g = dict(f0_min=(k_lo + 20) / t_sft, f0_step=20.0 / n_f0, n_f0=n_f0, tau=np.geomspace(2000.0, 60000.0, groups // 2 if groups % 2 == 0 else groups),
+             brake=[3.0, 5.0] if groups % 2 == 0 else [4.0], sky=[SKY], t0=0.0)
     s, c, N = ctx.eval_templates(**g, det_mask=(1 << dets) - 1)
-    pp = ctx.psi("power", n_f0 * 2048).cpu().numpy()
+    pp = ctx.psi("power", n_f0 * groups).cpu().numpy()
     got, total = N.cpu().numpy().reshape(-1), ctx.diagnostics()["in_band"]
     ctx.close()
     ref = oracle.evaluate(od if dets > 1 else od[0], oracle.Grid(*[g[k] for k in ("f0_min", "f0_step", "n_f0", "tau",
