@@ -298,7 +298,8 @@ int32_t ltgw_topk_candidates(ltgw_ctx *ctx, uint32_t stat, int32_t k, ltgw_candi
  *        is 0 (e.g. zero strain) gives rho = 0.
  *   n_fft even, 2 .. 2^24; n_seg 1 .. 65535; window odd, 1 .. 257; the bins
  *   k_lo - window/2 .. k_lo + n_bins - 1 + window/2 must lie in 0 .. n_fft/2.
- * Non-finite strain propagates to rho (ltgw_load_spectrogram rejects it).
+ * A segment with a NaN or infinite sample has NaN powers and medians, and rho = 0; powers
+ * and medians that overflow to infinity give rho NaN (ltgw_load_spectrogram rejects it).
  * Works in chunks of segments with about 512 MB of powers or spectra; tables are
  * kept per on-chip length, FFT plans per (n_fft, chunk).  Asynchronous.  Errors: INVALID_ARG (sizes,
  * host pointers), NOMEM, DEVICE. */

@@ -196,3 +196,19 @@ def test_tiles_of_a_call(n_fft, n_seg, n_bins, window):
     m = min(n_seg, 5)
     assert (np.abs(got[:m] - want[:m]) / (1.0 + want[:m])).max() <= 2e-5
     assert all(np.array_equal(got[j], got[j % 5]) for j in range(n_seg))
+
+
+@pytest.mark.parametrize("n_fft", [1024, 4096])  # the library's transform and the on-chip one
+def test_strain_that_is_not_finite(n_fft):
+    """A NaN or infinite sample: rho = 0 in its segment.  Strain whose powers overflow: NaN.
+    The segments between are as without them."""
+    r = np.random.default_rng(71)
+    x = r.normal(0.0, 2.0, (6, n_fft)).astype(np.float32)
+    want = _run(x.reshape(-1), n_fft, 100, 300, 101)
+    x[1, 77] = np.nan
+    x[3, n_fft // 2] = np.inf
+    x[4] *= 1e25
+    got = _run(x.reshape(-1), n_fft, 100, 300, 101)
+    assert not got[1].any() and not got[3].any() and np.isnan(got[4]).all()
+    for j in (0, 2, 5):
+        assert np.array_equal(got[j], want[j])
