@@ -807,185 +807,184 @@ __device__ inline int first_at_least(double f0_min, double f0_step, int n, doubl
     return lo;
 }
 
-// One workgroup per (group, part of the f0): the range ends of every segment
-// added into differences in LDS (integers: any order gives the same sums), and the
+// T threads per (group, part of the f0), R groups a workgroup: the range ends of every
+// segment added into differences in LDS (integers: any order gives the same sums), and the
 // prefix sums of those.  Ends below the part count at its start, which most segments
 // share, so those are summed in registers; ends beyond it count nowhere.
 // Differences in device memory with binary searches, 32 segments a lane, took 54 us for
 // 12 groups of 1024 segments (this: 6), 95 and a 9 us scan for 456 groups of two times
-// 4465 (53), and beside the statistic, with four sums a template, 1.22 ms and a scan
+// 4465 (MOMB), and beside the statistic, with four sums a template, 1.22 ms and a scan
 // of 0.47 ms for 288 groups of 10800 (1.12).
 template <int NA, int T>
 constexpr int kMomPart = 8 * T / NA;  // f0 of a part: with 512 threads 32 KB of differences
-constexpr int kMomBlocks = 4096;  // workgroups of a launch, which share its groups
 
-template <int NA, int T>
-__global__ __launch_bounds__(T) void moments_kernel(const EvalArgs a, int e0) {
-    __shared__ unsigned long long diff[NA][kMomPart<NA, T>];
-    __shared__ unsigned long long part[NA][T / 64];
+template <int NA, int T, int R>
+__global__ __launch_bounds__(T *R) void moments_kernel(const EvalArgs a, int e0) {
+    __shared__ unsigned long long diffs[R][NA][kMomPart<NA, T>];
+    __shared__ unsigned long long parts[R][NA][T / 64];
     __shared__ unsigned long long in_band;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int sub = R > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / T) : 0, tid = R > 1 ? threadIdx.x % T : threadIdx.x;
+    const int lane = tid & 63, wv = tid >> 6;
+    auto &diff = diffs[sub];
+    auto &part = parts[sub];
+    const bool mine = (int)blockIdx.y * R + sub < a.n_groups;  // the others take its last group along
+    const int row = mine ? blockIdx.y * R + sub : a.n_groups - 1;
     const int i0 = blockIdx.x * kMomPart<NA, T>, i1 = min(i0 + kMomPart<NA, T>, a.n_f0);
+    for (int k = tid; k < i1 - i0; k += T)
+#pragma unroll
+        for (int q = 0; q < NA; ++q) diff[q][k] = 0ull;
+    if (threadIdx.x == 0) in_band = 0ull;
+    __syncthreads();
+    const int tn = row % a.n_tn, sky = row / a.n_tn;
     const double per_step = 1.0 / a.f0_step;
-    if (tid == 0) in_band = 0ull;
-    for (int row = blockIdx.y; row < a.n_groups; row += gridDim.y) {
-        for (int k = tid; k < i1 - i0; k += T)
+    unsigned long long inb = 0, at0[NA];
 #pragma unroll
-            for (int q = 0; q < NA; ++q) diff[q][k] = 0ull;
-        __syncthreads();
-        const int tn = row % a.n_tn, sky = row / a.n_tn;
-        unsigned long long inb = 0, at0[NA];
+    for (int q = 0; q < NA; ++q) at0[q] = 0ull;
+    for (int d = 0; d < a.n_det; ++d) {
+        const DetView &D = a.det[d];
+        for (int j4 = tid; j4 < D.n_seg; j4 += 4 * T) {
+            double h4[4];  // four track factors in flight
 #pragma unroll
-        for (int q = 0; q < NA; ++q) at0[q] = 0ull;
-        for (int d = 0; d < a.n_det; ++d) {
-            const DetView &D = a.det[d];
-            for (int j4 = tid; j4 < D.n_seg; j4 += 4 * T) {
-                double h4[4];  // four track factors in flight
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const int j = min(j4 + k * T, D.n_seg - 1);
-                    if (D.H) {
-                        h4[k] = D.H[(int64_t)row * D.n_seg + j];
-                    } else {
-                        const double h = D.g[(int64_t)tn * D.n_seg + j] * D.D[(int64_t)sky * D.n_seg + j];
-                        h4[k] = h * D.t_sft;
-                    }
+            for (int k = 0; k < 4; ++k) {
+                const int j = min(j4 + k * T, D.n_seg - 1);
+                if (D.H) {
+                    h4[k] = D.H[(int64_t)row * D.n_seg + j];
+                } else {
+                    const double h = D.g[(int64_t)tn * D.n_seg + j] * D.D[(int64_t)sky * D.n_seg + j];
+                    h4[k] = h * D.t_sft;
                 }
+            }
 #pragma unroll 1
-                for (int k = 0; k < 4; ++k) {
-                    const int j = j4 + k * T;
-                    if (j >= D.n_seg) break;
-                    const double H = k == 0 ? h4[0] : k == 1 ? h4[1] : k == 2 ? h4[2] : h4[3];
-                    // 1 / H to about 2^-50: where to look, no more
-                    double inv = __builtin_amdgcn_rcp(H);
-                    inv = __builtin_fma(__builtin_fma(-H, inv, 1.0), inv, inv);
-                    inv = __builtin_fma(__builtin_fma(-H, inv, 1.0), inv, inv);
-                    const int lo = max(i0, first_at_least(a.f0_min, a.f0_step, a.n_f0, H, D.cshift, 1,
-                                                          ((1.0 - D.cshift) * inv - a.f0_min) * per_step));
-                    const int hi = min(i1, first_at_least(a.f0_min, a.f0_step, a.n_f0, H, D.cshift, D.n_bins + 1,
-                                                          (((double)D.n_bins + 1.0 - D.cshift) * inv - a.f0_min) * per_step));
-                    if (lo >= hi) continue;
-                    inb += (unsigned long long)(hi - lo);
-                    unsigned long long val[NA];
-                    val[0] = 1ull;
+            for (int k = 0; k < 4; ++k) {
+                const int j = j4 + k * T;
+                if (j >= D.n_seg) break;
+                const double H = k == 0 ? h4[0] : k == 1 ? h4[1] : k == 2 ? h4[2] : h4[3];
+                // 1 / H to about 2^-50: where to look, no more
+                double inv = __builtin_amdgcn_rcp(H);
+                inv = __builtin_fma(__builtin_fma(-H, inv, 1.0), inv, inv);
+                inv = __builtin_fma(__builtin_fma(-H, inv, 1.0), inv, inv);
+                const int lo = max(i0, first_at_least(a.f0_min, a.f0_step, a.n_f0, H, D.cshift, 1,
+                                                      ((1.0 - D.cshift) * inv - a.f0_min) * per_step));
+                const int hi = min(i1, first_at_least(a.f0_min, a.f0_step, a.n_f0, H, D.cshift, D.n_bins + 1,
+                                                      (((double)D.n_bins + 1.0 - D.cshift) * inv - a.f0_min) * per_step));
+                if (lo >= hi) continue;
+                inb += (unsigned long long)(hi - lo);
+                unsigned long long val[NA];
+                val[0] = 1ull;
 #pragma unroll
-                    for (int q = 1; q < NA; ++q) val[q] = (unsigned long long)D.wfix[3 * j + q - 1];
+                for (int q = 1; q < NA; ++q) val[q] = (unsigned long long)D.wfix[3 * j + q - 1];
 #pragma unroll
-                    for (int q = 0; q < NA; ++q) {
-                        if (lo == i0)
-                            at0[q] += val[q];
-                        else
-                            atomicAdd(&diff[q][lo - i0], val[q]);
-                        if (hi < i1) atomicAdd(&diff[q][hi - i0], 0ull - val[q]);
-                    }
+                for (int q = 0; q < NA; ++q) {
+                    if (lo == i0)
+                        at0[q] += val[q];
+                    else
+                        atomicAdd(&diff[q][lo - i0], val[q]);
+                    if (hi < i1) atomicAdd(&diff[q][hi - i0], 0ull - val[q]);
                 }
             }
         }
-        for (int o = 32; o > 0; o >>= 1) {
-            inb += __shfl_xor(inb, o, 64);
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        inb += __shfl_xor(inb, o, 64);
 #pragma unroll
-            for (int q = 0; q < NA; ++q) at0[q] += __shfl_xor(at0[q], o, 64);
-        }
-        if (lane == 0) {
-            if (inb) atomicAdd(&in_band, inb);
+        for (int q = 0; q < NA; ++q) at0[q] += __shfl_xor(at0[q], o, 64);
+    }
+    if (lane == 0) {
+        if (mine && inb) atomicAdd(&in_band, inb);
 #pragma unroll
-            for (int q = 0; q < NA; ++q) atomicAdd(&diff[q][0], at0[q]);
+        for (int q = 0; q < NA; ++q) atomicAdd(&diff[q][0], at0[q]);
+    }
+    __syncthreads();
+    // one addition per workgroup to the search's total: they queue at its address, 12 ns
+    // each (25,000 from the wavefronts of 3150 workgroups were all of a launch's 311 us; with
+    // a workgroup for each of 60000 groups of 64 segments, 1 f0, the evaluation took 907 us,
+    // with eight groups a workgroup 424; a loop over groups took 438, but twice the
+    // registers beside a batch, 1166 ms against 985 for 64 searches)
+    if (threadIdx.x == 0 && in_band && a.in_band_total) atomicAdd(a.in_band_total, in_band);
+    // each thread's run of consecutive f0: its sum, the sums before it, its prefix sums
+    const int per = (i1 - i0 + T - 1) / T;
+    const int k0 = tid * per, k1 = min(k0 + per, i1 - i0);
+    int64_t run[NA];
+#pragma unroll
+    for (int q = 0; q < NA; ++q) {
+        int64_t v = 0;
+        for (int k = k0; k < k1; ++k) v += (int64_t)diff[q][k];
+        int64_t u = v;
+        for (int o = 1; o < 64; o <<= 1) {
+            const int64_t w = __shfl_up(u, o, 64);
+            if (lane >= o) u += w;
         }
-        __syncthreads();
-        // each thread's run of consecutive f0: its sum, the sums before it, its prefix sums
-        const int per = (i1 - i0 + T - 1) / T;
-        const int k0 = tid * per, k1 = min(k0 + per, i1 - i0);
-        int64_t run[NA];
+        if (lane == 63) part[q][wv] = (unsigned long long)u;
+        run[q] = u - v;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < NA; ++q)
+        for (int k = 0; k < wv; ++k) run[q] += (int64_t)part[q][k];
+    const double wu = (double)a.w_uniform;
+    const int64_t t0 = (int64_t)row * a.n_f0 + i0;
+    auto put = [&](int k, const int64_t (&r)[NA]) {
+        if (!mine) return;
+        const int nin = (int)r[0];
+        double w1, w2;
+        if constexpr (NA > 1) {
+            w1 = ldexp((double)r[1], e0);
+            w2 = ldexp((double)r[2] * 4294967296.0 + (double)r[3], 2 * e0);
+        } else {
+            w1 = (double)nin * wu;
+            w2 = (double)nin * (wu * wu);
+        }
+        a.n[t0 + k] = nin;
+        a.w1[t0 + k] = w1;
+        a.w2[t0 + k] = w2;
+        if (a.out_n) a.out_n[t0 + k] = nin;
+    };
+    if (per == 1) {
+        if (k0 < k1) {
+#pragma unroll
+            for (int q = 0; q < NA; ++q) run[q] += (int64_t)diff[q][k0];
+            put(k0, run);
+        }
+        return;
+    }
+    // runs: the sums back to their places, from where neighbouring lanes write neighbouring
+    // templates (a thread's run of 8 written by itself, 64 bytes from the next one's, took a
+    // search of 17 million templates of 3 segments 594 us, so 317)
+    for (int k = k0; k < k1; ++k)
 #pragma unroll
         for (int q = 0; q < NA; ++q) {
-            int64_t v = 0;
-            for (int k = k0; k < k1; ++k) v += (int64_t)diff[q][k];
-            int64_t u = v;
-            for (int o = 1; o < 64; o <<= 1) {
-                const int64_t w = __shfl_up(u, o, 64);
-                if (lane >= o) u += w;
-            }
-            if (lane == 63) part[q][wv] = (unsigned long long)u;
-            run[q] = u - v;
+            run[q] += (int64_t)diff[q][k];
+            diff[q][k] = (unsigned long long)run[q];
         }
-        __syncthreads();
+    __syncthreads();
+    for (int k = tid; k < i1 - i0; k += T) {
+        int64_t r[NA];
 #pragma unroll
-        for (int q = 0; q < NA; ++q)
-            for (int k = 0; k < wv; ++k) run[q] += (int64_t)part[q][k];
-        const double wu = (double)a.w_uniform;
-        const int64_t t0 = (int64_t)row * a.n_f0 + i0;
-        auto put = [&](int k, const int64_t (&r)[NA]) {
-            const int nin = (int)r[0];
-            double w1, w2;
-            if constexpr (NA > 1) {
-                w1 = ldexp((double)r[1], e0);
-                w2 = ldexp((double)r[2] * 4294967296.0 + (double)r[3], 2 * e0);
-            } else {
-                w1 = (double)nin * wu;
-                w2 = (double)nin * (wu * wu);
-            }
-            a.n[t0 + k] = nin;
-            a.w1[t0 + k] = w1;
-            a.w2[t0 + k] = w2;
-            if (a.out_n) a.out_n[t0 + k] = nin;
-        };
-        if (per == 1) {
-            if (k0 < k1) {
-#pragma unroll
-                for (int q = 0; q < NA; ++q) run[q] += (int64_t)diff[q][k0];
-                put(k0, run);
-            }
-            __syncthreads();
-            continue;
-        }
-        // runs: the sums back to their places, from where neighbouring lanes write neighbouring
-        // templates (a thread's run of 8 written by itself, 64 bytes from the next one's, took a
-        // search of 17 million templates of 3 segments 594 us, so 317)
-        for (int k = k0; k < k1; ++k)
-#pragma unroll
-            for (int q = 0; q < NA; ++q) {
-                run[q] += (int64_t)diff[q][k];
-                diff[q][k] = (unsigned long long)run[q];
-            }
-        __syncthreads();
-        for (int k = tid; k < i1 - i0; k += T) {
-            int64_t r[NA];
-#pragma unroll
-            for (int q = 0; q < NA; ++q) r[q] = (int64_t)diff[q][k];
-            put(k, r);
-        }
-        __syncthreads();
+        for (int q = 0; q < NA; ++q) r[q] = (int64_t)diff[q][k];
+        put(k, r);
     }
-    // one addition per workgroup to the search's total: they queue at its address, 12 ns
-    // each (25,000 from the wavefronts of 3150 workgroups were all of a launch's 311 us;
-    // with a workgroup for each of 60000 groups of 64 segments, 1 f0, the evaluation took
-    // 907 us, so 438)
-    if (tid == 0 && in_band && a.in_band_total) atomicAdd(a.in_band_total, in_band);
 }
 
-template <int T>
+template <int T, int R>
 static hipError_t launch_moments_t(const EvalArgs &a, int weights, int e0, hipStream_t st) {
     const int per = weights ? kMomPart<4, T> : kMomPart<1, T>;
-    const int parts = (a.n_f0 - 1) / per + 1, rows = std::max(1, kMomBlocks / parts);
-    const int each = (a.n_groups - 1) / rows + 1;  // groups of a workgroup
-    const dim3 grid((unsigned)parts, (unsigned)((a.n_groups - 1) / each + 1));
+    const dim3 grid((unsigned)((a.n_f0 - 1) / per + 1), (unsigned)((a.n_groups - 1) / R + 1));
     if (weights)
-        hipLaunchKernelGGL((moments_kernel<4, T>), grid, dim3(T), 0, st, a, e0);
+        hipLaunchKernelGGL((moments_kernel<4, T, R>), grid, dim3(T * R), 0, st, a, e0);
     else
-        hipLaunchKernelGGL((moments_kernel<1, T>), grid, dim3(T), 0, st, a, e0);
+        hipLaunchKernelGGL((moments_kernel<1, T, R>), grid, dim3(T * R), 0, st, a, e0);
     return hipGetLastError();
 }
 
-// 64 threads where the groups fill the chip and one part of them holds the f0: with 512
-// most of a workgroup waits for its segments, and its LDS keeps others out (60000 groups
-// of 64 segments, the evaluation: 1 f0 438 us with 64, 656 with 512, weighted 447 and 1078;
-// 300 f0 695 and 898), while for fewer groups the segments are the work to share
-// (300 groups of 5000 segments: 128 us with 64, 104 with 512), and so are parts (weighted, 300
-// f0 x 3000 groups of 1000 segments: 221 and 215; 5000 x 300 209 and 177).
+// 64 threads a group where the groups fill the chip and one part of them holds the f0:
+// with 512 most of them wait for segments (60000 groups of 64 segments, the evaluation: 1 f0
+// 424 us, 656 with 512, weighted 453 and 1078), while for fewer groups the segments are
+// the work to share (300 groups of 5000 segments: 128 us with 64, 104 with 512), and so are
+// parts (weighted, 5000 f0 x 300 groups of 1000 segments: 209 and 177).
 hipError_t launch_moments(const EvalArgs &a, int weights, int e0, hipStream_t st) {
     if (a.n_groups >= 2048 && a.n_f0 <= (weights ? kMomPart<4, 64> : kMomPart<1, 64>))
-        return launch_moments_t<64>(a, weights, e0, st);
-    return launch_moments_t<512>(a, weights, e0, st);
+        return launch_moments_t<64, 8>(a, weights, e0, st);
+    return launch_moments_t<512, 1>(a, weights, e0, st);
 }
 
 // ---------------------------------------------------------------------------

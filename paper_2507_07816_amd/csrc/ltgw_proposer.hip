@@ -45,7 +45,7 @@ __device__ inline void philox4x32_10(uint32_t c[4], uint32_t k0, uint32_t k1) {
 // What bounds it is VALU issue (the writes alone take 177 us for 256 realisations of
 // 1024 x 800, which took 654 us with an FP64 library log per element and take 255 now).
 // With v = 2 word + 1 = 2^e m and r, -log(r) of the table for m's top 7 bits,
-// -log(u) = (33 - e) ln 2 + log(r) - log1p(m r - 1); |m r - 1| < 2^-7 is exact, seven
+// -log(u) = (33 - e) ln 2 + log(r) - log1p(m r - 1); |m r - 1| < 2^-7 is exact, six
 // terms of the series leave 2^-51.  All rounding together stays below 2^-47, the
 // library's log is within 2^-47 of the logarithm for every word, so where
 // y - 2^-45 and y + 2^-45 round to one FP32 value that is the library's as well; the

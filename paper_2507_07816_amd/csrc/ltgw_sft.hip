@@ -434,7 +434,7 @@ int32_t ltgw_sft_normalise(ltgw_ctx *c, const float *strain, int32_t n_seg, int3
     int batch = (int)std::max<int64_t>(1, std::min<int64_t>(n_seg, ((int64_t)512 << 20) / per_seg));
     if ((rc = ensure(c, c->sft_spec, (size_t)batch * (n_fft / 2 + 1) * 8, "spectra")) != LTGW_OK) return rc;
     // More than one chunk: alternate two spectra buffers, and normalise on the
-    // side stream, so that a chunk's normalisation (LDS-bound) overlaps the
+    // side stream, so that a chunk's normalisation (VALU issue) overlaps the
     // next chunk's copy and transform (HBM-bound).  The copy into a buffer
     // waits for the normalisation that last read it; the context's stream
     // waits for the last normalisations before the call's work ends.

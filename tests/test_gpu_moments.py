@@ -61,12 +61,11 @@ def test_moments_at_part_edges(n_f0, step, weighted, dets):
 @pytest.mark.parametrize("n_f0,weighted,dets,ns,groups", [
     (1, False, 1, 41, 2048), (512, False, 2, 41, 2048), (513, False, 1, 300, 2048),  # parts of 512 f0
     (128, True, 1, 300, 2048), (129, True, 2, 41, 2048),                             # of 128 with weights
-    (3, False, 1, 65, 4097), (2, True, 2, 41, 9000),        # workgroups of two groups and one, of three
-    (4097, False, 1, 5, 2049), (1025, True, 1, 5, 2049),    # and in two parts, of 4096 and 1024
+    (3, False, 1, 65, 4097), (2, True, 2, 41, 9000),        # a workgroup with one of its eight groups
+    (4097, False, 1, 5, 2049), (1025, True, 1, 5, 2049),    # two parts, of 4096 and 1024
 ])
 def test_moments_of_many_groups(n_f0, weighted, dets, ns, groups):
-    """2048 groups, from which on a wavefront takes a group, and more than 4096 workgroups,
-    from which on each takes several."""
+    """2048 groups, from which on a wavefront takes a group and a workgroup eight."""
     import torch
     from paper_2507_07816_amd import ltgw
 
