@@ -236,10 +236,10 @@ typedef struct {
  * an FP64 enclosure of the correctly rounded power (the column is monotone in
  * it); the power itself is computed only where the enclosure straddles a
  * column boundary (counted in ltgw_diag.pow_exact), so the results are those
- * of the correctly rounded power.  The evaluation runs in the order of the
- * templates' tracks (cells of their drop over the searched time, of tau and
- * of f0; results stay in list order); without antenna weights a chunk of 32
- * segments expands each track about its middle.  Outputs as ltgw_eval_templates, in list order;
+ * of the correctly rounded power.  The evaluation runs in the order of f0 or, where
+ * a long search repays it, of the templates' tracks (cells of their drop over the
+ * searched time, of tau and of f0); results stay in list order.  Without antenna weights
+ * a chunk of 32 segments expands each track about its middle.  Outputs as ltgw_eval_templates, in list order;
  * the results are kept for ltgw_psi and ltgw_topk_candidates (whose records
  * then carry the listed parameters, index = list position and sky = -1).
  * Asynchronous (the list is copied before the call returns).  Errors:

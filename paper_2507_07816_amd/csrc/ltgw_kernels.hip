@@ -813,8 +813,8 @@ __device__ inline int first_at_least(double f0_min, double f0_step, int n, doubl
 // share, so those are summed in registers; ends beyond it count nowhere.
 // Differences in device memory with binary searches, 32 segments a lane, took 54 us for
 // 12 groups of 1024 segments (this: 6), 95 and a 9 us scan for 456 groups of two times
-// 4465 (MOMB), and beside the statistic, with four sums a template, 1.22 ms and a scan
-// of 0.47 ms for 288 groups of 10800 (1.12).
+// 4465 (28), and beside the statistic, with four sums a template, 1.22 ms and a scan
+// of 0.47 ms for 288 groups of 10800 (113 us alone).
 template <int NA, int T>
 constexpr int kMomPart = 8 * T / NA;  // f0 of a part: with 512 threads 32 KB of differences
 

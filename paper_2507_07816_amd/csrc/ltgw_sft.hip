@@ -162,10 +162,10 @@ __device__ __forceinline__ int tree_slot(int i) {
 //   bank): an output removes a rank, adds a rank, and moves the median to the
 //   next member up or down, or not at all.
 // The W wavefronts share the ranks, the first windows and the outputs; the first one slides.
-// 10800 rows of 8000 outputs, window 101: 0.90 ms (70 % of VALU issue; 3.07 ms for a
-// workgroup sort in LDS with a count of every sorted block per output).  Tiles of 1024
-// positions took 1.53 ms: half the waves fit a CU's LDS, and only windows of 257 gain
-// what they lose.
+// 10800 rows of 8000 outputs, window 101, in the first calls after the device idled: 0.90 ms
+// (3.07 ms for a workgroup sort in LDS with a count of every sorted block per output);
+// tiles of 1024 positions took 1.53: half the waves fit a CU's LDS, and only windows of
+// 257 gain what they lose.  With the clocks up 0.73 ms, 95 % of VALU issue.
 // The entry is the (h + 1)-th smallest power of the window, exactly.
 template <bool SPEC, int E, int W>
 __global__ __launch_bounds__(64 * W) void normalise_kernel(const void *__restrict__ rows, int64_t pitch, int64_t k_lo,
